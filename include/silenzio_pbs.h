@@ -90,7 +90,9 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      rows from the L2; a wait as long as the waiting workgroup's own ciphertext took ends the
                                      pacing for that launch; 0 lets them run free.  Value 2 (for tests of that give-up path):
                                      paced, but a wait that is not satisfied at once gives up.  Results are identical in
-                                     every mode.  SLZ_E_INVALID_ARG on other paths */
+                                     every mode.  Larger batches of parameter sets whose products are exact through floating-point
+                                    transforms (every base this shape admits) take another kernel, which does not pace and
+                                    ignores the value.  SLZ_E_INVALID_ARG on other paths */
 
 #define SLZ_OPT_FAIL_ALLOC_AFTER 4 /* for tests of the out-of-memory handling: value v >= 0 makes the (v+1)-th scratch allocation
                                      from now (of any context of the process) return SLZ_E_NOMEM without touching the device,
@@ -118,7 +120,8 @@ int slz_lut_encode(const slz_params *params, const uint64_t *table_host, uint32_
 
 /* One-off key preparation: standard-domain BSK (device) -> library-private transform-domain form in
  * caller-provided device memory.  Call with dst_dev == NULL to obtain the required size in *dst_bytes;
- * otherwise *dst_bytes must be at least that size. */
+ * otherwise *dst_bytes must be at least that size.  The form belongs to the build of the library that made it: size and layout
+ * may change between versions, so what is stored across versions is the standard-domain key. */
 int slz_bsk_prepare(slz_ctx *ctx, const uint64_t *bsk_dev, void *dst_dev, size_t *dst_bytes,
                     void *hip_stream);
 

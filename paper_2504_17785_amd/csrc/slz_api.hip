@@ -63,6 +63,10 @@ extern "C" int slz_ctx_create(const slz_params *params, uint32_t max_batch, slz_
         ctx->fused_pacing = 1;
         if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
     }
+    if (rc == SLZ_OK && slz_fft_supported(params)) {
+        rc = slz_fft_init(ctx);
+        ctx->has_fft = (rc == SLZ_OK);
+    }
     if (rc == SLZ_OK && slz_fused4096_supported(params)) {
         rc = slz_fused4096_init(ctx);
         ctx->has_fused4096 = (rc == SLZ_OK);
@@ -91,6 +95,7 @@ extern "C" int slz_ctx_create(const slz_params *params, uint32_t max_batch, slz_
 extern "C" int slz_ctx_destroy(slz_ctx *ctx) {
     if (!ctx) return SLZ_E_INVALID_ARG;
     slz_fused_destroy(ctx);
+    slz_fft_destroy(ctx);
     slz_fused1024_destroy(ctx);
     slz_fused512_destroy(ctx);
     slz_fused4096_destroy(ctx);
@@ -171,15 +176,21 @@ extern "C" int slz_lut_encode(const slz_params *p, const uint64_t *table, uint32
     return SLZ_OK;
 }
 
-static size_t prepared_bytes(const slz_params &p) {
+// The residue form (every path's except the one through floating-point transforms), then that path's form where it exists.
+static size_t residue_key_bytes(const slz_params &p) {
     return (size_t)p.n * 2 * (p.k + 1) * p.pbs_level * (p.k + 1) * p.N * sizeof(double);
 }
+static size_t prepared_bytes(const slz_params &p) { return residue_key_bytes(p) + slz_fft_key_bytes(&p); }
 
 extern "C" int slz_bsk_prepare(slz_ctx *ctx, const uint64_t *bsk_dev, void *dst_dev, size_t *dst_bytes, void *hip_stream) {
     if (!ctx || !dst_bytes) return SLZ_E_INVALID_ARG;
     const size_t need = prepared_bytes(ctx->prm);
     if (!dst_dev) { *dst_bytes = need; return SLZ_OK; }
     if (!bsk_dev || *dst_bytes < need || misaligned(bsk_dev) || misaligned(dst_dev)) return SLZ_E_INVALID_ARG;
+    if (ctx->has_fft) {
+        int rc = slz_fft_prepare(ctx, bsk_dev, (char *)dst_dev + residue_key_bytes(ctx->prm), (hipStream_t)hip_stream);
+        if (rc != SLZ_OK) return rc;
+    }
     return slz_generic_bsk_prepare(ctx, bsk_dev, (double *)dst_dev, (hipStream_t)hip_stream);
 }
 
@@ -221,6 +232,12 @@ static int blind_rotate_common(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
         ((uintptr_t)lut_idx & 3u))
         return SLZ_E_INVALID_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
+    // Up to one ciphertext per compute unit the residue kernel's four waves per ciphertext are faster than the two of the
+    // floating-point kernel (742 steps: 9.5 against 14.4 ms); from 257 on, where both run two ciphertexts on some unit, it is 14.3
+    // against 15.4 ms at 301 and 20.4 against 31.2 ms at 1024.
+    if (ctx->has_fft && !ctx->force_generic && batch > 256)
+        return slz_fft2048_blind_rotate(ctx, lwe_in, luts, lut_idx, (const char *)bskp + residue_key_bytes(ctx->prm), n_steps, acc_out,
+                                        lwe_out, batch, s);
     if (ctx->has_fused && !ctx->force_generic)
         return slz_fused_blind_rotate(ctx, lwe_in, luts, lut_idx, (const double *)bskp, n_steps, acc_out, lwe_out, batch, s);
     if (ctx->has_fused4096 && !ctx->force_generic)

@@ -1,0 +1,36 @@
+// Exact negacyclic products through double-precision complex transforms: the pieces shared by the host code, the key
+// preparation and the N = 2048 blind rotation.
+//
+// A key word is cut into SLZ_FFT_PIECES balanced digits of SLZ_FFT_PIECE_BITS bits, w = sum_j K_j 2^(13 j) mod 2^64 with
+// |K_j| <= 2^12.  For every piece the integer polynomial y_j = sum_r d_r K_(r,j) mod X^N + 1 (d_r: gadget digits) is
+// computed with floating-point transforms of N / 2 complex points (coefficients c and c + N/2 as real and imaginary part,
+// evaluated at the roots of Z^(N/2) = i) and rounded to the nearest integer.  slz_fft_error_bound proves for every input
+// that the error before rounding is below 1/2, so the rounded y_j, and with them sum_j y_j 2^(13 j) mod 2^64, are exact.
+#pragma once
+#include "slz_internal.h"
+
+#define SLZ_FFT_PIECES 5
+#define SLZ_FFT_PIECE_BITS 13
+
+// Tables of the N = 2048 kernels (complex entries; device memory, built by slz_fft_init).  M = 1024 points; W(m, b) is the
+// twiddle of block b at the forward stage with m blocks: the square root of the constant of that block's Z^n = c.
+//   F2 [15][16]      forward strides 32/16 (v, v^2, v^3) and 8/4 (four blocks of three), by the four top position bits
+//   F3 [2][6][64]    forward strides 2/1, by (top bit, lane): two blocks of three
+//   I2 [8][8]        inverse half-sizes 8..64, by the three lowest position bits, as (cos, tan)
+//   I3 [19][64]      inverse half-sizes 128 (1), 256 (2) as (cos, tan); 512: eight (c1, c2) pairs, c1 = psi^-j plain, c2 = psi^-j w as (cos, tan)
+#define FFT_F2_OFF 0u
+#define FFT_F2_LEN (15u * 16u)
+#define FFT_I2_OFF (FFT_F2_OFF + FFT_F2_LEN)
+#define FFT_I2_LEN (8u * 8u)
+#define FFT_I3_OFF (FFT_I2_OFF + FFT_I2_LEN)
+#define FFT_I3_LEN (19u * 64u)
+#define FFT_LDS_TAB (FFT_I3_OFF + FFT_I3_LEN)          // everything up to here is staged in LDS
+#define FFT_F3_OFF FFT_LDS_TAB
+#define FFT_F3_LEN (2u * 6u * 64u)
+#define FFT_TAB_LEN (FFT_F3_OFF + FFT_F3_LEN)
+
+// complex entries of the transform-domain key of one step: [piece][half g][k][row, component][lane]
+#define FFT_KEY_STEP (SLZ_FFT_PIECES * 2u * 8u * 4u * 64u)
+
+// Worst-case error (absolute, before rounding) of one y_j over all inputs, see slz_fft.hip.
+double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta);

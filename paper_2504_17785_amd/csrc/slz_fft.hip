@@ -1,0 +1,187 @@
+// Host side and key preparation of the floating-point transform path (see slz_fft.h): error bound, tables, key spectra.
+#include "slz_fft.h"
+#include <cmath>
+#include <vector>
+
+// ---- the error bound ------------------------------------------------------------------------------------------------
+// u = 2^-53.  All constants are multiples of u; M = N / 2 points; d = all digits of a row, K = a piece (2-norms over the N
+// real coefficients, which are the 2-norms of the M folded complex ones).
+//  Forward (radix-4 butterflies, each a0 + v^2 a2 +- (v a1 + v^3 a3) and a0 - v^2 a2 +- i (v a1 - v^3 a3)): a complex product
+//  of two multiplications and two fused multiply-adds errs by at most 2 u |w| |a|, the rounding of the twiddle's two
+//  components adds sqrt(1/2) u, the two layers of additions u each: 4.71 u per butterfly relative to the 2-norm, five layers
+//  of butterflies for M = 1024.  So ||dX||_2 <= 23.6 u ||X||_2 = 23.6 u sqrt(M) ||d||_2.
+//  Products: S = D0 K0 + D1 K1 as a chain of four fused multiply-adds per component: partial results are at most
+//  |D0 K0| (twice), |D0 K0| + |D1 K1| (twice), so the error is at most u (4 |D0 K0| + 2 |D1 K1|); the key spectrum is a
+//  correctly rounded value of a double-double transform: another u |D K| (1.05 u with the transform's own error).
+//  Inverse (decimation in time): every output is (1 / M) sum_k S_k with unit weights, so it is bounded along paths, relative
+//  to (1 / M) sum |S_k| <= ||d||_2 ||K||_2: half-sizes 1 and 2 only add (u each); half-size 4 adds, multiplies by sqrt(1/2)
+//  inside the second addition (u + 0.61 u + u, 0.61 u being the constant's rounding); half-sizes 8 to 256 are o = a +- wr (b -+ tau i b) with w = wr (1 + i tau): rounding of
+//  wr and tau at most 2 u |b|, of the bracket u |b|, of the result u |o|, together 4 u; half-size 512 with the twist is the
+//  same with a already multiplied by a plain complex factor (2.71 u, not above the 3 u of the other operand), and the second
+//  half of its outputs is turned by 45 degrees: an addition and the constant sqrt(1/2) (1.61 u; the product itself is inside the
+//  fused rounding add).  1 + 1 + 2.61 + 6 * 4 + 4 + 1.61 = 34.22 u.
+//  Second-order terms are covered by the factor 1 + 2^-40.
+// Every row r contributes ||d_r|| ||K_(r,j)||.  The chain of four constants above is for two rows.
+double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
+    if (N != 2048 || rows != 2) return 1e300;
+    const double u = std::ldexp(1.0, -53);
+    const double fwd = 5 * 4.7072, key = 1.05, inv = 34.22;
+    const double norm_d = std::ldexp(std::sqrt((double)N), (int)beta - 1);
+    const double norm_k = std::ldexp(std::sqrt((double)N), SLZ_FFT_PIECE_BITS - 1);
+    // products: (4 + 2) u for the two rows together = 3 u per row at equal bounds
+    return (fwd + 3.0 + key + inv) * u * (double)rows * norm_d * norm_k * (1.0 + std::ldexp(1.0, -40));
+}
+
+int slz_fft_supported(const slz_params *p) {
+    return p->N == 2048 && p->k == 1 && p->pbs_level == 1 && p->pbs_base_log <= 30 &&
+           slz_fft_error_bound(p->N, 2, p->pbs_base_log) < 0.499;
+}
+
+// ---- tables ---------------------------------------------------------------------------------------------------------
+static const long double PI_L = 3.14159265358979323846264338327950288L;
+struct cpl { double r, i; };
+
+// angle of W(m, blk), in units of pi: the constant of the root is i (1/2), W halves it, the children of a block have +-W
+static long double node_angle(uint32_t m, uint32_t blk) {
+    long double phi = 0.5L;                                        // constant of the root block
+    uint32_t bits = 0;
+    while ((1u << bits) < m) bits++;
+    for (uint32_t s = 0; s < bits; s++) {
+        const uint32_t right = (blk >> (bits - 1 - s)) & 1u;
+        phi = phi / 2 + (right ? 1.0L : 0.0L);
+    }
+    return phi / 2;
+}
+static cpl unit(long double a) { return {(double)cosl(PI_L * a), (double)sinl(PI_L * a)}; }
+// (cos, tan) of an angle in units of pi; a quarter turn gets a tiny cosine instead of zero, so that cos * tan = +-1 exactly
+// and the error is 2^-60
+static cpl cos_tan(long double a) {
+    long double c = cosl(PI_L * a), s = sinl(PI_L * a);
+    if (fabsl(c) < 1e-15L) return {std::ldexp(1.0, -60), s > 0 ? std::ldexp(1.0, 60) : -std::ldexp(1.0, 60)};
+    return {(double)c, (double)(s / c)};
+}
+static void three(cpl *out, size_t stride, uint32_t m, uint32_t blk) {
+    const long double v = node_angle(2 * m, 2 * blk);
+    for (int q = 0; q < 3; q++) out[q * stride] = unit((q + 1) * v);
+}
+
+int slz_fft_init(slz_ctx *ctx) {
+    const uint32_t M = ctx->prm.N / 2;
+    std::vector<cpl> t(FFT_TAB_LEN);
+    for (uint32_t x = 0; x < 16; x++) {
+        three(&t[FFT_F2_OFF + x], 16, 16, x);
+        for (uint32_t q = 0; q < 4; q++) three(&t[FFT_F2_OFF + (3 + 3 * q) * 16 + x], 16, 64, 4 * x + q);
+    }
+    for (uint32_t g = 0; g < 2; g++)
+        for (uint32_t l = 0; l < 64; l++)
+            for (uint32_t b = 0; b < 2; b++) three(&t[FFT_F3_OFF + (g * 6 + 3 * b) * 64 + l], 64, 256, g * 128 + 2 * l + b);
+    for (uint32_t l = 0; l < 8; l++) {
+        cpl *o = &t[FFT_I2_OFF + l];
+        o[0] = cos_tan(-(long double)l / 8);
+        o[8] = cos_tan(-(long double)l / 16);
+        for (uint32_t q = 0; q < 2; q++) o[8 * (2 + q)] = cos_tan(-(long double)(8 * q + l) / 32);
+        for (uint32_t q = 0; q < 4; q++) o[8 * (4 + q)] = cos_tan(-(long double)(8 * q + l) / 64);
+    }
+    for (uint32_t l = 0; l < 64; l++) {
+        cpl *o = &t[FFT_I3_OFF + l];
+        o[0] = cos_tan(-(long double)l / 128);
+        for (uint32_t q = 0; q < 2; q++) o[64 * (1 + q)] = cos_tan(-(long double)(64 * q + l) / 256);
+        for (uint32_t q = 0; q < 8; q++) {
+            const long double j = 64 * q + l;
+            o[64 * (3 + 2 * q)] = unit(-j / (2 * M));
+            o[64 * (4 + 2 * q)] = cos_tan(-j / (2 * M) - j / 512);
+        }
+    }
+    cpl f1[15];
+    three(f1, 1, 1, 0);
+    for (uint32_t q = 0; q < 4; q++) three(f1 + 3 + 3 * q, 1, 4, q);
+    for (int q = 0; q < 15; q++) { ctx->fft_f1[q][0] = f1[q].r; ctx->fft_f1[q][1] = f1[q].i; }
+    // twiddles of the key preparation as double-doubles (64 bits of them): W(m, blk) at m + blk
+    std::vector<double> w(4 * (size_t)M);
+    for (uint32_t x = 1; x < M; x++) {
+        uint32_t m = 1;
+        while (2 * m <= x) m *= 2;
+        const long double a = PI_L * node_angle(m, x - m), c = cosl(a), s = sinl(a);
+        w[4 * x] = (double)c; w[4 * x + 1] = (double)(c - (long double)(double)c);
+        w[4 * x + 2] = (double)s; w[4 * x + 3] = (double)(s - (long double)(double)s);
+    }
+    SLZ_HIP(hipMalloc((void **)&ctx->fft_tab, t.size() * sizeof(cpl)));
+    SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, w.size() * sizeof(double)));
+    SLZ_HIP(hipMemcpy(ctx->fft_tab, t.data(), t.size() * sizeof(cpl), hipMemcpyHostToDevice));
+    SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice));
+    return slz_fft2048_setup();
+}
+
+void slz_fft_destroy(slz_ctx *ctx) {
+    if (ctx->fft_tab) (void)hipFree(ctx->fft_tab);
+    if (ctx->fft_prep_tab) (void)hipFree(ctx->fft_prep_tab);
+    ctx->fft_tab = nullptr;
+    ctx->fft_prep_tab = nullptr;
+}
+
+size_t slz_fft_key_bytes(const slz_params *p) { return slz_fft_supported(p) ? (size_t)p->n * FFT_KEY_STEP * 16 : 0; }
+
+// ---- key spectra ----------------------------------------------------------------------------------------------------
+// Double-double arithmetic (error-free sums and products; the build contracts nothing by itself).
+struct dd { double h, l; };
+__device__ __forceinline__ dd dd_norm(double a, double b) { const double s = a + b; return {s, b - (s - a)}; }      // |a| >= |b|
+__device__ __forceinline__ dd dd_add(dd a, dd b) {
+    const double s = a.h + b.h, t = s - a.h;
+    const double e = (a.h - (s - t)) + (b.h - t);
+    return dd_norm(s, e + (a.l + b.l));
+}
+__device__ __forceinline__ dd dd_neg(dd a) { return {-a.h, -a.l}; }
+__device__ __forceinline__ dd dd_mul(dd a, dd b) {
+    const double p = a.h * b.h;
+    return dd_norm(p, __builtin_fma(a.h, b.h, -p) + (a.h * b.l + a.l * b.h));
+}
+
+// One workgroup per (key polynomial, piece): the forward transform of the piece in double-double, times -1 / M, rounded (the
+// kernel keeps its accumulator negated).
+__global__ void __launch_bounds__(256)
+k_fft_prepare(const uint64_t *__restrict__ bsk, const double *__restrict__ wtab, double2 *__restrict__ dst) {
+    __shared__ double rh[1024], rl[1024], ih[1024], il[1024];
+    const uint32_t poly = blockIdx.x, piece = blockIdx.y;          // poly = step * 4 + row * 2 + component
+    const uint64_t *src = bsk + (size_t)poly * 2048;
+    auto digit = [&](uint64_t w) {
+        int64_t v = (int64_t)w, d = 0;
+        for (uint32_t j = 0; j <= piece; j++) {
+            const int bits = j == SLZ_FFT_PIECES - 1 ? 64 - SLZ_FFT_PIECE_BITS * (SLZ_FFT_PIECES - 1) : SLZ_FFT_PIECE_BITS;
+            d = (int64_t)((uint64_t)v << (64 - bits)) >> (64 - bits);
+            v = (int64_t)((uint64_t)v - (uint64_t)d) >> SLZ_FFT_PIECE_BITS;
+        }
+        return (double)d;
+    };
+    for (uint32_t x = threadIdx.x; x < 1024; x += 256) {
+        rh[x] = digit(src[x]);
+        ih[x] = digit(src[x + 1024]);
+        rl[x] = il[x] = 0.0;
+    }
+    __syncthreads();
+    for (uint32_t m = 1, half = 512; m < 1024; m *= 2, half /= 2) {
+        for (uint32_t b = threadIdx.x; b < 512; b += 256) {
+            const uint32_t blk = b / half, x = blk * 2 * half + b % half, y = x + half;
+            const double *w = wtab + 4 * (size_t)(m + blk);
+            const dd wr = {w[0], w[1]}, wi = {w[2], w[3]}, ar = {rh[x], rl[x]}, ai = {ih[x], il[x]}, br = {rh[y], rl[y]}, bi = {ih[y], il[y]};
+            const dd tr = dd_add(dd_mul(br, wr), dd_neg(dd_mul(bi, wi))), ti = dd_add(dd_mul(br, wi), dd_mul(bi, wr));
+            const dd pr = dd_add(ar, tr), pi = dd_add(ai, ti), qr = dd_add(ar, dd_neg(tr)), qi = dd_add(ai, dd_neg(ti));
+            rh[x] = pr.h; rl[x] = pr.l; ih[x] = pi.h; il[x] = pi.l;
+            rh[y] = qr.h; rl[y] = qr.l; ih[y] = qi.h; il[y] = qi.l;
+        }
+        __syncthreads();
+    }
+    const uint32_t step = poly / 4, rc = poly % 4;
+    for (uint32_t x = threadIdx.x; x < 1024; x += 256) {
+        const uint32_t g = x >> 9, lane = (x >> 3) & 63u, k = x & 7u;
+        double2 v;
+        v.x = rh[x] * (-1.0 / 1024.0);
+        v.y = ih[x] * (-1.0 / 1024.0);
+        dst[(size_t)step * FFT_KEY_STEP + (((piece * 2 + g) * 8 + k) * 4 + rc) * 64 + lane] = v;
+    }
+}
+
+int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s) {
+    hipLaunchKernelGGL(k_fft_prepare, dim3(ctx->prm.n * 4, SLZ_FFT_PIECES), dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
+    SLZ_HIP(hipGetLastError());
+    return SLZ_OK;
+}

@@ -1,0 +1,494 @@
+// Blind rotation for N = 2048, k = 1, l = 1 through exact double-precision transforms (slz_fft.h).
+//
+// Two wavefronts own one ciphertext for the whole rotation.  Wave h keeps component h of the accumulator in registers
+// (32 words per lane) and transforms it; between the transforms, wave g holds the spectra of both components at the half g of
+// the 1024 points, so the products with the key need no exchange of their own.  Per CMux step and wave:
+//   1. the accumulator goes through LDS to be rotated; subtract, round, one signed digit per coefficient; digits c and
+//      c + 1024 are the real and imaginary part of one of 1024 points, 16 per lane
+//   2. forward transform (merged twiddles, five radix-4 layers) with two LDS exchanges, the second one across the two waves
+//   3. for each of the five key pieces: products and their sum over the two rows, inverse transform (decimation in time, ten
+//      radix-2 stages) with two LDS exchanges, the first one across the two waves; rounding to integers, shifted add into
+//      the accumulator.
+// Positions: p = 0 .. 1023 with bits b9 .. b0; before the forward and after the inverse transform p is the coefficient, in
+// between the bit-reversed evaluation point.  Layouts (registers / lane bits from the top / wave):
+//   F1, I3: b9..b6 / b5..b0      F2: b5..b2 / b9..b6 b1 b0      F3, I1: component b2..b0 / b8..b3 / wave b9
+//   I2: b6..b3 / b9 b8 b7 b2 b1 b0
+// Exchanges place a point at 272 * (two bits) + 17 * (four bits) + (four bits) of a wave's buffer: the odd stride spreads the bits in
+// the middle over the 16 columns (of 16 bytes) that LDS serves at a time, so that with the orders below 16 neighbouring lanes always
+// touch 16 different columns when writing and when reading, and every register's slot is one lane base plus an immediate:
+//   F1 -> F2: b9 b8 / b7 b6 b5 b4 / b3 b2 b1 b0     F2 -> F3: b9 b8 / b5 b2 b4 b3 / b7 b6 b1 b0
+//   I1 -> I2 and I2 -> I3: b9 b8 / b3 b6 b5 b4 / b7 b2 b1 b0
+// The accumulator is kept negated (and so are the key's spectra): X^a ACC - ACC is then one exclusive-or and one addition with
+// carry per word.
+// Bound and shape: a step is about 4.8 k VALU instructions per wave (3.8 k of them FP64) against 17.3 k wave-instructions per
+// ciphertext of the residue kernel (slz_fused.hip).  Registers decide the rest: accumulator 64, spectra 64, transform 64 of 256,
+// two waves per SIMD; key words stream from L2 (320 KiB per step, every ciphertext reads all of it) through what is left.  Eight
+// waves (four ciphertexts) share one workgroup, i.e. one copy of the tables in LDS, and only the two waves of a ciphertext wait
+// for each other.  Measured with 742 steps (the residue kernel on the same card in brackets): 1024 ciphertexts 21.7 ms (33.0),
+// 16384: 352 ms (530), 301: 13.8 ms (15.7).
+#include "slz_fft.h"
+#include "slz_modarith.h"
+#include "slz_fused_common.h"
+
+#define FFT_WAVES 8                                 // waves per workgroup: four ciphertexts share one copy of the tables
+#define FFT_PAIRS (FFT_WAVES / 2)
+#define FFT_THREADS (64 * FFT_WAVES)
+#define FFT_BUF (4u * 272u * 16u)                   // bytes of a wave's exchange buffer: 1024 points, padded
+#define FFT_AHEAD 0                                 // positions (of four key words each) requested before the last inverse stage
+#define FFT_EARLY (FFT_AHEAD + 4)                   // and by its end: each of its eight butterflies frees the registers of half a position
+#define FFT_RING 4                                  // positions in registers at a time during the products
+#define FFT_FLAGS_OFF (FFT_WAVES * FFT_BUF + FFT_LDS_TAB * 16u)
+#define FFT_LDS_BYTES (FFT_FLAGS_OFF + 64u)
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+#define FFT_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// LDS by byte offset (32-bit addresses in the LDS address space)
+#define LDS_AS __attribute__((address_space(3)))
+__device__ __forceinline__ d2 lds_get(uint32_t byte) { return *(const LDS_AS d2 *)(uintptr_t)byte; }
+__device__ __forceinline__ void lds_put(uint32_t byte, d2 v) { *(LDS_AS d2 *)(uintptr_t)byte = v; }
+
+// global memory as "uniform base + 32-bit lane offset": one address register for all loads
+__device__ __forceinline__ d2 lane_get(const d2 *uniform_base, uint32_t lane) {
+    return *reinterpret_cast<const d2 *>(reinterpret_cast<const char *>(uniform_base) + lane * 16u);
+}
+
+template <int V> struct fft_int { static constexpr int value = V; };
+
+struct fft_args {
+    const uint64_t *lwe_in;
+    const uint64_t *luts;
+    const uint32_t *lut_idx;
+    const d2 *key;            // [n][FFT_KEY_STEP]
+    const d2 *tab;            // FFT_TAB_LEN entries
+    uint64_t *acc_out;
+    uint64_t *lwe_out;
+    uint32_t n, n_steps, batch, beta;
+    double f1[15][2];         // lane-uniform twiddles of the first two forward layers: (v, v^2, v^3) of block 0 and of the next four blocks
+};
+
+// x w for a plain complex factor
+__device__ __forceinline__ d2 cmul(d2 x, d2 w) {
+    d2 r;
+    r.x = __builtin_fma(-x.y, w.y, x.x * w.x);
+    r.y = __builtin_fma(x.y, w.x, x.x * w.y);
+    return r;
+}
+// forward radix-4: strides 2 n and n over (a0, a1, a2, a3) with v, v^2, v^3
+__device__ __forceinline__ void fwd4(d2 &a0, d2 &a1, d2 &a2, d2 &a3, d2 v, d2 v2, d2 v3) {
+    const d2 b1 = cmul(a1, v), b2 = cmul(a2, v2), b3 = cmul(a3, v3);
+    const d2 s = a0 + b2, d = a0 - b2, e = b1 + b3, f = b1 - b3;
+    a0 = s + e;
+    a1 = s - e;
+    a2.x = d.x - f.y; a2.y = d.y + f.x;
+    a3.x = d.x + f.y; a3.y = d.y - f.x;
+}
+// inverse radix-2, a +- w b with w = c (1 + i t) given as (c, t); TURN: w is further multiplied by -i
+template <bool TURN>
+__device__ __forceinline__ void inv2(d2 &a, d2 &b, d2 ct) {
+    const double ur = __builtin_fma(-ct.y, b.y, b.x), ui = __builtin_fma(ct.y, b.x, b.y);
+    const double vr = TURN ? ui : ur, vi = TURN ? -ur : ui;
+    b.x = __builtin_fma(-ct.x, vr, a.x);
+    b.y = __builtin_fma(-ct.x, vi, a.y);
+    a.x = __builtin_fma(ct.x, vr, a.x);
+    a.y = __builtin_fma(ct.x, vi, a.y);
+}
+// a +- b and a -+ i b
+__device__ __forceinline__ void add2(d2 &a, d2 &b) { const d2 t = b; b = a - t; a = a + t; }
+__device__ __forceinline__ void add2i(d2 &a, d2 &b) {                 // b <- a + i b, a <- a - i b  (twiddle -i)
+    const d2 t = b;
+    b.x = a.x - t.y; b.y = a.y + t.x;
+    a.x = a.x + t.y; a.y = a.y - t.x;
+}
+
+// acc += y 2^s for the bits y of (integer + 1.5 * 2^52): the bits of that constant lie above bit 50, so they leave the word with any
+// shift of 13 or more; a shift past 32 only concerns the upper half
+template <int s>
+__device__ __forceinline__ void add_shifted(uint64_t &acc, uint64_t y) {
+    if constexpr (s >= 32) {
+        // one 32-bit operation (spelled out: the compiler widens the plain expression to a 64-bit addition with its moves)
+        uint32_t hi = (uint32_t)(acc >> 32);
+        asm("v_lshl_add_u32 %0, %1, %2, %0" : "+v"(hi) : "v"((uint32_t)y), "n"(s - 32));
+        acc = ((uint64_t)hi << 32) | (uint32_t)acc;
+    } else {
+        acc += y << s;
+    }
+}
+
+// The two waves of a ciphertext follow each other through two counters per wave in LDS: `done` (its part of an exchange has
+// been written) and `free` (it has read what the other wave may overwrite next).  Both waves are resident in the same
+// workgroup and take the same sequence of steps, so every wait ends.  LDS operations of one wave execute in order, so a
+// counter written after data (or after reads) is seen after them.
+__device__ __forceinline__ void fft_signal(uint32_t flag, uint32_t value) {
+    asm volatile("" ::: "memory");
+    __hip_atomic_store((LDS_AS uint32_t *)(uintptr_t)flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ uint32_t fft_peek(uint32_t flag) {
+    return __hip_atomic_load((const LDS_AS uint32_t *)(uintptr_t)flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// `seen`: what an earlier fft_peek returned, so that a counter that has long arrived costs no LDS round trip here
+__device__ __forceinline__ void fft_wait(uint32_t flag, uint32_t seen, uint32_t value) {
+    asm volatile("" ::: "memory");
+    while ((int32_t)((uint32_t)__builtin_amdgcn_readfirstlane(seen) - value) < 0) {
+        __builtin_amdgcn_s_sleep(1);
+        seen = fft_peek(flag);
+    }
+    asm volatile("" ::: "memory");
+}
+
+// Values are complete here: pure arithmetic would otherwise be sunk past the waits below into the block that uses it.
+__device__ __forceinline__ void pin(d2 &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void pin(uint64_t &v) { asm volatile("" : "+v"(v)); }
+
+// A copy of the lane number that the compiler cannot trace back: the LDS addresses made from it are computed where they are
+// used (a few 32-bit operations) instead of being kept in registers across the whole step.
+__device__ __forceinline__ uint32_t fresh(uint32_t lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+template <int BETA>
+__global__ void __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_fft_blind_rotate(fft_args A) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const uint32_t lds = (uint32_t)(uintptr_t)(LDS_AS unsigned char *)lds_raw;
+    const uint32_t beta = BETA > 0 ? (uint32_t)BETA : A.beta;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t h = wave & 1u, pair = wave >> 1;
+    const uint32_t T0 = lds + wave * FFT_BUF, Tp0 = lds + (wave & ~1u) * FFT_BUF;   // buffer of component h; of both components
+    const uint32_t tab0 = lds + FFT_WAVES * FFT_BUF;
+    const uint32_t flags = lds + FFT_FLAGS_OFF;
+    const uint32_t my_done = flags + 4u * wave, my_free = my_done + 32u, his_done = flags + 4u * (wave ^ 1u), his_free = his_done + 32u;
+    for (uint32_t i = threadIdx.x; i < FFT_LDS_TAB; i += FFT_THREADS) lds_put(tab0 + 16u * i, A.tab[i]);
+    if (threadIdx.x < 16) *(LDS_AS uint32_t *)(uintptr_t)(flags + 4u * threadIdx.x) = 0;
+    __syncthreads();
+
+    const double magic = 6755399441055744.0;                          // 1.5 * 2^52: adding it rounds to an integer
+    uint32_t seq = 0;                                                 // exchanges so far
+    for (uint32_t c = blockIdx.x + pair * gridDim.x; c < A.batch; c += FFT_PAIRS * gridDim.x) {
+        const uint64_t *lwe = A.lwe_in + (size_t)c * (A.n + 1);
+        uint64_t accr[16], acci[16];                                  // negated coefficients 64 e + lane and 1024 + 64 e + lane of component h
+        if (h == 1) {
+            const uint32_t bt = slz_modswitch(lwe[A.n], 12);
+            const uint32_t r = (4096u - bt) & 4095u;
+            const uint64_t *lut = A.luts + (size_t)(A.lut_idx ? A.lut_idx[c] : 0) * 2048u;
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                accr[e] = (uint64_t)0 - slz_rot_coeff([&](uint32_t j) { return lut[j]; }, 64u * e + lane, r, 2048u);
+                acci[e] = (uint64_t)0 - slz_rot_coeff([&](uint32_t j) { return lut[j]; }, 1024u + 64u * e + lane, r, 2048u);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; e++) accr[e] = acci[e] = 0;
+        }
+
+        uint64_t mask = lwe[0];
+        for (uint32_t step = 0; step < A.n_steps; step++) {
+            // an opaque zero in every table and buffer address keeps the loads inside the step
+            int z;
+            asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+            uint32_t T = T0 + z;
+            // The SIMD serves its older wave first, which would let half of the ciphertexts of a compute unit run ahead and leave
+            // the SIMDs half empty at the end: of the two waves on a SIMD the one that is behind gets the priority.
+            if ((int32_t)(seq - (uint32_t)__builtin_amdgcn_readfirstlane(fft_peek(flags + 4u * (wave ^ 4u)))) > 0) __builtin_amdgcn_s_setprio(0);
+            else __builtin_amdgcn_s_setprio(2);
+            const uint32_t at = slz_modswitch(mask, 12);
+            mask = lwe[step + 1];                                     // the next step's word (the body after the last step)
+            // ---- 1. digits ----
+            d2 x[16];
+            {
+                LDS_AS uint64_t *S = (LDS_AS uint64_t *)(uintptr_t)T;
+#pragma unroll
+                for (int e = 0; e < 16; e++) { S[64 * e + lane] = accr[e]; S[1024 + 64 * e + lane] = acci[e]; }
+                // word (idx - at) mod 4096 of X^at ACC: eleven bits of address, the twelfth is the sign; its opposite (bit 14 of t)
+                // tells where the stored, negated word has to be negated again
+                const uint32_t rnd = 1u << (31 - beta), t0 = 8u * fresh(lane) + 0x4000u - 8u * at;
+                auto digit = [&](uint32_t t, uint64_t own) {
+                    const uint64_t a = *(const LDS_AS uint64_t *)(uintptr_t)(T + (t & 0x3ff8u));
+                    const uint32_t m = (uint32_t)((int32_t)(t << 17) >> 31);
+                    uint32_t carry;
+                    (void)__builtin_addc((uint32_t)a ^ m, (uint32_t)own, m & 1u, &carry);
+                    const uint32_t hi = __builtin_addc((uint32_t)(a >> 32) ^ m, (uint32_t)(own >> 32), carry, &carry);
+                    return (double)((int32_t)(hi + rnd) >> (32 - beta));
+                };
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    x[e].x = digit(t0 + 512u * e, accr[e]);
+                    x[e].y = digit(t0 + 8192u + 512u * e, acci[e]);
+                }
+            }
+            // ---- 2. forward transform ----
+            auto f1 = [&](int q) { d2 w; w.x = A.f1[q + z][0]; w.y = A.f1[q + z][1]; return w; };
+#pragma unroll
+            for (int e = 0; e < 4; e++) fwd4(x[e], x[e + 4], x[e + 8], x[e + 12], f1(0), f1(1), f1(2));
+#pragma unroll
+            for (int q = 0; q < 4; q++) fwd4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3], f1(3 + 3 * q), f1(4 + 3 * q), f1(5 + 3 * q));
+            {
+                const uint32_t ln = fresh(lane);
+                const uint32_t w = T + (ln >> 4) * 272u + (ln & 15u) * 16u;                              // b5 b4 / b3 b2 b1 b0
+#pragma unroll
+                for (int e = 0; e < 16; e++) lds_put(w + 16 * (272 * (e >> 2) + 68 * (e & 3)), x[e]);
+                const uint32_t r = T + (ln >> 4) * 4352u + ((ln >> 2) & 3u) * 1088u + (ln & 3u) * 16u;   // b9 b8 / b7 b6 / b1 b0
+#pragma unroll
+                for (int i = 0; i < 16; i++) x[i] = lds_get(r + 16 * (17 * (i >> 2) + 4 * (i & 3)));
+            }
+            {
+                const uint32_t tf = tab0 + z + FFT_F2_OFF * 16u + 16u * (fresh(lane) >> 2);
+                const d2 v = lds_get(tf), v2 = lds_get(tf + 256), v3 = lds_get(tf + 512);
+#pragma unroll
+                for (int i = 0; i < 4; i++) fwd4(x[i], x[i + 4], x[i + 8], x[i + 12], v, v2, v3);
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    fwd4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3], lds_get(tf + 256 * (3 + 3 * q)), lds_get(tf + 256 * (4 + 3 * q)),
+                         lds_get(tf + 256 * (5 + 3 * q)));
+            }
+            // key words of the first positions are requested one phase ahead of their use, here and at the end of every piece
+            const d2 *kp = A.key + (size_t)step * FFT_KEY_STEP + h * 2048u + z;
+            d2 kb[8][4];
+            d2 D[2][8];
+            {
+                const uint32_t ln = fresh(lane);
+                const uint32_t w = T + (ln >> 4) * 4352u + (ln & 15u) * 16u;                             // b9 b8 / b7 b6 b1 b0
+#pragma unroll
+                for (int i = 0; i < 16; i++)
+                    lds_put(w + 16 * 17 * (((i >> 3) & 1) * 8 + (i & 1) * 4 + ((i >> 2) & 1) * 2 + ((i >> 1) & 1)), x[i]);
+                seq++;
+                fft_signal(my_done, seq);
+                d2 f3[6];
+                const d2 *tabF3 = A.tab + FFT_F3_OFF + h * 384u + z;
+#pragma unroll
+                for (int q = 0; q < 6; q++) f3[q] = lane_get(tabF3 + 64 * q, lane);
+#pragma unroll
+                for (int k = 0; k < FFT_EARLY; k++)
+#pragma unroll
+                    for (int q = 0; q < 4; q++) kb[k][q] = lane_get(kp + (4 * k + q) * 64, lane);
+                FFT_FENCE();
+                fft_wait(his_done, fft_peek(his_done), seq);
+                const uint32_t lr = fresh(lane);                                                        // b8 b7 b6 b5 b4 b3
+                const uint32_t rd = Tp0 + z + h * 8704u + (lr >> 5) * 4352u + ((lr >> 2) & 1u) * 2176u + (lr & 3u) * 272u + ((lr >> 3) & 3u) * 64u;
+#pragma unroll
+                for (int cc = 0; cc < 2; cc++)
+#pragma unroll
+                    for (int k = 0; k < 8; k++) D[cc][k] = lds_get(rd + cc * FFT_BUF + 16 * (68 * (k >> 2) + (k & 3)));
+                fft_signal(my_free, seq);
+#pragma unroll
+                for (int cc = 0; cc < 2; cc++)
+#pragma unroll
+                    for (int b = 0; b < 2; b++) fwd4(D[cc][4 * b], D[cc][4 * b + 1], D[cc][4 * b + 2], D[cc][4 * b + 3], f3[3 * b], f3[3 * b + 1], f3[3 * b + 2]);
+            }
+            // ---- 3. key pieces ----
+            auto run_piece = [&](auto which) __attribute__((always_inline)) {
+                constexpr int piece = decltype(which)::value;
+                asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+                T = T0 + z;
+                d2 S[2][8];
+                FFT_FENCE();
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    FFT_FENCE();
+#pragma unroll
+                    for (int n = (k ? k + FFT_RING - 1 : FFT_EARLY); n < 8 && n < k + FFT_RING; n++)
+#pragma unroll
+                        for (int q = 0; q < 4; q++) kb[n][q] = lane_get(kp + (4 * n + q) * 64, lane);
+                    FFT_FENCE();
+#pragma unroll
+                    for (int cc = 0; cc < 2; cc++) {
+                        const d2 k0 = kb[k][cc], k1 = kb[k][2 + cc], a = D[0][k], b = D[1][k];
+                        S[cc][k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
+                        S[cc][k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
+                        pin(S[cc][k]);
+                    }
+                }
+                const uint32_t free_seen = fft_peek(his_free);
+                FFT_FENCE();
+                // I1: half-sizes 1, 2, 4 with constant twiddles
+                const double r2 = 0.70710678118654752440;
+#pragma unroll
+                for (int cc = 0; cc < 2; cc++) {
+                    d2 *s = S[cc];
+#pragma unroll
+                    for (int k = 0; k < 8; k += 2) add2(s[k], s[k + 1]);
+#pragma unroll
+                    for (int k = 0; k < 8; k += 4) { add2(s[k], s[k + 2]); add2i(s[k + 1], s[k + 3]); }
+                    add2(s[0], s[4]);
+                    add2i(s[2], s[6]);
+                    {   // twiddle sqrt(1/2) (1 - i)
+                        const double p = s[5].x + s[5].y, q = s[5].y - s[5].x;
+                        s[5].x = __builtin_fma(-r2, p, s[1].x); s[5].y = __builtin_fma(-r2, q, s[1].y);
+                        s[1].x = __builtin_fma(r2, p, s[1].x); s[1].y = __builtin_fma(r2, q, s[1].y);
+                    }
+                    {   // twiddle sqrt(1/2) (-1 - i)
+                        const double p = s[7].y - s[7].x, q = s[7].x + s[7].y;
+                        s[7].x = __builtin_fma(-r2, p, s[3].x); s[7].y = __builtin_fma(r2, q, s[3].y);
+                        s[3].x = __builtin_fma(r2, p, s[3].x); s[3].y = __builtin_fma(-r2, q, s[3].y);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 8; k++) { pin(S[0][k]); pin(S[1][k]); }
+                fft_wait(his_free, free_seen, seq);                  // the other wave has read the previous exchange
+                {
+                    const uint32_t ln = fresh(lane);                                                    // b8 b7 b6 b5 b4 b3
+                    const uint32_t w = Tp0 + z + h * 8704u + (ln >> 5) * 4352u + (ln & 1u) * 2176u + ((ln >> 1) & 7u) * 272u + ((ln >> 4) & 1u) * 128u;
+#pragma unroll
+                    for (int k = 0; k < 8; k++)
+#pragma unroll
+                        for (int cc = 0; cc < 2; cc++) lds_put(w + cc * FFT_BUF + 16 * k, S[cc][k]);
+                }
+                seq++;
+                fft_signal(my_done, seq);
+                // I2: half-sizes 8, 16, 32, 64; twiddles are requested ahead of the values they meet
+                const uint32_t t2 = tab0 + z + FFT_I2_OFF * 16u + 16u * (fresh(lane) & 7u);
+                const uint32_t t3 = tab0 + z + FFT_I3_OFF * 16u + 16u * fresh(lane);
+                {
+                    const d2 w0 = lds_get(t2), w1 = lds_get(t2 + 128);
+                    FFT_FENCE();
+                    fft_wait(his_done, fft_peek(his_done), seq);
+                    const uint32_t ln = fresh(lane);
+                    const uint32_t r0 = T + (ln >> 4) * 4352u + (ln & 15u) * 16u;                       // b9 b8 / b7 b2 b1 b0
+                    auto slot = [](int m) { return 16 * 17 * ((m & 1) * 8 + (m >> 1)); };                // register m = b6 b5 b4 b3
+#pragma unroll
+                    for (int m = 0; m < 16; m++) x[m] = lds_get(r0 + slot(m));
+                    const d2 w2 = lds_get(t2 + 256), w3 = lds_get(t2 + 384);
+                    FFT_FENCE();
+#pragma unroll
+                    for (int m = 0; m < 16; m += 2) inv2<false>(x[m], x[m + 1], w0);
+                    FFT_FENCE();
+#pragma unroll
+                    for (int m = 0; m < 16; m += 4) { inv2<false>(x[m], x[m + 2], w1); inv2<true>(x[m + 1], x[m + 3], w1); }
+                    FFT_FENCE();
+                    const d2 w4 = lds_get(t2 + 512), w5 = lds_get(t2 + 640), w6 = lds_get(t2 + 768), w7 = lds_get(t2 + 896);
+                    FFT_FENCE();
+#pragma unroll
+                    for (int m = 0; m < 16; m += 8) {
+                        inv2<false>(x[m], x[m + 4], w2); inv2<true>(x[m + 2], x[m + 6], w2);
+                        inv2<false>(x[m + 1], x[m + 5], w3); inv2<true>(x[m + 3], x[m + 7], w3);
+                    }
+                    // the last stage's results go out two butterflies at a time
+                    auto put = [&](int m) { lds_put(r0 + slot(m), x[m]); };
+                    FFT_FENCE();
+                    inv2<false>(x[0], x[8], w4); inv2<true>(x[4], x[12], w4);
+                    inv2<false>(x[1], x[9], w5); inv2<true>(x[5], x[13], w5);
+                    FFT_FENCE();
+                    put(0); put(8); put(4); put(12); put(1); put(9); put(5); put(13);
+                    inv2<false>(x[2], x[10], w6); inv2<true>(x[6], x[14], w6);
+                    inv2<false>(x[3], x[11], w7); inv2<true>(x[7], x[15], w7);
+                    put(2); put(10); put(6); put(14); put(3); put(11); put(7); put(15);
+                }
+                // I3: half-sizes 128, 256, 512 with the twist
+                {
+                    FFT_FENCE();
+                    const d2 w0 = lds_get(t3);
+                    const uint32_t ln = fresh(lane);                                                    // b5 b4 b3 b2 b1 b0
+                    const uint32_t r0 = T + ((ln >> 3) & 1u) * 2176u + (ln >> 4) * 272u + (ln & 7u) * 16u;
+#pragma unroll
+                    for (int e = 0; e < 16; e += 4)
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            const int f = e + (q >> 1) + 2 * (q & 1);          // b9 b8 b7 b6, in the order of the butterflies below
+                            x[f] = lds_get(r0 + 16 * (272 * (f >> 2) + 68 * (f & 1) + 8 * ((f >> 1) & 1)));
+                        }
+                    fft_signal(my_free, seq);
+                    const d2 w1 = lds_get(t3 + 1024), w2 = lds_get(t3 + 2048);
+                    FFT_FENCE();
+#pragma unroll
+                    for (int e = 0; e < 16; e += 4) { inv2<false>(x[e], x[e + 2], w0); inv2<true>(x[e + 1], x[e + 3], w0); }
+                    FFT_FENCE();
+                    kp += 4096u;
+                    if (piece + 1 < SLZ_FFT_PIECES) {
+#pragma unroll
+                        for (int k = 0; k < FFT_AHEAD; k++)
+#pragma unroll
+                            for (int q = 0; q < 4; q++) kb[k][q] = lane_get(kp + (4 * k + q) * 64, lane);
+                    }
+                    d2 c1[2], c2[2];
+                    c1[0] = lds_get(t3 + 3072); c2[0] = lds_get(t3 + 4096);
+                    FFT_FENCE();
+#pragma unroll
+                    for (int e = 0; e < 16; e += 8) {
+                        inv2<false>(x[e], x[e + 4], w1); inv2<true>(x[e + 2], x[e + 6], w1);
+                        inv2<false>(x[e + 1], x[e + 5], w2); inv2<true>(x[e + 3], x[e + 7], w2);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; e++) {
+                        FFT_FENCE();
+                        if (e + 1 < 8) { c1[(e + 1) & 1] = lds_get(t3 + 1024 * (5 + 2 * e)); c2[(e + 1) & 1] = lds_get(t3 + 1024 * (6 + 2 * e)); }
+                        FFT_FENCE();
+                        d2 a = cmul(x[e], c1[e & 1]), b = x[e + 8];
+                        inv2<false>(a, b, c2[e & 1]);
+                        // coefficients 64 e + lane (a) and 512 + 64 e + lane (b turned by -45 degrees), rounded
+                        const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
+                        const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
+                        const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 8], y2);
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 8], y3);
+                        pin(accr[e]); pin(acci[e]); pin(accr[e + 8]); pin(acci[e + 8]);
+                        if (piece + 1 < SLZ_FFT_PIECES) {
+                            FFT_FENCE();
+#pragma unroll
+                            for (int q = 0; q < 2; q++)
+                                kb[FFT_AHEAD + e / 2][2 * (e & 1) + q] = lane_get(kp + (4 * (FFT_AHEAD + e / 2) + 2 * (e & 1) + q) * 64, lane);
+                        }
+                    }
+                }
+            };
+            run_piece(fft_int<0>());
+            run_piece(fft_int<1>());
+            run_piece(fft_int<2>());
+            run_piece(fft_int<3>());
+            run_piece(fft_int<4>());
+            // ... and are taken back here for the piece with shift 0
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                accr[e] -= 0x4338000000000000ull;
+                acci[e] -= 0x4338000000000000ull;
+            }
+        }
+
+        if (A.acc_out) {
+            uint64_t *dst = A.acc_out + ((size_t)c * 2 + h) * 2048u;
+#pragma unroll
+            for (int e = 0; e < 16; e++) { dst[64u * e + lane] = (uint64_t)0 - accr[e]; dst[1024u + 64u * e + lane] = (uint64_t)0 - acci[e]; }
+        }
+        if (A.lwe_out) {
+            uint64_t *dst = A.lwe_out + (size_t)c * 2049u;
+            if (h == 0) {
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const uint32_t idx = 64u * e + lane;
+                    if (idx == 0) dst[0] = (uint64_t)0 - accr[0];
+                    else dst[2048u - idx] = accr[e];
+                    dst[1024u - idx] = acci[e];
+                }
+            } else if (lane == 0) {
+                dst[2048] = (uint64_t)0 - accr[0];
+            }
+        }
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------------------------------
+
+int slz_fft2048_setup() {
+    SLZ_HIP(hipFuncSetAttribute((const void *)k_fft_blind_rotate<23>, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
+    SLZ_HIP(hipFuncSetAttribute((const void *)k_fft_blind_rotate<0>, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
+    return SLZ_OK;
+}
+
+int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                             uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
+    fft_args A;
+    A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;
+    A.acc_out = acc_out; A.lwe_out = lwe_out;
+    A.n = ctx->prm.n; A.n_steps = n_steps; A.batch = batch; A.beta = ctx->prm.pbs_base_log;
+    for (int q = 0; q < 15; q++)
+        for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
+    const dim3 grid(slz_fused_grid(batch, 1));
+    if (A.beta == 23) hipLaunchKernelGGL(k_fft_blind_rotate<23>, grid, dim3(FFT_THREADS), FFT_LDS_BYTES, s, A);
+    else hipLaunchKernelGGL(k_fft_blind_rotate<0>, grid, dim3(FFT_THREADS), FFT_LDS_BYTES, s, A);
+    SLZ_HIP(hipGetLastError());
+    return SLZ_OK;
+}

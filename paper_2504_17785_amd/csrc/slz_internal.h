@@ -58,6 +58,10 @@ struct slz_ctx {
     uint32_t *fused_sync;     // arrival counters of the fused kernel's pacing between ciphertexts
     int fused_pacing;         // 1: workgroups of the N = 2048 fused kernel wait for each other between ciphertexts
     double fused_scalars[2][2][32];   // [prime][forward, inverse]: the lane-uniform twiddles of the fused kernel
+    int has_fft;              // N = 2048 through floating-point transforms: the error bound holds for this parameter set
+    void *fft_tab;            // its tables (slz_fft.h)
+    double *fft_prep_tab;     // double-double twiddles of the key preparation
+    double fft_f1[15][2];     // host copy of its lane-uniform twiddles
     int has_bign;             // large-N three-pass path available (N = 2048 G, k = 1)
     double *bign_rowA;        // [2][G][64] block-specific lane-uniform forward twiddles
     double *bign_rowB;        // [2][G][31][64] block-specific per-lane forward twiddles
@@ -131,6 +135,16 @@ void slz_fused_destroy(slz_ctx *ctx);
 int slz_fused_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx,
                            const double *bskp, uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out,
                            uint32_t batch, hipStream_t s);
+// floating-point transforms for N = 2048 (slz_fft.hip: tables and key, slz_fft2048.hip: kernel); their key form follows the
+// residue form of every prepared key
+int slz_fft_supported(const slz_params *p);
+int slz_fft_init(slz_ctx *ctx);
+void slz_fft_destroy(slz_ctx *ctx);
+size_t slz_fft_key_bytes(const slz_params *p);
+int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s);
+int slz_fft2048_setup();
+int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                             uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
 // large-N path (slz_bign.hip)
 int slz_bign_supported(const slz_params *p);
 int slz_bign_init(slz_ctx *ctx);

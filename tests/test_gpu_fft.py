@@ -1,0 +1,64 @@
+"""N = 2048 through exact floating-point transforms (batches above 256): bit for bit against the oracle and the generic path."""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slz():
+    import paper_2504_17785_amd as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    return oracle
+
+
+def _inputs(slz, batch, beta, n=3, extreme=False):
+    p = synth.CONFIGS[2].with_(name="fft", n=n, pbs_base_log=beta, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", n * 4 * 2048)
+    luts = synth.raw_words(p, "misc", 2 * 2048).reshape(2, 2048)
+    cts = synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1)
+    if extreme:
+        # key words whose pieces are all of the largest magnitude and sign patterns that line their spectra up, digits at
+        # -B/2 and B/2 - 1, rotations by N (X^N = -1: every difference is -2 ACC) and by odd amounts
+        bsk[:2 * 2048] = np.uint64(0x7FFF7FFBFFDFFEFF)
+        bsk[2 * 2048:4 * 2048:2] = np.uint64(1 << 63)
+        bsk[4 * 2048:8 * 2048:3] = np.uint64(0xF001800C00600300)
+        bsk[8 * 2048:] = np.uint64(0x0010008004002001) * np.uint64(0xFFF)
+        luts[0] = np.uint64(1 << 62)
+        luts[1, 0::2] = np.uint64((1 << 63) - (1 << 40))
+        luts[1, 1::2] = np.uint64(1 << 63)
+        cts[0::3] = np.uint64(1 << 63)
+        cts[1::3, 0] = np.uint64(1 << 63)
+    idx = (np.arange(batch) % 2).astype(np.uint32)
+    ctx = slz.Context(p, batch)
+    assert ctx.path == "fused_n2048"
+    d = [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy(idx.astype(np.int32)).cuda(),
+         ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, 1, 2, 2048)))]
+    return p, ctx, bsk.reshape(n, 2, 1, 2, 2048), luts, cts, idx, d
+
+
+# 2^23 is the largest base a context of this shape takes; 257 ciphertexts are the
+# smallest batch of this path, 1025 and 1300 give some pairs of waves a second one
+@pytest.mark.parametrize("batch,beta,extreme", [(257, 23, False), (300, 23, True), (300, 1, True), (260, 12, False),
+                                                (1025, 23, False), (1300, 22, True)])
+def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, batch, beta, extreme):
+    p, ctx, bsk, luts, cts, idx, d = _inputs(slz, batch, beta, extreme=extreme)
+    sample = np.array([0, 1, 2, 255, 256, batch - 1])
+    got = {s: ctx.blind_rotate_batch(*d, s) for s in (0, 1, p.n)}
+    out, out0 = ctx.pbs_batch(*d), ctx.pbs_batch(d[0], d[1], None, d[3])
+    ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)                       # the same prepared key
+    for s, acc in got.items():
+        assert torch.equal(acc, ctx.blind_rotate_batch(*d, s)), s
+        want = orc.blind_rotate_batch(p, cts[sample], luts, idx[sample], bsk, s)
+        assert np.array_equal(slz.to_host_u64(acc)[sample], want), s
+    assert torch.equal(out, ctx.pbs_batch(*d))
+    assert torch.equal(out0, ctx.pbs_batch(d[0], d[1], None, d[3]))
+    assert np.array_equal(slz.to_host_u64(out)[sample], orc.pbs_batch(p, cts[sample], luts, idx[sample], bsk))
