@@ -26,13 +26,20 @@ if ROOT not in sys.path:
 PEAK_ALU_TINSTR = 256 * 4 * 16 * 2.4e9 / 1e12      # 256 CUs x 4 SIMD16 x 2.4 GHz: FP64/INT32 lane-instructions per second
 
 
-def alu_model_ops_per_pbs(p) -> float:
+def alu_model_ops_per_pbs(p, generic=False) -> float:
     """Algorithmic VALU lane-instructions of one PBS, from this op table:
     8 per butterfly (6 modular multiply + add + sub), 7 per pointwise multiply-accumulate, 3 per inverse
     post-scaling beyond the butterflies' share (6-instruction modular multiply per coefficient), 12 per
-    decomposed coefficient (rotate, subtract, round, digit, convert) and 20 per CRT-lifted coefficient."""
+    decomposed coefficient (rotate, subtract, round, digit, convert) and 20 per CRT-lifted coefficient.
+    N = 2048, k = 1, l = 1 (floating-point transforms of 1024 complex points): forward 28 per radix-4 butterfly in five layers,
+    4 per complex multiply-add for two rows, two components and five key pieces, inverse 6 per butterfly in ten layers for two
+    components and five pieces, 12 per decomposed coefficient and 2 per coefficient and piece for rounding and adding."""
     logN = p.N.bit_length() - 1
     R, C = (p.k + 1) * p.pbs_level, p.k + 1
+    if (p.N, p.k, p.pbs_level) == (2048, 1, 1) and not generic:
+        M, pieces = p.N // 2, 5
+        return float(p.n) * (R * 5 * (M // 4) * 28 + pieces * R * C * M * 4 + pieces * C * 10 * (M // 2) * 6 + C * p.N * 12 +
+                             pieces * C * p.N * 2)
     per_prime = (R + C) * (p.N // 2) * logN * 8 + R * C * p.N * 7 + C * p.N * 6
     per_cmux = 2 * per_prime + C * p.N * (12 + 4 * (p.pbs_level - 1)) + C * p.N * 20
     return float(p.n) * per_cmux
@@ -287,7 +294,7 @@ def bench_loss(args):
 # ---- the PBS + keyswitch step of one configuration ---------------------------------------------------------------------
 
 PATH_SOURCES = {       # sources of the dominant kernel of each path (for the check that a stored traffic figure is current)
-    "fused_n2048": ("slz_fused.hip", "slz_wave_ntt.h", "slz_modarith.h"),
+    "fused_n2048": ("slz_fft2048.hip", "slz_fft.h", "slz_modarith.h"),
     "fused_n512": ("slz_fused_n512.hip", "slz_wave_ntt.h", "slz_modarith.h"),
     "three_pass_large_n": ("slz_bign.hip", "slz_wave_ntt.h", "slz_modarith.h"),
 }
@@ -434,7 +441,7 @@ class Workload:
     def report(self, t, generic=False):
         """Rates and roofline fractions of one timed run (`t` from run())."""
         p, batch, synth = self.p, self.batch, self.synth
-        achieved = alu_model_ops_per_pbs(p) * batch / (t["pbs_ms"] * 1e-3) / 1e12
+        achieved = alu_model_ops_per_pbs(p, generic) * batch / (t["pbs_ms"] * 1e-3) / 1e12
         prepared_bytes = self.ctx.bsk_prepared_bytes()
         r = {"workload": "%s: batch %d, n=%d, k=%d, N=%d, PBS 2^%d x %d, KS 2^%d x %d" % (
                  p.name, batch, p.n, p.k, p.N, p.pbs_base_log, p.pbs_level, p.ks_base_log, p.ks_level),
@@ -552,7 +559,7 @@ def main():
     ap.add_argument("--no-per-config", action="store_true", help="default run: skip configurations 1 to 4")
     ap.add_argument("--generic", action="store_true", help="force the generic multi-kernel path")
     ap.add_argument("--override", default="", help="comma-separated parameter overrides of the configuration, e.g. N=4096,pbs_base_log=22,n=256")
-    ap.add_argument("--no-pacing", action="store_true", help="fused N = 2048 kernel: let the workgroups run free between ciphertexts")
+    ap.add_argument("--no-pacing", action="store_true", help="set the pacing option of the N = 2048 path to 0 (accepted, without effect)")
     ap.add_argument("--large-n-block", type=int, default=0, help="large-N path: block size of the row pass, 1024 or 2048")
     ap.add_argument("--large-n-lanes", type=int, default=0, help="large-N path: 1 = one chunk at a time, 2 = two half chunks on two streams")
     ap.add_argument("--ksk-standard", action="store_true",

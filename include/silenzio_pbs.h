@@ -85,14 +85,9 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      scratch of 2 (k+1) l (k+1) N doubles per such ciphertext is allocated by the first such call);
                                      0 keeps the throughput kernels at every batch size; SLZ_E_INVALID_ARG without a large-N path */
 
-#define SLZ_OPT_FUSED_PACING 6    /* value 1 (default) or 0: the N = 2048 fused kernel's workgroups wait for each other between
-                                     ciphertexts (launches of more than 1024 ciphertexts) so that they keep reading the same key
-                                     rows from the L2; a wait as long as the waiting workgroup's own ciphertext took ends the
-                                     pacing for that launch; 0 lets them run free.  Value 2 (for tests of that give-up path):
-                                     paced, but a wait that is not satisfied at once gives up.  Results are identical in
-                                     every mode.  Larger batches of parameter sets whose products are exact through floating-point
-                                    transforms (every base this shape admits) take another kernel, which does not pace and
-                                    ignores the value.  SLZ_E_INVALID_ARG on other paths */
+#define SLZ_OPT_FUSED_PACING 6    /* values 0, 1 and 2, on the N = 2048 fused path: accepted and without effect.  They paced the workgroups of
+                                     an earlier kernel of this path; the present one reads its key from the caches evenly without.
+                                     SLZ_E_INVALID_ARG for other values and on other paths */
 
 #define SLZ_OPT_FAIL_ALLOC_AFTER 4 /* for tests of the out-of-memory handling: value v >= 0 makes the (v+1)-th scratch allocation
                                      from now (of any context of the process) return SLZ_E_NOMEM without touching the device,

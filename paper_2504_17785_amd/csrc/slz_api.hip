@@ -57,12 +57,6 @@ extern "C" int slz_ctx_create(const slz_params *params, uint32_t max_batch, slz_
     if (hipGetDevice(&ctx->device) != hipSuccess) { delete ctx; return SLZ_E_HIP; }
     rc = slz_build_tables(ctx);
     // specialised paths are optional: a shape they decline (SLZ_E_UNSUPPORTED) runs on the generic path
-    if (rc == SLZ_OK && slz_fused_supported(params)) {
-        rc = slz_fused_init(ctx);
-        ctx->has_fused = (rc == SLZ_OK);
-        ctx->fused_pacing = 1;
-        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
-    }
     if (rc == SLZ_OK && slz_fft_supported(params)) {
         rc = slz_fft_init(ctx);
         ctx->has_fft = (rc == SLZ_OK);
@@ -94,7 +88,6 @@ extern "C" int slz_ctx_create(const slz_params *params, uint32_t max_batch, slz_
 
 extern "C" int slz_ctx_destroy(slz_ctx *ctx) {
     if (!ctx) return SLZ_E_INVALID_ARG;
-    slz_fused_destroy(ctx);
     slz_fft_destroy(ctx);
     slz_fused1024_destroy(ctx);
     slz_fused512_destroy(ctx);
@@ -123,9 +116,7 @@ extern "C" int slz_ctx_set_option(slz_ctx *ctx, int option, int value) {
         return SLZ_E_INVALID_ARG;
     }
     if (option == SLZ_OPT_FUSED_PACING) {
-        if (!ctx->has_fused || value < 0 || value > 2) return SLZ_E_INVALID_ARG;
-        ctx->fused_pacing = value;
-        return SLZ_OK;
+        return !ctx->has_fft || value < 0 || value > 2 ? SLZ_E_INVALID_ARG : SLZ_OK;      // nothing paces any more
     }
     if (option == SLZ_OPT_LARGE_N_LATENCY) {
         if (!ctx->has_bign || (value != 0 && value != 1)) return SLZ_E_INVALID_ARG;
@@ -146,7 +137,7 @@ extern "C" const char *slz_pbs_path(const slz_ctx *ctx) {
     if (ctx->has_fused1024) return "fused_n1024";
     if (ctx->has_fused512) return "fused_n512";
     if (ctx->has_fused4096) return "fused_n4096";
-    return ctx->has_fused ? "fused_n2048" : (ctx->has_bign ? "three_pass_large_n" : "generic");
+    return ctx->has_fft ? "fused_n2048" : (ctx->has_bign ? "three_pass_large_n" : "generic");
 }
 
 extern "C" int slz_lut_encode(const slz_params *p, const uint64_t *table, uint32_t n_tables, uint64_t *lut_out) {
@@ -232,14 +223,9 @@ static int blind_rotate_common(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
         ((uintptr_t)lut_idx & 3u))
         return SLZ_E_INVALID_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
-    // Up to one ciphertext per compute unit the residue kernel's four waves per ciphertext are faster than the two of the
-    // floating-point kernel (742 steps: 9.5 against 14.4 ms); from 257 on, where both run two ciphertexts on some unit, it is 14.3
-    // against 15.4 ms at 301 and 20.4 against 31.2 ms at 1024.
-    if (ctx->has_fft && !ctx->force_generic && batch > 256)
+    if (ctx->has_fft && !ctx->force_generic)
         return slz_fft2048_blind_rotate(ctx, lwe_in, luts, lut_idx, (const char *)bskp + residue_key_bytes(ctx->prm), n_steps, acc_out,
                                         lwe_out, batch, s);
-    if (ctx->has_fused && !ctx->force_generic)
-        return slz_fused_blind_rotate(ctx, lwe_in, luts, lut_idx, (const double *)bskp, n_steps, acc_out, lwe_out, batch, s);
     if (ctx->has_fused4096 && !ctx->force_generic)
         return slz_fused4096_blind_rotate(ctx, lwe_in, luts, lut_idx, (const double *)bskp, n_steps, acc_out, lwe_out, batch, s);
     if (ctx->has_fused512 && !ctx->force_generic)

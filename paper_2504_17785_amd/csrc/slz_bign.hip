@@ -172,7 +172,7 @@ k_big_rows(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
 #pragma unroll
             for (int u = 0; u < 8; u++) x[8 * g + u] = r8[u];
         }
-        fused_inv<false>(x, T, tb.inv, tb.inv, tb.post, m, lane, z);
+        fused_inv(x, T, tb.inv, tb.inv, m, lane, z);
         double *dst = A.Y + (((size_t)b * 2 + q) * 2 + comp) * N + 2048u * row;
 #pragma unroll
         for (int g = 0; g < 4; g++) {

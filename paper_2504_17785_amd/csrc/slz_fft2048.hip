@@ -20,25 +20,30 @@
 //   I1 -> I2 and I2 -> I3: b9 b8 / b3 b6 b5 b4 / b7 b2 b1 b0
 // The accumulator is kept negated (and so are the key's spectra): X^a ACC - ACC is then one exclusive-or and one addition with
 // carry per word.
-// Bound and shape: a step is about 4.8 k VALU instructions per wave (3.8 k of them FP64) against 17.3 k wave-instructions per
-// ciphertext of the residue kernel (slz_fused.hip).  Registers decide the rest: accumulator 64, spectra 64, transform 64 of 256,
-// two waves per SIMD; key words stream from L2 (320 KiB per step, every ciphertext reads all of it) through what is left.  Eight
-// waves (four ciphertexts) share one workgroup, i.e. one copy of the tables in LDS, and only the two waves of a ciphertext wait
-// for each other.  Measured with 742 steps (the residue kernel on the same card in brackets): 1024 ciphertexts 21.7 ms (33.0),
-// 16384: 352 ms (530), 301: 13.8 ms (15.7).
+// Bound and shape: a step is about 4.6 k VALU instructions per wave (3.8 k of them FP64); two 50-bit residues took 17.3 k
+// wave-instructions per ciphertext.  Registers decide the rest: accumulator 64, spectra 64, transform 64 of 256, two waves per
+// SIMD; key words stream from L2 (320 KiB per step, every ciphertext reads all of it) through what is left.  Eight waves (four
+// ciphertexts) share one workgroup, i.e. one copy of the tables in LDS, and only the two waves of a ciphertext wait for each other.
+// Two waves hide little of each other's LDS round trips, so loads are requested in groups ahead of the arithmetic, and results are
+// written while the next ones are computed.  Measured with 742 steps (in brackets: two residues on the same card): 1024 ciphertexts
+// 20.2 ms (31.5), 4096: 80.6 (126.6), 301: 12.9 (15.4).
+// Batches up to 256 leave three of a compute unit's four pairs idle, and a pair alone needs 12.9 ms; there all four work on one
+// ciphertext (WIDE): 256 ciphertexts 8.2 ms (9.7 with residues), one 8.9 ms (9.5).
 #include "slz_fft.h"
 #include "slz_modarith.h"
 #include "slz_fused_common.h"
 
 #define FFT_WAVES 8                                 // waves per workgroup: four ciphertexts share one copy of the tables
 #define FFT_PAIRS (FFT_WAVES / 2)
+#define FFT_WIDE_MAX 256                            // batches up to this take the shared form, one workgroup per ciphertext
 #define FFT_THREADS (64 * FFT_WAVES)
 #define FFT_BUF (4u * 272u * 16u)                   // bytes of a wave's exchange buffer: 1024 points, padded
 #define FFT_AHEAD 0                                 // positions (of four key words each) requested before the last inverse stage
 #define FFT_EARLY (FFT_AHEAD + 4)                   // and by its end: each of its eight butterflies frees the registers of half a position
 #define FFT_RING 4                                  // positions in registers at a time during the products
 #define FFT_FLAGS_OFF (FFT_WAVES * FFT_BUF + FFT_LDS_TAB * 16u)
-#define FFT_LDS_BYTES (FFT_FLAGS_OFF + 64u)
+#define FFT_FLAGS 34u                               // done and free per wave; for WIDE: spectra written (2), read (8), sums written (8)
+#define FFT_LDS_BYTES (FFT_FLAGS_OFF + 4u * FFT_FLAGS)
 
 typedef double d2 __attribute__((ext_vector_type(2)));
 #define FFT_FENCE() __builtin_amdgcn_sched_barrier(0)
@@ -148,7 +153,11 @@ __device__ __forceinline__ uint32_t fresh(uint32_t lane) {
     return lane;
 }
 
-template <int BETA>
+// WIDE = false: a workgroup's four pairs of waves take a ciphertext each.  WIDE = true, for batches of at most one ciphertext per
+// compute unit: all four pairs work on one.  Pair 0 owns the accumulator and runs step 1 and the forward transform; every pair reads
+// the spectra from pair 0's exchange buffers and takes one or two of the key pieces (its first piece's key words wait in registers
+// by then); the sums of the other pairs come back through their exchange buffers.
+template <int BETA, bool WIDE>
 __global__ void __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_fft_blind_rotate(fft_args A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -162,319 +171,424 @@ k_fft_blind_rotate(fft_args A) {
     const uint32_t flags = lds + FFT_FLAGS_OFF;
     const uint32_t my_done = flags + 4u * wave, my_free = my_done + 32u, his_done = flags + 4u * (wave ^ 1u), his_free = his_done + 32u;
     for (uint32_t i = threadIdx.x; i < FFT_LDS_TAB; i += FFT_THREADS) lds_put(tab0 + 16u * i, A.tab[i]);
-    if (threadIdx.x < 16) *(LDS_AS uint32_t *)(uintptr_t)(flags + 4u * threadIdx.x) = 0;
+    if (threadIdx.x < FFT_FLAGS) *(LDS_AS uint32_t *)(uintptr_t)(flags + 4u * threadIdx.x) = 0;
+    const uint32_t spectra_done = flags + 64u, spectra_read = flags + 72u, sums_done = flags + 104u;     // WIDE: counted in steps
     __syncthreads();
 
     const double magic = 6755399441055744.0;                          // 1.5 * 2^52: adding it rounds to an integer
-    uint32_t seq = 0;                                                 // exchanges so far
-    for (uint32_t c = blockIdx.x + pair * gridDim.x; c < A.batch; c += FFT_PAIRS * gridDim.x) {
-        const uint64_t *lwe = A.lwe_in + (size_t)c * (A.n + 1);
-        uint64_t accr[16], acci[16];                                  // negated coefficients 64 e + lane and 1024 + 64 e + lane of component h
-        if (h == 1) {
-            const uint32_t bt = slz_modswitch(lwe[A.n], 12);
-            const uint32_t r = (4096u - bt) & 4095u;
-            const uint64_t *lut = A.luts + (size_t)(A.lut_idx ? A.lut_idx[c] : 0) * 2048u;
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                accr[e] = (uint64_t)0 - slz_rot_coeff([&](uint32_t j) { return lut[j]; }, 64u * e + lane, r, 2048u);
-                acci[e] = (uint64_t)0 - slz_rot_coeff([&](uint32_t j) { return lut[j]; }, 1024u + 64u * e + lane, r, 2048u);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 16; e++) accr[e] = acci[e] = 0;
-        }
-
-        uint64_t mask = lwe[0];
-        for (uint32_t step = 0; step < A.n_steps; step++) {
-            // an opaque zero in every table and buffer address keeps the loads inside the step
-            int z;
-            asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-            uint32_t T = T0 + z;
-            // The SIMD serves its older wave first, which would let half of the ciphertexts of a compute unit run ahead and leave
-            // the SIMDs half empty at the end: of the two waves on a SIMD the one that is behind gets the priority.
-            if ((int32_t)(seq - (uint32_t)__builtin_amdgcn_readfirstlane(fft_peek(flags + 4u * (wave ^ 4u)))) > 0) __builtin_amdgcn_s_setprio(0);
-            else __builtin_amdgcn_s_setprio(2);
-            const uint32_t at = slz_modswitch(mask, 12);
-            mask = lwe[step + 1];                                     // the next step's word (the body after the last step)
-            // ---- 1. digits ----
-            d2 x[16];
-            {
-                LDS_AS uint64_t *S = (LDS_AS uint64_t *)(uintptr_t)T;
-#pragma unroll
-                for (int e = 0; e < 16; e++) { S[64 * e + lane] = accr[e]; S[1024 + 64 * e + lane] = acci[e]; }
-                // word (idx - at) mod 4096 of X^at ACC: eleven bits of address, the twelfth is the sign; its opposite (bit 14 of t)
-                // tells where the stored, negated word has to be negated again
-                const uint32_t rnd = 1u << (31 - beta), t0 = 8u * fresh(lane) + 0x4000u - 8u * at;
-                auto digit = [&](uint32_t t, uint64_t own) {
-                    const uint64_t a = *(const LDS_AS uint64_t *)(uintptr_t)(T + (t & 0x3ff8u));
-                    const uint32_t m = (uint32_t)((int32_t)(t << 17) >> 31);
-                    uint32_t carry;
-                    (void)__builtin_addc((uint32_t)a ^ m, (uint32_t)own, m & 1u, &carry);
-                    const uint32_t hi = __builtin_addc((uint32_t)(a >> 32) ^ m, (uint32_t)(own >> 32), carry, &carry);
-                    return (double)((int32_t)(hi + rnd) >> (32 - beta));
-                };
+    uint32_t seq = 0;                                                 // exchanges of this pair so far
+    uint32_t tick = 0;                                                // WIDE: steps so far
+    // One loop per kind of wave, so that each keeps only its own values in registers.  ROLE: pair number, or FFT_PAIRS when the pair has
+    // the ciphertext to itself.
+    auto rotate = [&](auto role) __attribute__((always_inline)) {
+        constexpr int ROLE = decltype(role)::value;
+        constexpr bool owner = ROLE == 0 || ROLE == FFT_PAIRS;
+        for (uint32_t c = WIDE ? blockIdx.x : blockIdx.x + pair * gridDim.x; c < A.batch; c += (WIDE ? 1u : FFT_PAIRS) * gridDim.x) {
+            const uint64_t *lwe = A.lwe_in + (size_t)c * (A.n + 1);
+            uint64_t accr[16], acci[16];                                  // negated coefficients 64 e + lane and 1024 + 64 e + lane of component h
+            const uint32_t li = fresh(lane);
+            if (owner && h == 1) {
+                const uint32_t bt = slz_modswitch(lwe[A.n], 12);
+                const uint32_t r = (4096u - bt) & 4095u;
+                const uint64_t *lut = A.luts + (size_t)(A.lut_idx ? A.lut_idx[c] : 0) * 2048u;
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
-                    x[e].x = digit(t0 + 512u * e, accr[e]);
-                    x[e].y = digit(t0 + 8192u + 512u * e, acci[e]);
+                    accr[e] = (uint64_t)0 - slz_rot_coeff([&](uint32_t j) { return lut[j]; }, 64u * e + li, r, 2048u);
+                    acci[e] = (uint64_t)0 - slz_rot_coeff([&](uint32_t j) { return lut[j]; }, 1024u + 64u * e + li, r, 2048u);
                 }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; e++) accr[e] = acci[e] = 0;
             }
-            // ---- 2. forward transform ----
-            auto f1 = [&](int q) { d2 w; w.x = A.f1[q + z][0]; w.y = A.f1[q + z][1]; return w; };
+
+            // The owner's accumulator is written to its buffer whenever it is complete: here and at the end of every step.
+            auto stage = [&](int e) {
+                LDS_AS uint64_t *S = (LDS_AS uint64_t *)(uintptr_t)T0;
+                S[64 * e + lane] = accr[e];
+                S[1024 + 64 * e + lane] = acci[e];
+            };
+            if constexpr (owner) {
 #pragma unroll
-            for (int e = 0; e < 4; e++) fwd4(x[e], x[e + 4], x[e + 8], x[e + 12], f1(0), f1(1), f1(2));
-#pragma unroll
-            for (int q = 0; q < 4; q++) fwd4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3], f1(3 + 3 * q), f1(4 + 3 * q), f1(5 + 3 * q));
-            {
-                const uint32_t ln = fresh(lane);
-                const uint32_t w = T + (ln >> 4) * 272u + (ln & 15u) * 16u;                              // b5 b4 / b3 b2 b1 b0
-#pragma unroll
-                for (int e = 0; e < 16; e++) lds_put(w + 16 * (272 * (e >> 2) + 68 * (e & 3)), x[e]);
-                const uint32_t r = T + (ln >> 4) * 4352u + ((ln >> 2) & 3u) * 1088u + (ln & 3u) * 16u;   // b9 b8 / b7 b6 / b1 b0
-#pragma unroll
-                for (int i = 0; i < 16; i++) x[i] = lds_get(r + 16 * (17 * (i >> 2) + 4 * (i & 3)));
+                for (int e = 0; e < 16; e++) stage(e);
             }
-            {
-                const uint32_t tf = tab0 + z + FFT_F2_OFF * 16u + 16u * (fresh(lane) >> 2);
-                const d2 v = lds_get(tf), v2 = lds_get(tf + 256), v3 = lds_get(tf + 512);
-#pragma unroll
-                for (int i = 0; i < 4; i++) fwd4(x[i], x[i + 4], x[i + 8], x[i + 12], v, v2, v3);
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-                    fwd4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3], lds_get(tf + 256 * (3 + 3 * q)), lds_get(tf + 256 * (4 + 3 * q)),
-                         lds_get(tf + 256 * (5 + 3 * q)));
-            }
-            // key words of the first positions are requested one phase ahead of their use, here and at the end of every piece
-            const d2 *kp = A.key + (size_t)step * FFT_KEY_STEP + h * 2048u + z;
-            d2 kb[8][4];
-            d2 D[2][8];
-            {
-                const uint32_t ln = fresh(lane);
-                const uint32_t w = T + (ln >> 4) * 4352u + (ln & 15u) * 16u;                             // b9 b8 / b7 b6 b1 b0
-#pragma unroll
-                for (int i = 0; i < 16; i++)
-                    lds_put(w + 16 * 17 * (((i >> 3) & 1) * 8 + (i & 1) * 4 + ((i >> 2) & 1) * 2 + ((i >> 1) & 1)), x[i]);
-                seq++;
-                fft_signal(my_done, seq);
-                d2 f3[6];
-                const d2 *tabF3 = A.tab + FFT_F3_OFF + h * 384u + z;
-#pragma unroll
-                for (int q = 0; q < 6; q++) f3[q] = lane_get(tabF3 + 64 * q, lane);
-#pragma unroll
-                for (int k = 0; k < FFT_EARLY; k++)
-#pragma unroll
-                    for (int q = 0; q < 4; q++) kb[k][q] = lane_get(kp + (4 * k + q) * 64, lane);
-                FFT_FENCE();
-                fft_wait(his_done, fft_peek(his_done), seq);
-                const uint32_t lr = fresh(lane);                                                        // b8 b7 b6 b5 b4 b3
-                const uint32_t rd = Tp0 + z + h * 8704u + (lr >> 5) * 4352u + ((lr >> 2) & 1u) * 2176u + (lr & 3u) * 272u + ((lr >> 3) & 3u) * 64u;
-#pragma unroll
-                for (int cc = 0; cc < 2; cc++)
-#pragma unroll
-                    for (int k = 0; k < 8; k++) D[cc][k] = lds_get(rd + cc * FFT_BUF + 16 * (68 * (k >> 2) + (k & 3)));
-                fft_signal(my_free, seq);
-#pragma unroll
-                for (int cc = 0; cc < 2; cc++)
-#pragma unroll
-                    for (int b = 0; b < 2; b++) fwd4(D[cc][4 * b], D[cc][4 * b + 1], D[cc][4 * b + 2], D[cc][4 * b + 3], f3[3 * b], f3[3 * b + 1], f3[3 * b + 2]);
-            }
-            // ---- 3. key pieces ----
-            auto run_piece = [&](auto which) __attribute__((always_inline)) {
-                constexpr int piece = decltype(which)::value;
+            uint64_t mask = owner ? lwe[0] : 0;
+            for (uint32_t step = 0; step < A.n_steps; step++) {
+                // an opaque zero in every table and buffer address keeps the loads inside the step
+                int z;
                 asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-                T = T0 + z;
-                d2 S[2][8];
-                FFT_FENCE();
-#pragma unroll
-                for (int k = 0; k < 8; k++) {
-                    FFT_FENCE();
-#pragma unroll
-                    for (int n = (k ? k + FFT_RING - 1 : FFT_EARLY); n < 8 && n < k + FFT_RING; n++)
-#pragma unroll
-                        for (int q = 0; q < 4; q++) kb[n][q] = lane_get(kp + (4 * n + q) * 64, lane);
-                    FFT_FENCE();
-#pragma unroll
-                    for (int cc = 0; cc < 2; cc++) {
-                        const d2 k0 = kb[k][cc], k1 = kb[k][2 + cc], a = D[0][k], b = D[1][k];
-                        S[cc][k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
-                        S[cc][k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
-                        pin(S[cc][k]);
-                    }
+                uint32_t T = T0 + z;
+                tick++;
+                if (!WIDE) {
+                    // The SIMD serves its older wave first, which would let half of the ciphertexts of a compute unit run ahead and leave
+                    // the SIMDs half empty at the end: of the two waves on a SIMD the one that is behind gets the priority.
+                    if ((int32_t)(seq - (uint32_t)__builtin_amdgcn_readfirstlane(fft_peek(flags + 4u * (wave ^ 4u)))) > 0) __builtin_amdgcn_s_setprio(0);
+                    else __builtin_amdgcn_s_setprio(2);
                 }
-                const uint32_t free_seen = fft_peek(his_free);
-                FFT_FENCE();
-                // I1: half-sizes 1, 2, 4 with constant twiddles
-                const double r2 = 0.70710678118654752440;
+                const d2 *kp = A.key + (size_t)step * FFT_KEY_STEP + h * 2048u + z;
+                d2 kb[8][4];
+                uint32_t kl = fresh(lane);
+                auto request = [&](int k) {
 #pragma unroll
-                for (int cc = 0; cc < 2; cc++) {
-                    d2 *s = S[cc];
+                    for (int q = 0; q < 4; q++) kb[k][q] = lane_get(kp + (4 * k + q) * 64, kl);
+                };
+                d2 x[16];
+                if constexpr (owner) {
+                    const uint32_t at = slz_modswitch(mask, 12);
+                    mask = lwe[step + 1];                                     // the next step's word (the body after the last step)
+                    // ---- 1. digits ----
+                    {
+                        // word (idx - at) mod 4096 of X^at ACC: eleven bits of address, the twelfth is the sign; its opposite (bit 14 of t)
+                        // tells where the stored, negated word has to be negated again
+                        const uint32_t rnd = 1u << (31 - beta), t0 = 8u * fresh(lane) + 0x4000u - 8u * at;
+                        auto word = [&](uint32_t t) { return *(const LDS_AS uint64_t *)(uintptr_t)(T + (t & 0x3ff8u)); };
+                        auto digit = [&](uint32_t t, uint64_t a, uint64_t own) {
+                            const uint32_t m = (uint32_t)((int32_t)(t << 17) >> 31);
+                            uint32_t lo = (uint32_t)a ^ m, hi = (uint32_t)(a >> 32) ^ m;
+                            asm("v_cmp_ne_u32_e32 vcc, 0, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %3, vcc\n\tv_addc_co_u32_e32 %1, vcc, %1, %4, vcc"
+                                : "+v"(lo), "+v"(hi) : "v"(m), "v"((uint32_t)own), "v"((uint32_t)(own >> 32)) : "vcc");
+                            return (double)((int32_t)(hi + rnd) >> (32 - beta));
+                        };
+                        // eight words are in flight while the previous eight become digits
+                        uint64_t a[2][8];
 #pragma unroll
-                    for (int k = 0; k < 8; k += 2) add2(s[k], s[k + 1]);
+                        for (int i = 0; i < 8; i++) a[0][i] = word(t0 + 512u * i);
 #pragma unroll
-                    for (int k = 0; k < 8; k += 4) { add2(s[k], s[k + 2]); add2i(s[k + 1], s[k + 3]); }
-                    add2(s[0], s[4]);
-                    add2i(s[2], s[6]);
-                    {   // twiddle sqrt(1/2) (1 - i)
-                        const double p = s[5].x + s[5].y, q = s[5].y - s[5].x;
-                        s[5].x = __builtin_fma(-r2, p, s[1].x); s[5].y = __builtin_fma(-r2, q, s[1].y);
-                        s[1].x = __builtin_fma(r2, p, s[1].x); s[1].y = __builtin_fma(r2, q, s[1].y);
-                    }
-                    {   // twiddle sqrt(1/2) (-1 - i)
-                        const double p = s[7].y - s[7].x, q = s[7].x + s[7].y;
-                        s[7].x = __builtin_fma(-r2, p, s[3].x); s[7].y = __builtin_fma(r2, q, s[3].y);
-                        s[3].x = __builtin_fma(r2, p, s[3].x); s[3].y = __builtin_fma(-r2, q, s[3].y);
-                    }
-                }
+                        for (int g = 0; g < 4; g++) {                        // real parts 0..7, 8..15, imaginary parts 0..7, 8..15
+                            FFT_FENCE();
+                            if (g < 3) {
 #pragma unroll
-                for (int k = 0; k < 8; k++) { pin(S[0][k]); pin(S[1][k]); }
-                fft_wait(his_free, free_seen, seq);                  // the other wave has read the previous exchange
-                {
-                    const uint32_t ln = fresh(lane);                                                    // b8 b7 b6 b5 b4 b3
-                    const uint32_t w = Tp0 + z + h * 8704u + (ln >> 5) * 4352u + (ln & 1u) * 2176u + ((ln >> 1) & 7u) * 272u + ((ln >> 4) & 1u) * 128u;
-#pragma unroll
-                    for (int k = 0; k < 8; k++)
-#pragma unroll
-                        for (int cc = 0; cc < 2; cc++) lds_put(w + cc * FFT_BUF + 16 * k, S[cc][k]);
-                }
-                seq++;
-                fft_signal(my_done, seq);
-                // I2: half-sizes 8, 16, 32, 64; twiddles are requested ahead of the values they meet
-                const uint32_t t2 = tab0 + z + FFT_I2_OFF * 16u + 16u * (fresh(lane) & 7u);
-                const uint32_t t3 = tab0 + z + FFT_I3_OFF * 16u + 16u * fresh(lane);
-                {
-                    const d2 w0 = lds_get(t2), w1 = lds_get(t2 + 128);
-                    FFT_FENCE();
-                    fft_wait(his_done, fft_peek(his_done), seq);
-                    const uint32_t ln = fresh(lane);
-                    const uint32_t r0 = T + (ln >> 4) * 4352u + (ln & 15u) * 16u;                       // b9 b8 / b7 b2 b1 b0
-                    auto slot = [](int m) { return 16 * 17 * ((m & 1) * 8 + (m >> 1)); };                // register m = b6 b5 b4 b3
-#pragma unroll
-                    for (int m = 0; m < 16; m++) x[m] = lds_get(r0 + slot(m));
-                    const d2 w2 = lds_get(t2 + 256), w3 = lds_get(t2 + 384);
-                    FFT_FENCE();
-#pragma unroll
-                    for (int m = 0; m < 16; m += 2) inv2<false>(x[m], x[m + 1], w0);
-                    FFT_FENCE();
-#pragma unroll
-                    for (int m = 0; m < 16; m += 4) { inv2<false>(x[m], x[m + 2], w1); inv2<true>(x[m + 1], x[m + 3], w1); }
-                    FFT_FENCE();
-                    const d2 w4 = lds_get(t2 + 512), w5 = lds_get(t2 + 640), w6 = lds_get(t2 + 768), w7 = lds_get(t2 + 896);
-                    FFT_FENCE();
-#pragma unroll
-                    for (int m = 0; m < 16; m += 8) {
-                        inv2<false>(x[m], x[m + 4], w2); inv2<true>(x[m + 2], x[m + 6], w2);
-                        inv2<false>(x[m + 1], x[m + 5], w3); inv2<true>(x[m + 3], x[m + 7], w3);
-                    }
-                    // the last stage's results go out two butterflies at a time
-                    auto put = [&](int m) { lds_put(r0 + slot(m), x[m]); };
-                    FFT_FENCE();
-                    inv2<false>(x[0], x[8], w4); inv2<true>(x[4], x[12], w4);
-                    inv2<false>(x[1], x[9], w5); inv2<true>(x[5], x[13], w5);
-                    FFT_FENCE();
-                    put(0); put(8); put(4); put(12); put(1); put(9); put(5); put(13);
-                    inv2<false>(x[2], x[10], w6); inv2<true>(x[6], x[14], w6);
-                    inv2<false>(x[3], x[11], w7); inv2<true>(x[7], x[15], w7);
-                    put(2); put(10); put(6); put(14); put(3); put(11); put(7); put(15);
-                }
-                // I3: half-sizes 128, 256, 512 with the twist
-                {
-                    FFT_FENCE();
-                    const d2 w0 = lds_get(t3);
-                    const uint32_t ln = fresh(lane);                                                    // b5 b4 b3 b2 b1 b0
-                    const uint32_t r0 = T + ((ln >> 3) & 1u) * 2176u + (ln >> 4) * 272u + (ln & 7u) * 16u;
-#pragma unroll
-                    for (int e = 0; e < 16; e += 4)
-#pragma unroll
-                        for (int q = 0; q < 4; q++) {
-                            const int f = e + (q >> 1) + 2 * (q & 1);          // b9 b8 b7 b6, in the order of the butterflies below
-                            x[f] = lds_get(r0 + 16 * (272 * (f >> 2) + 68 * (f & 1) + 8 * ((f >> 1) & 1)));
-                        }
-                    fft_signal(my_free, seq);
-                    const d2 w1 = lds_get(t3 + 1024), w2 = lds_get(t3 + 2048);
-                    FFT_FENCE();
-#pragma unroll
-                    for (int e = 0; e < 16; e += 4) { inv2<false>(x[e], x[e + 2], w0); inv2<true>(x[e + 1], x[e + 3], w0); }
-                    FFT_FENCE();
-                    kp += 4096u;
-                    if (piece + 1 < SLZ_FFT_PIECES) {
-#pragma unroll
-                        for (int k = 0; k < FFT_AHEAD; k++)
-#pragma unroll
-                            for (int q = 0; q < 4; q++) kb[k][q] = lane_get(kp + (4 * k + q) * 64, lane);
-                    }
-                    d2 c1[2], c2[2];
-                    c1[0] = lds_get(t3 + 3072); c2[0] = lds_get(t3 + 4096);
-                    FFT_FENCE();
-#pragma unroll
-                    for (int e = 0; e < 16; e += 8) {
-                        inv2<false>(x[e], x[e + 4], w1); inv2<true>(x[e + 2], x[e + 6], w1);
-                        inv2<false>(x[e + 1], x[e + 5], w2); inv2<true>(x[e + 3], x[e + 7], w2);
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; e++) {
-                        FFT_FENCE();
-                        if (e + 1 < 8) { c1[(e + 1) & 1] = lds_get(t3 + 1024 * (5 + 2 * e)); c2[(e + 1) & 1] = lds_get(t3 + 1024 * (6 + 2 * e)); }
-                        FFT_FENCE();
-                        d2 a = cmul(x[e], c1[e & 1]), b = x[e + 8];
-                        inv2<false>(a, b, c2[e & 1]);
-                        // coefficients 64 e + lane (a) and 512 + 64 e + lane (b turned by -45 degrees), rounded
-                        const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
-                        const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
-                        const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 8], y2);
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 8], y3);
-                        pin(accr[e]); pin(acci[e]); pin(accr[e + 8]); pin(acci[e + 8]);
-                        if (piece + 1 < SLZ_FFT_PIECES) {
+                                for (int i = 0; i < 8; i++) a[(g + 1) & 1][i] = word(t0 + 4096u * (g + 1) + 512u * i);
+                            }
                             FFT_FENCE();
 #pragma unroll
-                            for (int q = 0; q < 2; q++)
-                                kb[FFT_AHEAD + e / 2][2 * (e & 1) + q] = lane_get(kp + (4 * (FFT_AHEAD + e / 2) + 2 * (e & 1) + q) * 64, lane);
+                            for (int i = 0; i < 8; i++) {
+                                const uint32_t t = t0 + 4096u * g + 512u * i;
+                                if (g < 2) x[8 * g + i].x = digit(t, a[g & 1][i], accr[8 * g + i]);
+                                else x[8 * (g - 2) + i].y = digit(t, a[g & 1][i], acci[8 * (g - 2) + i]);
+                            }
+                        }
+                    }
+                    // ---- 2. forward transform ----
+                    auto f1 = [&](int q) { d2 w; w.x = A.f1[q + z][0]; w.y = A.f1[q + z][1]; return w; };
+#pragma unroll
+                    for (int e = 0; e < 4; e++) fwd4(x[e], x[e + 4], x[e + 8], x[e + 12], f1(0), f1(1), f1(2));
+                    {
+                        // results go out as they are made; the next layer's twiddles are requested ahead of the values they meet
+                        const uint32_t ln = fresh(lane);
+                        const uint32_t w = T + (ln >> 4) * 272u + (ln & 15u) * 16u;                              // b5 b4 / b3 b2 b1 b0
+                        const uint32_t r = T + (ln >> 4) * 4352u + ((ln >> 2) & 3u) * 1088u + (ln & 3u) * 16u;   // b9 b8 / b7 b6 / b1 b0
+                        const uint32_t tf = tab0 + z + FFT_F2_OFF * 16u + 16u * (ln >> 2);
+                        d2 v[3], u[2][3];
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            fwd4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3], f1(3 + 3 * q), f1(4 + 3 * q), f1(5 + 3 * q));
+                            FFT_FENCE();
+#pragma unroll
+                            for (int e = 4 * q; e < 4 * q + 4; e++) lds_put(w + 16 * (272 * (e >> 2) + 68 * (e & 3)), x[e]);
+                        }
+#pragma unroll
+                        for (int t = 0; t < 3; t++) v[t] = lds_get(tf + 256 * t);
+#pragma unroll
+                        for (int i = 0; i < 4; i++)
+#pragma unroll
+                            for (int m = i; m < 16; m += 4) x[m] = lds_get(r + 16 * (17 * (m >> 2) + 4 * (m & 3)));
+#pragma unroll
+                        for (int t = 0; t < 3; t++) u[0][t] = lds_get(tf + 256 * (3 + t));
+                        FFT_FENCE();
+#pragma unroll
+                        for (int i = 0; i < 4; i++) fwd4(x[i], x[i + 4], x[i + 8], x[i + 12], v[0], v[1], v[2]);
+                        const uint32_t le = fresh(lane);
+                        const uint32_t o = T + (le >> 4) * 4352u + (le & 15u) * 16u;                             // b9 b8 / b7 b6 b1 b0
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            FFT_FENCE();
+                            if (q < 3) {
+#pragma unroll
+                                for (int t = 0; t < 3; t++) u[(q + 1) & 1][t] = lds_get(tf + 256 * (6 + 3 * q + t));
+                            }
+                            FFT_FENCE();
+                            fwd4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3], u[q & 1][0], u[q & 1][1], u[q & 1][2]);
+                            FFT_FENCE();
+#pragma unroll
+                            for (int i = 4 * q; i < 4 * q + 4; i++)
+                                lds_put(o + 16 * 17 * (((i >> 3) & 1) * 8 + (i & 1) * 4 + ((i >> 2) & 1) * 2 + ((i >> 1) & 1)), x[i]);
+                        }
+                        if (WIDE) {
+                            fft_signal(spectra_done + 4u * wave, tick);
+                        } else {
+                            seq++;
+                            fft_signal(my_done, seq);
                         }
                     }
                 }
-            };
-            run_piece(fft_int<0>());
-            run_piece(fft_int<1>());
-            run_piece(fft_int<2>());
-            run_piece(fft_int<3>());
-            run_piece(fft_int<4>());
-            // ... and are taken back here for the piece with shift 0
+                d2 D[2][8];
+                {
+                    d2 f3[6];
+                    const d2 *tabF3 = A.tab + FFT_F3_OFF + h * 384u + z;
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                accr[e] -= 0x4338000000000000ull;
-                acci[e] -= 0x4338000000000000ull;
-            }
-        }
-
-        if (A.acc_out) {
-            uint64_t *dst = A.acc_out + ((size_t)c * 2 + h) * 2048u;
+                    for (int q = 0; q < 6; q++) f3[q] = lane_get(tabF3 + 64 * q, kl);
+                    // key words of the first positions are requested one phase ahead of their use, here and at the end of every piece
+                    if constexpr (!owner) {
+                        kp += ROLE * 4096u;                               // pairs 1, 2, 3 begin with pieces 1, 2, 3
 #pragma unroll
-            for (int e = 0; e < 16; e++) { dst[64u * e + lane] = (uint64_t)0 - accr[e]; dst[1024u + 64u * e + lane] = (uint64_t)0 - acci[e]; }
-        }
-        if (A.lwe_out) {
-            uint64_t *dst = A.lwe_out + (size_t)c * 2049u;
-            if (h == 0) {
+                        for (int k = 0; k < 8; k++) request(k);
+                    } else {
 #pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    const uint32_t idx = 64u * e + lane;
-                    if (idx == 0) dst[0] = (uint64_t)0 - accr[0];
-                    else dst[2048u - idx] = accr[e];
-                    dst[1024u - idx] = acci[e];
+                        for (int k = 0; k < FFT_EARLY; k++) request(k);
+                    }
+                    FFT_FENCE();
+                    if (WIDE) {
+                        fft_wait(spectra_done, fft_peek(spectra_done), tick);
+                        fft_wait(spectra_done + 4u, fft_peek(spectra_done + 4u), tick);
+                    } else {
+                        fft_wait(his_done, fft_peek(his_done), seq);
+                    }
+                    const uint32_t lr = fresh(lane);                                                        // b8 b7 b6 b5 b4 b3
+                    const uint32_t rd = (WIDE ? lds : Tp0) + z + h * 8704u + (lr >> 5) * 4352u + ((lr >> 2) & 1u) * 2176u + (lr & 3u) * 272u + ((lr >> 3) & 3u) * 64u;
+#pragma unroll
+                    for (int cc = 0; cc < 2; cc++)
+#pragma unroll
+                        for (int k = 0; k < 8; k++) D[cc][k] = lds_get(rd + cc * FFT_BUF + 16 * (68 * (k >> 2) + (k & 3)));
+                    if (WIDE) fft_signal(spectra_read + 4u * wave, tick);
+                    else fft_signal(my_free, seq);
+#pragma unroll
+                    for (int cc = 0; cc < 2; cc++)
+#pragma unroll
+                        for (int b = 0; b < 2; b++) fwd4(D[cc][4 * b], D[cc][4 * b + 1], D[cc][4 * b + 2], D[cc][4 * b + 3], f3[3 * b], f3[3 * b + 1], f3[3 * b + 2]);
                 }
-            } else if (lane == 0) {
-                dst[2048] = (uint64_t)0 - accr[0];
+                // ---- 3. key pieces ----
+                // `early`: positions requested before the piece begins; `next`: the piece that this wave takes afterwards, or -1
+                auto run_piece = [&](auto which, auto early, auto then) __attribute__((always_inline)) {
+                    constexpr int piece = decltype(which)::value, ahead = decltype(early)::value, next = decltype(then)::value;
+                    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+                    T = T0 + z;
+                    d2 S[2][8];
+                    FFT_FENCE();
+                    const uint32_t free_seen = fft_peek(his_free);
+#pragma unroll
+                    for (int k = 0; k < 8; k++) {
+                        FFT_FENCE();
+#pragma unroll
+                        for (int n = (k ? k + FFT_RING - 1 : ahead); n < 8 && n < k + FFT_RING; n++)
+                            if (n >= ahead) request(n);
+                        FFT_FENCE();
+#pragma unroll
+                        for (int cc = 0; cc < 2; cc++) {
+                            const d2 k0 = kb[k][cc], k1 = kb[k][2 + cc], a = D[0][k], b = D[1][k];
+                            S[cc][k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
+                            S[cc][k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
+                            pin(S[cc][k]);
+                        }
+                    }
+                    FFT_FENCE();
+                    // I1: half-sizes 1, 2, 4 with constant twiddles
+                    const double r2 = 0.70710678118654752440;
+                    auto inv8 = [&](d2 *s) {
+#pragma unroll
+                        for (int k = 0; k < 8; k += 2) add2(s[k], s[k + 1]);
+#pragma unroll
+                        for (int k = 0; k < 8; k += 4) { add2(s[k], s[k + 2]); add2i(s[k + 1], s[k + 3]); }
+                        add2(s[0], s[4]);
+                        add2i(s[2], s[6]);
+                        {   // twiddle sqrt(1/2) (1 - i)
+                            const double p = s[5].x + s[5].y, q = s[5].y - s[5].x;
+                            s[5].x = __builtin_fma(-r2, p, s[1].x); s[5].y = __builtin_fma(-r2, q, s[1].y);
+                            s[1].x = __builtin_fma(r2, p, s[1].x); s[1].y = __builtin_fma(r2, q, s[1].y);
+                        }
+                        {   // twiddle sqrt(1/2) (-1 - i)
+                            const double p = s[7].y - s[7].x, q = s[7].x + s[7].y;
+                            s[7].x = __builtin_fma(-r2, p, s[3].x); s[7].y = __builtin_fma(r2, q, s[3].y);
+                            s[3].x = __builtin_fma(r2, p, s[3].x); s[3].y = __builtin_fma(-r2, q, s[3].y);
+                        }
+                    };
+                    inv8(S[0]);
+#pragma unroll
+                    for (int k = 0; k < 8; k++) pin(S[0][k]);
+                    fft_wait(his_free, free_seen, seq);                  // the other wave has read the previous exchange
+                    if (WIDE && piece == 0) {                            // pair 0 writes where all eight waves read the spectra
+#pragma unroll
+                        for (uint32_t q = 0; q < FFT_WAVES; q++) fft_wait(spectra_read + 4u * q, fft_peek(spectra_read + 4u * q), tick);
+                    }
+                    {
+                        const uint32_t ln = fresh(lane);                                                    // b8 b7 b6 b5 b4 b3
+                        const uint32_t w = Tp0 + z + h * 8704u + (ln >> 5) * 4352u + (ln & 1u) * 2176u + ((ln >> 1) & 7u) * 272u + ((ln >> 4) & 1u) * 128u;
+#pragma unroll
+                        for (int k = 0; k < 8; k++) lds_put(w + 16 * k, S[0][k]);
+                        inv8(S[1]);
+#pragma unroll
+                        for (int k = 0; k < 8; k++) lds_put(w + FFT_BUF + 16 * k, S[1][k]);
+                    }
+                    seq++;
+                    fft_signal(my_done, seq);
+                    // I2: half-sizes 8, 16, 32, 64; twiddles are requested ahead of the values they meet
+                    const uint32_t t2 = tab0 + z + FFT_I2_OFF * 16u + 16u * (fresh(lane) & 7u);
+                    const uint32_t t3 = tab0 + z + FFT_I3_OFF * 16u + 16u * fresh(lane);
+                    {
+                        const d2 w0 = lds_get(t2), w1 = lds_get(t2 + 128);
+                        FFT_FENCE();
+                        fft_wait(his_done, fft_peek(his_done), seq);
+                        const uint32_t ln = fresh(lane);
+                        const uint32_t r0 = T + (ln >> 4) * 4352u + (ln & 15u) * 16u;                       // b9 b8 / b7 b2 b1 b0
+                        auto slot = [](int m) { return 16 * 17 * ((m & 1) * 8 + (m >> 1)); };                // register m = b6 b5 b4 b3
+#pragma unroll
+                        for (int m = 0; m < 16; m++) x[m] = lds_get(r0 + slot(m));
+                        const d2 w2 = lds_get(t2 + 256), w3 = lds_get(t2 + 384);
+                        FFT_FENCE();
+#pragma unroll
+                        for (int m = 0; m < 16; m += 2) inv2<false>(x[m], x[m + 1], w0);
+                        FFT_FENCE();
+#pragma unroll
+                        for (int m = 0; m < 16; m += 4) { inv2<false>(x[m], x[m + 2], w1); inv2<true>(x[m + 1], x[m + 3], w1); }
+                        FFT_FENCE();
+                        const d2 w4 = lds_get(t2 + 512), w5 = lds_get(t2 + 640), w6 = lds_get(t2 + 768), w7 = lds_get(t2 + 896);
+                        FFT_FENCE();
+#pragma unroll
+                        for (int m = 0; m < 16; m += 8) {
+                            inv2<false>(x[m], x[m + 4], w2); inv2<true>(x[m + 2], x[m + 6], w2);
+                            inv2<false>(x[m + 1], x[m + 5], w3); inv2<true>(x[m + 3], x[m + 7], w3);
+                        }
+                        // the last stage's results go out two butterflies at a time
+                        auto put = [&](int m) { lds_put(r0 + slot(m), x[m]); };
+                        FFT_FENCE();
+                        inv2<false>(x[0], x[8], w4); inv2<true>(x[4], x[12], w4);
+                        inv2<false>(x[1], x[9], w5); inv2<true>(x[5], x[13], w5);
+                        FFT_FENCE();
+                        put(0); put(8); put(4); put(12); put(1); put(9); put(5); put(13);
+                        inv2<false>(x[2], x[10], w6); inv2<true>(x[6], x[14], w6);
+                        inv2<false>(x[3], x[11], w7); inv2<true>(x[7], x[15], w7);
+                        put(2); put(10); put(6); put(14); put(3); put(11); put(7); put(15);
+                    }
+                    // I3: half-sizes 128, 256, 512 with the twist
+                    {
+                        FFT_FENCE();
+                        const d2 w0 = lds_get(t3);
+                        const uint32_t ln = fresh(lane);                                                    // b5 b4 b3 b2 b1 b0
+                        const uint32_t r0 = T + ((ln >> 3) & 1u) * 2176u + (ln >> 4) * 272u + (ln & 7u) * 16u;
+#pragma unroll
+                        for (int e = 0; e < 16; e += 4)
+#pragma unroll
+                            for (int q = 0; q < 4; q++) {
+                                const int f = e + (q >> 1) + 2 * (q & 1);          // b9 b8 b7 b6, in the order of the butterflies below
+                                x[f] = lds_get(r0 + 16 * (272 * (f >> 2) + 68 * (f & 1) + 8 * ((f >> 1) & 1)));
+                            }
+                        fft_signal(my_free, seq);
+                        const d2 w1 = lds_get(t3 + 1024), w2 = lds_get(t3 + 2048);
+                        FFT_FENCE();
+#pragma unroll
+                        for (int e = 0; e < 16; e += 4) { inv2<false>(x[e], x[e + 2], w0); inv2<true>(x[e + 1], x[e + 3], w0); }
+                        FFT_FENCE();
+                        kp += 4096u;
+                        if (next >= 0) {
+#pragma unroll
+                            for (int k = 0; k < FFT_AHEAD; k++) request(k);
+                        }
+                        d2 c1[2], c2[2];
+                        c1[0] = lds_get(t3 + 3072); c2[0] = lds_get(t3 + 4096);
+                        FFT_FENCE();
+#pragma unroll
+                        for (int e = 0; e < 16; e += 8) {
+                            inv2<false>(x[e], x[e + 4], w1); inv2<true>(x[e + 2], x[e + 6], w1);
+                            inv2<false>(x[e + 1], x[e + 5], w2); inv2<true>(x[e + 3], x[e + 7], w2);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 8; e++) {
+                            FFT_FENCE();
+                            if (e + 1 < 8) { c1[(e + 1) & 1] = lds_get(t3 + 1024 * (5 + 2 * e)); c2[(e + 1) & 1] = lds_get(t3 + 1024 * (6 + 2 * e)); }
+                            FFT_FENCE();
+                            d2 a = cmul(x[e], c1[e & 1]), b = x[e + 8];
+                            inv2<false>(a, b, c2[e & 1]);
+                            // coefficients 64 e + lane (a) and 512 + 64 e + lane (b turned by -45 degrees), rounded
+                            const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
+                            const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
+                            const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
+                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
+                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
+                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 8], y2);
+                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 8], y3);
+                            if (piece == 0) {                            // the bits of `magic` that shift 0 has left
+                                accr[e] -= 0x4338000000000000ull; acci[e] -= 0x4338000000000000ull;
+                                accr[e + 8] -= 0x4338000000000000ull; acci[e + 8] -= 0x4338000000000000ull;
+                            }
+                            pin(accr[e]); pin(acci[e]); pin(accr[e + 8]); pin(acci[e + 8]);
+                            if (!WIDE && next < 0) { stage(e); stage(e + 8); }
+                            if (next >= 0) {
+                                FFT_FENCE();
+#pragma unroll
+                                for (int q = 0; q < 2; q++)
+                                    kb[FFT_AHEAD + e / 2][2 * (e & 1) + q] = lane_get(kp + (4 * (FFT_AHEAD + e / 2) + 2 * (e & 1) + q) * 64, kl);
+                            }
+                        }
+                    }
+                };
+                fft_int<FFT_EARLY> first;
+                fft_int<8> all;
+                fft_int<-1> none;
+                if constexpr (!WIDE) {
+                    run_piece(fft_int<0>(), first, fft_int<1>());
+                    run_piece(fft_int<1>(), first, fft_int<2>());
+                    run_piece(fft_int<2>(), first, fft_int<3>());
+                    run_piece(fft_int<3>(), first, fft_int<4>());
+                    run_piece(fft_int<4>(), first, none);
+                } else if constexpr (owner) {
+                    run_piece(fft_int<0>(), first, none);
+#pragma unroll 1
+                    for (uint32_t q = 1; q < FFT_PAIRS; q++) {
+                        const uint32_t flag = sums_done + 4u * (2 * q + h);
+                        fft_wait(flag, fft_peek(flag), tick);
+                        const LDS_AS uint64_t *S = (const LDS_AS uint64_t *)(uintptr_t)(T + 2u * q * FFT_BUF);
+#pragma unroll
+                        for (int e = 0; e < 16; e++) { accr[e] += S[64 * e + lane]; acci[e] += S[1024 + 64 * e + lane]; }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 16; e++) stage(e);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16; e++) accr[e] = acci[e] = 0;
+                    if constexpr (ROLE < 3) run_piece(fft_int<ROLE>(), all, none);
+                    else { run_piece(fft_int<3>(), all, fft_int<4>()); run_piece(fft_int<4>(), first, none); }
+                    LDS_AS uint64_t *S = (LDS_AS uint64_t *)(uintptr_t)T;
+#pragma unroll
+                    for (int e = 0; e < 16; e++) { S[64 * e + lane] = accr[e]; S[1024 + 64 * e + lane] = acci[e]; }
+                    fft_signal(sums_done + 4u * wave, tick);
+                }
+            }
+
+            if constexpr (!owner) continue;
+            const uint32_t lo = fresh(lane);
+            if (A.acc_out) {
+                uint64_t *dst = A.acc_out + ((size_t)c * 2 + h) * 2048u;
+#pragma unroll
+                for (int e = 0; e < 16; e++) { dst[64u * e + lo] = (uint64_t)0 - accr[e]; dst[1024u + 64u * e + lo] = (uint64_t)0 - acci[e]; }
+            }
+            if (A.lwe_out) {
+                uint64_t *dst = A.lwe_out + (size_t)c * 2049u;
+                if (h == 0) {
+#pragma unroll
+                    for (int e = 0; e < 16; e++) {
+                        const uint32_t idx = 64u * e + lo;
+                        if (idx == 0) dst[0] = (uint64_t)0 - accr[0];
+                        else dst[2048u - idx] = accr[e];
+                        dst[1024u - idx] = acci[e];
+                    }
+                } else if (lo == 0) {
+                    dst[2048] = (uint64_t)0 - accr[0];
+                }
             }
         }
-    }
+    };
+    if constexpr (!WIDE) rotate(fft_int<FFT_PAIRS>());
+    else if (pair == 0) rotate(fft_int<0>());
+    else if (pair == 1) rotate(fft_int<1>());
+    else if (pair == 2) rotate(fft_int<2>());
+    else rotate(fft_int<3>());
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------------
 
 int slz_fft2048_setup() {
-    SLZ_HIP(hipFuncSetAttribute((const void *)k_fft_blind_rotate<23>, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
-    SLZ_HIP(hipFuncSetAttribute((const void *)k_fft_blind_rotate<0>, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
+    const void *const kernels[4] = {(const void *)k_fft_blind_rotate<23, false>, (const void *)k_fft_blind_rotate<0, false>,
+                                    (const void *)k_fft_blind_rotate<23, true>, (const void *)k_fft_blind_rotate<0, true>};
+    for (const void *k : kernels) SLZ_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
     return SLZ_OK;
 }
 
@@ -486,9 +600,17 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
     A.n = ctx->prm.n; A.n_steps = n_steps; A.batch = batch; A.beta = ctx->prm.pbs_base_log;
     for (int q = 0; q < 15; q++)
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
-    const dim3 grid(slz_fused_grid(batch, 1));
-    if (A.beta == 23) hipLaunchKernelGGL(k_fft_blind_rotate<23>, grid, dim3(FFT_THREADS), FFT_LDS_BYTES, s, A);
-    else hipLaunchKernelGGL(k_fft_blind_rotate<0>, grid, dim3(FFT_THREADS), FFT_LDS_BYTES, s, A);
+    const uint32_t grid = slz_fused_grid(batch, 1);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(FFT_THREADS), FFT_LDS_BYTES, s, A); };
+    // Up to one ciphertext per compute unit, its four pairs share the ciphertext's work: 8.2 ms for 256 ciphertexts and 742 steps,
+    // 12.9 ms with a pair for each.  From 257 on, the shared form needs a second round: 17.1 ms against 12.9 ms.
+    if (batch <= FFT_WIDE_MAX) {
+        if (A.beta == 23) launch(k_fft_blind_rotate<23, true>);
+        else launch(k_fft_blind_rotate<0, true>);
+    } else {
+        if (A.beta == 23) launch(k_fft_blind_rotate<23, false>);
+        else launch(k_fft_blind_rotate<0, false>);
+    }
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;
 }

@@ -1,4 +1,4 @@
-// Host-side pieces shared by the fused blind-rotation kernels (N = 512, 1024, 2048, 4096): the argument fields every one
+// Host-side pieces shared by the fused blind-rotation kernels (N = 512, 1024, 4096): the argument fields every one
 // of them takes, the worst-case bound check of their fixed reduction schedules, and the launch shape.
 #pragma once
 #include "slz_internal.h"
@@ -67,6 +67,6 @@ static inline uint32_t slz_fused_grid(uint32_t batch, uint32_t per_cu) {
 // host copy of the lane-uniform inverse twiddles inv[t + j], t + j < 32, of both primes (kernel-argument scalars)
 static inline int slz_fused_load_inv_scalars(slz_ctx *ctx) {
     for (int q = 0; q < 2; q++)
-        SLZ_HIP(hipMemcpy(ctx->fused_scalars[q][1], ctx->tab[q].inv, 32 * sizeof(double), hipMemcpyDeviceToHost));
+        SLZ_HIP(hipMemcpy(ctx->fused_scalars[q], ctx->tab[q].inv, 32 * sizeof(double), hipMemcpyDeviceToHost));
     return SLZ_OK;
 }

@@ -287,7 +287,7 @@ int slz_fused1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
     for (int q = 0; q < 2; q++) {
         A.rowA[q] = ctx->fused1024_rowA + (size_t)q * 64;
         A.rowB[q] = ctx->fused1024_rowB + (size_t)q * 15 * 64;
-        for (int x = 0; x < 16; x++) A.tw_inv[q][x] = ctx->fused_scalars[q][1][x];
+        for (int x = 0; x < 16; x++) A.tw_inv[q][x] = ctx->fused_scalars[q][x];
     }
     if (ctx->prm.k == 2) {
         const uint32_t grid = slz_fused_grid(batch, 2);    // six waves and 70 KiB of LDS per workgroup: two per compute unit

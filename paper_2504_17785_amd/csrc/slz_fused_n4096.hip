@@ -165,7 +165,7 @@ k_fused_blind_rotate_n4096(fused4096_args A) {
             }
             __syncthreads();                          // sibling has read my buffer before I reuse it
             // 4. inverse transform inside the block, then the stage across the two blocks and the twist
-            fused_inv<false>(x, T, twS, invt, post, m, lane, z);
+            fused_inv(x, T, twS, invt, m, lane, z);
             // twiddles of the stage across the blocks (inv[2048 + c]) and the twist (post[2048 b + c]), c = 64 e + lane: requested
             // one group of four coefficients ahead of their use, the first group before the exchange
             double wv[2][4], pw[2][4];
@@ -269,7 +269,7 @@ int slz_fused4096_init(slz_ctx *ctx) {
     if (rc != SLZ_OK) return rc;
     for (int q = 0; q < 2; q++) {
         SLZ_HIP(hipMemcpy(ctx->fused4096_scalars[q], ctx->fused4096_rowA + (size_t)q * 2 * 64, 2 * 64 * sizeof(double), hipMemcpyDeviceToHost));
-        SLZ_HIP(hipMemcpy(ctx->fused_scalars[q][1], ctx->tab[q].inv, 32 * sizeof(double), hipMemcpyDeviceToHost));
+        SLZ_HIP(hipMemcpy(ctx->fused_scalars[q], ctx->tab[q].inv, 32 * sizeof(double), hipMemcpyDeviceToHost));
         SLZ_HIP(hipMemcpy(&ctx->fused4096_w1[q], ctx->tab[q].fwd + 1, sizeof(double), hipMemcpyDeviceToHost));
     }
     SLZ_HIP(hipFuncSetAttribute((const void *)k_fused_blind_rotate_n4096<22>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -295,7 +295,7 @@ int slz_fused4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
         A.rowB[q] = ctx->fused4096_rowB + (size_t)q * 2 * 31 * 64;
         for (int blk = 0; blk < 2; blk++)
             for (int x = 0; x < 32; x++) A.tw_fwd[q][blk][x] = ctx->fused4096_scalars[q][blk * 64 + x];
-        for (int x = 0; x < 32; x++) A.tw_inv[q][x] = ctx->fused_scalars[q][1][x];
+        for (int x = 0; x < 32; x++) A.tw_inv[q][x] = ctx->fused_scalars[q][x];
         A.w_first[q] = ctx->fused4096_w1[q];
     }
     const uint32_t grid = slz_fused_grid(batch, 1);    // one workgroup (136 KiB of LDS, eight waves) per compute unit

@@ -438,7 +438,7 @@ int slz_fused512_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64
     for (int q = 0; q < 2; q++) {
         A.rowA[q] = ctx->fused512_rowA + (size_t)q * 64;
         A.rowB[q] = ctx->fused512_rowB + (size_t)q * 15 * 64;
-        for (int x = 0; x < 16; x++) A.tw_inv[q][x] = ctx->fused_scalars[q][1][x];
+        for (int x = 0; x < 16; x++) A.tw_inv[q][x] = ctx->fused_scalars[q][x];
     }
     if (ctx->prm.pbs_level == 2) {
         const uint32_t grid = slz_fused_grid(batch, 2);

@@ -40,7 +40,6 @@ struct slz_ctx {
     uint32_t max_batch;
     int device;
     int force_generic;
-    int has_fused;
     int has_fused4096;        // the N = 4096 fused kernel is available
     double *fused4096_rowA, *fused4096_rowB;   // its block tables: [2][2][64] and [2][2][31][64]
     double fused4096_scalars[2][128];          // host copy of fused4096_rowA (lane-uniform entries go into the kernel arguments)
@@ -54,10 +53,7 @@ struct slz_ctx {
     double two32[2];          // 2^32 mod p_i (centred)
     double p1inv_mod_p2;      // p1^{-1} mod p2 (centred)
     slz_tables tab[2];
-    double *fused_tab;        // tables re-laid-out for the fused kernel (or null)
-    uint32_t *fused_sync;     // arrival counters of the fused kernel's pacing between ciphertexts
-    int fused_pacing;         // 1: workgroups of the N = 2048 fused kernel wait for each other between ciphertexts
-    double fused_scalars[2][2][32];   // [prime][forward, inverse]: the lane-uniform twiddles of the fused kernel
+    double fused_scalars[2][32];      // [prime]: the lane-uniform inverse twiddles of the fused kernels
     int has_fft;              // N = 2048 through floating-point transforms: the error bound holds for this parameter set
     void *fft_tab;            // its tables (slz_fft.h)
     double *fft_prep_tab;     // double-double twiddles of the key preparation
@@ -128,13 +124,6 @@ int slz_fused1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
 // *dB [2][N/BS][BS/64 - 1][64], device memory owned by the caller
 int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB);
 
-// fused path (slz_fused.hip)
-int slz_fused_supported(const slz_params *p);
-int slz_fused_init(slz_ctx *ctx);
-void slz_fused_destroy(slz_ctx *ctx);
-int slz_fused_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx,
-                           const double *bskp, uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out,
-                           uint32_t batch, hipStream_t s);
 // floating-point transforms for N = 2048 (slz_fft.hip: tables and key, slz_fft2048.hip: kernel); their key form follows the
 // residue form of every prepared key
 int slz_fft_supported(const slz_params *p);

@@ -1,5 +1,5 @@
 // Wave-level negacyclic transforms on doubles: 2048 points (one wavefront = one polynomial or one 2048-block of a larger
-// one, 32 coefficients per lane), shared by the fused N = 2048 kernel and the large-N path, and 1024 points (16
+// one, 32 coefficients per lane), shared by the fused N = 4096 kernel and the large-N path, and 1024 points (16
 // coefficients per lane, at the end of the file) for the large-N path.
 #pragma once
 #include "slz_internal.h"
@@ -111,12 +111,8 @@ __device__ __forceinline__ void bfly_nomul(double &a, double &b) {
 // digits to 4.81 p, one full reduction brings them back to p/2, five more stages end at 4.81 p.
 // tw6 (stage with stride 32) is loaded by the caller; twA = lane-uniform twiddles; the per-lane twiddles of the last
 // five stages are fetched here before the first stage starts.  z is an opaque zero (see the kernel).
-struct fwd_no_hook { __device__ __forceinline__ void operator()() const {} };
-// `hook` runs after the second of the last five stages: a place for the caller to request what it needs right after the
-// transform (three stages of arithmetic then cover the loads' latency).
-template <class Hook = fwd_no_hook>
 __device__ __forceinline__ void fused_fwd(double (&x)[32], double *T, const double (&tw6)[16], const double *twA,
-                                          const double *fwdB, slz_mod m, uint32_t lane, int z, Hook hook = Hook()) {
+                                          const double *fwdB, slz_mod m, uint32_t lane, int z) {
     const uint32_t hh = lane >> 5, l5 = lane & 31u;
     double twB[31];
 #pragma unroll
@@ -167,7 +163,7 @@ __device__ __forceinline__ void fused_fwd(double (&x)[32], double *T, const doub
 #pragma unroll
     for (int s = 0; s < 5; s++) {
         const int t = 16 >> s;
-        if (s == 2) { SCHED_FENCE(); hook(); SCHED_FENCE(); }
+        if (s == 2) SCHED_FENCE();
 #pragma unroll
         for (int g = 0; g < 4; g++) {
 #define FB_I(b) (((b) / t) * 2 * t + (b) % t)
@@ -179,12 +175,11 @@ __device__ __forceinline__ void fused_fwd(double (&x)[32], double *T, const doub
 }
 
 // Inverse transform.  In: x[i] = spectrum position 32*lane + i, |x| <= 0.51 p.  Out: x[e] = coefficient 64e + lane
-// of the product polynomial mod p, |x| <= 1.7 p.  Bounds: stages 1,2 have unit twiddles (no multiply): 0.5 -> 1 -> 2;
-// stages 3..5 -> 2.88, 3.91, 5.15; reduce to 0.5; stages 6..11 -> 6.2; the final twist multiply gives 0.5 + 0.1875*6.2.
-// POST = false stops before the twist (the large-N path continues with stages across 2048-blocks first).
-template <bool POST>
+// of the product polynomial mod p, |x| <= 6.2 p.  Bounds: stages 1,2 have unit twiddles (no multiply): 0.5 -> 1 -> 2;
+// stages 3..5 -> 2.88, 3.91, 5.15; reduce to 0.5; stages 6..11 -> 6.2.  It stops before the twist: stages across the blocks of a
+// larger polynomial follow.
 __device__ __forceinline__ void fused_inv(double (&x)[32], double *T, const double *twS, const double *inv,
-                                          const double *post, slz_mod m, uint32_t lane, int z) {
+                                          slz_mod m, uint32_t lane, int z) {
     const uint32_t hh = lane >> 5, l5 = lane & 31u;
     // per-lane twiddles of the stages with half-size 32 .. 1024, fetched before the first stage
     double twL[31];
@@ -251,22 +246,9 @@ __device__ __forceinline__ void fused_inv(double (&x)[32], double *T, const doub
 #pragma unroll
     for (int j = 0; j < 16; j++) twL[15 + j] = ldl(inv + 64 * 16 + 64 * j + z, lane * 8u);
     SCHED_FENCE();
-    double pw[32];
 #pragma unroll
     for (int s = 0; s < 5; s++) {                                                       // t = 64 .. 1024
         const int half = 1 << s;
-        if (POST && s == 3) {
-            SCHED_FENCE();
-#pragma unroll
-            for (int e = 0; e < 16; e++) pw[e] = ldl(post + 64 * e + z, lane * 8u);
-            SCHED_FENCE();
-        }
-        if (POST && s == 4) {
-            SCHED_FENCE();
-#pragma unroll
-            for (int e = 16; e < 32; e++) pw[e] = ldl(post + 64 * e + z, lane * 8u);
-            SCHED_FENCE();
-        }
 #pragma unroll
         for (int g = 0; g < 4; g++) {
             // butterfly b in [0,16): position j = b % half in block b / half; per-lane twiddle twL[half - 1 + j]
@@ -276,18 +258,7 @@ __device__ __forceinline__ void fused_inv(double (&x)[32], double *T, const doub
                 IA_I(4 * g + 2), IA_I(4 * g + 2) + half, IA_W(4 * g + 2), IA_I(4 * g + 3), IA_I(4 * g + 3) + half, IA_W(4 * g + 3));
         }
     }
-    if (!POST) return;
-#pragma unroll
-    for (int g = 0; g < 8; g++) {
-        double r4[4];
-        const double x4[4] = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
-        const double w4[4] = {pw[4 * g], pw[4 * g + 1], pw[4 * g + 2], pw[4 * g + 3]};
-        mulmod_k<4>(r4, x4, w4, m);
-#pragma unroll
-        for (int u = 0; u < 4; u++) x[4 * g + u] = r4[u];
-    }
 }
-
 
 // ---- 1024-point wave transforms: 16 coefficients per lane ---------------------------------------------------------------
 // Half the registers of the 2048-point version, so that a kernel holding accumulators besides the transform fits two

@@ -1,4 +1,5 @@
-"""N = 2048 through exact floating-point transforms (batches above 256): bit for bit against the oracle and the generic path."""
+"""N = 2048 through exact floating-point transforms (batches up to 256: one workgroup per
+ciphertext; above: a pair of waves each): bit for bit against the oracle and the generic path."""
 import numpy as np
 import pytest
 
@@ -45,13 +46,13 @@ def _inputs(slz, batch, beta, n=3, extreme=False):
     return p, ctx, bsk.reshape(n, 2, 1, 2, 2048), luts, cts, idx, d
 
 
-# 2^23 is the largest base a context of this shape takes; 257 ciphertexts are the
-# smallest batch of this path, 1025 and 1300 give some pairs of waves a second one
-@pytest.mark.parametrize("batch,beta,extreme", [(257, 23, False), (300, 23, True), (300, 1, True), (260, 12, False),
+# 2^23 is the largest base a context of this shape takes; 256 and 257 ciphertexts are the two sides of the line between the two
+# forms of the kernel, 1025 and 1300 give some pairs of waves a second ciphertext
+@pytest.mark.parametrize("batch,beta,extreme", [(1, 23, False), (5, 12, True), (37, 1, False), (256, 23, True), (257, 23, False), (300, 23, True), (300, 1, True), (260, 12, False),
                                                 (1025, 23, False), (1300, 22, True)])
 def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, batch, beta, extreme):
     p, ctx, bsk, luts, cts, idx, d = _inputs(slz, batch, beta, extreme=extreme)
-    sample = np.array([0, 1, 2, 255, 256, batch - 1])
+    sample = np.unique(np.minimum([0, 1, 2, 255, 256, batch - 1], batch - 1))
     got = {s: ctx.blind_rotate_batch(*d, s) for s in (0, 1, p.n)}
     out, out0 = ctx.pbs_batch(*d), ctx.pbs_batch(d[0], d[1], None, d[3])
     ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)                       # the same prepared key
