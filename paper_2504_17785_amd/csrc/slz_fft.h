@@ -1,5 +1,5 @@
 // Exact negacyclic products through double-precision complex transforms: the pieces shared by the host code, the key
-// preparation and the N = 2048 blind rotation.
+// preparation and the N = 1024 and N = 2048 blind rotations.
 //
 // A key word is cut into SLZ_FFT_PIECES balanced digits of SLZ_FFT_PIECE_BITS bits, w = sum_j K_j 2^(13 j) mod 2^64 with
 // |K_j| <= 2^12.  For every piece the integer polynomial y_j = sum_r d_r K_(r,j) mod X^N + 1 (d_r: gadget digits) is
@@ -31,6 +31,20 @@
 
 // complex entries of the transform-domain key of one step: [piece][half g][k][row, component][lane]
 #define FFT_KEY_STEP (SLZ_FFT_PIECES * 2u * 8u * 4u * 64u)
+
+// Tables of the N = 1024 kernel, M = 512, all entries (cos, tan); the second of two sibling blocks takes i times the first one's:
+//   F2 [4][8]        forward strides 32 (1), 16 (1), 8 (2), by the three top position bits
+//   I2 [4][8]        inverse half-sizes 8 (1), 16 (1), 32 (2), by the three lowest position bits
+//   I3 [10][64]      inverse half-sizes 64 (1), 128 (1); 256: four (c1, c2) pairs as above
+//   F3 [4][64]       forward strides 4 (1), 2 (1), 1 (2), by the six top position bits
+#define F10_F2_OFF 0u
+#define F10_I2_OFF 32u
+#define F10_I3_OFF 64u
+#define F10_LDS_TAB (F10_I3_OFF + 640u)
+#define F10_F3_OFF F10_LDS_TAB
+#define F10_TAB_LEN (F10_F3_OFF + 256u)
+// complex entries of the transform-domain key of one step: [piece][k][row, component][lane]
+#define F10_KEY_STEP (SLZ_FFT_PIECES * 8u * 4u * 64u)
 
 // Worst-case error (absolute, before rounding) of one y_j over all inputs, see slz_fft.hip.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta);

@@ -1,6 +1,7 @@
 // Host side and key preparation of the floating-point transform path (see slz_fft.h): error bound, tables, key spectra.
 #include "slz_fft.h"
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 // ---- the error bound ------------------------------------------------------------------------------------------------
@@ -22,10 +23,13 @@
 //  fused rounding add).  1 + 1 + 2.61 + 6 * 4 + 4 + 1.61 = 34.22 u.
 //  Second-order terms are covered by the factor 1 + 2^-40.
 // Every row r contributes ||d_r|| ||K_(r,j)||.  The chain of four constants above is for two rows.
+// N = 1024, M = 512: the forward layers are radix-2 butterflies of the inverse's form, at most 4 u each relative to the 2-norm
+// (final rounding u |o|, the rest 3 u |b|, and the two outputs' norm is at least sqrt(2) |b|): nine of them, 36 u; the inverse
+// has one stage less: 30.22 u.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
-    if (N != 2048 || rows != 2) return 1e300;
+    if ((N != 2048 && N != 1024) || rows != 2) return 1e300;
     const double u = std::ldexp(1.0, -53);
-    const double fwd = 5 * 4.7072, key = 1.05, inv = 34.22;
+    const double fwd = N == 2048 ? 5 * 4.7072 : 9 * 4.0, key = 1.05, inv = N == 2048 ? 34.22 : 30.22;
     const double norm_d = std::ldexp(std::sqrt((double)N), (int)beta - 1);
     const double norm_k = std::ldexp(std::sqrt((double)N), SLZ_FFT_PIECE_BITS - 1);
     // products: (4 + 2) u for the two rows together = 3 u per row at equal bounds
@@ -33,7 +37,7 @@ double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
 }
 
 int slz_fft_supported(const slz_params *p) {
-    return p->N == 2048 && p->k == 1 && p->pbs_level == 1 && p->pbs_base_log <= 30 &&
+    return (p->N == 2048 || p->N == 1024) && p->k == 1 && p->pbs_level == 1 && p->pbs_base_log <= 30 &&
            slz_fft_error_bound(p->N, 2, p->pbs_base_log) < 0.499;
 }
 
@@ -65,9 +69,9 @@ static void three(cpl *out, size_t stride, uint32_t m, uint32_t blk) {
     for (int q = 0; q < 3; q++) out[q * stride] = unit((q + 1) * v);
 }
 
-int slz_fft_init(slz_ctx *ctx) {
-    const uint32_t M = ctx->prm.N / 2;
-    std::vector<cpl> t(FFT_TAB_LEN);
+static void build_2048(std::vector<cpl> &t, double (&f1_out)[15][2]) {
+    const uint32_t M = 1024;
+    t.resize(FFT_TAB_LEN);
     for (uint32_t x = 0; x < 16; x++) {
         three(&t[FFT_F2_OFF + x], 16, 16, x);
         for (uint32_t q = 0; q < 4; q++) three(&t[FFT_F2_OFF + (3 + 3 * q) * 16 + x], 16, 64, 4 * x + q);
@@ -95,21 +99,76 @@ int slz_fft_init(slz_ctx *ctx) {
     cpl f1[15];
     three(f1, 1, 1, 0);
     for (uint32_t q = 0; q < 4; q++) three(f1 + 3 + 3 * q, 1, 4, q);
-    for (int q = 0; q < 15; q++) { ctx->fft_f1[q][0] = f1[q].r; ctx->fft_f1[q][1] = f1[q].i; }
-    // twiddles of the key preparation as double-doubles (64 bits of them): W(m, blk) at m + blk
-    std::vector<double> w(4 * (size_t)M);
+    for (int q = 0; q < 15; q++) { f1_out[q][0] = f1[q].r; f1_out[q][1] = f1[q].i; }
+}
+
+// the four twiddles of three layers that begin with m blocks, for block `blk` of the first
+static void four(cpl *out, size_t stride, uint32_t m, uint32_t blk) {
+    out[0] = cos_tan(node_angle(m, blk));
+    out[stride] = cos_tan(node_angle(2 * m, 2 * blk));
+    for (uint32_t q = 0; q < 2; q++) out[(2 + q) * stride] = cos_tan(node_angle(4 * m, 4 * blk + 2 * q));
+}
+static void build_1024(std::vector<cpl> &t, double (&f1_out)[15][2]) {
+    const uint32_t M = 512;
+    t.resize(F10_TAB_LEN);
+    for (uint32_t x = 0; x < 8; x++) four(&t[F10_F2_OFF + x], 8, 8, x);
+    for (uint32_t l = 0; l < 64; l++) four(&t[F10_F3_OFF + l], 64, 64, l);
+    for (uint32_t l = 0; l < 8; l++) {
+        cpl *o = &t[F10_I2_OFF + l];
+        o[0] = cos_tan(-(long double)l / 8);
+        o[8] = cos_tan(-(long double)l / 16);
+        for (uint32_t q = 0; q < 2; q++) o[8 * (2 + q)] = cos_tan(-(long double)(8 * q + l) / 32);
+    }
+    for (uint32_t l = 0; l < 64; l++) {
+        cpl *o = &t[F10_I3_OFF + l];
+        o[0] = cos_tan(-(long double)l / 64);
+        o[64] = cos_tan(-(long double)l / 128);
+        for (uint32_t q = 0; q < 4; q++) {
+            const long double j = 64 * q + l;
+            o[64 * (2 + 2 * q)] = unit(-j / (2 * M));
+            o[64 * (3 + 2 * q)] = cos_tan(-j / (2 * M) - j / 256);
+        }
+    }
+    cpl f1[4];
+    four(f1, 1, 1, 0);
+    for (int q = 0; q < 4; q++) { f1_out[q][0] = f1[q].r; f1_out[q][1] = f1[q].i; }
+}
+
+// Host copies of the tables of one size, built by the first context that needs them (a millisecond of long-double functions).
+struct host_tables {
+    std::vector<cpl> t;
+    double f1[15][2];
+    std::vector<double> w;                                         // twiddles of the key preparation as double-doubles: W(m, blk) at m + blk
+};
+static host_tables build(uint32_t N) {
+    host_tables r{};
+    const uint32_t M = N / 2;
+    if (N == 2048) build_2048(r.t, r.f1);
+    else build_1024(r.t, r.f1);
+    r.w.resize(4 * (size_t)M);
     for (uint32_t x = 1; x < M; x++) {
         uint32_t m = 1;
         while (2 * m <= x) m *= 2;
         const long double a = PI_L * node_angle(m, x - m), c = cosl(a), s = sinl(a);
-        w[4 * x] = (double)c; w[4 * x + 1] = (double)(c - (long double)(double)c);
-        w[4 * x + 2] = (double)s; w[4 * x + 3] = (double)(s - (long double)(double)s);
+        r.w[4 * x] = (double)c; r.w[4 * x + 1] = (double)(c - (long double)(double)c);
+        r.w[4 * x + 2] = (double)s; r.w[4 * x + 3] = (double)(s - (long double)(double)s);
     }
-    SLZ_HIP(hipMalloc((void **)&ctx->fft_tab, t.size() * sizeof(cpl)));
-    SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, w.size() * sizeof(double)));
-    SLZ_HIP(hipMemcpy(ctx->fft_tab, t.data(), t.size() * sizeof(cpl), hipMemcpyHostToDevice));
-    SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice));
-    return slz_fft2048_setup();
+    return r;
+}
+static const host_tables &tables(uint32_t N) {
+    if (N == 2048) { static const host_tables t2048 = build(2048); return t2048; }
+    static const host_tables t1024 = build(1024);
+    return t1024;
+}
+
+int slz_fft_init(slz_ctx *ctx) {
+    const host_tables &h = tables(ctx->prm.N);
+    std::memcpy(ctx->fft_f1, h.f1, sizeof(h.f1));
+    SLZ_HIP(hipMalloc((void **)&ctx->fft_tab, h.t.size() * sizeof(cpl)));
+    SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, h.w.size() * sizeof(double)));
+    SLZ_HIP(hipMemcpy(ctx->fft_tab, h.t.data(), h.t.size() * sizeof(cpl), hipMemcpyHostToDevice));
+    SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, h.w.data(), h.w.size() * sizeof(double), hipMemcpyHostToDevice));
+    return ctx->prm.N == 2048 ? slz_fft2048_setup() : slz_fft1024_setup();
 }
 
 void slz_fft_destroy(slz_ctx *ctx) {
@@ -119,7 +178,7 @@ void slz_fft_destroy(slz_ctx *ctx) {
     ctx->fft_prep_tab = nullptr;
 }
 
-size_t slz_fft_key_bytes(const slz_params *p) { return slz_fft_supported(p) ? (size_t)p->n * FFT_KEY_STEP * 16 : 0; }
+size_t slz_fft_key_bytes(const slz_params *p) { return slz_fft_supported(p) ? (size_t)p->n * (p->N == 2048 ? FFT_KEY_STEP : F10_KEY_STEP) * 16 : 0; }
 
 // ---- key spectra ----------------------------------------------------------------------------------------------------
 // Double-double arithmetic (error-free sums and products; the build contracts nothing by itself).
@@ -138,11 +197,12 @@ __device__ __forceinline__ dd dd_mul(dd a, dd b) {
 
 // One workgroup per (key polynomial, piece): the forward transform of the piece in double-double, times -1 / M, rounded (the
 // kernel keeps its accumulator negated).
+template <uint32_t M>
 __global__ void __launch_bounds__(256)
 k_fft_prepare(const uint64_t *__restrict__ bsk, const double *__restrict__ wtab, double2 *__restrict__ dst) {
-    __shared__ double rh[1024], rl[1024], ih[1024], il[1024];
+    __shared__ double rh[M], rl[M], ih[M], il[M];
     const uint32_t poly = blockIdx.x, piece = blockIdx.y;          // poly = step * 4 + row * 2 + component
-    const uint64_t *src = bsk + (size_t)poly * 2048;
+    const uint64_t *src = bsk + (size_t)poly * (2 * M);
     auto digit = [&](uint64_t w) {
         int64_t v = (int64_t)w, d = 0;
         for (uint32_t j = 0; j <= piece; j++) {
@@ -152,14 +212,14 @@ k_fft_prepare(const uint64_t *__restrict__ bsk, const double *__restrict__ wtab,
         }
         return (double)d;
     };
-    for (uint32_t x = threadIdx.x; x < 1024; x += 256) {
+    for (uint32_t x = threadIdx.x; x < M; x += 256) {
         rh[x] = digit(src[x]);
-        ih[x] = digit(src[x + 1024]);
+        ih[x] = digit(src[x + M]);
         rl[x] = il[x] = 0.0;
     }
     __syncthreads();
-    for (uint32_t m = 1, half = 512; m < 1024; m *= 2, half /= 2) {
-        for (uint32_t b = threadIdx.x; b < 512; b += 256) {
+    for (uint32_t m = 1, half = M / 2; m < M; m *= 2, half /= 2) {
+        for (uint32_t b = threadIdx.x; b < M / 2; b += 256) {
             const uint32_t blk = b / half, x = blk * 2 * half + b % half, y = x + half;
             const double *w = wtab + 4 * (size_t)(m + blk);
             const dd wr = {w[0], w[1]}, wi = {w[2], w[3]}, ar = {rh[x], rl[x]}, ai = {ih[x], il[x]}, br = {rh[y], rl[y]}, bi = {ih[y], il[y]};
@@ -171,17 +231,20 @@ k_fft_prepare(const uint64_t *__restrict__ bsk, const double *__restrict__ wtab,
         __syncthreads();
     }
     const uint32_t step = poly / 4, rc = poly % 4;
-    for (uint32_t x = threadIdx.x; x < 1024; x += 256) {
+    constexpr uint32_t halves = M / 512, step_len = SLZ_FFT_PIECES * halves * 2048u;
+    for (uint32_t x = threadIdx.x; x < M; x += 256) {
         const uint32_t g = x >> 9, lane = (x >> 3) & 63u, k = x & 7u;
         double2 v;
-        v.x = rh[x] * (-1.0 / 1024.0);
-        v.y = ih[x] * (-1.0 / 1024.0);
-        dst[(size_t)step * FFT_KEY_STEP + (((piece * 2 + g) * 8 + k) * 4 + rc) * 64 + lane] = v;
+        v.x = rh[x] * (-1.0 / M);
+        v.y = ih[x] * (-1.0 / M);
+        dst[(size_t)step * step_len + (((piece * halves + g) * 8 + k) * 4 + rc) * 64 + lane] = v;
     }
 }
 
 int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s) {
-    hipLaunchKernelGGL(k_fft_prepare, dim3(ctx->prm.n * 4, SLZ_FFT_PIECES), dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
+    const dim3 grid(ctx->prm.n * 4, SLZ_FFT_PIECES);
+    if (ctx->prm.N == 2048) hipLaunchKernelGGL(k_fft_prepare<1024>, grid, dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
+    else hipLaunchKernelGGL(k_fft_prepare<512>, grid, dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;
 }

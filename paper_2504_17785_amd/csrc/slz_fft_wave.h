@@ -1,0 +1,121 @@
+// Device pieces of the transform kernels: LDS and global access by offset, butterflies, and the counters through which waves of
+// one workgroup follow each other.
+#pragma once
+#include <hip/hip_runtime.h>
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+#define FFT_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// LDS by byte offset (32-bit addresses in the LDS address space)
+#define LDS_AS __attribute__((address_space(3)))
+__device__ __forceinline__ d2 lds_get(uint32_t byte) { return *(const LDS_AS d2 *)(uintptr_t)byte; }
+__device__ __forceinline__ void lds_put(uint32_t byte, d2 v) { *(LDS_AS d2 *)(uintptr_t)byte = v; }
+
+// global memory as "uniform base + 32-bit lane offset": one address register for all loads
+__device__ __forceinline__ d2 lane_get(const d2 *uniform_base, uint32_t lane) {
+    return *reinterpret_cast<const d2 *>(reinterpret_cast<const char *>(uniform_base) + lane * 16u);
+}
+
+template <int V> struct fft_int { static constexpr int value = V; };
+
+// x w for a plain complex factor
+__device__ __forceinline__ d2 cmul(d2 x, d2 w) {
+    d2 r;
+    r.x = __builtin_fma(-x.y, w.y, x.x * w.x);
+    r.y = __builtin_fma(x.y, w.x, x.x * w.y);
+    return r;
+}
+// inverse radix-2, a +- w b with w = c (1 + i t) given as (c, t); TURN: w is further multiplied by -i
+template <bool TURN>
+__device__ __forceinline__ void inv2(d2 &a, d2 &b, d2 ct) {
+    const double ur = __builtin_fma(-ct.y, b.y, b.x), ui = __builtin_fma(ct.y, b.x, b.y);
+    const double vr = TURN ? ui : ur, vi = TURN ? -ur : ui;
+    b.x = __builtin_fma(-ct.x, vr, a.x);
+    b.y = __builtin_fma(-ct.x, vi, a.y);
+    a.x = __builtin_fma(ct.x, vr, a.x);
+    a.y = __builtin_fma(ct.x, vi, a.y);
+}
+// forward radix-2 whose twiddle is i w: the second block of every pair of blocks
+__device__ __forceinline__ void fwd2i(d2 &a, d2 &b, d2 ct) {
+    const double vr = __builtin_fma(-ct.y, b.x, -b.y), vi = __builtin_fma(-ct.y, b.y, b.x);
+    b.x = __builtin_fma(-ct.x, vr, a.x);
+    b.y = __builtin_fma(-ct.x, vi, a.y);
+    a.x = __builtin_fma(ct.x, vr, a.x);
+    a.y = __builtin_fma(ct.x, vi, a.y);
+}
+// a +- b and a -+ i b
+__device__ __forceinline__ void add2(d2 &a, d2 &b) { const d2 t = b; b = a - t; a = a + t; }
+__device__ __forceinline__ void add2i(d2 &a, d2 &b) {                 // b <- a + i b, a <- a - i b  (twiddle -i)
+    const d2 t = b;
+    b.x = a.x - t.y; b.y = a.y + t.x;
+    a.x = a.x + t.y; a.y = a.y - t.x;
+}
+
+// inverse half-sizes 1, 2, 4: constant twiddles
+#define FFT_SQRT_HALF 0.70710678118654752440
+__device__ __forceinline__ void inv8(d2 *s) {
+    const double r2 = FFT_SQRT_HALF;
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) add2(s[k], s[k + 1]);
+#pragma unroll
+    for (int k = 0; k < 8; k += 4) { add2(s[k], s[k + 2]); add2i(s[k + 1], s[k + 3]); }
+    add2(s[0], s[4]);
+    add2i(s[2], s[6]);
+    {   // twiddle sqrt(1/2) (1 - i)
+        const double p = s[5].x + s[5].y, q = s[5].y - s[5].x;
+        s[5].x = __builtin_fma(-r2, p, s[1].x); s[5].y = __builtin_fma(-r2, q, s[1].y);
+        s[1].x = __builtin_fma(r2, p, s[1].x); s[1].y = __builtin_fma(r2, q, s[1].y);
+    }
+    {   // twiddle sqrt(1/2) (-1 - i)
+        const double p = s[7].y - s[7].x, q = s[7].x + s[7].y;
+        s[7].x = __builtin_fma(-r2, p, s[3].x); s[7].y = __builtin_fma(r2, q, s[3].y);
+        s[3].x = __builtin_fma(r2, p, s[3].x); s[3].y = __builtin_fma(-r2, q, s[3].y);
+    }
+}
+
+// acc += y 2^s for the bits y of (integer + 1.5 * 2^52): the bits of that constant lie above bit 50, so they leave the word with any
+// shift of 13 or more; a shift past 32 only concerns the upper half
+template <int s>
+__device__ __forceinline__ void add_shifted(uint64_t &acc, uint64_t y) {
+    if constexpr (s >= 32) {
+        // one 32-bit operation (spelled out: the compiler widens the plain expression to a 64-bit addition with its moves)
+        uint32_t hi = (uint32_t)(acc >> 32);
+        asm("v_lshl_add_u32 %0, %1, %2, %0" : "+v"(hi) : "v"((uint32_t)y), "n"(s - 32));
+        acc = ((uint64_t)hi << 32) | (uint32_t)acc;
+    } else {
+        acc += y << s;
+    }
+}
+
+// The two waves of a ciphertext follow each other through two counters per wave in LDS: `done` (its part of an exchange has
+// been written) and `free` (it has read what the other wave may overwrite next).  Both waves are resident in the same
+// workgroup and take the same sequence of steps, so every wait ends.  LDS operations of one wave execute in order, so a
+// counter written after data (or after reads) is seen after them.
+__device__ __forceinline__ void fft_signal(uint32_t flag, uint32_t value) {
+    asm volatile("" ::: "memory");
+    __hip_atomic_store((LDS_AS uint32_t *)(uintptr_t)flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ uint32_t fft_peek(uint32_t flag) {
+    return __hip_atomic_load((const LDS_AS uint32_t *)(uintptr_t)flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// `seen`: what an earlier fft_peek returned, so that a counter that has long arrived costs no LDS round trip here
+__device__ __forceinline__ void fft_wait(uint32_t flag, uint32_t seen, uint32_t value) {
+    asm volatile("" ::: "memory");
+    while ((int32_t)((uint32_t)__builtin_amdgcn_readfirstlane(seen) - value) < 0) {
+        __builtin_amdgcn_s_sleep(1);
+        seen = fft_peek(flag);
+    }
+    asm volatile("" ::: "memory");
+}
+
+// Values are complete here: pure arithmetic would otherwise be sunk past the waits below into the block that uses it.
+__device__ __forceinline__ void pin(d2 &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void pin(uint64_t &v) { asm volatile("" : "+v"(v)); }
+
+// A copy of the lane number that the compiler cannot trace back: the LDS addresses made from it are computed where they are
+// used (a few 32-bit operations) instead of being kept in registers across the whole step.
+__device__ __forceinline__ uint32_t fresh(uint32_t lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}

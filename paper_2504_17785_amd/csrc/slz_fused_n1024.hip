@@ -1,5 +1,5 @@
-// Fused blind rotation for N = 1024, l = 1, k = 1 or 2, any base: the N = 2048 kernel's design on the 16-coefficient-per-lane
-// wave transform.
+// Fused blind rotation for N = 1024, l = 1, k = 1 or 2 through two 50-bit residues on the 16-coefficient-per-lane wave transform:
+// what k = 2 takes, and k = 1 at the base 2^24, whose floating-point transforms are not proven exact.
 //
 // One workgroup of 2 (k + 1) wavefronts owns one ciphertext for the whole blind rotation; the accumulator never leaves the
 // chip.  Wave (q, h): q = transform prime, h = GGSW row = accumulator component; each wave keeps 512 accumulator words
@@ -35,11 +35,11 @@ struct fused1024_args : slz_fused_io {
     double tw_inv[2][16];     // inv[t + j], t + j < 16: lane-uniform inverse twiddles (scalar loads)
 };
 
-template <int BETA, int K>
+template <int K>
 __global__ void __launch_bounds__(128 * (K + 1)) __attribute__((amdgpu_waves_per_eu(G_WAVES, G_WAVES)))
 k_fused_blind_rotate_n1024(fused1024_args A) {
     constexpr uint32_t C = K + 1;                    // accumulator components = GGSW rows
-    const uint32_t beta = BETA > 0 ? (uint32_t)BETA : A.beta;
+    const uint32_t beta = A.beta;
     extern __shared__ double lds[];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -264,11 +264,9 @@ int slz_fused1024_init(slz_ctx *ctx) {
     if (rc != SLZ_OK) return rc;
     rc = slz_fused_load_inv_scalars(ctx);
     if (rc != SLZ_OK) return rc;
-    SLZ_HIP(hipFuncSetAttribute((const void *)k_fused_blind_rotate_n1024<23, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    SLZ_HIP(hipFuncSetAttribute((const void *)k_fused_blind_rotate_n1024<1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 G_LDS_DOUBLES(2) * sizeof(double)));
-    SLZ_HIP(hipFuncSetAttribute((const void *)k_fused_blind_rotate_n1024<0, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                G_LDS_DOUBLES(2) * sizeof(double)));
-    SLZ_HIP(hipFuncSetAttribute((const void *)k_fused_blind_rotate_n1024<0, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    SLZ_HIP(hipFuncSetAttribute((const void *)k_fused_blind_rotate_n1024<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 G_LDS_DOUBLES(3) * sizeof(double)));
     return SLZ_OK;
 }
@@ -291,13 +289,10 @@ int slz_fused1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
     }
     if (ctx->prm.k == 2) {
         const uint32_t grid = slz_fused_grid(batch, 2);    // six waves and 70 KiB of LDS per workgroup: two per compute unit
-        hipLaunchKernelGGL((k_fused_blind_rotate_n1024<0, 2>), dim3(grid), dim3(384), G_LDS_DOUBLES(3) * sizeof(double), s, A);
+        hipLaunchKernelGGL(k_fused_blind_rotate_n1024<2>, dim3(grid), dim3(384), G_LDS_DOUBLES(3) * sizeof(double), s, A);
     } else {
         const uint32_t grid = slz_fused_grid(batch, G_WAVES);
-        if (A.beta == 23)
-            hipLaunchKernelGGL((k_fused_blind_rotate_n1024<23, 1>), dim3(grid), dim3(G_THREADS), G_LDS_DOUBLES(2) * sizeof(double), s, A);
-        else
-            hipLaunchKernelGGL((k_fused_blind_rotate_n1024<0, 1>), dim3(grid), dim3(G_THREADS), G_LDS_DOUBLES(2) * sizeof(double), s, A);
+        hipLaunchKernelGGL(k_fused_blind_rotate_n1024<1>, dim3(grid), dim3(G_THREADS), G_LDS_DOUBLES(2) * sizeof(double), s, A);
     }
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;

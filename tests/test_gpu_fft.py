@@ -1,5 +1,4 @@
-"""N = 2048 through exact floating-point transforms (batches up to 256: one workgroup per
-ciphertext; above: a pair of waves each): bit for bit against the oracle and the generic path."""
+"""N = 1024 and 2048 through exact floating-point transforms: bit for bit against the oracle and the generic path."""
 import numpy as np
 import pytest
 
@@ -21,18 +20,18 @@ def orc():
     return oracle
 
 
-def _inputs(slz, batch, beta, n=3, extreme=False):
-    p = synth.CONFIGS[2].with_(name="fft", n=n, pbs_base_log=beta, msg_bits=3, batch=batch)
-    bsk = synth.raw_words(p, "raw_bsk", n * 4 * 2048)
-    luts = synth.raw_words(p, "misc", 2 * 2048).reshape(2, 2048)
+def _inputs(slz, batch, beta, n=3, extreme=False, N=2048):
+    p = synth.CONFIGS[2].with_(name="fft", N=N, n=n, pbs_base_log=beta, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", n * 4 * N)
+    luts = synth.raw_words(p, "misc", 2 * N).reshape(2, N)
     cts = synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1)
     if extreme:
         # key words whose pieces are all of the largest magnitude and sign patterns that line their spectra up, digits at
         # -B/2 and B/2 - 1, rotations by N (X^N = -1: every difference is -2 ACC) and by odd amounts
-        bsk[:2 * 2048] = np.uint64(0x7FFF7FFBFFDFFEFF)
-        bsk[2 * 2048:4 * 2048:2] = np.uint64(1 << 63)
-        bsk[4 * 2048:8 * 2048:3] = np.uint64(0xF001800C00600300)
-        bsk[8 * 2048:] = np.uint64(0x0010008004002001) * np.uint64(0xFFF)
+        bsk[:2 * N] = np.uint64(0x7FFF7FFBFFDFFEFF)
+        bsk[2 * N:4 * N:2] = np.uint64(1 << 63)
+        bsk[4 * N:8 * N:3] = np.uint64(0xF001800C00600300)
+        bsk[8 * N:] = np.uint64(0x0010008004002001) * np.uint64(0xFFF)
         luts[0] = np.uint64(1 << 62)
         luts[1, 0::2] = np.uint64((1 << 63) - (1 << 40))
         luts[1, 1::2] = np.uint64(1 << 63)
@@ -40,18 +39,22 @@ def _inputs(slz, batch, beta, n=3, extreme=False):
         cts[1::3, 0] = np.uint64(1 << 63)
     idx = (np.arange(batch) % 2).astype(np.uint32)
     ctx = slz.Context(p, batch)
-    assert ctx.path == "fused_n2048"
+    assert ctx.path == "fused_n%d" % N
     d = [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy(idx.astype(np.int32)).cuda(),
-         ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, 1, 2, 2048)))]
-    return p, ctx, bsk.reshape(n, 2, 1, 2, 2048), luts, cts, idx, d
+         ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, 1, 2, N)))]
+    return p, ctx, bsk.reshape(n, 2, 1, 2, N), luts, cts, idx, d
 
 
-# 2^23 is the largest base a context of this shape takes; 256 and 257 ciphertexts are the two sides of the line between the two
-# forms of the kernel, 1025 and 1300 give some pairs of waves a second ciphertext
-@pytest.mark.parametrize("batch,beta,extreme", [(1, 23, False), (5, 12, True), (37, 1, False), (256, 23, True), (257, 23, False), (300, 23, True), (300, 1, True), (260, 12, False),
-                                                (1025, 23, False), (1300, 22, True)])
-def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, batch, beta, extreme):
-    p, ctx, bsk, luts, cts, idx, d = _inputs(slz, batch, beta, extreme=extreme)
+# N = 2048: 2^23 is the largest base a context takes; 256 and 257 ciphertexts are the two sides of the line between the two forms of
+# the kernel, 1025 and 1300 give some pairs of waves a second ciphertext.  N = 1024: the lines are at 256 and 1024, 2100 gives some
+# waves a second ciphertext; 2^23 is the largest base whose error bound holds (2^24 stays on residues).
+@pytest.mark.parametrize("N,batch,beta,extreme", [
+    (2048, 1, 23, False), (2048, 5, 12, True), (2048, 37, 1, False), (2048, 256, 23, True), (2048, 257, 23, False),
+    (2048, 300, 23, True), (2048, 300, 1, True), (2048, 260, 12, False), (2048, 1025, 23, False), (2048, 1300, 22, True),
+    (1024, 1, 23, False), (1024, 3, 12, True), (1024, 256, 23, True), (1024, 257, 23, True), (1024, 512, 23, False), (1024, 600, 1, False),
+    (1024, 1024, 23, False), (1024, 1025, 23, True), (1024, 2100, 22, True), (1024, 40, 24, True)])
+def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch, beta, extreme):
+    p, ctx, bsk, luts, cts, idx, d = _inputs(slz, batch, beta, extreme=extreme, N=N)
     sample = np.unique(np.minimum([0, 1, 2, 255, 256, batch - 1], batch - 1))
     got = {s: ctx.blind_rotate_batch(*d, s) for s in (0, 1, p.n)}
     out, out0 = ctx.pbs_batch(*d), ctx.pbs_batch(d[0], d[1], None, d[3])
