@@ -223,8 +223,8 @@ static int blind_rotate_common(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
         ((uintptr_t)lut_idx & 3u))
         return SLZ_E_INVALID_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
-    if (ctx->has_fft && !ctx->force_generic)     // N = 1024 and 2048: 1.2 to 1.7 times as fast as through residues at every batch size
-        return (ctx->prm.N == 2048 ? slz_fft2048_blind_rotate : slz_fft1024_blind_rotate)(
+    if (ctx->has_fft && !ctx->force_generic)     // 1.1 to 3.3 times as fast as through residues, at every batch size
+        return (ctx->prm.N == 2048 ? slz_fft2048_blind_rotate : ctx->prm.N == 1024 ? slz_fft1024_blind_rotate : slz_fft512_blind_rotate)(
             ctx, lwe_in, luts, lut_idx, (const char *)bskp + residue_key_bytes(ctx->prm), n_steps, acc_out, lwe_out, batch, s);
     if (ctx->has_fused4096 && !ctx->force_generic)
         return slz_fused4096_blind_rotate(ctx, lwe_in, luts, lut_idx, (const double *)bskp, n_steps, acc_out, lwe_out, batch, s);

@@ -1,8 +1,8 @@
 // Exact negacyclic products through double-precision complex transforms: the pieces shared by the host code, the key
-// preparation and the N = 1024 and N = 2048 blind rotations.
+// preparation and the N = 512, 1024 and 2048 blind rotations.
 //
 // A key word is cut into SLZ_FFT_PIECES balanced digits of SLZ_FFT_PIECE_BITS bits, w = sum_j K_j 2^(13 j) mod 2^64 with
-// |K_j| <= 2^12.  For every piece the integer polynomial y_j = sum_r d_r K_(r,j) mod X^N + 1 (d_r: gadget digits) is
+// |K_j| <= 2^12 (N = 512, whose bases are smaller: three digits of 22 bits).  For every piece the integer polynomial y_j = sum_r d_r K_(r,j) mod X^N + 1 (d_r: gadget digits) is
 // computed with floating-point transforms of N / 2 complex points (coefficients c and c + N/2 as real and imaginary part,
 // evaluated at the roots of Z^(N/2) = i) and rounded to the nearest integer.  slz_fft_error_bound proves for every input
 // that the error before rounding is below 1/2, so the rounded y_j, and with them sum_j y_j 2^(13 j) mod 2^64, are exact.
@@ -45,6 +45,22 @@
 #define F10_TAB_LEN (F10_F3_OFF + 256u)
 // complex entries of the transform-domain key of one step: [piece][k][row, component][lane]
 #define F10_KEY_STEP (SLZ_FFT_PIECES * 8u * 4u * 64u)
+
+// Tables of the N = 512 kernel, M = 256, in the same form:
+//   F2 [4][8]        forward strides 16 (1), 8 (1), 4 (2), by the three top position bits
+//   I2 [4][4]        inverse half-sizes 4 (1), 8 (1), 16 (2), by the two lowest position bits
+//   I3 [10][32]      inverse half-sizes 32 (1), 64 (1); 128: four (c1, c2) pairs
+//   F3 [2][64]       forward strides 2 (1), 1 (1), by the six top position bits
+#define F9_PIECES 3
+#define F9_PIECE_BITS 22
+#define F9_F2_OFF 0u
+#define F9_I2_OFF 32u
+#define F9_I3_OFF 48u
+#define F9_LDS_TAB (F9_I3_OFF + 320u)
+#define F9_F3_OFF F9_LDS_TAB
+#define F9_TAB_LEN (F9_F3_OFF + 128u)
+// complex entries of the transform-domain key of one step: [piece][k][row, component][lane]
+#define F9_KEY_STEP (F9_PIECES * 4u * 8u * 64u)
 
 // Worst-case error (absolute, before rounding) of one y_j over all inputs, see slz_fft.hip.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta);

@@ -26,19 +26,24 @@
 // N = 1024, M = 512: the forward layers are radix-2 butterflies of the inverse's form, at most 4 u each relative to the 2-norm
 // (final rounding u |o|, the rest 3 u |b|, and the two outputs' norm is at least sqrt(2) |b|): nine of them, 36 u; the inverse
 // has one stage less: 30.22 u.
+// N = 512, M = 256: eight forward layers, 32 u; half-size 4 is a butterfly like the others, 27.61 u; four rows, so the chain of
+// fused multiply-adds gives (8 + 6 + 4 + 2) u |D K|, 5 u per row.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
-    if ((N != 2048 && N != 1024) || rows != 2) return 1e300;
-    const double u = std::ldexp(1.0, -53);
-    const double fwd = N == 2048 ? 5 * 4.7072 : 9 * 4.0, key = 1.05, inv = N == 2048 ? 34.22 : 30.22;
+    const double u = std::ldexp(1.0, -53), key = 1.05;
+    double fwd, inv;
+    int bits = SLZ_FFT_PIECE_BITS;
+    if (N == 2048 && rows == 2) { fwd = 5 * 4.7072; inv = 34.22; }
+    else if (N == 1024 && rows == 2) { fwd = 9 * 4.0; inv = 30.22; }
+    else if (N == 512 && rows == 4) { fwd = 8 * 4.0; inv = 27.61; bits = F9_PIECE_BITS; }
+    else return 1e300;
     const double norm_d = std::ldexp(std::sqrt((double)N), (int)beta - 1);
-    const double norm_k = std::ldexp(std::sqrt((double)N), SLZ_FFT_PIECE_BITS - 1);
-    // products: (4 + 2) u for the two rows together = 3 u per row at equal bounds
-    return (fwd + 3.0 + key + inv) * u * (double)rows * norm_d * norm_k * (1.0 + std::ldexp(1.0, -40));
+    const double norm_k = std::ldexp(std::sqrt((double)N), bits - 1);
+    // products: 3 u per row for two rows at equal bounds, 5 u for four
+    return (fwd + rows + 1.0 + key + inv) * u * (double)rows * norm_d * norm_k * (1.0 + std::ldexp(1.0, -40));
 }
 
 int slz_fft_supported(const slz_params *p) {
-    return (p->N == 2048 || p->N == 1024) && p->k == 1 && p->pbs_level == 1 && p->pbs_base_log <= 30 &&
-           slz_fft_error_bound(p->N, 2, p->pbs_base_log) < 0.499;
+    return p->k == 1 && p->pbs_base_log <= 30 && slz_fft_error_bound(p->N, 2 * p->pbs_level, p->pbs_base_log) < 0.499;
 }
 
 // ---- tables ---------------------------------------------------------------------------------------------------------
@@ -134,6 +139,35 @@ static void build_1024(std::vector<cpl> &t, double (&f1_out)[15][2]) {
     for (int q = 0; q < 4; q++) { f1_out[q][0] = f1[q].r; f1_out[q][1] = f1[q].i; }
 }
 
+static void build_512(std::vector<cpl> &t, double (&f1_out)[15][2]) {
+    const uint32_t M = 256;
+    t.resize(F9_TAB_LEN);
+    for (uint32_t x = 0; x < 8; x++) four(&t[F9_F2_OFF + x], 8, 8, x);
+    for (uint32_t l = 0; l < 64; l++) {
+        t[F9_F3_OFF + l] = cos_tan(node_angle(64, l));
+        t[F9_F3_OFF + 64 + l] = cos_tan(node_angle(128, 2 * l));
+    }
+    for (uint32_t l = 0; l < 4; l++) {
+        cpl *o = &t[F9_I2_OFF + l];
+        o[0] = cos_tan(-(long double)l / 4);
+        o[4] = cos_tan(-(long double)l / 8);
+        for (uint32_t q = 0; q < 2; q++) o[4 * (2 + q)] = cos_tan(-(long double)(4 * q + l) / 16);
+    }
+    for (uint32_t l = 0; l < 32; l++) {
+        cpl *o = &t[F9_I3_OFF + l];
+        o[0] = cos_tan(-(long double)l / 32);
+        o[32] = cos_tan(-(long double)l / 64);
+        for (uint32_t q = 0; q < 4; q++) {
+            const long double j = 32 * q + l;
+            o[32 * (2 + 2 * q)] = unit(-j / (2 * M));
+            o[32 * (3 + 2 * q)] = cos_tan(-j / (2 * M) - j / 128);
+        }
+    }
+    cpl f1[4];
+    four(f1, 1, 1, 0);
+    for (int q = 0; q < 4; q++) { f1_out[q][0] = f1[q].r; f1_out[q][1] = f1[q].i; }
+}
+
 // Host copies of the tables of one size, built by the first context that needs them (a millisecond of long-double functions).
 struct host_tables {
     std::vector<cpl> t;
@@ -144,7 +178,8 @@ static host_tables build(uint32_t N) {
     host_tables r{};
     const uint32_t M = N / 2;
     if (N == 2048) build_2048(r.t, r.f1);
-    else build_1024(r.t, r.f1);
+    else if (N == 1024) build_1024(r.t, r.f1);
+    else build_512(r.t, r.f1);
     r.w.resize(4 * (size_t)M);
     for (uint32_t x = 1; x < M; x++) {
         uint32_t m = 1;
@@ -157,8 +192,9 @@ static host_tables build(uint32_t N) {
 }
 static const host_tables &tables(uint32_t N) {
     if (N == 2048) { static const host_tables t2048 = build(2048); return t2048; }
-    static const host_tables t1024 = build(1024);
-    return t1024;
+    if (N == 1024) { static const host_tables t1024 = build(1024); return t1024; }
+    static const host_tables t512 = build(512);
+    return t512;
 }
 
 int slz_fft_init(slz_ctx *ctx) {
@@ -168,7 +204,7 @@ int slz_fft_init(slz_ctx *ctx) {
     SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, h.w.size() * sizeof(double)));
     SLZ_HIP(hipMemcpy(ctx->fft_tab, h.t.data(), h.t.size() * sizeof(cpl), hipMemcpyHostToDevice));
     SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, h.w.data(), h.w.size() * sizeof(double), hipMemcpyHostToDevice));
-    return ctx->prm.N == 2048 ? slz_fft2048_setup() : slz_fft1024_setup();
+    return ctx->prm.N == 2048 ? slz_fft2048_setup() : ctx->prm.N == 1024 ? slz_fft1024_setup() : slz_fft512_setup();
 }
 
 void slz_fft_destroy(slz_ctx *ctx) {
@@ -178,7 +214,7 @@ void slz_fft_destroy(slz_ctx *ctx) {
     ctx->fft_prep_tab = nullptr;
 }
 
-size_t slz_fft_key_bytes(const slz_params *p) { return slz_fft_supported(p) ? (size_t)p->n * (p->N == 2048 ? FFT_KEY_STEP : F10_KEY_STEP) * 16 : 0; }
+size_t slz_fft_key_bytes(const slz_params *p) { return slz_fft_supported(p) ? (size_t)p->n * (p->N == 2048 ? FFT_KEY_STEP : p->N == 1024 ? F10_KEY_STEP : F9_KEY_STEP) * 16 : 0; }
 
 // ---- key spectra ----------------------------------------------------------------------------------------------------
 // Double-double arithmetic (error-free sums and products; the build contracts nothing by itself).
@@ -197,18 +233,19 @@ __device__ __forceinline__ dd dd_mul(dd a, dd b) {
 
 // One workgroup per (key polynomial, piece): the forward transform of the piece in double-double, times -1 / M, rounded (the
 // kernel keeps its accumulator negated).
-template <uint32_t M>
+// Step layout [piece][half g][k][row, component][lane]: K points per lane, M / (64 K) halves.
+template <uint32_t M, uint32_t ROWS, uint32_t K, int PIECES, int BITS>
 __global__ void __launch_bounds__(256)
 k_fft_prepare(const uint64_t *__restrict__ bsk, const double *__restrict__ wtab, double2 *__restrict__ dst) {
     __shared__ double rh[M], rl[M], ih[M], il[M];
-    const uint32_t poly = blockIdx.x, piece = blockIdx.y;          // poly = step * 4 + row * 2 + component
+    const uint32_t poly = blockIdx.x, piece = blockIdx.y;          // poly = (step * ROWS + row) * 2 + component
     const uint64_t *src = bsk + (size_t)poly * (2 * M);
     auto digit = [&](uint64_t w) {
         int64_t v = (int64_t)w, d = 0;
         for (uint32_t j = 0; j <= piece; j++) {
-            const int bits = j == SLZ_FFT_PIECES - 1 ? 64 - SLZ_FFT_PIECE_BITS * (SLZ_FFT_PIECES - 1) : SLZ_FFT_PIECE_BITS;
+            const int bits = j == PIECES - 1 ? 64 - BITS * (PIECES - 1) : BITS;
             d = (int64_t)((uint64_t)v << (64 - bits)) >> (64 - bits);
-            v = (int64_t)((uint64_t)v - (uint64_t)d) >> SLZ_FFT_PIECE_BITS;
+            v = (int64_t)((uint64_t)v - (uint64_t)d) >> BITS;
         }
         return (double)d;
     };
@@ -230,21 +267,25 @@ k_fft_prepare(const uint64_t *__restrict__ bsk, const double *__restrict__ wtab,
         }
         __syncthreads();
     }
-    const uint32_t step = poly / 4, rc = poly % 4;
-    constexpr uint32_t halves = M / 512, step_len = SLZ_FFT_PIECES * halves * 2048u;
+    constexpr uint32_t RC = 2 * ROWS, halves = M / (64 * K), step_len = PIECES * M * RC;
+    const uint32_t step = poly / RC, rc = poly % RC;
     for (uint32_t x = threadIdx.x; x < M; x += 256) {
-        const uint32_t g = x >> 9, lane = (x >> 3) & 63u, k = x & 7u;
+        const uint32_t g = x / (64 * K), lane = (x / K) & 63u, k = x % K;
         double2 v;
         v.x = rh[x] * (-1.0 / M);
         v.y = ih[x] * (-1.0 / M);
-        dst[(size_t)step * step_len + (((piece * halves + g) * 8 + k) * 4 + rc) * 64 + lane] = v;
+        dst[(size_t)step * step_len + (((piece * halves + g) * K + k) * RC + rc) * 64 + lane] = v;
     }
 }
 
 int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s) {
-    const dim3 grid(ctx->prm.n * 4, SLZ_FFT_PIECES);
-    if (ctx->prm.N == 2048) hipLaunchKernelGGL(k_fft_prepare<1024>, grid, dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
-    else hipLaunchKernelGGL(k_fft_prepare<512>, grid, dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
+    const uint32_t polys = ctx->prm.n * 4 * ctx->prm.pbs_level;
+    auto launch = [&](auto kernel, uint32_t pieces) {
+        hipLaunchKernelGGL(kernel, dim3(polys, pieces), dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
+    };
+    if (ctx->prm.N == 2048) launch(k_fft_prepare<1024, 2, 8, SLZ_FFT_PIECES, SLZ_FFT_PIECE_BITS>, SLZ_FFT_PIECES);
+    else if (ctx->prm.N == 1024) launch(k_fft_prepare<512, 2, 8, SLZ_FFT_PIECES, SLZ_FFT_PIECE_BITS>, SLZ_FFT_PIECES);
+    else launch(k_fft_prepare<256, 4, 4, F9_PIECES, F9_PIECE_BITS>, F9_PIECES);
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;
 }

@@ -10,7 +10,7 @@
 //   F1, I3: b8 b7 b6 / b5..b0     F2, I2: b5 b4 b3 / b8 b7 b6 b2 b1 b0     F3, I1: b2 b1 b0 / b8..b3
 // Exchanges between the first two layouts place a point at 72 (b8 b7 b6) + (b5..b0), between the last two at 72 (b8 b7 b6) +
 // 9 (b5 b4 b3) + (b2 b1 b0): 16 neighbouring lanes always touch 16 different columns of 16 bytes, writing and reading.
-// Bound and shape: FP64 issue.  A step is about 7.2 k VALU instructions per ciphertext; registers (accumulator 64, spectra 64, transform 64,
+// Bound and shape: FP64 issue.  A step is about 4.2 k VALU instructions per ciphertext; registers (accumulator 64, spectra 64, transform 64,
 // key words 64 of 256) allow two waves per SIMD.  The two components of a wave hide each other's LDS round trips.  Smaller batches
 // leave compute units with fewer than eight ciphertexts, so waves share one (SHARE below).  Measured with 630 steps and the
 // keyswitch (in brackets: two 50-bit residues on the same card): one ciphertext 3.6 ms (4.6), 512: 5.6 (6.9), 777: 8.5 (13.2),

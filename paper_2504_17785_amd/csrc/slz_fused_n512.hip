@@ -1,5 +1,5 @@
-// Fused blind rotation for N = 512, any base: l = 1 with k = 1 or 3 (k = 3 is the shape of 2-bit parameter sets), and
-// k = 1 with l = 2 (second kernel, further down).
+// Fused blind rotation for N = 512 through two 50-bit residues, any base: l = 1 with k = 1 or 3 (k = 3 is the shape of 2-bit
+// parameter sets), and k = 1 with l = 2 at bases above 2^14 (second kernel, further down; smaller bases: slz_fft512.hip).
 //
 // One wavefront transforms two 512-point polynomials at once (the 1024-point wave transform without the stage that would
 // pair them): in the coefficient domain registers 0..7 hold the first and 8..15 the second polynomial (coefficient

@@ -54,7 +54,7 @@ struct slz_ctx {
     double p1inv_mod_p2;      // p1^{-1} mod p2 (centred)
     slz_tables tab[2];
     double fused_scalars[2][32];      // [prime]: the lane-uniform inverse twiddles of the fused kernels
-    int has_fft;              // N = 1024 or 2048 through floating-point transforms: the error bound holds for this parameter set
+    int has_fft;              // N = 512, 1024 or 2048 through floating-point transforms: the error bound holds for this parameter set
     void *fft_tab;            // its tables (slz_fft.h)
     double *fft_prep_tab;     // double-double twiddles of the key preparation
     double fft_f1[15][2];     // host copy of its lane-uniform twiddles
@@ -124,7 +124,8 @@ int slz_fused1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
 // *dB [2][N/BS][BS/64 - 1][64], device memory owned by the caller
 int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB);
 
-// floating-point transforms for N = 1024 and 2048 (slz_fft.hip: tables and key, slz_fft1024.hip, slz_fft2048.hip: kernels); their key form follows the
+// floating-point transforms for N = 512 (l = 2), 1024 and 2048 (slz_fft.hip: tables and key; slz_fft512.hip, slz_fft1024.hip,
+// slz_fft2048.hip: kernels); their key form follows the
 // residue form of every prepared key
 int slz_fft_supported(const slz_params *p);
 int slz_fft_init(slz_ctx *ctx);
@@ -133,6 +134,9 @@ size_t slz_fft_key_bytes(const slz_params *p);
 int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s);
 int slz_fft2048_setup();
 int slz_fft1024_setup();
+int slz_fft512_setup();
+int slz_fft512_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                            uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
 int slz_fft1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
 int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,

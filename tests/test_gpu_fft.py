@@ -1,4 +1,4 @@
-"""N = 1024 and 2048 through exact floating-point transforms: bit for bit against the oracle and the generic path."""
+"""N = 512 (two levels), 1024 and 2048 through exact floating-point transforms: bit for bit against the oracle and the generic path."""
 import numpy as np
 import pytest
 
@@ -21,8 +21,9 @@ def orc():
 
 
 def _inputs(slz, batch, beta, n=3, extreme=False, N=2048):
-    p = synth.CONFIGS[2].with_(name="fft", N=N, n=n, pbs_base_log=beta, msg_bits=3, batch=batch)
-    bsk = synth.raw_words(p, "raw_bsk", n * 4 * N)
+    l = 2 if N == 512 else 1
+    p = synth.CONFIGS[2].with_(name="fft", N=N, n=n, pbs_level=l, pbs_base_log=beta, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", n * 4 * l * N)
     luts = synth.raw_words(p, "misc", 2 * N).reshape(2, N)
     cts = synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1)
     if extreme:
@@ -41,18 +42,21 @@ def _inputs(slz, batch, beta, n=3, extreme=False, N=2048):
     ctx = slz.Context(p, batch)
     assert ctx.path == "fused_n%d" % N
     d = [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy(idx.astype(np.int32)).cuda(),
-         ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, 1, 2, N)))]
-    return p, ctx, bsk.reshape(n, 2, 1, 2, N), luts, cts, idx, d
+         ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, l, 2, N)))]
+    return p, ctx, bsk.reshape(n, 2, l, 2, N), luts, cts, idx, d
 
 
 # N = 2048: 2^23 is the largest base a context takes; 256 and 257 ciphertexts are the two sides of the line between the two forms of
 # the kernel, 1025 and 1300 give some pairs of waves a second ciphertext.  N = 1024: the lines are at 256 and 1024, 2100 gives some
-# waves a second ciphertext; 2^23 is the largest base whose error bound holds (2^24 stays on residues).
+# waves a second ciphertext; 2^23 is the largest base whose error bound holds (2^24 stays on residues).  N = 512: the lines are at 256
+# and 512; 2^14 is the largest base whose bound holds.
 @pytest.mark.parametrize("N,batch,beta,extreme", [
     (2048, 1, 23, False), (2048, 5, 12, True), (2048, 37, 1, False), (2048, 256, 23, True), (2048, 257, 23, False),
     (2048, 300, 23, True), (2048, 300, 1, True), (2048, 260, 12, False), (2048, 1025, 23, False), (2048, 1300, 22, True),
     (1024, 1, 23, False), (1024, 3, 12, True), (1024, 256, 23, True), (1024, 257, 23, True), (1024, 512, 23, False), (1024, 600, 1, False),
-    (1024, 1024, 23, False), (1024, 1025, 23, True), (1024, 2100, 22, True), (1024, 40, 24, True)])
+    (1024, 1024, 23, False), (1024, 1025, 23, True), (1024, 2100, 22, True), (1024, 40, 24, True),
+    (512, 1, 8, False), (512, 7, 14, True), (512, 256, 1, False), (512, 257, 14, True), (512, 512, 8, False), (512, 513, 8, True),
+    (512, 1024, 14, False), (512, 1025, 14, True), (512, 2100, 8, False), (512, 40, 15, True)])
 def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch, beta, extreme):
     p, ctx, bsk, luts, cts, idx, d = _inputs(slz, batch, beta, extreme=extreme, N=N)
     sample = np.unique(np.minimum([0, 1, 2, 255, 256, batch - 1], batch - 1))
