@@ -31,15 +31,17 @@ def alu_model_ops_per_pbs(p, generic=False) -> float:
     8 per butterfly (6 modular multiply + add + sub), 7 per pointwise multiply-accumulate, 3 per inverse
     post-scaling beyond the butterflies' share (6-instruction modular multiply per coefficient), 12 per
     decomposed coefficient (rotate, subtract, round, digit, convert) and 20 per CRT-lifted coefficient.
-    N = 2048, k = 1, l = 1 (floating-point transforms of 1024 complex points): forward 28 per radix-4 butterfly in five layers,
-    4 per complex multiply-add for two rows, two components and five key pieces, inverse 6 per butterfly in ten layers for two
-    components and five pieces, 12 per decomposed coefficient and 2 per coefficient and piece for rounding and adding."""
+    Shapes that run through floating-point transforms of M = N / 2 complex points (N = 1024 and 2048 with k = l = 1, five key pieces;
+    N = 512 with k = 1, l = 2, three): 6 per radix-2 butterfly (N = 2048 forward: 28 per radix-4 butterfly), 4 per complex
+    multiply-add, the same 12 (+ 4 per level) per decomposed coefficient and 2 per coefficient and piece for rounding and adding."""
     logN = p.N.bit_length() - 1
     R, C = (p.k + 1) * p.pbs_level, p.k + 1
-    if (p.N, p.k, p.pbs_level) == (2048, 1, 1) and not generic:
-        M, pieces = p.N // 2, 5
-        return float(p.n) * (R * 5 * (M // 4) * 28 + pieces * R * C * M * 4 + pieces * C * 10 * (M // 2) * 6 + C * p.N * 12 +
-                             pieces * C * p.N * 2)
+    top = {(2048, 1, 1): 23, (1024, 1, 1): 23, (512, 1, 2): 14}.get((p.N, p.k, p.pbs_level), -1)   # largest base 2^top of that path
+    if p.pbs_base_log <= top and not generic:
+        M, pieces = p.N // 2, 3 if p.N == 512 else 5
+        forward = 5 * (M // 4) * 28 if p.N == 2048 else (logN - 1) * (M // 2) * 6
+        return float(p.n) * (R * forward + pieces * R * C * M * 4 + pieces * C * (logN - 1) * (M // 2) * 6 +
+                             C * p.N * (12 + 4 * (p.pbs_level - 1)) + pieces * C * p.N * 2)
     per_prime = (R + C) * (p.N // 2) * logN * 8 + R * C * p.N * 7 + C * p.N * 6
     per_cmux = 2 * per_prime + C * p.N * (12 + 4 * (p.pbs_level - 1)) + C * p.N * 20
     return float(p.n) * per_cmux
@@ -295,7 +297,7 @@ def bench_loss(args):
 
 PATH_SOURCES = {       # sources of the dominant kernel of each path (for the check that a stored traffic figure is current)
     "fused_n2048": ("slz_fft2048.hip", "slz_fft_wave.h", "slz_modarith.h"),
-    "fused_n512": ("slz_fused_n512.hip", "slz_wave_ntt.h", "slz_modarith.h"),
+    "fused_n512": ("slz_fft512.hip", "slz_fft_wave.h", "slz_modarith.h"),
     "three_pass_large_n": ("slz_bign.hip", "slz_wave_ntt.h", "slz_modarith.h"),
 }
 

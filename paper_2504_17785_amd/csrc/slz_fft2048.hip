@@ -20,7 +20,7 @@
 //   I1 -> I2 and I2 -> I3: b9 b8 / b3 b6 b5 b4 / b7 b2 b1 b0
 // The accumulator is kept negated (and so are the key's spectra): X^a ACC - ACC is then one exclusive-or and one addition with
 // carry per word.
-// Bound and shape: a step is about 4.6 k VALU instructions per wave (3.8 k of them FP64); two 50-bit residues took 17.3 k
+// Bound and shape: a step is about 4.8 k VALU instructions per wave (3.8 k of them FP64); two 50-bit residues took 17.3 k
 // wave-instructions per ciphertext.  Registers decide the rest: accumulator 64, spectra 64, transform 64 of 256, two waves per
 // SIMD; key words stream from L2 (320 KiB per step, every ciphertext reads all of it) through what is left.  Eight waves (four
 // ciphertexts) share one workgroup, i.e. one copy of the tables in LDS, and only the two waves of a ciphertext wait for each other.
