@@ -659,8 +659,8 @@ static int ensure_lanes(slz_ctx *ctx) {
     return SLZ_OK;
 }
 
-// Ciphertexts the latency-oriented kernels are used for: while their row tasks (2 G per ciphertext) fill at most half of
-// the 2048 resident-wave slots of the row pass.  Measured at N = 32768, us per CMux step against the throughput kernels:
+// Ciphertexts the latency-oriented kernels are used for on one stream: while their row tasks (2 G per ciphertext) fill at most half
+// of the 2048 resident-wave slots of the row pass.  Measured at N = 32768, us per CMux step against the throughput kernels:
 // 34 / 47 at one ciphertext, 40 / 52 at 4, 41 / 57 at 8, 50 / 58 at 12, 53 / 61 at 16; from 20 on they are equal.
 static uint32_t latency_max_batch(uint32_t G) { return 1024u / (2 * G) ? 1024u / (2 * G) : 1u; }
 // Up to this many ciphertexts the row pass is cut into per-GGSW-row and per-component launches, above it into one launch
@@ -675,9 +675,10 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     uint32_t logG = 0;
     while ((1u << logG) < G) logG++;
     // A handful of ciphertexts: every step in four shorter launches (1024-blocks only)
-    const bool lat = ctx->bign_latency && BS == 1024 && batch <= latency_max_batch(G);
+    const uint32_t lat_max = latency_max_batch(G);
+    const bool lat = ctx->bign_latency && BS == 1024 && batch <= lat_max;
     if (lat && !ctx->bign_partial) {
-        const size_t cts = ctx->max_batch < latency_max_batch(G) ? ctx->max_batch : latency_max_batch(G);
+        const size_t cts = ctx->max_batch < lat_max ? ctx->max_batch : lat_max;
         void *buf = nullptr;
         if (slz_scratch_alloc(&buf, cts * 2 * R * 2 * N * sizeof(double)) != SLZ_OK) return SLZ_E_NOMEM;
         ctx->bign_partial = (double *)buf;
@@ -692,16 +693,25 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     if (chunk < fill) chunk = fill;
     // Two lanes: the chunk is cut in two halves that run on two streams, so that the row pass of one half (bound by
     // arithmetic) overlaps the column passes of the other (bound by memory).  Measured at N = 32768: 5 % faster than one
-    // lane; three or four lanes of the same size overflow the Infinity Cache and are slower.
-    uint32_t lanes = lat ? 1u : (uint32_t)ctx->bign_lanes;
+    // lane; three or four lanes of the same size overflow the Infinity Cache and are slower.  What fits two halves is cut evenly, so that
+    // the hand-over between the launches of one half hides behind the other: 73 -> 69 us per step at 24 ciphertexts, 82 -> 77 at 32,
+    // 101 -> 99 at 48.
+    uint32_t lanes = (uint32_t)ctx->bign_lanes;
+    if (lanes >= 2 && !ctx->bign_lane_stream[0]) {                  // no stream is created while the caller's is being captured
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        SLZ_HIP(hipStreamIsCapturing(s, &capture));
+        if (capture != hipStreamCaptureStatusNone) lanes = 1;
+    }
     if (lanes >= 2) {
         uint32_t half = chunk / 2 / fill * fill;
         if (half < fill) half = fill;
-        if (batch > half) chunk = half; else lanes = 1;
+        if (BS == 1024 && batch > lat_max && batch <= 2 * half) chunk = (batch + 1) / 2;
+        else if (batch > half) chunk = half;
+        else lanes = 1;
     }
     if (chunk > batch) chunk = batch;
     if (lanes >= 2) {
-        int rc = ensure_lanes(ctx);
+        int rc = ensure_lanes(ctx);                                 // only where they are used: idle queues cost a lone stream 3 % of its launches
         if (rc != SLZ_OK) return rc;
         SLZ_HIP(hipEventRecord((hipEvent_t)ctx->bign_fork, s));
         for (uint32_t j = 0; j < lanes; j++) SLZ_HIP(hipStreamWaitEvent((hipStream_t)ctx->bign_lane_stream[j], (hipEvent_t)ctx->bign_fork, 0));

@@ -1,4 +1,5 @@
-"""N = 512 (two levels), 1024 and 2048 through exact floating-point transforms: bit for bit against the oracle and the generic path."""
+"""N = 512 (two levels), 1024 and 2048 through exact floating-point transforms, and how the large-N path cuts its batches: bit for bit
+against the oracle and the generic path or one lane."""
 import numpy as np
 import pytest
 
@@ -70,3 +71,22 @@ def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch
     assert torch.equal(out, ctx.pbs_batch(*d))
     assert torch.equal(out0, ctx.pbs_batch(d[0], d[1], None, d[3]))
     assert np.array_equal(slz.to_host_u64(out)[sample], orc.pbs_batch(p, cts[sample], luts, idx[sample], bsk))
+
+
+# N = 16384: one lane up to 32 ciphertexts, two even halves from 33 to 128, halves of 64 past that
+@pytest.mark.parametrize("batch", [32, 33, 49, 128, 129])
+def test_large_n_halves_match_one_lane_and_oracle(slz, orc, batch):
+    p = synth.CONFIGS[2].with_(name="halves", N=16384, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", p.n * 8 * p.N).reshape(p.n, 2, 2, 2, p.N)
+    luts = synth.raw_words(p, "misc", p.N).reshape(1, p.N)
+    cts = synth.raw_words(p, "raw_ct", batch * (p.n + 1)).reshape(batch, p.n + 1)
+    ctx = slz.Context(p, batch)
+    assert ctx.path == "three_pass_large_n"
+    d = [slz.to_device_u64(cts), slz.to_device_u64(luts), None, ctx.bsk_prepare(slz.to_device_u64(bsk))]
+    got = [ctx.pbs_batch(*d) for _ in range(3)]
+    ctx.set_option(slz.SLZ_OPT_LARGE_N_LANES, 1)
+    ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
+    want = ctx.pbs_batch(*d)
+    assert all(torch.equal(g, want) for g in got)
+    idx = np.array([0, batch // 2 - 1, (batch + 1) // 2, batch - 1])
+    assert np.array_equal(slz.to_host_u64(want)[idx], orc.pbs_batch(p, cts[idx], luts, np.zeros(4, np.uint32), bsk))
