@@ -666,6 +666,22 @@ static uint32_t latency_max_batch(uint32_t G) { return 1024u / (2 * G) ? 1024u /
 // Up to this many ciphertexts the row pass is cut into per-GGSW-row and per-component launches, above it into one launch
 // of one-component tasks.
 static uint32_t latency_split_rows_max(uint32_t G) { return 256u / (2 * G) ? 256u / (2 * G) : 1u; }
+// Ciphertexts of the first of two lanes for a batch past latency_max_batch (1024-blocks); 0: the lanes take chunks of `half`, or one
+// lane takes all.  `half` ciphertexts are 2048 row tasks or more: alone on the chip they fill it, so a smaller batch leaves the chip idle at
+// every hand-over between its launches, which a second lane fills; a batch a little larger would be a full lane and a small rest.  From a
+// quarter above `half` on (G = 2: an eighth) the rest is large enough to hide its launches behind the full lane, while two even halves are
+// one and a half rounds of row tasks each; G >= 16 and the upper part of G = 8 move so much memory per ciphertext that even lanes win.
+// us per CMux step, one lane or full lane and rest -> even lanes:
+//   G = 2, l = 2: 260 ciphertexts 52 -> 47, 520: 74 -> 65, 640: 79 -> 80     G = 4, l = 2: 140: 54 -> 50, 288: 76 -> 73, 384: 88 -> 94
+//   G = 8, l = 2: 110: 63.6 -> 60.3, 152: 81 -> 77, 176: 83 -> 88, 208: 101 -> 98; l = 1: 66: 43.5 -> 40.4, 88: 45.0 -> 45.7, 112: 49.6 -> 47.7
+//   G = 16, l = 2: 38: 65 -> 59, 92: 94 -> 91     G = 32, l = 2: 24: 76 -> 73, 33: 94 -> 86, 48: 103 -> 101, 64: 129 -> 129
+// The cut leaves the second lane, and the first where the batch allows, a count that the XCD-aware order of the row pass takes (16 / G
+// ciphertexts at G = 4 and 8): 132 at G = 4 51 -> 48.5, 66 at G = 8, l = 2 54 -> 51.
+uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half) {
+    const bool even = batch <= half + half / (G == 2 ? 8 : 4) || G >= 16 || (G == 8 && batch >= half + half * 5 / 8);
+    const uint32_t unit = G == 4 || G == 8 ? 16 / G : 1;
+    return even && batch <= 2 * half ? batch - batch / 2 / unit * unit : 0;
+}
 
 // Runs steps [0, n_steps) on accumulators that the caller has initialised in `acc` ([batch][2][N]).
 int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc,
@@ -693,9 +709,7 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     if (chunk < fill) chunk = fill;
     // Two lanes: the chunk is cut in two halves that run on two streams, so that the row pass of one half (bound by
     // arithmetic) overlaps the column passes of the other (bound by memory).  Measured at N = 32768: 5 % faster than one
-    // lane; three or four lanes of the same size overflow the Infinity Cache and are slower.  What fits two halves is cut evenly, so that
-    // the hand-over between the launches of one half hides behind the other: 73 -> 69 us per step at 24 ciphertexts, 82 -> 77 at 32,
-    // 101 -> 99 at 48.
+    // lane; three or four lanes of the same size overflow the Infinity Cache and are slower.
     uint32_t lanes = (uint32_t)ctx->bign_lanes;
     if (lanes >= 2 && !ctx->bign_lane_stream[0]) {                  // no stream is created while the caller's is being captured
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -705,7 +719,8 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     if (lanes >= 2) {
         uint32_t half = chunk / 2 / fill * fill;
         if (half < fill) half = fill;
-        if (BS == 1024 && batch > lat_max && batch <= 2 * half) chunk = (batch + 1) / 2;
+        const uint32_t first = BS == 1024 && batch > lat_max ? slz_bign_first_of_even_lanes(G, batch, half) : 0;
+        if (first) chunk = first;
         else if (batch > half) chunk = half;
         else lanes = 1;
     }

@@ -175,6 +175,30 @@ def test_headers_are_plain_c():
         assert r.returncode == 0, r.stderr
 
 
+@pytest.mark.parametrize("G,half", [(2, 512), (4, 256), (8, 128), (16, 64), (32, 32)])
+def test_large_n_lanes_are_cut_where_it_wins_and_keep_the_order_of_the_row_pass(G, half):
+    # an internal host function, by its mangled name: ciphertexts of the first lane for a batch past half / 2, 0: not even
+    f = slz.lib()._Z28slz_bign_first_of_even_lanesjjj
+    f.argtypes, f.restype = [ctypes.c_uint32] * 3, ctypes.c_uint32
+    unit = 16 // G if G in (4, 8) else 1                    # what the XCD-aware order takes: batch * 2 G a multiple of 32
+    got = {b: f(G, b, half) for b in range(half // 2 + 1, 2 * half + 8)}
+    for b, first in got.items():
+        if first:
+            rest = b - first
+            assert b <= 2 * half and rest % unit == 0 and rest <= first < rest + 2 * unit
+            assert first % unit == 0 or b % unit            # both lanes in that order where the batch allows it
+            assert (b + first - 1) // first <= 2            # the two lanes take everything in one round
+    last = half + half // (8 if G == 2 else 4)              # measured: a full lane and the rest are faster past this ...
+    assert all(got[b] for b in got if b <= last)
+    if G < 16:
+        again = {8: half + half * 5 // 8}.get(G, 2 * half + 1)
+        assert not any(got[b] for b in range(last + 1, again))
+        assert all(got[b] for b in range(again, 2 * half + 1))
+    else:                                                   # ... and never here
+        assert all(got[b] for b in got if b <= 2 * half)
+    assert not any(got[b] for b in got if b > 2 * half)
+
+
 def test_stored_traffic_figures_belong_to_the_current_kernel_sources():
     # bench.py reports a stored FETCH_SIZE / WRITE_SIZE figure only when the kernel's sources still hash to the value recorded
     # with it; a line that has gone stale is dropped silently there, so it is caught here

@@ -73,10 +73,12 @@ def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch
     assert np.array_equal(slz.to_host_u64(out)[sample], orc.pbs_batch(p, cts[sample], luts, idx[sample], bsk))
 
 
-# N = 16384: one lane up to 32 ciphertexts, two even halves from 33 to 128, halves of 64 past that
-@pytest.mark.parametrize("batch", [32, 33, 49, 128, 129])
-def test_large_n_halves_match_one_lane_and_oracle(slz, orc, batch):
-    p = synth.CONFIGS[2].with_(name="halves", N=16384, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
+# N = 16384: one lane up to 32 ciphertexts, two even halves from 33 to 128, halves of 64 past that.  N = 8192: even lanes from 65 to 160
+# and from 208 to 256, a lane of 128 and the rest in between; N = 4096: even lanes from 129 to 320, then a lane of 256 and the rest.
+@pytest.mark.parametrize("N,batch", [(16384, 32), (16384, 33), (16384, 49), (16384, 128), (16384, 129), (8192, 66), (8192, 67), (8192, 161),
+                                     (8192, 208), (4096, 129), (4096, 134), (4096, 321)])
+def test_large_n_halves_match_one_lane_and_oracle(slz, orc, N, batch):
+    p = synth.CONFIGS[2].with_(name="halves", N=N, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
     bsk = synth.raw_words(p, "raw_bsk", p.n * 8 * p.N).reshape(p.n, 2, 2, 2, p.N)
     luts = synth.raw_words(p, "misc", p.N).reshape(1, p.N)
     cts = synth.raw_words(p, "raw_ct", batch * (p.n + 1)).reshape(batch, p.n + 1)
