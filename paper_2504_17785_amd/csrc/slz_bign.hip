@@ -642,7 +642,8 @@ static void launch_cols_any(bool fwd, int mode, uint32_t G, uint32_t BS, const b
     }
 }
 
-// Streams and events of the concurrent lanes (created at the first use, default priority).
+// Streams and events of the concurrent lanes (created at the first use, default priority; also while the caller's stream is being
+// captured, which records nothing: a graph gets its two lanes whether or not the context has used them before).
 static int ensure_lanes(slz_ctx *ctx) {
     if (ctx->bign_lane_stream[0]) return SLZ_OK;
     for (int j = 0; j < 2; j++) {
@@ -711,11 +712,6 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     // arithmetic) overlaps the column passes of the other (bound by memory).  Measured at N = 32768: 5 % faster than one
     // lane; three or four lanes of the same size overflow the Infinity Cache and are slower.
     uint32_t lanes = (uint32_t)ctx->bign_lanes;
-    if (lanes >= 2 && !ctx->bign_lane_stream[0]) {                  // no stream is created while the caller's is being captured
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        SLZ_HIP(hipStreamIsCapturing(s, &capture));
-        if (capture != hipStreamCaptureStatusNone) lanes = 1;
-    }
     if (lanes >= 2) {
         uint32_t half = chunk / 2 / fill * fill;
         if (half < fill) half = fill;

@@ -92,3 +92,34 @@ def test_large_n_halves_match_one_lane_and_oracle(slz, orc, N, batch):
     assert all(torch.equal(g, want) for g in got)
     idx = np.array([0, batch // 2 - 1, (batch + 1) // 2, batch - 1])
     assert np.array_equal(slz.to_host_u64(want)[idx], orc.pbs_batch(p, cts[idx], luts, np.zeros(4, np.uint32), bsk))
+
+
+# One lane up to 32 ciphertexts, so a context that has only seen 20 has no lane streams when the capture begins
+@pytest.mark.parametrize("batch", [49, 65])
+def test_large_n_graph_gets_both_lanes_whatever_the_context_ran_before(slz, batch):
+    import ctypes
+    p = synth.CONFIGS[2].with_(name="halves", N=16384, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", p.n * 8 * p.N).reshape(p.n, 2, 2, 2, p.N)
+    d_luts = slz.to_device_u64(synth.raw_words(p, "misc", p.N).reshape(1, p.N))
+    d_in = slz.to_device_u64(synth.raw_words(p, "raw_ct", batch * (p.n + 1)).reshape(batch, p.n + 1))
+    out = torch.empty((batch, p.N + 1), dtype=torch.int64, device="cuda")
+    nodes = {}
+    for warm in (batch, 20):
+        ctx = slz.Context(p, batch)
+        d_key = ctx.bsk_prepare(slz.to_device_u64(bsk))
+        ctx.pbs_batch(d_in[:warm], d_luts, None, d_key)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            ctx.pbs_batch(d_in, d_luts, None, d_key, out=out)
+        count = ctypes.c_size_t(0)
+        assert slz.lib().hipGraphGetNodes(ctypes.c_void_p(int(graph.raw_cuda_graph())), None, ctypes.byref(count)) == 0
+        nodes[warm] = count.value
+        graph.instantiate()
+        for rep in range(3):
+            d_in.copy_(slz.to_device_u64(synth.raw_words(p, "raw_ct", batch * (p.n + 1), offset=999 * rep + warm).reshape(batch, p.n + 1)))
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ctx.pbs_batch(d_in, d_luts, None, d_key)), (warm, rep)
+    assert nodes[20] == nodes[batch] >= 2 * 3 * p.n          # three kernels a step and lane, and the accumulators' start and extraction
