@@ -29,6 +29,38 @@ int slz_scratch_alloc(void **out, size_t bytes) {
     return SLZ_OK;
 }
 
+// Tables of the context and of every path that takes its parameter set (host vectors: may throw std::bad_alloc).
+static int init_paths(slz_ctx *ctx) {
+    const slz_params *params = &ctx->prm;
+    int rc = slz_build_tables(ctx);
+    // specialised paths are optional: a shape they decline (SLZ_E_UNSUPPORTED) runs on the generic path
+    if (rc == SLZ_OK && slz_fft_supported(params)) {
+        rc = slz_fft_init(ctx);
+        ctx->has_fft = (rc == SLZ_OK);
+    }
+    if (rc == SLZ_OK && slz_fused4096_supported(params)) {
+        rc = slz_fused4096_init(ctx);
+        ctx->has_fused4096 = (rc == SLZ_OK);
+        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
+    }
+    if (rc == SLZ_OK && slz_fused512_supported(params)) {
+        rc = slz_fused512_init(ctx);
+        ctx->has_fused512 = (rc == SLZ_OK);
+        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
+    }
+    if (rc == SLZ_OK && slz_fused1024_supported(params)) {
+        rc = slz_fused1024_init(ctx);
+        ctx->has_fused1024 = (rc == SLZ_OK);
+        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
+    }
+    if (rc == SLZ_OK && slz_bign_supported(params)) {
+        rc = slz_bign_init(ctx);
+        ctx->has_bign = (rc == SLZ_OK);
+        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
+    }
+    return rc;
+}
+
 extern "C" int slz_ctx_create(const slz_params *params, uint32_t max_batch, slz_ctx **out) {
     if (!out) return SLZ_E_INVALID_ARG;
     *out = nullptr;
@@ -55,31 +87,10 @@ extern "C" int slz_ctx_create(const slz_params *params, uint32_t max_batch, slz_
     ctx->max_batch = max_batch;
     ctx->logN = logN;
     if (hipGetDevice(&ctx->device) != hipSuccess) { delete ctx; return SLZ_E_HIP; }
-    rc = slz_build_tables(ctx);
-    // specialised paths are optional: a shape they decline (SLZ_E_UNSUPPORTED) runs on the generic path
-    if (rc == SLZ_OK && slz_fft_supported(params)) {
-        rc = slz_fft_init(ctx);
-        ctx->has_fft = (rc == SLZ_OK);
-    }
-    if (rc == SLZ_OK && slz_fused4096_supported(params)) {
-        rc = slz_fused4096_init(ctx);
-        ctx->has_fused4096 = (rc == SLZ_OK);
-        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
-    }
-    if (rc == SLZ_OK && slz_fused512_supported(params)) {
-        rc = slz_fused512_init(ctx);
-        ctx->has_fused512 = (rc == SLZ_OK);
-        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
-    }
-    if (rc == SLZ_OK && slz_fused1024_supported(params)) {
-        rc = slz_fused1024_init(ctx);
-        ctx->has_fused1024 = (rc == SLZ_OK);
-        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
-    }
-    if (rc == SLZ_OK && slz_bign_supported(params)) {
-        rc = slz_bign_init(ctx);
-        ctx->has_bign = (rc == SLZ_OK);
-        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
+    try {
+        rc = init_paths(ctx);
+    } catch (const std::bad_alloc &) {
+        rc = SLZ_E_NOMEM;
     }
     if (rc != SLZ_OK) { slz_ctx_destroy(ctx); return rc; }
     *out = ctx;
