@@ -7,10 +7,14 @@
 // ---- the error bound ------------------------------------------------------------------------------------------------
 // u = 2^-53.  All constants are multiples of u; M = N / 2 points; d = all digits of a row, K = a piece (2-norms over the N
 // real coefficients, which are the 2-norms of the M folded complex ones).
+//  Tables: a twiddle is computed in long double (64-bit significand) and rounded once.  Its angle is pi times an exact number below 3,
+//  off by at most 2 * 3 pi * 2^-64 (pi itself and the product); cosine, sine and their quotient err by at most 2^-63 together, and
+//  rounding to double after rounding to long double adds at most 2^-64 per component: below 26 * 2^-64 = 0.013 u; a quarter turn given
+//  the cosine 2^-60 has that as its only error, 0.008 u.  TABLE = 0.02 u stands for this below, once per use of a twiddle.
 //  Forward (radix-4 butterflies, each a0 + v^2 a2 +- (v a1 + v^3 a3) and a0 - v^2 a2 +- i (v a1 - v^3 a3)): a complex product
 //  of two multiplications and two fused multiply-adds errs by at most 2 u |w| |a|, the rounding of the twiddle's two
-//  components adds sqrt(1/2) u, the two layers of additions u each: 4.71 u per butterfly relative to the 2-norm, five layers
-//  of butterflies for M = 1024.  So ||dX||_2 <= 23.6 u ||X||_2 = 23.6 u sqrt(M) ||d||_2.
+//  components adds sqrt(1/2) u and TABLE, the two layers of additions u each: 4.73 u per butterfly relative to the 2-norm, five
+//  layers of butterflies for M = 1024.  So ||dX||_2 <= 23.7 u ||X||_2 = 23.7 u sqrt(M) ||d||_2.
 //  Products: S = D0 K0 + D1 K1 as a chain of four fused multiply-adds per component: partial results are at most
 //  |D0 K0| (twice), |D0 K0| + |D1 K1| (twice), so the error is at most u (4 |D0 K0| + 2 |D1 K1|); the key spectrum is a
 //  correctly rounded value of a double-double transform: another u |D K| (1.05 u with the transform's own error).
@@ -20,21 +24,21 @@
 //  wr and tau at most 2 u |b|, of the bracket u |b|, of the result u |o|, together 4 u; half-size 512 with the twist is the
 //  same with a already multiplied by a plain complex factor (2.71 u, not above the 3 u of the other operand), and the second
 //  half of its outputs is turned by 45 degrees: an addition and the constant sqrt(1/2) (1.61 u; the product itself is inside the
-//  fused rounding add).  1 + 1 + 2.61 + 6 * 4 + 4 + 1.61 = 34.22 u.
+//  fused rounding add).  1 + 1 + 2.61 + 6 * 4 + 4 + 1.61 = 34.22 u, and TABLE for each of the seven stages with table twiddles.
 //  Second-order terms are covered by the factor 1 + 2^-40.
 // Every row r contributes ||d_r|| ||K_(r,j)||.  The chain of four constants above is for two rows.
-// N = 1024, M = 512: the forward layers are radix-2 butterflies of the inverse's form, at most 4 u each relative to the 2-norm
-// (final rounding u |o|, the rest 3 u |b|, and the two outputs' norm is at least sqrt(2) |b|): nine of them, 36 u; the inverse
-// has one stage less: 30.22 u.
-// N = 512, M = 256: eight forward layers, 32 u; half-size 4 is a butterfly like the others, 27.61 u; four rows, so the chain of
-// fused multiply-adds gives (8 + 6 + 4 + 2) u |D K|, 5 u per row.
+// N = 1024, M = 512: the forward layers are radix-2 butterflies of the inverse's form, at most 4 u and TABLE each relative to the 2-norm
+// (final rounding u |o|, the rest 3 u |b|, and the two outputs' norm is at least sqrt(2) |b|): nine of them; the inverse
+// has one stage less: 30.22 u and six times TABLE.
+// N = 512, M = 256: eight forward layers; half-size 4 is a butterfly like the others, 27.61 u and six times TABLE; four rows, so the
+// chain of fused multiply-adds gives (8 + 6 + 4 + 2) u |D K|, 5 u per row.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
-    const double u = std::ldexp(1.0, -53), key = 1.05;
+    const double u = std::ldexp(1.0, -53), key = 1.05, table = 0.02;
     double fwd, inv;
     int bits = SLZ_FFT_PIECE_BITS;
-    if (N == 2048 && rows == 2) { fwd = 5 * 4.7072; inv = 34.22; }
-    else if (N == 1024 && rows == 2) { fwd = 9 * 4.0; inv = 30.22; }
-    else if (N == 512 && rows == 4) { fwd = 8 * 4.0; inv = 27.61; bits = F9_PIECE_BITS; }
+    if (N == 2048 && rows == 2) { fwd = 5 * (4.7072 + table); inv = 34.22 + 7 * table; }
+    else if (N == 1024 && rows == 2) { fwd = 9 * (4.0 + table); inv = 30.22 + 6 * table; }
+    else if (N == 512 && rows == 4) { fwd = 8 * (4.0 + table); inv = 27.61 + 6 * table; bits = F9_PIECE_BITS; }
     else return 1e300;
     const double norm_d = std::ldexp(std::sqrt((double)N), (int)beta - 1);
     const double norm_k = std::ldexp(std::sqrt((double)N), bits - 1);

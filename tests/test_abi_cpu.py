@@ -1,6 +1,7 @@
 """Host-only checks of the C-ABI library (no GPU): it loads, exports every symbol the header declares,
 its pure host function slz_lut_encode agrees with the oracle, and argument errors are reported."""
 import ctypes
+import decimal
 import os
 import re
 
@@ -173,6 +174,36 @@ def test_headers_are_plain_c():
         r = subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-fsyntax-only", "-x", "c", os.path.join(inc, h)],
                            capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def test_transform_error_bound_and_the_bases_it_admits():
+    # internal host functions, by their mangled names.  The sum is written out again: rounding of the layers (a radix-4 layer 2 for the
+    # product, sqrt(1/2) for its twiddle, 2 for two additions; a radix-2 layer 4), of the products (one per fused multiply-add, the
+    # partial results of a row counted as often as they are rounded), of the key spectrum, of the inverse's stages and the constant
+    # sqrt(1/2) in two of them, and for every table
+    # twiddle what its computation in long double leaves, 26 * 2^-64 of angle, functions and second rounding.
+    L = slz.lib()
+    bound, supported = L._Z19slz_fft_error_boundjjj, L._Z17slz_fft_supportedPK10slz_params
+    bound.argtypes, bound.restype = [ctypes.c_uint32] * 3, ctypes.c_double
+    table = 26 * 2.0 ** -11
+    half = 0.5 ** 0.5                                                 # as a double; its relative error in units of 2^-53:
+    root = decimal.Context(prec=40).sqrt(decimal.Decimal("0.5"))
+    constant = float(abs(decimal.Decimal(half) / root - 1)) * 2.0 ** 53
+    shapes = {(2048, 1): (23, 5, 13, 5 * (4 + half + table) + 3 + 1.05 + 2 + (2 + constant) + 7 * (4 + table) + 1 + constant),
+              (1024, 1): (23, 5, 13, 9 * (4 + table) + 3 + 1.05 + 2 + (2 + constant) + 6 * (4 + table) + 1 + constant),
+              (512, 2): (14, 3, 22, 8 * (4 + table) + 5 + 1.05 + 2 + 6 * (4 + table) + 1 + constant)}
+    for (N, level), (top, pieces, bits, units) in shapes.items():
+        assert pieces * bits >= 64                                    # the pieces make up a key word
+        rows = 2 * level
+        for beta in range(1, top + 2):
+            want = units * 2.0 ** -53 * rows * N * 2.0 ** (beta - 1) * 2.0 ** (bits - 1)
+            got = bound(N, rows, beta)
+            assert want <= got <= 1.01 * want, (N, beta)
+            assert bool(supported(ctypes.byref(slz.make_params(synth.CONFIGS[2].with_(N=N, pbs_level=level, pbs_base_log=beta))))) == \
+                (got < 0.499) == (beta <= top), (N, beta)
+    for kw in (dict(N=2048, pbs_level=2), dict(N=1024, pbs_level=2), dict(N=512, pbs_level=1), dict(N=4096), dict(N=1024, k=2), dict(N=256)):
+        q = synth.CONFIGS[2].with_(pbs_base_log=kw.pop("beta", 8), **kw)
+        assert not supported(ctypes.byref(slz.make_params(q))), kw
 
 
 @pytest.mark.parametrize("G,half", [(2, 512), (4, 256), (8, 128), (16, 64), (32, 32)])
