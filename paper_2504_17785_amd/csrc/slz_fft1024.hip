@@ -13,8 +13,8 @@
 // Bound and shape: FP64 issue.  A step is about 4.2 k VALU instructions per ciphertext; registers (accumulator 64, spectra 64, transform 64,
 // key words 64 of 256) allow two waves per SIMD.  The two components of a wave hide each other's LDS round trips.  Smaller batches
 // leave compute units with fewer than eight ciphertexts, so waves share one (SHARE below).  Measured with 630 steps and the
-// keyswitch (in brackets: two 50-bit residues on the same card): one ciphertext 3.6 ms (4.6), 512: 5.6 (6.9), 777: 8.5 (13.2),
-// 2048: 14.9 (24.0), 8192: 60.9 (102).
+// keyswitch (in brackets: two 50-bit residues on the same card): one ciphertext 3.7 ms (4.6), 512: 5.6 (7.0), 777: 8.5 (13.1),
+// 2048: 15.4 (24.4), 8192: 60.3 (102).
 #include "slz_fft.h"
 #include "slz_fft_wave.h"
 #include "slz_modarith.h"
@@ -446,10 +446,9 @@ k_fft1024_blind_rotate(fft1024_args A) {
 // ---- host side ------------------------------------------------------------------------------------------------------
 
 int slz_fft1024_setup() {
-    const void *const kernels[8] = {(const void *)k_fft1024_blind_rotate<23, 4>, (const void *)k_fft1024_blind_rotate<0, 4>,
-                                    (const void *)k_fft1024_blind_rotate<23, 1>, (const void *)k_fft1024_blind_rotate<0, 1>,
+    const void *const kernels[6] = {(const void *)k_fft1024_blind_rotate<0, 8>, (const void *)k_fft1024_blind_rotate<0, 4>,
                                     (const void *)k_fft1024_blind_rotate<23, 2>, (const void *)k_fft1024_blind_rotate<0, 2>,
-                                    (const void *)k_fft1024_blind_rotate<23, 8>, (const void *)k_fft1024_blind_rotate<0, 8>};
+                                    (const void *)k_fft1024_blind_rotate<23, 1>, (const void *)k_fft1024_blind_rotate<0, 1>};
     for (const void *k : kernels) SLZ_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, F10_LDS_BYTES));
     return SLZ_OK;
 }
@@ -471,9 +470,11 @@ int slz_fft1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
     const uint32_t grid = slz_fused_grid(batch, 1);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(F10_THREADS), F10_LDS_BYTES, s, A); };
+    // The base 2^23 of the parameter sets as a constant: 1024 ciphertexts with SHARE = 2 8.96 ms instead of 9.20, 1025 with SHARE = 1 12.04
+    // instead of 12.30.  With SHARE = 8 and 4 the base as an argument is as fast (200: 3.64, 512: 5.63 against 5.67).
     const bool b23 = A.beta == 23;
-    if (batch <= F10_MAX_8) b23 ? launch(k_fft1024_blind_rotate<23, 8>) : launch(k_fft1024_blind_rotate<0, 8>);
-    else if (batch <= F10_MAX_4) b23 ? launch(k_fft1024_blind_rotate<23, 4>) : launch(k_fft1024_blind_rotate<0, 4>);
+    if (batch <= F10_MAX_8) launch(k_fft1024_blind_rotate<0, 8>);
+    else if (batch <= F10_MAX_4) launch(k_fft1024_blind_rotate<0, 4>);
     else if (batch <= F10_MAX_2) b23 ? launch(k_fft1024_blind_rotate<23, 2>) : launch(k_fft1024_blind_rotate<0, 2>);
     else b23 ? launch(k_fft1024_blind_rotate<23, 1>) : launch(k_fft1024_blind_rotate<0, 1>);
     SLZ_HIP(hipGetLastError());

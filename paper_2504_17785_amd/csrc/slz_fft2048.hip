@@ -39,8 +39,8 @@
 #define FFT_WIDE_MAX 256                            // batches up to this take the shared form, one workgroup per ciphertext
 #define FFT_THREADS (64 * FFT_WAVES)
 #define FFT_BUF (4u * 272u * 16u)                   // bytes of a wave's exchange buffer: 1024 points, padded
-#define FFT_AHEAD 0                                 // positions (of four key words each) requested before the last inverse stage
-#define FFT_EARLY (FFT_AHEAD + 4)                   // and by its end: each of its eight butterflies frees the registers of half a position
+#define FFT_EARLY 4                                 // positions (of four key words each) requested during the last inverse stage: each of its
+                                                    // eight butterflies frees the registers of half a position
 #define FFT_RING 4                                  // positions in registers at a time during the products
 #define FFT_FLAGS_OFF (FFT_WAVES * FFT_BUF + FFT_LDS_TAB * 16u)
 #define FFT_FLAGS 34u                               // done and free per wave; for WIDE: spectra written (2), read (8), sums written (8)
@@ -71,12 +71,13 @@ __device__ __forceinline__ void fwd4(d2 &a0, d2 &a1, d2 &a2, d2 &a3, d2 v, d2 v2
 // compute unit: all four pairs work on one.  Pair 0 owns the accumulator and runs step 1 and the forward transform; every pair reads
 // the spectra from pair 0's exchange buffers and takes one or two of the key pieces (its first piece's key words wait in registers
 // by then); the sums of the other pairs come back through their exchange buffers.
-template <int BETA, bool WIDE>
+// The base is an argument: an instance with 23 as a constant measured the same (256 ciphertexts 8.28 ms, 301: 12.95, 1024: 20.2).
+template <bool WIDE>
 __global__ void __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_fft_blind_rotate(fft_args A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const uint32_t lds = (uint32_t)(uintptr_t)(LDS_AS unsigned char *)lds_raw;
-    const uint32_t beta = BETA > 0 ? (uint32_t)BETA : A.beta;
+    const uint32_t beta = A.beta;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t h = wave & 1u, pair = wave >> 1;
@@ -374,10 +375,6 @@ k_fft_blind_rotate(fft_args A) {
                         for (int e = 0; e < 16; e += 4) { inv2<false>(x[e], x[e + 2], w0); inv2<true>(x[e + 1], x[e + 3], w0); }
                         FFT_FENCE();
                         kp += 4096u;
-                        if (next >= 0) {
-#pragma unroll
-                            for (int k = 0; k < FFT_AHEAD; k++) request(k);
-                        }
                         d2 c1[2], c2[2];
                         c1[0] = lds_get(t3 + 3072); c2[0] = lds_get(t3 + 4096);
                         FFT_FENCE();
@@ -411,7 +408,7 @@ k_fft_blind_rotate(fft_args A) {
                                 FFT_FENCE();
 #pragma unroll
                                 for (int q = 0; q < 2; q++)
-                                    kb[FFT_AHEAD + e / 2][2 * (e & 1) + q] = lane_get(kp + (4 * (FFT_AHEAD + e / 2) + 2 * (e & 1) + q) * 64, kl);
+                                    kb[e / 2][2 * (e & 1) + q] = lane_get(kp + (4 * (e / 2) + 2 * (e & 1) + q) * 64, kl);
                             }
                         }
                     }
@@ -482,8 +479,7 @@ k_fft_blind_rotate(fft_args A) {
 // ---- host side ------------------------------------------------------------------------------------------------------
 
 int slz_fft2048_setup() {
-    const void *const kernels[4] = {(const void *)k_fft_blind_rotate<23, false>, (const void *)k_fft_blind_rotate<0, false>,
-                                    (const void *)k_fft_blind_rotate<23, true>, (const void *)k_fft_blind_rotate<0, true>};
+    const void *const kernels[2] = {(const void *)k_fft_blind_rotate<false>, (const void *)k_fft_blind_rotate<true>};
     for (const void *k : kernels) SLZ_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
     return SLZ_OK;
 }
@@ -500,13 +496,8 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(FFT_THREADS), FFT_LDS_BYTES, s, A); };
     // Up to one ciphertext per compute unit, its four pairs share the ciphertext's work: 8.2 ms for 256 ciphertexts and 742 steps,
     // 12.9 ms with a pair for each.  From 257 on, the shared form needs a second round: 17.1 ms against 12.9 ms.
-    if (batch <= FFT_WIDE_MAX) {
-        if (A.beta == 23) launch(k_fft_blind_rotate<23, true>);
-        else launch(k_fft_blind_rotate<0, true>);
-    } else {
-        if (A.beta == 23) launch(k_fft_blind_rotate<23, false>);
-        else launch(k_fft_blind_rotate<0, false>);
-    }
+    if (batch <= FFT_WIDE_MAX) launch(k_fft_blind_rotate<true>);
+    else launch(k_fft_blind_rotate<false>);
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;
 }
