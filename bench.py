@@ -26,18 +26,30 @@ if ROOT not in sys.path:
 PEAK_ALU_TINSTR = 256 * 4 * 16 * 2.4e9 / 1e12      # 256 CUs x 4 SIMD16 x 2.4 GHz: FP64/INT32 lane-instructions per second
 
 
-def alu_model_ops_per_pbs(p, generic=False) -> float:
+def residue_key_bytes(p) -> int:
+    """Size of a prepared key's residue form (slz_bsk_prepare): doubles for two primes."""
+    return p.n * 2 * (p.k + 1) * p.pbs_level * (p.k + 1) * p.N * 8
+
+
+def key_bytes_read(p, prepared_bytes, generic=False):
+    """(bytes of the prepared key that a launch reads, whether that is the transform form).  A key holds the residue form and, where
+    the context takes floating-point transforms, their form behind it; a launch reads one of the two."""
+    residue = residue_key_bytes(p)
+    transforms = prepared_bytes > residue and not generic
+    return (prepared_bytes - residue if transforms else residue), transforms
+
+
+def alu_model_ops_per_pbs(p, transforms=False) -> float:
     """Algorithmic VALU lane-instructions of one PBS, from this op table:
     8 per butterfly (6 modular multiply + add + sub), 7 per pointwise multiply-accumulate, 3 per inverse
     post-scaling beyond the butterflies' share (6-instruction modular multiply per coefficient), 12 per
     decomposed coefficient (rotate, subtract, round, digit, convert) and 20 per CRT-lifted coefficient.
-    Shapes that run through floating-point transforms of M = N / 2 complex points (N = 1024 and 2048 with k = l = 1, five key pieces;
-    N = 512 with k = 1, l = 2, three): 6 per radix-2 butterfly (N = 2048 forward: 28 per radix-4 butterfly), 4 per complex
+    transforms: a context that takes floating-point transforms of M = N / 2 complex points (N = 1024 and 2048: five key pieces;
+    N = 512: three), which is what the size of its prepared key says: 6 per radix-2 butterfly (N = 2048 forward: 28 per radix-4 butterfly), 4 per complex
     multiply-add, the same 12 (+ 4 per level) per decomposed coefficient and 2 per coefficient and piece for rounding and adding."""
     logN = p.N.bit_length() - 1
     R, C = (p.k + 1) * p.pbs_level, p.k + 1
-    top = {(2048, 1, 1): 23, (1024, 1, 1): 23, (512, 1, 2): 14}.get((p.N, p.k, p.pbs_level), -1)   # largest base 2^top of that path
-    if p.pbs_base_log <= top and not generic:
+    if transforms:
         M, pieces = p.N // 2, 3 if p.N == 512 else 5
         forward = 5 * (M // 4) * 28 if p.N == 2048 else (logN - 1) * (M // 2) * 6
         return float(p.n) * (R * forward + pieces * R * C * M * 4 + pieces * C * (logN - 1) * (M // 2) * 6 +
@@ -96,7 +108,7 @@ def bench_matmul_rns(args):
         ctx.matmul_rns(d_x, d_w, m, d_luts, d_bskp, d_ksk, out=d_y, highres=highres)
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / args.steps
-    achieved = lookups * alu_model_ops_per_pbs(p) / (ms * 1e-3) / 1e12
+    achieved = lookups * alu_model_ops_per_pbs(p, key_bytes_read(p, ctx.bsk_prepared_bytes())[1]) / (ms * 1e-3) / 1e12
     result = {
         "metric": "%s_lookups_per_s" % args.gadget, "value": lookups / (ms * 1e-3), "unit": "PBS+KS/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
@@ -175,7 +187,7 @@ def bench_sign_rns(args):
         d_s, d_shift = run()
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / args.steps
-    achieved = lookups * alu_model_ops_per_pbs(p) / (ms * 1e-3) / 1e12
+    achieved = lookups * alu_model_ops_per_pbs(p, key_bytes_read(p, ctx.bsk_prepared_bytes())[1]) / (ms * 1e-3) / 1e12
     result = {
         "metric": "%s_lookups_per_s" % args.gadget, "value": lookups / (ms * 1e-3), "unit": "PBS+KS/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
@@ -261,7 +273,7 @@ def bench_loss(args):
         d_out = run()
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / args.steps
-    achieved = lookups * alu_model_ops_per_pbs(p) / (ms * 1e-3) / 1e12
+    achieved = lookups * alu_model_ops_per_pbs(p, key_bytes_read(p, ctx.bsk_prepared_bytes())[1]) / (ms * 1e-3) / 1e12
     what = ("IntCELossDeriv of %d x %d logits (Gamma %d, kappa %d)" % (a, b, Gamma, kappa)) if loss else \
         ("clipped update of %d weights (alpha %d)" % (count, alpha))
     result = {
@@ -296,8 +308,8 @@ def bench_loss(args):
 # ---- the PBS + keyswitch step of one configuration ---------------------------------------------------------------------
 
 PATH_SOURCES = {       # sources of the dominant kernel of each path (for the check that a stored traffic figure is current)
-    "fused_n2048": ("slz_fft2048.hip", "slz_fft_wave.h", "slz_modarith.h"),
-    "fused_n512": ("slz_fft512.hip", "slz_fft_wave.h", "slz_modarith.h"),
+    "fused_n2048": ("slz_fft2048.hip", "slz_fft.h", "slz_fft_wave.h", "slz_modarith.h"),
+    "fused_n512": ("slz_fft512.hip", "slz_fft.h", "slz_fft_wave.h", "slz_modarith.h"),
     "three_pass_large_n": ("slz_bign.hip", "slz_wave_ntt.h", "slz_modarith.h"),
 }
 
@@ -443,8 +455,9 @@ class Workload:
     def report(self, t, generic=False):
         """Rates and roofline fractions of one timed run (`t` from run())."""
         p, batch, synth = self.p, self.batch, self.synth
-        achieved = alu_model_ops_per_pbs(p, generic) * batch / (t["pbs_ms"] * 1e-3) / 1e12
         prepared_bytes = self.ctx.bsk_prepared_bytes()
+        key_bytes, transforms = key_bytes_read(p, prepared_bytes, generic)
+        achieved = alu_model_ops_per_pbs(p, transforms) * batch / (t["pbs_ms"] * 1e-3) / 1e12
         r = {"workload": "%s: batch %d, n=%d, k=%d, N=%d, PBS 2^%d x %d, KS 2^%d x %d" % (
                  p.name, batch, p.n, p.k, p.N, p.pbs_base_log, p.pbs_level, p.ks_base_log, p.ks_level),
              "path": self.ctx.path,
@@ -453,7 +466,7 @@ class Workload:
              "ms_per_step": t["ms_per_step"], "pbs_ms": t["pbs_ms"], "keyswitch_ms": t["ks_ms"], "lincomb_ms": t["lin_ms"],
              "keyswitch_key": "prepared" if self.d_kskp is not None else "standard",
              "bsk_prepared_bytes": prepared_bytes,
-             "bsk_stream_GBps_min": prepared_bytes / (t["pbs_ms"] * 1e-3) / 1e9,
+             "bsk_stream_GBps_min": key_bytes / (t["pbs_ms"] * 1e-3) / 1e9,
              "roofline": {"bound": "alu", "kernel": "blind rotation (slz_pbs_batch)", "achieved": achieved,
                           "peak": PEAK_ALU_TINSTR, "unit": "Tinstr/s", "frac": achieved / PEAK_ALU_TINSTR,
                           "traffic": stored_traffic(self.ctx.path, "%s_batch%d" % (p.name, batch))}}

@@ -230,6 +230,23 @@ def test_large_n_lanes_are_cut_where_it_wins_and_keep_the_order_of_the_row_pass(
     assert not any(got[b] for b in got if b > 2 * half)
 
 
+def test_bench_counts_the_key_form_and_the_operations_of_the_path_that_runs():
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    p = synth.CONFIGS[2]
+    residue, transform = 742 * 2 * 4 * 2048 * 8, 742 * 5 * 2 * 8 * 4 * 64 * 16          # 97 and 243 MB
+    assert bench.residue_key_bytes(p) == residue
+    assert bench.key_bytes_read(p, residue + transform) == (transform, True)
+    assert bench.key_bytes_read(p, residue + transform, generic=True) == (residue, False)
+    assert bench.key_bytes_read(p, residue) == (residue, False)
+    assert bench.alu_model_ops_per_pbs(p, True) == 742 * 550912.0
+    assert bench.alu_model_ops_per_pbs(p, False) == bench.alu_model_ops_per_pbs(p) > 1.8 * 742 * 550912.0
+    # what changes the traffic of a kernel is in the hash of its sources: the header holds the piece count and the key's step size
+    for path in ("fused_n2048", "fused_n512"):
+        assert "slz_fft.h" in bench.PATH_SOURCES[path]
+
+
 def test_stored_traffic_figures_belong_to_the_current_kernel_sources():
     # bench.py reports a stored FETCH_SIZE / WRITE_SIZE figure only when the kernel's sources still hash to the value recorded
     # with it; a line that has gone stale is dropped silently there, so it is caught here
