@@ -441,28 +441,23 @@ def test_fused_more_ciphertexts_than_resident_workgroups(slz, orc):
     assert np.array_equal(fused[idx], want)
 
 
-def test_fused_pacing_between_ciphertexts_changes_nothing(slz, orc):
-    # 1100 ciphertexts on 512 workgroups: three rounds, the last one ragged (76 workgroups).  Between rounds the workgroups wait
-    # for each other (a timing hint with a bounded wait); with it off they run free.  Same bits either way, on repeated
-    # launches (the arrival counters are cleared per launch), and with a batch that needs no pacing in between.
+def test_fused_several_ciphertexts_per_pair_of_waves_and_the_pacing_option(slz, orc):
+    # 1100 ciphertexts on 256 workgroups of four pairs of waves: 76 pairs take a second one.  Repeated launches and a batch that needs
+    # no second ciphertext give the same bits.
     p, case = _fused_case(slz, orc, 2, 1100)
     ctx = case.ctx
-    paced = slz.to_host_u64(ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
+    first = slz.to_host_u64(ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
     small = slz.to_host_u64(ctx.pbs_batch(case.d_cts[:300], case.d_luts, case.d_idx[:300], case.d_bsk))
     again = slz.to_host_u64(ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
-    ctx.set_option(slz.SLZ_OPT_FUSED_PACING, 0)
-    free = slz.to_host_u64(ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
-    assert np.array_equal(paced, free) and np.array_equal(again, free) and np.array_equal(small, free[:300])
+    assert np.array_equal(again, first) and np.array_equal(small, first[:300])
     idx = np.array([0, 511, 512, 1023, 1024, 1099])
-    assert np.array_equal(paced[idx], orc.pbs_batch(p, case.cts[idx], case.luts, case.lut_idx[idx], case.keys.bsk))
-    # the give-up path: paced, but the first wait that is not satisfied at once switches the pacing off for the launch
-    ctx.set_option(slz.SLZ_OPT_FUSED_PACING, 2)
-    gave_up = slz.to_host_u64(ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
-    ctx.set_option(slz.SLZ_OPT_FUSED_PACING, 1)
-    after = slz.to_host_u64(ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
-    assert np.array_equal(gave_up, free) and np.array_equal(after, free)
-    with pytest.raises(slz.SlzError):
-        ctx.set_option(slz.SLZ_OPT_FUSED_PACING, 3)
+    assert np.array_equal(first[idx], orc.pbs_batch(p, case.cts[idx], case.luts, case.lut_idx[idx], case.keys.bsk))
+    # the option of an earlier kernel of this path: still accepted here and refused elsewhere
+    for value in (0, 2, 1):
+        ctx.set_option(slz.SLZ_OPT_FUSED_PACING, value)
+    for value in (3, -1):
+        with pytest.raises(slz.SlzError):
+            ctx.set_option(slz.SLZ_OPT_FUSED_PACING, value)
     with pytest.raises(slz.SlzError):
         slz.Context(tiny(), 4).set_option(slz.SLZ_OPT_FUSED_PACING, 1)      # not the N = 2048 fused path
 
@@ -914,7 +909,7 @@ def test_keyswitch_first_error_codes(slz, orc):
                                          (dict(n=2, N=16384, k=1, pbs_base_log=15, pbs_level=1), 70),
                                          (dict(n=2, N=2048, k=1, pbs_base_log=23, pbs_level=1, ks_base_log=4, ks_level=8), 1100),
                                          (dict(n=2, N=8192, k=1, pbs_base_log=15, pbs_level=2), 3)],
-                         ids=["fused_n2048", "fused_n1024", "generic_k2", "large_n_two_lanes", "fused_n2048_paced_rounds",
+                         ids=["fused_n2048", "fused_n1024", "generic_k2", "large_n_two_lanes", "fused_n2048_second_ciphertexts",
                               "large_n_latency_kernels"])
 def test_lookup_replays_from_a_hip_graph(slz, orc, shape, batch):
     """A serving loop captures one lookup (bootstrapping + keyswitch) once and replays it: after a warm-up call (which makes
