@@ -428,9 +428,9 @@ def test_fused_other_gadget_bases(slz, orc):
         assert np.array_equal(got, want), beta
 
 
-def test_fused_more_ciphertexts_than_resident_workgroups(slz, orc):
-    # 600 ciphertexts > 512 resident workgroups: some workgroups process two; compare the fused path with the
-    # generic path on all, and with the oracle on a sample
+def test_fused_several_ciphertexts_per_workgroup(slz, orc):
+    # 600 ciphertexts on 256 workgroups: two or three of a workgroup's four pairs of waves have one; compare the fused path with
+    # the generic path on all, and with the oracle on a sample
     p, case = _fused_case(slz, orc, 3, 600)
     fused = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
     case.ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)
@@ -527,7 +527,7 @@ def test_fused_n512_two_levels_states_and_outputs_match_oracle(slz, orc, beta):
     assert np.array_equal(slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)), want)
 
 
-def test_fused_n512_two_levels_worst_case_and_many_ciphertexts(slz, orc):
+def test_fused_n512_two_levels_worst_case_in_residues_and_many_ciphertexts_through_transforms(slz, orc):
     p = tiny(n=3, N=512, k=1, pbs_base_log=24, pbs_level=2)       # 4 * 512 * 2^23 * 2^63 = 2^97: the largest sums allowed
     case = Case(slz, orc, p, 3, raw_inputs=True)
     assert case.ctx.path == "fused_n512"
@@ -548,6 +548,23 @@ def test_fused_n512_two_levels_worst_case_and_many_ciphertexts(slz, orc):
     assert np.array_equal(fused[idx], orc.pbs_batch(many.p, many.cts[idx], many.luts, many.lut_idx[idx], many.keys.bsk))
     many.ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)
     assert np.array_equal(slz.to_host_u64(many.ctx.pbs_batch(many.d_cts, many.d_luts, many.d_idx, many.d_bsk)), fused)
+
+
+# Residue kernels that keep the bases beyond the transforms' error bound, with more ciphertexts than resident workgroups (512 and 768):
+# some workgroups process a second one in the same LDS.
+@pytest.mark.parametrize("N,l,beta,batch,grid", [(512, 2, 15, 600, 512), (512, 2, 24, 1100, 512), (1024, 1, 24, 800, 768), (1024, 1, 24, 1540, 768)])
+def test_residue_kernels_take_a_second_ciphertext_per_workgroup(slz, orc, N, l, beta, batch, grid):
+    p = tiny(n=3, N=N, k=1, pbs_base_log=beta, pbs_level=l)
+    case = Case(slz, orc, p, batch, raw_inputs=True)
+    assert case.ctx.path == "fused_n%d" % N
+    assert case.ctx.bsk_prepared_bytes() == p.n * 2 * 4 * l * N * 8           # no transform form: the residue kernel runs
+    out = case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)
+    state = case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, 2)
+    idx = np.array([0, 1, grid - 1, grid, grid + 1, batch - 1])
+    assert np.array_equal(slz.to_host_u64(out)[idx], orc.pbs_batch(p, case.cts[idx], case.luts, case.lut_idx[idx], case.keys.bsk))
+    case.ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)
+    assert torch.equal(out, case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
+    assert torch.equal(state, case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, 2))
 
 
 # ---------------------------------------------------------------- fused kernel for N = 1024 (k = 1, l = 1)
@@ -587,8 +604,9 @@ def test_fused_n1024_worst_case_magnitudes(slz, orc):
     assert np.array_equal(got, want)
 
 
-def test_fused_n1024_more_ciphertexts_than_resident_workgroups_and_decryption(slz, orc):
-    # 600 ciphertexts > 512 resident workgroups; real encryptions: the whole batch decrypts to the tables
+def test_fused_n1024_several_ciphertexts_per_workgroup_and_decryption(slz, orc):
+    # 600 ciphertexts through transforms, two waves each: two or three in a workgroup; real encryptions: the whole batch decrypts to
+    # the tables
     p = tiny(n=16, N=1024, k=1, pbs_base_log=23, pbs_level=1, ks_base_log=4, ks_level=4, msg_bits=3, sigma_lwe=2.0 ** -30,
              sigma_bsk=2.0 ** -50)
     case = Case(slz, orc, p, 600)
