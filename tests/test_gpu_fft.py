@@ -42,19 +42,23 @@ def _inputs(slz, batch, beta, n=3, extreme=False, N=2048):
     idx = (np.arange(batch) % 2).astype(np.uint32)
     ctx = slz.Context(p, batch)
     assert ctx.path == "fused_n%d" % N
+    # the prepared key: the residue form, and behind it the transform form where the error bound holds
+    steps = {2048: 5 * 2 * 8 * 4 * 64, 1024: 5 * 8 * 4 * 64, 512: 3 * 4 * 8 * 64}
+    transform = n * steps[N] * 16 if beta <= {2048: 23, 1024: 23, 512: 14}[N] else 0
+    assert ctx.bsk_prepared_bytes() == n * 2 * 4 * l * N * 8 + transform
     d = [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy(idx.astype(np.int32)).cuda(),
          ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, l, 2, N)))]
     return p, ctx, bsk.reshape(n, 2, l, 2, N), luts, cts, idx, d
 
 
 # N = 2048: 2^23 is the largest base a context takes; 256 and 257 ciphertexts are the two sides of the line between the two forms of
-# the kernel, 1025 and 1300 give some pairs of waves a second ciphertext.  N = 1024: the lines are at 256 and 1024, 2100 gives some
+# the kernel, 1025 and 1300 give some pairs of waves a second ciphertext.  N = 1024: the lines are at 256, 512 and 1024, 2100 gives some
 # waves a second ciphertext; 2^23 is the largest base whose error bound holds (2^24 stays on residues).  N = 512: the lines are at 256
 # and 512; 2^14 is the largest base whose bound holds.
 @pytest.mark.parametrize("N,batch,beta,extreme", [
     (2048, 1, 23, False), (2048, 5, 12, True), (2048, 37, 1, False), (2048, 256, 23, True), (2048, 257, 23, False),
     (2048, 300, 23, True), (2048, 300, 1, True), (2048, 260, 12, False), (2048, 1025, 23, False), (2048, 1300, 22, True),
-    (1024, 1, 23, False), (1024, 3, 12, True), (1024, 256, 23, True), (1024, 257, 23, True), (1024, 512, 23, False), (1024, 600, 1, False),
+    (1024, 1, 23, False), (1024, 3, 12, True), (1024, 256, 23, True), (1024, 257, 23, True), (1024, 512, 23, False), (1024, 513, 23, True), (1024, 600, 1, False),
     (1024, 1024, 23, False), (1024, 1025, 23, True), (1024, 2100, 22, True), (1024, 40, 24, True),
     (512, 1, 8, False), (512, 7, 14, True), (512, 256, 1, False), (512, 257, 14, True), (512, 512, 8, False), (512, 513, 8, True),
     (512, 1024, 14, False), (512, 1025, 14, True), (512, 2100, 8, False), (512, 40, 15, True)])
@@ -63,6 +67,10 @@ def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch
     sample = np.unique(np.minimum([0, 1, 2, 255, 256, batch - 1], batch - 1))
     got = {s: ctx.blind_rotate_batch(*d, s) for s in (0, 1, p.n)}
     out, out0 = ctx.pbs_batch(*d), ctx.pbs_batch(d[0], d[1], None, d[3])
+    # which of the two kernels behind one path name ran: without the residue form only the transform kernel gives the same
+    other = d[3].clone()
+    other[:bsk.size * 2] = 0
+    assert torch.equal(ctx.pbs_batch(*d[:3], other), out) == (other.numel() > bsk.size * 2)
     ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)                       # the same prepared key
     for s, acc in got.items():
         assert torch.equal(acc, ctx.blind_rotate_batch(*d, s)), s
