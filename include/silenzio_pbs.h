@@ -86,7 +86,7 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      0 keeps the throughput kernels at every batch size; SLZ_E_INVALID_ARG without a large-N path */
 
 #define SLZ_OPT_FUSED_PACING 6    /* values 0, 1 and 2, on the N = 2048 fused path: accepted and without effect.  They paced the workgroups of
-                                     an earlier kernel of this path; the present one reads its key from the caches evenly without.
+                                     an earlier kernel of this path; the present one takes the same time per ciphertext without.
                                      SLZ_E_INVALID_ARG for other values and on other paths */
 
 #define SLZ_OPT_FAIL_ALLOC_AFTER 4 /* for tests of the out-of-memory handling: value v >= 0 makes the (v+1)-th scratch allocation
