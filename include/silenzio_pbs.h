@@ -79,10 +79,10 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      overlaps the memory-bound column passes of the other; results are identical);
                                      SLZ_E_INVALID_ARG when the context has no large-N path */
 
-#define SLZ_OPT_LARGE_N_LATENCY 5 /* value 1 (default) or 0: on the large-N path with 1024-blocks, calls with so few ciphertexts that
-                                     the chip stays mostly empty (at most 1024 / (2 N / 1024): 16 at N = 32768) run every CMux step
-                                     as four shorter launches with four times the threads (lower latency, identical results; their
-                                     scratch of 2 (k+1) l (k+1) N doubles per such ciphertext is allocated by the first such call);
+#define SLZ_OPT_LARGE_N_LATENCY 5 /* value 1 (default) or 0: on the large-N path with 1024-blocks, calls with few ciphertexts (at most 32 at
+                                     N = 32768, 56 at 16384, 96 at 8192, 512 / (N / 1024) below) run every CMux step as two launches of
+                                     more, shorter threads instead of three (lower latency, identical results; their second accumulator
+                                     of (k+1) N words per such ciphertext is allocated by the first such call);
                                      0 keeps the throughput kernels at every batch size; SLZ_E_INVALID_ARG without a large-N path */
 
 #define SLZ_OPT_FUSED_PACING 6    /* values 0, 1 and 2, on the N = 2048 fused path: accepted and without effect.  They paced the workgroups of

@@ -16,10 +16,19 @@
 
 #define BIG_MAX_L 4
 
+// Stores of what the next launch reads, written through the L2: what is left dirty in the L2s is written back after the last workgroup of
+// a launch, before the next one may start.
+__device__ __forceinline__ void st_through(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_through(uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 struct bign_tabs {                 // per prime
     const double *fwd;             // natural forward table of the full transform (fwd[m + blk])
     const double *rowA;            // [G][64]      block-specific twiddles of stages with 1..32 sub-blocks (uniform per wave)
     const double *rowB;            // [G][31][64]  block-specific per-lane twiddles of the last five forward stages
+    // 1024-blocks: tables of the mirrored inverse
+    const double *rowAi, *rowBi;   // [G][64], [G][15][64]  inverses of rowA and rowB
+    const double *colI;            // [G]  column stages: inverses of fwd[2 .. G - 1]; [0] = 1 / N, [1] = 1 / (N fwd[1])
+    // 2048-blocks: decimation in time and twist
     const double *inv;             // natural inverse table
     const double *post;            // natural twist table
 };
@@ -36,18 +45,28 @@ struct bign_args {
     double p1inv_mod_p2;
 };
 
+// forward column stages (strides N/2 .. BS) on a column of G rows: pairs of rows, twiddle by block of rows (uniform)
+template <int G>
+__device__ __forceinline__ void cols_fwd(double (&y)[G], const double *tw, slz_mod m) {
+#pragma unroll
+    for (int half = G / 2, blocks = 1; half >= 1; half >>= 1, blocks <<= 1) {
+#pragma unroll
+        for (int blk = 0; blk < blocks; blk++) {
+            const double w = tw[blocks + blk];
+#pragma unroll
+            for (int j = 0; j < half; j++) bfly(y[blk * 2 * half + j], y[blk * 2 * half + j + half], w, m);
+        }
+    }
+}
+
 // ---- P1 ------------------------------------------------------------------------------------------
 // BS: block size of the row pass (2048 or 1024); G = N / BS rows of BS columns
-// SPLIT: one thread per (column, component, level, prime) instead of one per (column, component): four times (l = 2) as
-// many threads, each repeating the cheap rotate / subtract / round and doing one column transform.  For a handful of
-// ciphertexts, where the pass is one thread's latency.
-template <int G, int BS, bool SPLIT>
+template <int G, int BS>
 __global__ void __launch_bounds__(256)
 k_big_cols_fwd(bign_args A) {
     const uint32_t c = blockIdx.x * 256 + threadIdx.x;          // column, < BS
     const uint32_t b = blockIdx.z;
-    const uint32_t comp = SPLIT ? blockIdx.y / (2 * A.l) : blockIdx.y;
-    const int only_lev = SPLIT ? (int)((blockIdx.y >> 1) % A.l) : -1, only_q = SPLIT ? (int)(blockIdx.y & 1u) : -1;
+    const uint32_t comp = blockIdx.y;
     const uint32_t N = A.N, R = 2 * A.l;
     uint32_t logN2 = 1;                                          // log2(2N)
     for (uint32_t g = N; g > 1; g >>= 1) logN2++;
@@ -64,29 +83,17 @@ k_big_cols_fwd(bign_args A) {
         double d[G];
 #pragma unroll
         for (int i = 0; i < G; i++) d[i] = (double)slz_next_digit(lam[i], A.beta);
-        if (SPLIT && lev != only_lev) continue;                  // lower levels are only peeled for their carries
         for (int q = 0; q < 2; q++) {
-            if (SPLIT && q != only_q) continue;
             const slz_mod m = A.mod[q];
             const double *tw = A.tab[q].fwd;
             double y[G];
 #pragma unroll
             for (int i = 0; i < G; i++) y[i] = d[i];
-            // stages with strides N/2 .. BS: pairs of rows, twiddle by block of rows (uniform)
-#pragma unroll
-            for (int half = G / 2, blocks = 1; half >= 1; half >>= 1, blocks <<= 1) {
-#pragma unroll
-                for (int blk = 0; blk < blocks; blk++) {
-                    const double w = tw[blocks + blk];
-#pragma unroll
-                    for (int j = 0; j < half; j++) bfly(y[blk * 2 * half + j], y[blk * 2 * half + j + half], w, m);
-                }
-            }
+            cols_fwd<G>(y, tw, m);
             double *dst = A.X + (((size_t)b * 2 + q) * R + (comp * A.l + lev)) * N + c;
 #pragma unroll
             for (int i = 0; i < G; i++) dst[(uint32_t)BS * i] = slz_reduce(y[i], m);
         }
-        if (SPLIT) break;
     }
 }
 
@@ -191,9 +198,6 @@ k_big_rows(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
 // One wave per (ciphertext, prime, 1024-block), 16 coefficients per lane: the accumulators of both components, the block
 // and the tables fit 256 registers, so two waves share a SIMD and cover each other's memory latency (the 2048-block
 // kernel above needs more than 256 and runs one wave per SIMD, 43 % of it waiting for memory).
-// BOTH = false: one task per output component as well (twice the tasks, each with all R forward transforms but the products
-// and the inverse transform of one component only): for a few ciphertexts, where a pass lasts as long as its longest task.
-template <bool BOTH>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
     extern __shared__ double lds[];
@@ -206,8 +210,6 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
         task = (v / cpx) * 2 * G + xcd * cpx + v % cpx;
     }
     if (task >= n_tasks) return;                                 // whole wave leaves; no workgroup barriers below
-    const uint32_t only = BOTH ? 0u : task & 1u;                 // the component of a one-component task
-    if (!BOTH) task >>= 1;
     double *T = lds + wv * (TBUF16 + 1024u);
     double *twA = T + TBUF16, *twB = twA + 64;                  // this block's forward tables, staged in LDS
     const uint32_t row = task % G, q = (task / G) & 1u, b = task / (2 * G);
@@ -240,13 +242,13 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
         for (int e = 0; e < 16; e++) x[e] = xn[e];
         // the key words of this row and then the next row's block are requested here (vector memory completes in issue
         // order) and arrive while the transform runs
-        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + only) * N + 32u * row + z;
+        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + 0) * N + 32u * row + z;
         const double *k1 = k0 + N;
         double kk0[16], kk1[16];
 #pragma unroll
         for (int i = 0; i < 16; i++) {
             kk0[i] = ldl(k0 + (size_t)i * stride, key_lane_off);
-            if (BOTH) kk1[i] = ldl(k1 + (size_t)i * stride, key_lane_off);
+            kk1[i] = ldl(k1 + (size_t)i * stride, key_lane_off);
         }
         {
             const double *nxt = A.X + (((size_t)b * 2 + q) * R + (r + 1 < R ? r + 1 : r)) * N + 1024u * row + z;
@@ -262,14 +264,12 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
             const double x4[4] = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
             const double ka[4] = {kk0[4 * g], kk0[4 * g + 1], kk0[4 * g + 2], kk0[4 * g + 3]};
             mulmod_k<4>(r0, x4, ka, m);
-            if (BOTH) {
-                const double kb[4] = {kk1[4 * g], kk1[4 * g + 1], kk1[4 * g + 2], kk1[4 * g + 3]};
-                mulmod_k<4>(r1, x4, kb, m);
-            }
+            const double kb[4] = {kk1[4 * g], kk1[4 * g + 1], kk1[4 * g + 2], kk1[4 * g + 3]};
+            mulmod_k<4>(r1, x4, kb, m);
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 o0[4 * g + u] = (r == 0) ? r0[u] : o0[4 * g + u] + r0[u];
-                if (BOTH) o1[4 * g + u] = (r == 0) ? r1[u] : o1[4 * g + u] + r1[u];
+                o1[4 * g + u] = (r == 0) ? r1[u] : o1[4 * g + u] + r1[u];
             }
         }
         if ((r & 3u) == 3u && r + 1 < R) {                       // more than four rows: keep the running sums below 8 p
@@ -277,20 +277,17 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
             for (int g = 0; g < 4; g++) {
                 double a4[4], b4[4];
                 const double xa[4] = {o0[4 * g], o0[4 * g + 1], o0[4 * g + 2], o0[4 * g + 3]};
+                const double xb[4] = {o1[4 * g], o1[4 * g + 1], o1[4 * g + 2], o1[4 * g + 3]};
                 reduce_k<4>(a4, xa, m);
-                if (BOTH) {
-                    const double xb[4] = {o1[4 * g], o1[4 * g + 1], o1[4 * g + 2], o1[4 * g + 3]};
-                    reduce_k<4>(b4, xb, m);
-                }
+                reduce_k<4>(b4, xb, m);
 #pragma unroll
-                for (int u = 0; u < 4; u++) { o0[4 * g + u] = a4[u]; if (BOTH) o1[4 * g + u] = b4[u]; }
+                for (int u = 0; u < 4; u++) { o0[4 * g + u] = a4[u]; o1[4 * g + u] = b4[u]; }
             }
         }
         wave_sync();
     }
     // inverse: first 10 stages inside the block, reduce, hand the block to the column pass
-    for (int cc = 0; cc < (BOTH ? 2 : 1); cc++) {
-        const uint32_t comp = BOTH ? (uint32_t)cc : only;
+    for (int comp = 0; comp < 2; comp++) {
         int z;
         asm volatile("s_mov_b32 %0, 0" : "=s"(z));
         double x[16];
@@ -298,7 +295,7 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
         for (int g = 0; g < 2; g++) {
             double r8[8], x8[8];
 #pragma unroll
-            for (int u = 0; u < 8; u++) x8[u] = (BOTH && cc) ? o1[8 * g + u] : o0[8 * g + u];
+            for (int u = 0; u < 8; u++) x8[u] = comp ? o1[8 * g + u] : o0[8 * g + u];
             reduce_k<8>(r8, x8, m);
 #pragma unroll
             for (int u = 0; u < 8; u++) x[8 * g + u] = r8[u];
@@ -351,149 +348,343 @@ k_big_cols_inv(bign_args A) {
     for (int i = 0; i < G; i++) poly[(uint32_t)BS * i] += slz_crt64(res[0][i], res[1][i], A.mod[1], A.p1inv_mod_p2);
 }
 
-// ---- a handful of ciphertexts: the same step cut into more, shorter pieces --------------------------------------------
-// With few ciphertexts the chip is mostly empty and a step costs the latency of its longest thread: one row task runs R
-// forward transforms, the products and two inverse transforms one after the other.  Here a row task is one GGSW row
-// (k_big_rows16_lat_a: forward transform, products with both key columns, written to P) or one output component
-// (k_big_rows16_lat_b: sum of the R partial products, inverse transform), and the inverse column pass runs the two primes
-// of a column on two neighbouring lanes.  More launches and more traffic per step, several times the parallelism.
-// P: [batch][2 primes][R][2 components][N], a row-block stored as [16 registers][64 lanes].
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_big_rows16_lat_a(bign_args A, double *__restrict__ P, uint32_t G, uint32_t n_tasks) {
+// Column stages of the mirrored inverse inside a part of K rows (1024-blocks): block `first` .. of the forward stage with
+// the same strides.  bd: bounds in units of p.
+template <int K>
+__device__ __forceinline__ void cols_mirror(double (&x)[K], double (&bd)[K], const double *colI, uint32_t part, uint32_t parts, slz_mod m) {
+#pragma unroll
+    for (int half = 1; half < K; half <<= 1) {
+#pragma unroll
+        for (int blk = 0; blk < K / (2 * half); blk++) {
+            const double w = colI[(parts + part) * (K / (2 * half)) + blk];
+#pragma unroll
+            for (int j = 0; j < half; j++) {
+                double *pa[1] = {&x[blk * 2 * half + j]}, *pb[1] = {&x[blk * 2 * half + j + half]};
+                double *ua[1] = {&bd[blk * 2 * half + j]}, *ub[1] = {&bd[blk * 2 * half + j + half]};
+                const double pw[1] = {w};
+                gs_k<1>(pa, pb, ua, ub, pw, m);
+            }
+        }
+    }
+}
+// the last stage with the factor 1 / N: f, g <- (f + g) / N, (f - g) / (N w)
+__device__ __forceinline__ void cols_mirror_last(double &f, double &g, const double *colI, slz_mod m) {
+    const double s = f + g, d = f - g;
+    f = slz_mulmod(s, colI[0], m);
+    g = slz_mulmod(d, colI[1], m);
+}
+
+// both residues of column c of one component after the mirrored inverse
+template <int G>
+__device__ __forceinline__ void cols_mirror_both(double (&res)[2][G], const bign_args &A, uint32_t b, uint32_t comp, uint32_t c) {
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const slz_mod m = A.mod[q];
+        const double *src = A.Y + (((size_t)b * 2 + q) * 2 + comp) * A.N + c;
+        double lo[G / 2], hi[G / 2], ba[G / 2], bb[G / 2];
+#pragma unroll
+        for (int i = 0; i < G / 2; i++) { lo[i] = src[1024u * i]; hi[i] = src[1024u * (G / 2 + i)]; ba[i] = bb[i] = 0.51; }
+        cols_mirror<G / 2>(lo, ba, A.tab[q].colI, 0, 2, m);
+        cols_mirror<G / 2>(hi, bb, A.tab[q].colI, 1, 2, m);
+        lazy_limit(lo, ba, LAZY_MAX / 2, m);
+        lazy_limit(hi, bb, LAZY_MAX / 2, m);
+#pragma unroll
+        for (int i = 0; i < G / 2; i++) {
+            cols_mirror_last(lo[i], hi[i], A.tab[q].colI, m);
+            res[q][i] = lo[i];
+            res[q][G / 2 + i] = hi[i];
+        }
+    }
+}
+
+// The last column pass of the two-launch steps; acc_in: the accumulator before it (A.acc or the other buffer).
+template <int G>
+__global__ void __launch_bounds__(256)
+k_big_cols_last(bign_args A, const uint64_t *acc_in) {
+    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t comp = blockIdx.y, b = blockIdx.z;
+    double res[2][G];
+    cols_mirror_both<G>(res, A, b, comp, c);
+    const size_t poly = ((size_t)b * 2 + comp) * A.N + c;
+#pragma unroll
+    for (int i = 0; i < G; i++) A.acc[poly + 1024u * i] = acc_in[poly + 1024u * i] + slz_crt64(res[0][i], res[1][i], A.mod[1], A.p1inv_mod_p2);
+}
+
+// k_big_cols_turn (below) for few rows: a thread does a whole column and the rotated one.
+template <int G>
+__global__ void __launch_bounds__(256)
+k_big_cols_turn_short(bign_args A, const uint64_t *__restrict__ acc_in, uint64_t *__restrict__ acc_out) {
+    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t comp = blockIdx.y, b = blockIdx.z;
+    const uint32_t N = A.N, R = 2 * A.l;
+    uint32_t logN2 = 1;                                          // log2(2N)
+    for (uint32_t g = N; g > 1; g >>= 1) logN2++;
+    const uint32_t at = slz_modswitch(A.lwe_in[(size_t)b * (A.n + 1) + A.step], logN2);
+    const uint32_t u = c + 2 * N - at, urow = u >> 10;           // X^at moves coefficient u (mod 2N, negated from N on) to c
+    const size_t poly = ((size_t)b * 2 + comp) * N;
+    uint64_t own[G], other[G];
+#pragma unroll
+    for (int i = 0; i < G; i++) { own[i] = acc_in[poly + c + 1024u * i]; other[i] = acc_in[poly + (u & 1023u) + 1024u * i]; }
+    {
+        double res[2][G];
+        cols_mirror_both<G>(res, A, b, comp, c);
+#pragma unroll
+        for (int i = 0; i < G; i++) own[i] += slz_crt64(res[0][i], res[1][i], A.mod[1], A.p1inv_mod_p2);
+        cols_mirror_both<G>(res, A, b, comp, u & 1023u);
+#pragma unroll
+        for (int i = 0; i < G; i++) other[i] += slz_crt64(res[0][i], res[1][i], A.mod[1], A.p1inv_mod_p2);
+    }
+    uint64_t lam[G];
+#pragma unroll
+    for (int i = 0; i < G; i++) {
+        const uint32_t from = (urow + i) & (2 * G - 1);
+        uint64_t w = other[0];
+#pragma unroll
+        for (int k = 1; k < G; k++) w = (from & (G - 1)) == (uint32_t)k ? other[k] : w;
+        lam[i] = slz_round_top_bits((from & G ? (uint64_t)0 - w : w) - own[i], A.beta * A.l);
+        acc_out[poly + c + 1024u * i] = own[i];
+    }
+    for (int lev = (int)A.l - 1; lev >= 0; lev--) {              // least significant level first (carries go up)
+        double d[G];
+#pragma unroll
+        for (int i = 0; i < G; i++) d[i] = (double)slz_next_digit(lam[i], A.beta);
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            double y[G];
+#pragma unroll
+            for (int i = 0; i < G; i++) y[i] = d[i];
+            cols_fwd<G>(y, A.tab[q].fwd, A.mod[q]);
+            double *dst = A.X + (((size_t)b * 2 + q) * R + (comp * A.l + lev)) * N + c;
+#pragma unroll
+            for (int i = 0; i < G; i++) dst[1024u * i] = slz_reduce(y[i], A.mod[q]);
+        }
+    }
+}
+
+// ---- few ciphertexts: the same step as two launches of more, shorter threads -----------------------------------------
+// With few ciphertexts the chip is mostly empty and a step costs the latency of its longest thread and the hand-over between
+// dependent launches.  The row pass gives every GGSW row a wave of its own (k_big_rows16_team); the inverse column pass of a step
+// and the forward column pass of the next one are one launch (k_big_cols_turn).
+
+// One workgroup of R waves per (ciphertext, prime, 1024-block): wave r transforms GGSW row r and multiplies it with the row's key
+// columns; pairs of waves exchange their products through LDS (even waves sum component 0, odd ones component 1), and waves 0 and 1
+// collect the sums of the other pairs and run the inverse transforms.  LDS: R transform buffers, which also take the products, and the
+// block's forward tables: 45 KiB for four rows, three workgroups per compute unit.
+#define TEAM_LDS(R) (((R) * TBUF16 + 1024u) * sizeof(double))
+template <int R>
+__global__ void __launch_bounds__(64 * R) __attribute__((amdgpu_waves_per_eu(3, 3)))
+k_big_rows16_team(bign_args A, uint32_t G) {
     extern __shared__ double lds[];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t task = blockIdx.x * 4 + wv;
-    if (task >= n_tasks) return;                                 // whole wave leaves; no workgroup barriers below
-    double *T = lds + wv * (TBUF16 + 1024u);
-    double *twA = T + TBUF16, *twB = twA + 64;
-    const uint32_t N = A.N, R = 2 * A.l;
-    const uint32_t r = task % R, row = (task / R) % G, q = (task / (R * G)) & 1u, b = task / (2 * R * G);
+    const uint32_t r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t task = blockIdx.x;                                  // (ciphertext, prime, block), block fastest
+    if (2 * G % 8 == 0) {                                        // an XCD keeps to its 1/8 of the (prime, block) pairs, see k_big_rows
+        const uint32_t cpx = 2 * G / 8, xcd = blockIdx.x & 7u, v = blockIdx.x >> 3;
+        task = (v / cpx) * 2 * G + xcd * cpx + v % cpx;
+    }
+    const uint32_t row = task % G, q = (task / G) & 1u, b = task / (2 * G);
+    double *T = lds + r * TBUF16, *T_other = lds + (r ^ 1u) * TBUF16;
+    double *twA = lds + R * TBUF16, *twB = twA + 64;
+    const uint32_t N = A.N;
     const slz_mod m = A.mod[q];
     const bign_tabs tb = A.tab[q];
     const uint32_t stride = N / 32;
     const uint32_t key_lane_off = (16u * (lane & 1u) * stride + (lane >> 1)) * 8u;
     int z;
     asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-    double x[16], kk0[16], kk1[16];
+    double x[16], kk[2][16];
     {
+        constexpr uint32_t TAB = (1024 + 64 * R - 1) / (64 * R);
+        const double *gA = tb.rowA + (size_t)row * 64, *gB = tb.rowB + (size_t)row * 15 * 64;
+        double tab[TAB];
+#pragma unroll
+        for (uint32_t i = 0; i < TAB; i++) {
+            const uint32_t t = min(i * 64 * R + threadIdx.x, 1023u);
+            tab[i] = t < 64u ? gA[t] : gB[t - 64u];
+        }
         const double *src = A.X + (((size_t)b * 2 + q) * R + r) * N + 1024u * row;
 #pragma unroll
         for (int e = 0; e < 16; e++) x[e] = ldl(src + 64 * e, lane * 8u);
-        const double *gA = tb.rowA + (size_t)row * 64, *gB = tb.rowB + (size_t)row * 15 * 64;
-        twA[lane] = gA[lane];
+        const double *key = A.bskp_step + (((size_t)q * R + r) * 2) * N + 32u * row;
 #pragma unroll
-        for (int k = 0; k < 15; k++) twB[64 * k + lane] = gB[64 * k + lane];
-        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + 0) * N + 32u * row;
-        const double *k1 = k0 + N;
+        for (int i = 0; i < 16; i++)
 #pragma unroll
-        for (int i = 0; i < 16; i++) { kk0[i] = ldl(k0 + (size_t)i * stride, key_lane_off); kk1[i] = ldl(k1 + (size_t)i * stride, key_lane_off); }
-        wave_sync();
+            for (int c = 0; c < 2; c++) kk[c][i] = ldl(key + (size_t)c * N + (size_t)i * stride, key_lane_off);
+#pragma unroll
+        for (uint32_t i = 0; i < TAB; i++) if (i * 64 * R + threadIdx.x < 1024u) twA[i * 64 * R + threadIdx.x] = tab[i];
     }
+    __syncthreads();
     SCHED_FENCE();
     fwd16(x, T, twA, twB, m, lane, z);
-    double *dst = P + ((((size_t)b * 2 + q) * R + r) * 2) * N + 1024u * row + lane;
+    wave_sync();
+    double o[16];                                                // the component this wave sums: r & 1
 #pragma unroll
-    for (int g = 0; g < 4; g++) {
-        double r0[4], r1[4];
-        const double x4[4] = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
-        const double ka[4] = {kk0[4 * g], kk0[4 * g + 1], kk0[4 * g + 2], kk0[4 * g + 3]};
-        const double kb[4] = {kk1[4 * g], kk1[4 * g + 1], kk1[4 * g + 2], kk1[4 * g + 3]};
-        mulmod_k<4>(r0, x4, ka, m);
-        mulmod_k<4>(r1, x4, kb, m);
+    for (int g = 0; g < 2; g++) {
+        double r0[8], r1[8], x8[8], k0[8], k1[8];
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            dst[64 * (4 * g + u)] = r0[u];
-            dst[(size_t)N + 64 * (4 * g + u)] = r1[u];
+        for (int u = 0; u < 8; u++) { x8[u] = x[8 * g + u]; k0[u] = kk[0][8 * g + u]; k1[u] = kk[1][8 * g + u]; }
+        mulmod_k<8>(r0, x8, k0, m);
+        mulmod_k<8>(r1, x8, k1, m);
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            o[8 * g + u] = r & 1u ? r1[u] : r0[u];
+            T[64 * (8 * g + u) + lane] = r & 1u ? r0[u] : r1[u];
         }
     }
-}
-
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_big_rows16_lat_b(bign_args A, const double *__restrict__ P, uint32_t G, uint32_t n_tasks) {
-    extern __shared__ double lds[];
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t task = blockIdx.x * 4 + wv;
-    if (task >= n_tasks) return;
-    double *T = lds + wv * TBUF16;
-    const uint32_t N = A.N, R = 2 * A.l;
-    const uint32_t comp = task & 1u, row = (task >> 1) % G, q = (task / (2 * G)) & 1u, b = task / (4 * G);
-    const slz_mod m = A.mod[q];
-    const bign_tabs tb = A.tab[q];
-    int z;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-    double x[16];
-    {
-        const double *src = P + ((((size_t)b * 2 + q) * R) * 2 + comp) * N + 1024u * row + lane;
+    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 16; i++) x[i] = src[64 * i];
-        for (uint32_t r = 1; r < R; r++) {
-            const double *sr = src + (size_t)r * 2 * N;
+    for (int i = 0; i < 16; i++) o[i] += T_other[64 * i + lane];
+    if (R > 2) {
+        if (r >= 2) {
 #pragma unroll
-            for (int i = 0; i < 16; i++) x[i] += sr[64 * i];
-            if ((r & 3u) == 3u && r + 1 < R) {                   // as in the throughput kernel: at most four products per reduction
+            for (int i = 0; i < 16; i++) T_other[64 * i + lane] = o[i];         // read by this wave alone before
+        }
+        __syncthreads();
+        if (r >= 2) return;
 #pragma unroll
-                for (int i = 0; i < 16; i++) x[i] = slz_reduce(x[i], m);
+        for (int w = 2; w < R; w += 2) {
+            const double *P = lds + (w + (r ^ 1u)) * TBUF16;
+#pragma unroll
+            for (int i = 0; i < 16; i++) o[i] += P[64 * i + lane];
+            if (w == 2 && R > 4) {                                              // at most four products are summed before a reduction
+#pragma unroll
+                for (int i = 0; i < 16; i++) o[i] = slz_reduce(o[i], m);
             }
         }
     }
+    double twi[15];
+    const double *gBi = tb.rowBi + (size_t)row * 15 * 64;
+#pragma unroll
+    for (int k = 0; k < 15; k++) twi[k] = ldl(gBi + 64 * k, lane * 8u);
 #pragma unroll
     for (int g = 0; g < 2; g++) {
         double r8[8], x8[8];
 #pragma unroll
-        for (int u = 0; u < 8; u++) x8[u] = x[8 * g + u];
+        for (int u = 0; u < 8; u++) x8[u] = o[8 * g + u];
         reduce_k<8>(r8, x8, m);
 #pragma unroll
-        for (int u = 0; u < 8; u++) x[8 * g + u] = r8[u];
+        for (int u = 0; u < 8; u++) o[8 * g + u] = r8[u];
     }
-    inv16(x, T, tb.inv, tb.inv, m, lane, z);
-    double *dst = A.Y + (((size_t)b * 2 + q) * 2 + comp) * N + 1024u * row;
+    inv16_mirror(o, T_other, tb.rowAi + (size_t)row * 64, twi, m, lane, z);     // this buffer has no other reader any more
+    double *dst = A.Y + (((size_t)b * 2 + q) * 2 + r) * N + 1024u * row;
 #pragma unroll
     for (int g = 0; g < 2; g++) {
         double r8[8], x8[8];
 #pragma unroll
-        for (int u = 0; u < 8; u++) x8[u] = x[8 * g + u];
+        for (int u = 0; u < 8; u++) x8[u] = o[8 * g + u];
         reduce_k<8>(r8, x8, m);
 #pragma unroll
-        for (int u = 0; u < 8; u++) dst[64 * (8 * g + u) + lane] = r8[u];
+        for (int u = 0; u < 8; u++) st_through(&dst[64 * (8 * g + u) + lane], r8[u]);
     }
 }
 
-// P3 with the two primes of a column on lanes 2j and 2j + 1: each lane runs its prime's column stages and twist, the
-// lanes swap the halves they do not lift (rows below G/2 are lifted by the lane of prime 0, the others by prime 1's).
-template <int G, int BS>
-__global__ void __launch_bounds__(256)
-k_big_cols_inv_lat(bign_args A) {
-    const uint32_t c = blockIdx.x * 128 + (threadIdx.x >> 1);
-    const uint32_t q = threadIdx.x & 1u;
-    const uint32_t comp = blockIdx.y, b = blockIdx.z;
-    const uint32_t N = A.N;
-    const slz_mod m = A.mod[q];
-    const double *src = A.Y + (((size_t)b * 2 + q) * 2 + comp) * N + c;
-    const double *tw = A.tab[q].inv, *post = A.tab[q].post;
-    double y[G];
+// Inverse column pass of step A.step - 1 and forward column pass of step A.step for 64 columns of one component.  The forward pass of
+// column c needs the new accumulator in columns c and c - a~ (mod 1024), so both are computed (every column twice, which costs less
+// than a hand-over between launches).  Eight waves share the work, meeting in LDS: (own or rotated column, prime, half of the rows)
+// run the inverse stages inside a half; each then takes a quarter of the row pairs for the last stage, the twist and the lift; an eighth
+// of the rows for the differences; and (level, prime, half of the rows) run the forward stages.  Other workgroups read the old
+// accumulator, so the new one goes to a second buffer.
+template <int G>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_big_cols_turn(bign_args A, const uint64_t *__restrict__ acc_in, uint64_t *__restrict__ acc_out) {
+    constexpr int H = G / 2, J = H / 4, D = G / 8;
+    __shared__ double res[4 * G * 64];                           // [own, rotated][prime][row][column]
+    uint64_t *words = reinterpret_cast<uint64_t *>(res);         // afterwards [own, rotated][row][column] ...
+    uint64_t *diff = words + 2 * G * 64;                         // ... and [row][column]
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t pairs = 2 * A.batch;
+    // (ciphertext, component) and block of columns: with eight pairs and more an XCD keeps to its pairs, so that both readings of a
+    // column meet in one L2
+    uint32_t pair, x;
+    if (pairs >= 8) { pair = (blockIdx.x & 7u) + 8u * (blockIdx.x >> 7); x = (blockIdx.x >> 3) & 15u; }
+    else { pair = blockIdx.x >> 4; x = blockIdx.x & 15u; }
+    if (pair >= pairs) return;
+    const uint32_t comp = pair & 1u, b = pair >> 1, c = 64 * x + lane;
+    const uint32_t N = A.N, R = 2 * A.l;
+    uint32_t logN2 = 1;                                          // log2(2N)
+    for (uint32_t g = N; g > 1; g >>= 1) logN2++;
+    const uint32_t at = slz_modswitch(A.lwe_in[(size_t)b * (A.n + 1) + A.step], logN2);
+    const uint32_t u = c + 2 * N - at;                           // X^at moves coefficient u (mod 2N, negated from N on) to c
+    const uint32_t rot = wave >> 2, col = rot ? u & 1023u : c, urow = u >> 10;
+    const size_t poly = (size_t)pair * N;
+    const uint32_t j0 = (wave & 3u) * J;                         // this wave's row pairs (j, j + H) of the lift
+    uint64_t lo[J], hi[J];
+    {
+        const uint32_t q = (wave >> 1) & 1u, part = wave & 1u;
+        const slz_mod m = A.mod[q];
+        double y[H], bd[H];
+        const double *src = A.Y + (((size_t)b * 2 + q) * 2 + comp) * N + 1024u * part * H + col;
 #pragma unroll
-    for (int i = 0; i < G; i++) y[i] = src[(uint32_t)BS * i];
+        for (int i = 0; i < H; i++) { y[i] = src[1024u * i]; bd[i] = 0.51; }
+        cols_mirror<H>(y, bd, A.tab[q].colI, part, 2, m);
+        lazy_limit(y, bd, LAZY_MAX / 2, m);
 #pragma unroll
-    for (int half = 1; half < G; half <<= 1) {
+        for (int i = 0; i < H; i++) res[((rot * 2 + q) * G + part * H + i) * 64 + lane] = y[i];
 #pragma unroll
-        for (int j = 0; j < half; j++) {
-            const double w = tw[(uint32_t)BS * half + (uint32_t)BS * j + c];
-#pragma unroll
-            for (int blk = 0; blk < G / (2 * half); blk++) bfly(y[blk * 2 * half + j], y[blk * 2 * half + j + half], w, m);
+        for (int k = 0; k < J; k++) {
+            lo[k] = acc_in[poly + col + 1024u * (j0 + k)];
+            hi[k] = acc_in[poly + col + 1024u * (H + j0 + k)];
         }
     }
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < G; i++) y[i] = slz_mulmod(y[i], post[(uint32_t)BS * i + c], m);
-    uint64_t *poly = A.acc + ((size_t)b * 2 + comp) * N + c;
+    for (int k = 0; k < J; k++) {
+        double r[2][2];
 #pragma unroll
-    for (int j = 0; j < G / 2; j++) {
-        const double send = q ? y[j] : y[G / 2 + j];             // the half the partner lifts
-        const double got = __shfl_xor(send, 1);
-        const int i = q ? G / 2 + j : j;
-        const double r1 = q ? got : y[j], r2 = q ? y[G / 2 + j] : got;
-        poly[(uint32_t)BS * i] += slz_crt64(r1, r2, A.mod[1], A.p1inv_mod_p2);
+        for (int p = 0; p < 2; p++) {
+            r[0][p] = res[((rot * 2 + p) * G + j0 + k) * 64 + lane];
+            r[1][p] = res[((rot * 2 + p) * G + H + j0 + k) * 64 + lane];
+            cols_mirror_last(r[0][p], r[1][p], A.tab[p].colI, A.mod[p]);
+        }
+        lo[k] += slz_crt64(r[0][0], r[0][1], A.mod[1], A.p1inv_mod_p2);
+        hi[k] += slz_crt64(r[1][0], r[1][1], A.mod[1], A.p1inv_mod_p2);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < J; k++) {
+        words[(rot * G + j0 + k) * 64 + lane] = lo[k];
+        words[(rot * G + H + j0 + k) * 64 + lane] = hi[k];
+        if (!rot) {
+            st_through(&acc_out[poly + c + 1024u * (j0 + k)], lo[k]);
+            st_through(&acc_out[poly + c + 1024u * (H + j0 + k)], hi[k]);
+        }
+    }
+    __syncthreads();
+    // Differences, rounded to beta l bits, plus half a base in every digit: the digit of a level is then a bit field minus half a base.
+    uint64_t offset = 0;
+    for (uint32_t k = 0; k < A.l; k++) offset += 1ull << (A.beta * k + A.beta - 1);
+#pragma unroll
+    for (int k = 0; k < D; k++) {
+        const uint32_t i = wave * D + k, from = (urow + i) & (2 * G - 1);
+        const uint64_t w = words[(G + (from & (G - 1))) * 64 + lane];
+        diff[i * 64 + lane] = slz_round_top_bits((from & G ? (uint64_t)0 - w : w) - words[i * 64 + lane], A.beta * A.l) + offset;
+    }
+    __syncthreads();
+    const uint32_t mask = (1u << A.beta) - 1u, mid = 1u << (A.beta - 1);
+    for (uint32_t t = wave; t < 4 * A.l; t += 8) {
+        const uint32_t half = t & 1u, q = (t >> 1) & 1u, lev = t >> 2, shift = A.beta * (A.l - 1 - lev);
+        const slz_mod m = A.mod[q];
+        const double *tw = A.tab[q].fwd;
+        auto digit = [&](int i) { return (double)(int32_t)(((uint32_t)(diff[i * 64 + lane] >> shift) & mask) - mid); };
+        double y[H];
+#pragma unroll
+        for (int j = 0; j < H; j++) {
+            const double a = digit(j), v = slz_mulmod(digit(j + H), tw[1], m);
+            y[j] = half ? a - v : a + v;
+        }
+#pragma unroll
+        for (int d = H / 2, blocks = 1; d >= 1; d >>= 1, blocks <<= 1) {
+#pragma unroll
+            for (int blk = 0; blk < blocks; blk++) {
+                const double w = tw[2 * blocks + half * blocks + blk];
+#pragma unroll
+                for (int j = 0; j < d; j++) bfly(y[blk * 2 * d + j], y[blk * 2 * d + j + d], w, m);
+            }
+        }
+        double *dst = A.X + (((size_t)b * 2 + q) * R + (comp * A.l + lev)) * N + 1024u * half * H + c;
+#pragma unroll
+        for (int i = 0; i < H; i++) st_through(&dst[1024u * i], slz_reduce(y[i], m));
     }
 }
 
@@ -511,8 +702,18 @@ static bool block_fits(uint32_t N, uint32_t BS) {
     return N % BS == 0 && G >= 2 && G <= 32 && (G & (G - 1)) == 0;
 }
 
-// block-specific forward tables for blocks of BS = 64 * E coefficients (E = 32 or 16 per lane)
-int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB) {
+// block-specific forward tables for blocks of BS = 64 * E coefficients (E = 32 or 16 per lane), or with `inverse` the inverses of
+// their entries: fwd[x] = psi^bitrev(x), so 1 / fwd[x] = -psi^(N - bitrev(x))
+static double inverse_entry(const std::vector<double> &nat, uint32_t x) {
+    const uint32_t N = (uint32_t)nat.size();
+    auto bitrev = [&](uint32_t v) {
+        uint32_t r = 0;
+        for (uint32_t h = N >> 1, b = 1; h; h >>= 1, b <<= 1) r |= v & h ? b : 0;
+        return r;
+    };
+    return x ? -nat[bitrev(N - bitrev(x))] : 1.0;
+}
+int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, bool inverse, double **dA, double **dB) {
     const uint32_t N = ctx->prm.N, G = N / BS, E = BS / 64;
     int late = 0;                                   // stages done after the transposition: log2 E
     for (uint32_t e = E; e > 1; e >>= 1) late++;
@@ -520,6 +721,7 @@ int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB) 
     std::vector<double> nat(N), rowA((size_t)2 * G * 64), rowB((size_t)2 * G * nB * 64);
     for (int q = 0; q < 2; q++) {
         SLZ_HIP(hipMemcpy(nat.data(), ctx->tab[q].fwd, (size_t)N * sizeof(double), hipMemcpyDeviceToHost));
+        auto entry = [&](size_t x) { return inverse ? inverse_entry(nat, (uint32_t)x) : nat[x]; };
         for (uint32_t row = 0; row < G; row++) {
             // block `row` continues the transform with sub-block counts m' = 1, 2, ..., BS / 2; its sub-block blk at that
             // stage is block (G + row) m' + blk of the whole transform: table entry fwd[(G + row) m' + blk]
@@ -528,14 +730,14 @@ int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB) 
             for (uint32_t x = 1; x < 64; x++) {
                 uint32_t mp = 1;
                 while (mp * 2 <= x) mp *= 2;
-                ra[x] = nat[(size_t)(G + row) * mp + (x - mp)];
+                ra[x] = entry((size_t)(G + row) * mp + (x - mp));
             }
             int kk = 0;
             for (int s = 0; s < late; s++) {
                 const uint32_t t = (E / 2) >> s, mp = BS / (2 * t);
                 for (uint32_t blk = 0; blk < (1u << s); blk++, kk++)
                     for (uint32_t l = 0; l < 64; l++)
-                        rowB[(((size_t)q * G + row) * nB + kk) * 64 + l] = nat[(size_t)(G + row) * mp + (E * l) / (2 * t) + blk];
+                        rowB[(((size_t)q * G + row) * nB + kk) * 64 + l] = entry((size_t)(G + row) * mp + (E * l) / (2 * t) + blk);
             }
         }
     }
@@ -543,6 +745,21 @@ int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB) 
     SLZ_HIP(hipMalloc((void **)dB, rowB.size() * sizeof(double)));
     SLZ_HIP(hipMemcpy(*dA, rowA.data(), rowA.size() * sizeof(double), hipMemcpyHostToDevice));
     SLZ_HIP(hipMemcpy(*dB, rowB.data(), rowB.size() * sizeof(double), hipMemcpyHostToDevice));
+    return SLZ_OK;
+}
+
+// column constants of the mirrored inverse, [2][32]
+static int build_col_table(slz_ctx *ctx, uint32_t G) {
+    const uint32_t N = ctx->prm.N;
+    std::vector<double> nat(N), col(2 * 32, 0.0);
+    for (int q = 0; q < 2; q++) {
+        SLZ_HIP(hipMemcpy(nat.data(), ctx->tab[q].fwd, (size_t)N * sizeof(double), hipMemcpyDeviceToHost));
+        for (uint32_t x = 2; x < G; x++) col[32 * q + x] = inverse_entry(nat, x);
+        for (uint32_t x = 0; x < 2; x++)             // the twist table holds psi^-j / N, and fwd[1] = psi^(N / 2)
+            SLZ_HIP(hipMemcpy(&col[32 * q + x], ctx->tab[q].post + x * (N / 2), sizeof(double), hipMemcpyDeviceToHost));
+    }
+    SLZ_HIP(hipMalloc((void **)&ctx->bign16_colI, col.size() * sizeof(double)));
+    SLZ_HIP(hipMemcpy(ctx->bign16_colI, col.data(), col.size() * sizeof(double), hipMemcpyHostToDevice));
     return SLZ_OK;
 }
 
@@ -572,19 +789,21 @@ int slz_bign_init(slz_ctx *ctx) {
     ctx->bign_latency = 1;
     bool any = false;
     if (block_fits(N, 2048) && bounds_ok(N, 2048)) {
-        int rc = slz_build_block_tables(ctx, 2048, &ctx->bign_rowA, &ctx->bign_rowB);
+        int rc = slz_build_block_tables(ctx, 2048, false, &ctx->bign_rowA, &ctx->bign_rowB);
         if (rc != SLZ_OK) return rc;
         SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * TBUF * sizeof(double)));
         ctx->bign_block = 2048;
         any = true;
     }
     if (block_fits(N, 1024) && bounds_ok(N, 1024)) {
-        int rc = slz_build_block_tables(ctx, 1024, &ctx->bign16_rowA, &ctx->bign16_rowB);
+        int rc = slz_build_block_tables(ctx, 1024, false, &ctx->bign16_rowA, &ctx->bign16_rowB);
+        if (rc == SLZ_OK) rc = slz_build_block_tables(ctx, 1024, true, &ctx->bign16_rowAi, &ctx->bign16_rowBi);
+        if (rc == SLZ_OK) rc = build_col_table(ctx, N / 1024);
         if (rc != SLZ_OK) return rc;
-        SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows16<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (TBUF16 + 1024) * sizeof(double)));
-        SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows16<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (TBUF16 + 1024) * sizeof(double)));
-        SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows16_lat_a, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (TBUF16 + 1024) * sizeof(double)));
-        SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows16_lat_b, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * TBUF16 * sizeof(double)));
+        SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows16, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (TBUF16 + 1024) * sizeof(double)));
+        const struct { const void *kernel; uint32_t rows; } team[] = {{(const void *)k_big_rows16_team<2>, 2}, {(const void *)k_big_rows16_team<4>, 4},
+                                                                      {(const void *)k_big_rows16_team<6>, 6}, {(const void *)k_big_rows16_team<8>, 8}};
+        for (const auto &t : team) SLZ_HIP(hipFuncSetAttribute(t.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)TEAM_LDS(t.rows)));
         ctx->has_bign16 = 1;
         ctx->bign_block = 1024;                                  // preferred: two waves per SIMD in the row pass
         any = true;
@@ -597,8 +816,13 @@ void slz_bign_destroy(slz_ctx *ctx) {
     if (ctx->bign_rowB) (void)hipFree(ctx->bign_rowB);
     if (ctx->bign16_rowA) (void)hipFree(ctx->bign16_rowA);
     if (ctx->bign16_rowB) (void)hipFree(ctx->bign16_rowB);
-    if (ctx->bign_partial) (void)hipFree(ctx->bign_partial);
-    ctx->bign_rowA = ctx->bign_rowB = ctx->bign16_rowA = ctx->bign16_rowB = ctx->bign_partial = nullptr;
+    if (ctx->bign16_rowAi) (void)hipFree(ctx->bign16_rowAi);
+    if (ctx->bign16_rowBi) (void)hipFree(ctx->bign16_rowBi);
+    if (ctx->bign16_colI) (void)hipFree(ctx->bign16_colI);
+    if (ctx->bign_spare) (void)hipFree(ctx->bign_spare);
+    ctx->bign_rowA = ctx->bign_rowB = ctx->bign16_rowA = ctx->bign16_rowB = nullptr;
+    ctx->bign16_rowAi = ctx->bign16_rowBi = ctx->bign16_colI = nullptr;
+    ctx->bign_spare = nullptr;
     for (int j = 0; j < 2; j++) {
         if (ctx->bign_lane_stream[j]) (void)hipStreamDestroy((hipStream_t)ctx->bign_lane_stream[j]);
         if (ctx->bign_lane_done[j]) (void)hipEventDestroy((hipEvent_t)ctx->bign_lane_done[j]);
@@ -608,37 +832,58 @@ void slz_bign_destroy(slz_ctx *ctx) {
     ctx->bign_fork = nullptr;
 }
 
-// mode 0: the throughput kernels; mode 1: the latency-oriented ones (forward pass split over levels and primes, inverse
-// pass with the two primes of a column on neighbouring lanes)
 template <int G, int BS>
-static void launch_cols(bool fwd, int mode, const bign_args &A, uint32_t batch, hipStream_t s) {
-    if (mode == 0) {
-        dim3 grid(BS / 256, 2, batch);
-        if (fwd) hipLaunchKernelGGL((k_big_cols_fwd<G, BS, false>), grid, dim3(256), 0, s, A);
-        else hipLaunchKernelGGL((k_big_cols_inv<G, BS>), grid, dim3(256), 0, s, A);
+static void launch_cols(bool fwd, const bign_args &A, uint32_t batch, hipStream_t s) {
+    const dim3 grid(BS / 256, 2, batch);
+    if (fwd) hipLaunchKernelGGL((k_big_cols_fwd<G, BS>), grid, dim3(256), 0, s, A);
+    else hipLaunchKernelGGL((k_big_cols_inv<G, BS>), grid, dim3(256), 0, s, A);
+}
+
+static void launch_cols_any(bool fwd, uint32_t G, uint32_t BS, const bign_args &A, uint32_t batch, hipStream_t s) {
+    if (BS == 2048) {
+        switch (G) {
+            case 2: launch_cols<2, 2048>(fwd, A, batch, s); break;
+            case 4: launch_cols<4, 2048>(fwd, A, batch, s); break;
+            case 8: launch_cols<8, 2048>(fwd, A, batch, s); break;
+            case 16: launch_cols<16, 2048>(fwd, A, batch, s); break;
+            default: launch_cols<32, 2048>(fwd, A, batch, s); break;
+        }
     } else {
-        if (fwd) hipLaunchKernelGGL((k_big_cols_fwd<G, BS, true>), dim3(BS / 256, 2 * A.l * 2, batch), dim3(256), 0, s, A);
-        else hipLaunchKernelGGL((k_big_cols_inv_lat<G, BS>), dim3(BS / 128, 2, batch), dim3(256), 0, s, A);
+        switch (G) {
+            case 2: launch_cols<2, 1024>(fwd, A, batch, s); break;
+            case 4: launch_cols<4, 1024>(fwd, A, batch, s); break;
+            case 8: launch_cols<8, 1024>(fwd, A, batch, s); break;
+            case 16: launch_cols<16, 1024>(fwd, A, batch, s); break;
+            default: launch_cols<32, 1024>(fwd, A, batch, s); break;
+        }
     }
 }
 
-static void launch_cols_any(bool fwd, int mode, uint32_t G, uint32_t BS, const bign_args &A, uint32_t batch, hipStream_t s) {
-    if (BS == 2048) {
-        switch (G) {
-            case 2: launch_cols<2, 2048>(fwd, mode, A, batch, s); break;
-            case 4: launch_cols<4, 2048>(fwd, mode, A, batch, s); break;
-            case 8: launch_cols<8, 2048>(fwd, mode, A, batch, s); break;
-            case 16: launch_cols<16, 2048>(fwd, mode, A, batch, s); break;
-            default: launch_cols<32, 2048>(fwd, mode, A, batch, s); break;
-        }
-    } else {
-        switch (G) {
-            case 2: launch_cols<2, 1024>(fwd, mode, A, batch, s); break;
-            case 4: launch_cols<4, 1024>(fwd, mode, A, batch, s); break;
-            case 8: launch_cols<8, 1024>(fwd, mode, A, batch, s); break;
-            case 16: launch_cols<16, 1024>(fwd, mode, A, batch, s); break;
-            default: launch_cols<32, 1024>(fwd, mode, A, batch, s); break;
-        }
+// One step of the latency-oriented kernels (1024-blocks): first / turn between two steps / last column pass around the row pass.
+// The accumulator alternates between the caller's buffer and `spare`; the last pass leaves it in the caller's.
+template <int G>
+static void launch_step_lat(const bign_args &A, uint64_t *spare, uint32_t n_steps, hipStream_t s) {
+    uint64_t *cur = A.step & 1u ? spare : A.acc, *prev = A.step & 1u ? A.acc : spare;    // the accumulator after A.step steps, and before the last of them
+    if (A.step == 0) hipLaunchKernelGGL((k_big_cols_fwd<G, 1024>), dim3(4, 2, A.batch), dim3(256), 0, s, A);
+    // one thread per column below eight rows: eight waves for 64 columns would have one row pair each (us per step at N = 2048, l = 2, 256
+    // ciphertexts 68 against 38, at N = 4096, l = 2, 64: 30 against 27; at N = 8192 eight waves are faster, one ciphertext 14.7 against 18.0)
+    else if constexpr (G <= 4) hipLaunchKernelGGL((k_big_cols_turn_short<G>), dim3(4, 2, A.batch), dim3(256), 0, s, A, (const uint64_t *)prev, cur);
+    else hipLaunchKernelGGL((k_big_cols_turn<G>), dim3((2 * A.batch >= 8 ? (2 * A.batch + 7) / 8 * 8 : 2 * A.batch) * 16), dim3(512), 0, s, A, (const uint64_t *)prev, cur);
+    const dim3 tasks(A.batch * 2 * G);
+    if (A.l == 1) hipLaunchKernelGGL(k_big_rows16_team<2>, tasks, dim3(128), TEAM_LDS(2), s, A, (uint32_t)G);
+    else if (A.l == 2) hipLaunchKernelGGL(k_big_rows16_team<4>, tasks, dim3(256), TEAM_LDS(4), s, A, (uint32_t)G);
+    else if (A.l == 3) hipLaunchKernelGGL(k_big_rows16_team<6>, tasks, dim3(384), TEAM_LDS(6), s, A, (uint32_t)G);
+    else hipLaunchKernelGGL(k_big_rows16_team<8>, tasks, dim3(512), TEAM_LDS(8), s, A, (uint32_t)G);
+    if (A.step + 1 == n_steps)
+        hipLaunchKernelGGL((k_big_cols_last<G>), dim3(4, 2, A.batch), dim3(256), 0, s, A, (const uint64_t *)cur);
+}
+static void launch_step_lat_any(uint32_t G, const bign_args &A, uint64_t *spare, uint32_t n_steps, hipStream_t s) {
+    switch (G) {
+        case 2: launch_step_lat<2>(A, spare, n_steps, s); break;
+        case 4: launch_step_lat<4>(A, spare, n_steps, s); break;
+        case 8: launch_step_lat<8>(A, spare, n_steps, s); break;
+        case 16: launch_step_lat<16>(A, spare, n_steps, s); break;
+        default: launch_step_lat<32>(A, spare, n_steps, s); break;
     }
 }
 
@@ -660,13 +905,15 @@ static int ensure_lanes(slz_ctx *ctx) {
     return SLZ_OK;
 }
 
-// Ciphertexts the latency-oriented kernels are used for on one stream: while their row tasks (2 G per ciphertext) fill at most half
-// of the 2048 resident-wave slots of the row pass.  Measured at N = 32768, us per CMux step against the throughput kernels:
-// 34 / 47 at one ciphertext, 40 / 52 at 4, 41 / 57 at 8, 50 / 58 at 12, 53 / 61 at 16; from 20 on they are equal.
-static uint32_t latency_max_batch(uint32_t G) { return 1024u / (2 * G) ? 1024u / (2 * G) : 1u; }
-// Up to this many ciphertexts the row pass is cut into per-GGSW-row and per-component launches, above it into one launch
-// of one-component tasks.
-static uint32_t latency_split_rows_max(uint32_t G) { return 256u / (2 * G) ? 256u / (2 * G) : 1u; }
+// Ciphertexts up to which a step runs as the two launches above.  us per CMux step, three launches per step -> two (l = 2 unless said):
+//   N = 32768: 1: 34 -> 22, 4: 39 -> 25, 8: 41 -> 33, 16: 53 -> 44, 24: 74 -> 57, 32: 79 -> 71, 48: 101 -> 103
+//   N = 16384: 8: 34 -> 21, 32: 50 -> 40, 48: 61 -> 53, 56: 64 -> 62, 64: 68 -> 69     N = 8192: 64: 50 -> 41, 96: 58 -> 56, 112: 60 -> 64; l = 1: 112: 48 -> 49
+//   N = 4096: 64: 32 -> 27, 128: 48 -> 38; l = 3: 64: 39 -> 36, 128: 60 -> 60          N = 2048: 256: 50 -> 38; l = 3: 192: 57 -> 47, 256: 63 -> 59
+// Past that the column work done twice costs more than the launch and the accumulator's traffic that it saves.
+static uint32_t latency_max_batch(uint32_t G) { return G >= 32 ? 32u : G == 16 ? 56u : G == 8 ? 96u : 512u / G; }
+// From more than this many on they run as two even halves on the two lanes: N = 32768: 16: 44 either way, 24: 60 -> 57, 32: 75 -> 71;
+// N = 16384: 32: 40 either way, 48: 54 -> 53; N = 8192: 64: 41 -> 43.
+static uint32_t latency_one_lane_max(uint32_t G) { return G >= 16 ? 512u / G : 0xffffffffu; }
 // Ciphertexts of the first of two lanes for a batch past latency_max_batch (1024-blocks); 0: the lanes take chunks of `half`, or one
 // lane takes all.  `half` ciphertexts are 2048 row tasks or more: alone on the chip they fill it, so a smaller batch leaves the chip idle at
 // every hand-over between its launches, which a second lane fills; a batch a little larger would be a full lane and a small rest.  From a
@@ -691,14 +938,14 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     const uint32_t N = p.N, BS = (uint32_t)ctx->bign_block, G = N / BS, R = 2 * p.pbs_level;
     uint32_t logG = 0;
     while ((1u << logG) < G) logG++;
-    // A handful of ciphertexts: every step in four shorter launches (1024-blocks only)
+    // few ciphertexts: every step in two launches (1024-blocks only)
     const uint32_t lat_max = latency_max_batch(G);
     const bool lat = ctx->bign_latency && BS == 1024 && batch <= lat_max;
-    if (lat && !ctx->bign_partial) {
+    if (lat && !ctx->bign_spare) {
         const size_t cts = ctx->max_batch < lat_max ? ctx->max_batch : lat_max;
         void *buf = nullptr;
-        if (slz_scratch_alloc(&buf, cts * 2 * R * 2 * N * sizeof(double)) != SLZ_OK) return SLZ_E_NOMEM;
-        ctx->bign_partial = (double *)buf;
+        if (slz_scratch_alloc(&buf, cts * 2 * N * sizeof(uint64_t)) != SLZ_OK) return SLZ_E_NOMEM;
+        ctx->bign_spare = (uint64_t *)buf;
     }
     // Ciphertexts go through all steps in chunks whose workspace (X, Y, accumulators: (2R + 4 + 2) N doubles each) stays
     // in the 256 MB Infinity Cache; the key (read once per chunk and step) streams from HBM.
@@ -712,7 +959,10 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     // arithmetic) overlaps the column passes of the other (bound by memory).  Measured at N = 32768: 5 % faster than one
     // lane; three or four lanes of the same size overflow the Infinity Cache and are slower.
     uint32_t lanes = (uint32_t)ctx->bign_lanes;
-    if (lanes >= 2) {
+    if (lat) {
+        if (batch <= latency_one_lane_max(G)) lanes = 1;
+        chunk = lanes >= 2 ? (batch + 1) / 2 : batch;
+    } else if (lanes >= 2) {
         uint32_t half = chunk / 2 / fill * fill;
         if (half < fill) half = fill;
         const uint32_t first = BS == 1024 && batch > lat_max ? slz_bign_first_of_even_lanes(G, batch, half) : 0;
@@ -745,6 +995,9 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
                 a.tab[q].fwd = ctx->tab[q].fwd;
                 a.tab[q].rowA = (BS == 2048 ? ctx->bign_rowA : ctx->bign16_rowA) + (size_t)q * G * 64;
                 a.tab[q].rowB = BS == 2048 ? ctx->bign_rowB + (size_t)q * G * 31 * 64 : ctx->bign16_rowB + (size_t)q * G * 15 * 64;
+                a.tab[q].rowAi = ctx->bign16_rowAi + (size_t)q * G * 64;
+                a.tab[q].rowBi = ctx->bign16_rowBi + (size_t)q * G * 15 * 64;
+                a.tab[q].colI = ctx->bign16_colI + 32 * q;
                 a.tab[q].inv = ctx->tab[q].inv;
                 a.tab[q].post = ctx->tab[q].post;
                 a.mod[q] = ctx->mod[q];
@@ -760,33 +1013,20 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
                 bign_args &a = A[j];
                 a.step = step;
                 a.bskp_step = bskp + (size_t)step * 2 * R * 2 * N;
-                launch_cols_any(true, lat ? 1 : 0, G, BS, a, nbs[j], st[j]);
-                if (lat && nbs[j] > latency_split_rows_max(G)) {
-                    // upper part of the range: one launch of one-component row tasks
-                    const uint32_t tc = n_tasks[j] * 2;
-                    hipLaunchKernelGGL(k_big_rows16<false>, dim3((tc + 3) / 4), dim3(256), 4 * (TBUF16 + 1024) * sizeof(double), st[j], a, G,
-                                       tc, 0);
-                    launch_cols_any(false, 1, G, BS, a, nbs[j], st[j]);
-                    continue;
-                }
                 if (lat) {
-                    const uint32_t ta = n_tasks[j] * R, tb = n_tasks[j] * 2;
-                    hipLaunchKernelGGL(k_big_rows16_lat_a, dim3((ta + 3) / 4), dim3(256), 4 * (TBUF16 + 1024) * sizeof(double), st[j], a,
-                                       ctx->bign_partial, G, ta);
-                    hipLaunchKernelGGL(k_big_rows16_lat_b, dim3((tb + 3) / 4), dim3(256), 4 * TBUF16 * sizeof(double), st[j], a,
-                                       ctx->bign_partial, G, tb);
-                    launch_cols_any(false, 1, G, BS, a, nbs[j], st[j]);
+                    launch_step_lat_any(G, a, ctx->bign_spare + (a.acc - acc), n_steps, st[j]);
                     continue;
                 }
+                launch_cols_any(true, G, BS, a, nbs[j], st[j]);
                 // the XCD-aware order needs the task count to split evenly over 8 XCDs x 4 waves x (2G/8) combinations
                 const int xcd_aware = (2 * G) % 8 == 0 && n_tasks[j] % 32 == 0 && (n_tasks[j] / 8) % (2 * G / 8) == 0;
                 if (BS == 2048)
                     hipLaunchKernelGGL(k_big_rows, dim3((n_tasks[j] + 3) / 4), dim3(256), 4 * TBUF * sizeof(double), st[j], a, G,
                                        n_tasks[j], xcd_aware);
                 else
-                    hipLaunchKernelGGL(k_big_rows16<true>, dim3((n_tasks[j] + 3) / 4), dim3(256), 4 * (TBUF16 + 1024) * sizeof(double), st[j], a,
+                    hipLaunchKernelGGL(k_big_rows16, dim3((n_tasks[j] + 3) / 4), dim3(256), 4 * (TBUF16 + 1024) * sizeof(double), st[j], a,
                                        G, n_tasks[j], xcd_aware);
-                launch_cols_any(false, 0, G, BS, a, nbs[j], st[j]);
+                launch_cols_any(false, G, BS, a, nbs[j], st[j]);
             }
         }
     }

@@ -265,7 +265,7 @@ int slz_fused4096_init(slz_ctx *ctx) {
     // the stage across the blocks and six more on the digits, reduction, five more; two products summed; inverse 2 + 3
     // stages, reduction, six stages, reduction, the stage across the blocks, twist
     if (!slz_fused_schedule_ok(1, 6, 5, 2, 3, 6, true, 2)) return SLZ_E_UNSUPPORTED;
-    int rc = slz_build_block_tables(ctx, 2048, &ctx->fused4096_rowA, &ctx->fused4096_rowB);
+    int rc = slz_build_block_tables(ctx, 2048, false, &ctx->fused4096_rowA, &ctx->fused4096_rowB);
     if (rc != SLZ_OK) return rc;
     for (int q = 0; q < 2; q++) {
         SLZ_HIP(hipMemcpy(ctx->fused4096_scalars[q], ctx->fused4096_rowA + (size_t)q * 2 * 64, 2 * 64 * sizeof(double), hipMemcpyDeviceToHost));

@@ -431,3 +431,124 @@ __device__ __forceinline__ void inv16(double (&x)[16], double *T, const double *
         }
     }
 }
+
+// ---- the mirrored inverse ----------------------------------------------------------------------------------------------
+// Inverse as the forward transform run backwards: (a, b) -> (a + b, (a - b) / w) with the twiddle w of the forward butterfly, N times
+// the inverse in all.  Its twiddles depend on the block and not on the position inside it, so the column passes of the large-N path need a
+// handful of uniform constants and no twist, where the decimation-in-time form above reads 63 table words per column of 32.
+// Sums grow by doubling: every value carries a bound (in units of p; constants once the loops are unrolled), and a pair is reduced
+// where its sum could pass LAZY_MAX.
+#define LAZY_MAX 7.4
+// K independent pairs, interleaved like bfly_k
+template <int K>
+__device__ __forceinline__ void gs_k(double *(&a)[K], double *(&b)[K], double *(&ba)[K], double *(&bb)[K], const double (&w)[K], slz_mod m) {
+    double h[K], l[K], q[K], d[K];
+#pragma unroll
+    for (int i = 0; i < K; i++) {
+        if (*ba[i] + *bb[i] > LAZY_MAX && *ba[i] >= *bb[i]) { *a[i] = slz_reduce(*a[i], m); *ba[i] = 0.5 + 1e-9; }
+        if (*ba[i] + *bb[i] > LAZY_MAX) { *b[i] = slz_reduce(*b[i], m); *bb[i] = 0.5 + 1e-9; }
+        if (*ba[i] + *bb[i] > LAZY_MAX) { *a[i] = slz_reduce(*a[i], m); *ba[i] = 0.5 + 1e-9; }
+        const double s = *ba[i] + *bb[i];
+        *ba[i] = s;
+        *bb[i] = 0.5 + 0.1875 * s + 1e-9;                          // slz_mulmod_bound
+    }
+#pragma unroll
+    for (int i = 0; i < K; i++) d[i] = *a[i] - *b[i];
+#pragma unroll
+    for (int i = 0; i < K; i++) h[i] = d[i] * w[i];
+#pragma unroll
+    for (int i = 0; i < K; i++) *a[i] = *a[i] + *b[i];
+#pragma unroll
+    for (int i = 0; i < K; i++) q[i] = h[i] * m.pinv;
+#pragma unroll
+    for (int i = 0; i < K; i++) l[i] = __builtin_fma(d[i], w[i], -h[i]);
+#pragma unroll
+    for (int i = 0; i < K; i++) q[i] = __builtin_rint(q[i]);
+#pragma unroll
+    for (int i = 0; i < K; i++) h[i] = __builtin_fma(-q[i], m.p, h[i]);
+#pragma unroll
+    for (int i = 0; i < K; i++) *b[i] = h[i] + l[i];
+}
+// eight values stay below `limit` (units of p) from here on
+template <int K>
+__device__ __forceinline__ void lazy_limit(double (&x)[K], double (&bd)[K], double limit, slz_mod m) {
+#pragma unroll
+    for (int i = 0; i < K; i++)
+        if (bd[i] > limit) { x[i] = slz_reduce(x[i], m); bd[i] = 0.5 + 1e-9; }
+}
+#define GS4(i0, j0, w0, i1, j1, w1, i2, j2, w2, i3, j3, w3) do { \
+    double *pa_[4] = {&x[i0], &x[i1], &x[i2], &x[i3]}; double *pb_[4] = {&x[j0], &x[j1], &x[j2], &x[j3]}; \
+    double *ua_[4] = {&bd[i0], &bd[i1], &bd[i2], &bd[i3]}; double *ub_[4] = {&bd[j0], &bd[j1], &bd[j2], &bd[j3]}; \
+    const double pw_[4] = {w0, w1, w2, w3}; gs_k<4>(pa_, pb_, ua_, ub_, pw_, m); } while (0)
+
+// 1024 points.  In: layout B, |x| <= 0.51 p.  Out: layout A, |x| <= LAZY_MAX p.  twB: the 15 per-lane twiddles of the first four stages
+// (inverses of the entries fwd16 takes from twB_tab), twA: the block's 64 lane-uniform ones (inverses of fwd16's twA).
+__device__ __forceinline__ void inv16_mirror(double (&x)[16], double *T, const double *twA, const double (&twB)[15], slz_mod m, uint32_t lane, int z) {
+    const uint32_t hh = lane >> 5, v = (lane >> 4) & 1u, j = lane & 15u;
+    double bd[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) bd[i] = 0.51;
+#pragma unroll
+    for (int s = 3; s >= 0; s--) {                                          // t = 1, 2, 4, 8
+        const int t = 8 >> s;
+#pragma unroll
+        for (int g = 0; g < 2; g++) {
+#define GB16_I(b) (((b) / t) * 2 * t + (b) % t)
+#define GB16_W(b) twB[(1 << s) - 1 + (b) / t]
+            GS4(GB16_I(4 * g), GB16_I(4 * g) + t, GB16_W(4 * g), GB16_I(4 * g + 1), GB16_I(4 * g + 1) + t, GB16_W(4 * g + 1),
+                GB16_I(4 * g + 2), GB16_I(4 * g + 2) + t, GB16_W(4 * g + 2), GB16_I(4 * g + 3), GB16_I(4 * g + 3) + t, GB16_W(4 * g + 3));
+        }
+    }
+    lazy_limit(x, bd, 0.6, m);
+    wave_sync();                                                            // earlier reads of T are done
+    double *wb = T + 18u * lane;
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+        double2 t2;
+        t2.x = x[i];
+        t2.y = x[i + 1];
+        *reinterpret_cast<double2 *>(wb + i) = t2;
+    }
+    wave_sync();
+    const double *rb = T + 72u * hh + 36u * v + j;
+#pragma unroll
+    for (int mm = 0; mm < 8; mm++) {
+        x[2 * mm] = rb[144 * mm];
+        x[2 * mm + 1] = rb[144 * mm + 18];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; i++) bd[i] = 0.6;
+#pragma unroll
+    for (int g = 0; g < 2; g++) {                                           // t = 16: block 4 mm + 2 hh + v of 32
+#define GW6(mm) ldl(twA + 32 + 4 * (mm) + z, (lane >> 4) * 8u)
+        GS4(8 * g, 8 * g + 1, GW6(4 * g), 8 * g + 2, 8 * g + 3, GW6(4 * g + 1), 8 * g + 4, 8 * g + 5, GW6(4 * g + 2), 8 * g + 6, 8 * g + 7,
+            GW6(4 * g + 3));
+#pragma unroll
+        for (int mm = 4 * g; mm < 4 * g + 4; mm++) {
+            swap16(x[2 * mm], x[2 * mm + 1]);
+            bd[2 * mm] = bd[2 * mm + 1] = bd[2 * mm] > bd[2 * mm + 1] ? bd[2 * mm] : bd[2 * mm + 1];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < 2; g++) {                                           // t = 32: block 2 mm + hh of 16
+#define GW5(mm) ldl(twA + 16 + 2 * (mm) + z, hh * 8u)
+        GS4(8 * g, 8 * g + 1, GW5(4 * g), 8 * g + 2, 8 * g + 3, GW5(4 * g + 1), 8 * g + 4, 8 * g + 5, GW5(4 * g + 2), 8 * g + 6, 8 * g + 7,
+            GW5(4 * g + 3));
+#pragma unroll
+        for (int mm = 4 * g; mm < 4 * g + 4; mm++) {
+            swap32(x[2 * mm], x[2 * mm + 1]);
+            bd[2 * mm] = bd[2 * mm + 1] = bd[2 * mm] > bd[2 * mm + 1] ? bd[2 * mm] : bd[2 * mm + 1];
+        }
+    }
+#pragma unroll
+    for (int s = 3; s >= 0; s--) {                                          // t = 64 .. 512
+        const int half = 8 >> s;
+#pragma unroll
+        for (int g = 0; g < 2; g++) {
+#define GA16_I(b) (((b) / half) * 2 * half + (b) % half)
+#define GA16_W(b) twA[(1 << s) + (b) / half + z]
+            GS4(GA16_I(4 * g), GA16_I(4 * g) + half, GA16_W(4 * g), GA16_I(4 * g + 1), GA16_I(4 * g + 1) + half, GA16_W(4 * g + 1),
+                GA16_I(4 * g + 2), GA16_I(4 * g + 2) + half, GA16_W(4 * g + 2), GA16_I(4 * g + 3), GA16_I(4 * g + 3) + half, GA16_W(4 * g + 3));
+        }
+    }
+}

@@ -963,3 +963,26 @@ def test_lookup_replays_from_a_hip_graph(slz, orc, shape, batch):
             want = orc.pbs_batch(p, cts[idx], case.luts, case.lut_idx[idx], case.keys.bsk)
             assert np.array_equal(got_big[idx], want)
             assert np.array_equal(got_small[idx], orc.keyswitch_batch(p, want, case.keys.ksk))
+
+
+@pytest.mark.parametrize("N,l,beta,n,batches", [
+    (2048, 2, 12, 1, [1, 256]),             # G = 2, a thread per column; one step: no column pass between two row passes
+    (2048, 4, 7, 2, [3]),                   # eight GGSW rows per team
+    (4096, 3, 11, 3, [2, 128]),             # G = 4, six rows
+    (8192, 1, 20, 2, [1, 5, 96]),           # G = 8, eight waves per 64 columns, two rows; five ciphertexts: pairs split over the XCDs
+    (8192, 3, 12, 3, [4]),                  # three levels over eight waves
+    (16384, 2, 15, 3, [3, 32, 33, 56]),     # G = 16; one lane up to 32
+    (32768, 2, 15, 2, [2, 16, 17, 32]),     # G = 32; one lane up to 16
+])
+def test_large_n_two_launch_steps_match_the_throughput_kernels(slz, orc, N, l, beta, n, batches):
+    # the largest batches the two-launch steps take and sizes where their form changes, odd and even step counts (the accumulator
+    # alternates between two buffers); the throughput kernels are compared with the oracle elsewhere
+    p = tiny(n=n, N=N, k=1, pbs_base_log=beta, pbs_level=l)
+    case = Case(slz, orc, p, max(batches), raw_inputs=True)
+    assert case.ctx.path == "three_pass_large_n"
+    case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
+    want = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
+    case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 1)
+    for count in batches:
+        got = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts[:count], case.d_luts, case.d_idx[:count], case.d_bsk))
+        assert np.array_equal(got, want[:count]), count
