@@ -44,15 +44,21 @@ def alu_model_ops_per_pbs(p, transforms=False) -> float:
     8 per butterfly (6 modular multiply + add + sub), 7 per pointwise multiply-accumulate, 3 per inverse
     post-scaling beyond the butterflies' share (6-instruction modular multiply per coefficient), 12 per
     decomposed coefficient (rotate, subtract, round, digit, convert) and 20 per CRT-lifted coefficient.
-    transforms: a context that takes floating-point transforms of M = N / 2 complex points (N = 1024 and 2048: five key pieces;
-    N = 512: three), which is what the size of its prepared key says: 6 per radix-2 butterfly (N = 2048 forward: 28 per radix-4 butterfly), 4 per complex
+    transforms: a context that takes floating-point transforms of M = N / 2 complex points (five key pieces; N = 512: three), which is
+    what the size of its prepared key says: 6 per radix-2 butterfly (N = 2048 forward and parts of N = 4096: 28 per radix-4 butterfly,
+    80 per radix-8 one), 4 per complex
     multiply-add, the same 12 (+ 4 per level) per decomposed coefficient and 2 per coefficient and piece for rounding and adding."""
     logN = p.N.bit_length() - 1
     R, C = (p.k + 1) * p.pbs_level, p.k + 1
     if transforms:
         M, pieces = p.N // 2, 3 if p.N == 512 else 5
-        forward = 5 * (M // 4) * 28 if p.N == 2048 else (logN - 1) * (M // 2) * 6
-        return float(p.n) * (R * forward + pieces * R * C * M * 4 + pieces * C * (logN - 1) * (M // 2) * 6 +
+        forward = inverse = (logN - 1) * (M // 2) * 6
+        if p.N == 2048:
+            forward = 5 * (M // 4) * 28
+        if p.N == 4096:
+            forward = (M // 2) * 6 + 2 * (M // 4) * 28 + 2 * (M // 8) * 80
+            inverse = 7 * (M // 2) * 6 + 2 * (M // 4) * 28
+        return float(p.n) * (R * forward + pieces * R * C * M * 4 + pieces * C * inverse +
                              C * p.N * (12 + 4 * (p.pbs_level - 1)) + pieces * C * p.N * 2)
     per_prime = (R + C) * (p.N // 2) * logN * 8 + R * C * p.N * 7 + C * p.N * 6
     per_cmux = 2 * per_prime + C * p.N * (12 + 4 * (p.pbs_level - 1)) + C * p.N * 20

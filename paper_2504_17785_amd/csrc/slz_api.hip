@@ -34,14 +34,9 @@ static int init_paths(slz_ctx *ctx) {
     const slz_params *params = &ctx->prm;
     int rc = slz_build_tables(ctx);
     // specialised paths are optional: a shape they decline (SLZ_E_UNSUPPORTED) runs on the generic path
-    if (rc == SLZ_OK && slz_fft_supported(params)) {
+    if (rc == SLZ_OK && (slz_fft_supported(params) || slz_fft4096_supported(params))) {
         rc = slz_fft_init(ctx);
         ctx->has_fft = (rc == SLZ_OK);
-    }
-    if (rc == SLZ_OK && slz_fused4096_supported(params)) {
-        rc = slz_fused4096_init(ctx);
-        ctx->has_fused4096 = (rc == SLZ_OK);
-        if (rc == SLZ_E_UNSUPPORTED) rc = SLZ_OK;
     }
     if (rc == SLZ_OK && slz_fused512_supported(params)) {
         rc = slz_fused512_init(ctx);
@@ -102,7 +97,6 @@ extern "C" int slz_ctx_destroy(slz_ctx *ctx) {
     slz_fft_destroy(ctx);
     slz_fused1024_destroy(ctx);
     slz_fused512_destroy(ctx);
-    slz_fused4096_destroy(ctx);
     slz_bign_destroy(ctx);
     slz_ksm_destroy(ctx);
     slz_lcm_destroy(ctx);
@@ -147,8 +141,8 @@ extern "C" const char *slz_pbs_path(const slz_ctx *ctx) {
     if (ctx->force_generic) return "generic";
     if (ctx->has_fused1024) return "fused_n1024";
     if (ctx->has_fused512) return "fused_n512";
-    if (ctx->has_fused4096) return "fused_n4096";
-    return ctx->has_fft ? "fused_n2048" : (ctx->has_bign ? "three_pass_large_n" : "generic");
+    if (ctx->has_fft) return ctx->prm.N == 4096 ? "fused_n4096" : "fused_n2048";
+    return ctx->has_bign ? "three_pass_large_n" : "generic";
 }
 
 extern "C" int slz_lut_encode(const slz_params *p, const uint64_t *table, uint32_t n_tables, uint64_t *lut_out) {
@@ -235,10 +229,8 @@ static int blind_rotate_common(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
         return SLZ_E_INVALID_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     if (ctx->has_fft && !ctx->force_generic)     // 1.1 to 3.3 times as fast as through residues, at every batch size
-        return (ctx->prm.N == 2048 ? slz_fft2048_blind_rotate : ctx->prm.N == 1024 ? slz_fft1024_blind_rotate : slz_fft512_blind_rotate)(
+        return (ctx->prm.N == 4096 ? slz_fft4096_blind_rotate : ctx->prm.N == 2048 ? slz_fft2048_blind_rotate : ctx->prm.N == 1024 ? slz_fft1024_blind_rotate : slz_fft512_blind_rotate)(
             ctx, lwe_in, luts, lut_idx, (const char *)bskp + residue_key_bytes(ctx->prm), n_steps, acc_out, lwe_out, batch, s);
-    if (ctx->has_fused4096 && !ctx->force_generic)
-        return slz_fused4096_blind_rotate(ctx, lwe_in, luts, lut_idx, (const double *)bskp, n_steps, acc_out, lwe_out, batch, s);
     if (ctx->has_fused512 && !ctx->force_generic)
         return slz_fused512_blind_rotate(ctx, lwe_in, luts, lut_idx, (const double *)bskp, n_steps, acc_out, lwe_out, batch, s);
     if (ctx->has_fused1024 && !ctx->force_generic)

@@ -1,5 +1,5 @@
 // Exact negacyclic products through double-precision complex transforms: the pieces shared by the host code, the key
-// preparation and the N = 512, 1024 and 2048 blind rotations.
+// preparation and the N = 512, 1024, 2048 and 4096 blind rotations.
 //
 // A key word is cut into SLZ_FFT_PIECES balanced digits of SLZ_FFT_PIECE_BITS bits, w = sum_j K_j 2^(13 j) mod 2^64 with
 // |K_j| <= 2^12 (N = 512, whose bases are smaller: three digits of 22 bits).  For every piece the integer polynomial y_j = sum_r d_r K_(r,j) mod X^N + 1 (d_r: gadget digits) is
@@ -61,6 +61,24 @@
 #define F9_TAB_LEN (F9_F3_OFF + 128u)
 // complex entries of the transform-domain key of one step: [piece][k][row, component][lane]
 #define F9_KEY_STEP (F9_PIECES * 4u * 8u * 64u)
+
+// Tables of the N = 4096 kernel, M = 2048:
+//   F2 [7][8]        forward strides 128, 64, 32 as one radix-8 layer (u .. u^7), by the three top position bits
+//   F3 [7][64]       forward strides 16, 8, 4 likewise, by the six top position bits
+//   I2 [5][8]        inverse half-sizes 8 and 16 as one radix-4 layer (v, v^2, v^3), 32 (2, as (cos, tan)), by the three lowest position bits
+//   I3 [5][64]       inverse half-sizes 64 and 128, 256 (2) likewise
+//   I4 [9][256]      inverse half-sizes 512 (1, as (cos, tan)); 1024: four (c1, c2) pairs as above
+//   F4 [4][6][64]    forward strides 2/1, by (two top bits, lane): two blocks of three
+#define F12_F2_OFF 0u
+#define F12_F3_OFF 56u
+#define F12_I2_OFF (F12_F3_OFF + 448u)
+#define F12_I3_OFF (F12_I2_OFF + 40u)
+#define F12_I4_OFF (F12_I3_OFF + 320u)
+#define F12_LDS_TAB (F12_I4_OFF + 9u * 256u)
+#define F12_F4_OFF F12_LDS_TAB
+#define F12_TAB_LEN (F12_F4_OFF + 4u * 6u * 64u)
+// complex entries of the transform-domain key of one step: [piece][quarter g][k][row, component][lane]
+#define F12_KEY_STEP (SLZ_FFT_PIECES * 4u * 8u * 4u * 64u)
 
 // Worst-case error (absolute, before rounding) of one y_j over all inputs, see slz_fft.hip.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta);

@@ -32,6 +32,12 @@
 // has one stage less: 30.22 u and six times TABLE.
 // N = 512, M = 256: eight forward layers; half-size 4 is a butterfly like the others, 27.61 u and six times TABLE; four rows, so the
 // chain of fused multiply-adds gives (8 + 6 + 4 + 2) u |D K|, 5 u per row.
+// N = 4096, M = 2048: the first forward layer is radix 2 with the constant (1 + i) / sqrt(2) on integers, whose sums p = b.x -+ b.y are
+// exact: the constant's rounding 0.61 u and the result's u.  Then radix 4 (4.7072 u and TABLE), two radix-8 layers (a product 2.7072 u
+// and TABLE, two additions u each, and a third whose odd part may be a sum, rounded u, times sqrt(1/2), 0.61 u, inside the addition that
+// rounds u: 7.3172 u and TABLE) and radix 4.  Inverse: half-sizes 1, 2, 4 as above (4.61 u); twice a radix-4 layer (on a path one product,
+// 2.7072 u and TABLE, and two additions) and a radix-2 one (4 u and TABLE); 512, 1024 with the twist, the turn (9.61 u and TABLE twice):
+// 31.6344 u and six times TABLE.
 double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
     const double u = std::ldexp(1.0, -53), key = 1.05, table = 0.02;
     double fwd, inv;
@@ -39,6 +45,7 @@ double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
     if (N == 2048 && rows == 2) { fwd = 5 * (4.7072 + table); inv = 34.22 + 7 * table; }
     else if (N == 1024 && rows == 2) { fwd = 9 * (4.0 + table); inv = 30.22 + 6 * table; }
     else if (N == 512 && rows == 4) { fwd = 8 * (4.0 + table); inv = 27.61 + 6 * table; bits = F9_PIECE_BITS; }
+    else if (N == 4096 && rows == 2) { fwd = 1.61 + 2 * (4.7072 + table) + 2 * (7.3172 + table); inv = 4.61 + 2 * (4.7072 + 4.0) + 9.61 + 6 * table; }
     else return 1e300;
     const double norm_d = std::ldexp(std::sqrt((double)N), (int)beta - 1);
     const double norm_k = std::ldexp(std::sqrt((double)N), bits - 1);
@@ -46,8 +53,8 @@ double slz_fft_error_bound(uint32_t N, uint32_t rows, uint32_t beta) {
     return (fwd + rows + 1.0 + key + inv) * u * (double)rows * norm_d * norm_k * (1.0 + std::ldexp(1.0, -40));
 }
 
-int slz_fft_supported(const slz_params *p) {
-    return p->k == 1 && p->pbs_base_log <= 30 && slz_fft_error_bound(p->N, 2 * p->pbs_level, p->pbs_base_log) < 0.499;
+int slz_fft_supported(const slz_params *p) {                        // N = 4096: slz_fft4096_supported
+    return p->N != 4096 && p->k == 1 && p->pbs_base_log <= 30 && slz_fft_error_bound(p->N, 2 * p->pbs_level, p->pbs_base_log) < 0.499;
 }
 
 // ---- tables ---------------------------------------------------------------------------------------------------------
@@ -172,6 +179,41 @@ static void build_512(std::vector<cpl> &t, double (&f1_out)[15][2]) {
     for (int q = 0; q < 4; q++) { f1_out[q][0] = f1[q].r; f1_out[q][1] = f1[q].i; }
 }
 
+// the powers 1 .. 7 of the twiddle of a radix-8 layer that begins with m blocks, for block `blk`; the angle is reduced exactly
+static void eight(cpl *out, size_t stride, uint32_t m, uint32_t blk) {
+    const long double v = node_angle(4 * m, 4 * blk);
+    for (int q = 0; q < 7; q++) out[q * stride] = unit(fmodl((q + 1) * v, 2.0L));
+}
+static void build_4096(std::vector<cpl> &t, double (&f1_out)[15][2]) {
+    const uint32_t M = 2048;
+    t.resize(F12_TAB_LEN);
+    for (uint32_t x = 0; x < 8; x++) eight(&t[F12_F2_OFF + x], 8, 8, x);
+    for (uint32_t x = 0; x < 64; x++) eight(&t[F12_F3_OFF + x], 64, 64, x);
+    for (uint32_t g = 0; g < 4; g++)
+        for (uint32_t l = 0; l < 64; l++)
+            for (uint32_t b = 0; b < 2; b++) three(&t[F12_F4_OFF + (g * 6 + 3 * b) * 64 + l], 64, 512, (g * 64 + l) * 2 + b);
+    auto inverse = [&](cpl *o, uint32_t stride, uint32_t half) {      // half-sizes half and 2 half as (v, v^2, v^3), 4 half as (cos, tan)
+        for (uint32_t l = 0; l < half; l++) {
+            for (uint32_t q = 0; q < 3; q++) o[q * stride + l] = unit(-(long double)((q + 1) * l) / (2 * half));
+            for (uint32_t q = 0; q < 2; q++) o[(3 + q) * stride + l] = cos_tan(-(long double)(half * q + l) / (4 * half));
+        }
+    };
+    inverse(&t[F12_I2_OFF], 8, 8);
+    inverse(&t[F12_I3_OFF], 64, 64);
+    for (uint32_t l = 0; l < 256; l++) {
+        cpl *o = &t[F12_I4_OFF + l];
+        o[0] = cos_tan(-(long double)l / 512);
+        for (uint32_t q = 0; q < 4; q++) {
+            const long double j = 256 * q + l;
+            o[256 * (1 + 2 * q)] = unit(-j / (2 * M));
+            o[256 * (2 + 2 * q)] = cos_tan(-j / (2 * M) - j / 1024);
+        }
+    }
+    cpl f1[6];
+    for (uint32_t b = 0; b < 2; b++) three(f1 + 3 * b, 1, 2, b);
+    for (int q = 0; q < 6; q++) { f1_out[q][0] = f1[q].r; f1_out[q][1] = f1[q].i; }
+}
+
 // Host copies of the tables of one size, built by the first context that needs them (a millisecond of long-double functions).
 struct host_tables {
     std::vector<cpl> t;
@@ -181,7 +223,8 @@ struct host_tables {
 static host_tables build(uint32_t N) {
     host_tables r{};
     const uint32_t M = N / 2;
-    if (N == 2048) build_2048(r.t, r.f1);
+    if (N == 4096) build_4096(r.t, r.f1);
+    else if (N == 2048) build_2048(r.t, r.f1);
     else if (N == 1024) build_1024(r.t, r.f1);
     else build_512(r.t, r.f1);
     r.w.resize(4 * (size_t)M);
@@ -195,6 +238,7 @@ static host_tables build(uint32_t N) {
     return r;
 }
 static const host_tables &tables(uint32_t N) {
+    if (N == 4096) { static const host_tables t4096 = build(4096); return t4096; }
     if (N == 2048) { static const host_tables t2048 = build(2048); return t2048; }
     if (N == 1024) { static const host_tables t1024 = build(1024); return t1024; }
     static const host_tables t512 = build(512);
@@ -208,7 +252,7 @@ int slz_fft_init(slz_ctx *ctx) {
     SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, h.w.size() * sizeof(double)));
     SLZ_HIP(hipMemcpy(ctx->fft_tab, h.t.data(), h.t.size() * sizeof(cpl), hipMemcpyHostToDevice));
     SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, h.w.data(), h.w.size() * sizeof(double), hipMemcpyHostToDevice));
-    return ctx->prm.N == 2048 ? slz_fft2048_setup() : ctx->prm.N == 1024 ? slz_fft1024_setup() : slz_fft512_setup();
+    return ctx->prm.N == 4096 ? slz_fft4096_setup() : ctx->prm.N == 2048 ? slz_fft2048_setup() : ctx->prm.N == 1024 ? slz_fft1024_setup() : slz_fft512_setup();
 }
 
 void slz_fft_destroy(slz_ctx *ctx) {
@@ -218,7 +262,10 @@ void slz_fft_destroy(slz_ctx *ctx) {
     ctx->fft_prep_tab = nullptr;
 }
 
-size_t slz_fft_key_bytes(const slz_params *p) { return slz_fft_supported(p) ? (size_t)p->n * (p->N == 2048 ? FFT_KEY_STEP : p->N == 1024 ? F10_KEY_STEP : F9_KEY_STEP) * 16 : 0; }
+size_t slz_fft_key_bytes(const slz_params *p) {
+    if (slz_fft4096_supported(p)) return (size_t)p->n * F12_KEY_STEP * 16;
+    return slz_fft_supported(p) ? (size_t)p->n * (p->N == 2048 ? FFT_KEY_STEP : p->N == 1024 ? F10_KEY_STEP : F9_KEY_STEP) * 16 : 0;
+}
 
 // ---- key spectra ----------------------------------------------------------------------------------------------------
 // Double-double arithmetic (error-free sums and products; the build contracts nothing by itself).
@@ -287,7 +334,8 @@ int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s)
     auto launch = [&](auto kernel, uint32_t pieces) {
         hipLaunchKernelGGL(kernel, dim3(polys, pieces), dim3(256), 0, s, bsk, ctx->fft_prep_tab, (double2 *)dst);
     };
-    if (ctx->prm.N == 2048) launch(k_fft_prepare<1024, 2, 8, SLZ_FFT_PIECES, SLZ_FFT_PIECE_BITS>, SLZ_FFT_PIECES);
+    if (ctx->prm.N == 4096) launch(k_fft_prepare<2048, 2, 8, SLZ_FFT_PIECES, SLZ_FFT_PIECE_BITS>, SLZ_FFT_PIECES);
+    else if (ctx->prm.N == 2048) launch(k_fft_prepare<1024, 2, 8, SLZ_FFT_PIECES, SLZ_FFT_PIECE_BITS>, SLZ_FFT_PIECES);
     else if (ctx->prm.N == 1024) launch(k_fft_prepare<512, 2, 8, SLZ_FFT_PIECES, SLZ_FFT_PIECE_BITS>, SLZ_FFT_PIECES);
     else launch(k_fft_prepare<256, 4, 4, F9_PIECES, F9_PIECE_BITS>, F9_PIECES);
     SLZ_HIP(hipGetLastError());

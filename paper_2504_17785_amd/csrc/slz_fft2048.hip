@@ -58,15 +58,6 @@ struct fft_args {
     double f1[15][2];         // lane-uniform twiddles of the first two forward layers: (v, v^2, v^3) of block 0 and of the next four blocks
 };
 
-// forward radix-4: strides 2 n and n over (a0, a1, a2, a3) with v, v^2, v^3
-__device__ __forceinline__ void fwd4(d2 &a0, d2 &a1, d2 &a2, d2 &a3, d2 v, d2 v2, d2 v3) {
-    const d2 b1 = cmul(a1, v), b2 = cmul(a2, v2), b3 = cmul(a3, v3);
-    const d2 s = a0 + b2, d = a0 - b2, e = b1 + b3, f = b1 - b3;
-    a0 = s + e;
-    a1 = s - e;
-    a2.x = d.x - f.y; a2.y = d.y + f.x;
-    a3.x = d.x + f.y; a3.y = d.y - f.x;
-}
 // WIDE = false: a workgroup's four pairs of waves take a ciphertext each.  WIDE = true, for batches of at most one ciphertext per
 // compute unit: all four pairs work on one.  Pair 0 owns the accumulator and runs step 1 and the forward transform; every pair reads
 // the spectra from pair 0's exchange buffers and takes one or two of the key pieces (its first piece's key words wait in registers

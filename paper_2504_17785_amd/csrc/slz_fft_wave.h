@@ -51,6 +51,16 @@ __device__ __forceinline__ void add2i(d2 &a, d2 &b) {                 // b <- a 
     a.x = a.x + t.y; a.y = a.y - t.x;
 }
 
+// forward radix-4: strides 2 n and n over (a0, a1, a2, a3) with v, v^2, v^3
+__device__ __forceinline__ void fwd4(d2 &a0, d2 &a1, d2 &a2, d2 &a3, d2 v, d2 v2, d2 v3) {
+    const d2 b1 = cmul(a1, v), b2 = cmul(a2, v2), b3 = cmul(a3, v3);
+    const d2 s = a0 + b2, d = a0 - b2, e = b1 + b3, f = b1 - b3;
+    a0 = s + e;
+    a1 = s - e;
+    a2.x = d.x - f.y; a2.y = d.y + f.x;
+    a3.x = d.x + f.y; a3.y = d.y - f.x;
+}
+
 // inverse half-sizes 1, 2, 4: constant twiddles
 #define FFT_SQRT_HALF 0.70710678118654752440
 __device__ __forceinline__ void inv8(d2 *s) {

@@ -1,4 +1,4 @@
-// Host-side pieces shared by the fused blind-rotation kernels (N = 512, 1024, 4096): the argument fields every one
+// Host-side pieces shared by the fused blind-rotation kernels (N = 512, 1024): the argument fields every one
 // of them takes, the worst-case bound check of their fixed reduction schedules, and the launch shape.
 #pragma once
 #include "slz_internal.h"
@@ -34,15 +34,13 @@ static inline void slz_fused_fill_io(slz_fused_io &A, const slz_ctx *ctx, const 
 
 // The reduction schedule all fused kernels share, as stage counts (bounds in units of p; every value must stay below
 // 2^53 = 8 p, taken as 7.5 p):
-//   forward: `pre` stages across blocks on the digits (N = 4096: 1), `fwd_a` stages, one full reduction, `fwd_b` stages;
+//   forward: `fwd_a` stages on the digits, one full reduction, `fwd_b` stages;
 //   products: `summed` products of a forward output with a key word are added before the next reduction;
-//   inverse: two multiply-free stages (each doubles the bound), `inv_a` stages, one full reduction, `inv_b` stages, then
-//   `post_mul` further multiplies (twist; N = 4096: reduction, stage across the blocks, twist), after which the CRT lift
-//   needs |r| < 1.95 p.
-static inline bool slz_fused_schedule_ok(int pre, int fwd_a, int fwd_b, int summed, int inv_a, int inv_b, bool reduce_before_post,
-                                         int post_mul) {
+//   inverse: two multiply-free stages (each doubles the bound), `inv_a` stages, one full reduction, `inv_b` stages, then the twist,
+//   after which the CRT lift needs |r| < 1.95 p.
+static inline bool slz_fused_schedule_ok(int fwd_a, int fwd_b, int summed, int inv_a, int inv_b) {
     double a = 1e-6;
-    for (int s = 0; s < pre + fwd_a; s++) a += slz_mulmod_bound(a);
+    for (int s = 0; s < fwd_a; s++) a += slz_mulmod_bound(a);
     if (a > 7.5) return false;
     a = 0.5 + 1e-9;
     for (int s = 0; s < fwd_b; s++) a += slz_mulmod_bound(a);
@@ -52,10 +50,7 @@ static inline bool slz_fused_schedule_ok(int pre, int fwd_a, int fwd_b, int summ
     if (a > 7.5) return false;
     a = 0.5 + 1e-9;
     for (int s = 0; s < inv_b; s++) a += slz_mulmod_bound(a);
-    if (a > 7.5) return false;
-    if (reduce_before_post) a = 0.5 + 1e-9;
-    for (int s = 0; s + 1 < post_mul; s++) a += slz_mulmod_bound(a);
-    return slz_mulmod_bound(a) <= 1.95;
+    return a <= 7.5 && slz_mulmod_bound(a) <= 1.95;
 }
 
 // Persistent grid: one workgroup per ciphertext up to what is resident at `per_cu` workgroups per compute unit.

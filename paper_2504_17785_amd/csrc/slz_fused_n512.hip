@@ -410,7 +410,7 @@ static int build_pair_tables(slz_ctx *ctx, double **dA, double **dB) {
 int slz_fused512_init(slz_ctx *ctx) {
     // five forward stages on the digits, reduction, four more; four products summed (k = 3); inverse 2 + 2 stages,
     // reduction, five stages, twist
-    if (!slz_fused_schedule_ok(0, 5, 4, 4, 2, 5, false, 1)) return SLZ_E_UNSUPPORTED;
+    if (!slz_fused_schedule_ok(5, 4, 4, 2, 5)) return SLZ_E_UNSUPPORTED;
     int rc = build_pair_tables(ctx, &ctx->fused512_rowA, &ctx->fused512_rowB);
     if (rc != SLZ_OK) return rc;
     rc = slz_fused_load_inv_scalars(ctx);

@@ -40,10 +40,6 @@ struct slz_ctx {
     uint32_t max_batch;
     int device;
     int force_generic;
-    int has_fused4096;        // the N = 4096 fused kernel is available
-    double *fused4096_rowA, *fused4096_rowB;   // its block tables: [2][2][64] and [2][2][31][64]
-    double fused4096_scalars[2][128];          // host copy of fused4096_rowA (lane-uniform entries go into the kernel arguments)
-    double fused4096_w1[2];                    // fwd[1] per prime: the twiddle of the stage across the two blocks
     int has_fused512;         // the N = 512 fused kernel is available
     double *fused512_rowA, *fused512_rowB;     // its forward tables: [2][64] and [2][15][64]
     int has_fused1024;        // the N = 1024 fused kernel is available
@@ -54,7 +50,7 @@ struct slz_ctx {
     double p1inv_mod_p2;      // p1^{-1} mod p2 (centred)
     slz_tables tab[2];
     double fused_scalars[2][32];      // [prime]: the lane-uniform inverse twiddles of the fused kernels
-    int has_fft;              // N = 512, 1024 or 2048 through floating-point transforms: the error bound holds for this parameter set
+    int has_fft;              // N = 512, 1024, 2048 or 4096 through floating-point transforms: the error bound holds for this parameter set
     void *fft_tab;            // its tables (slz_fft.h)
     double *fft_prep_tab;     // double-double twiddles of the key preparation
     double fft_f1[15][2];     // host copy of its lane-uniform twiddles
@@ -100,13 +96,6 @@ int slz_generic_bsk_prepare(slz_ctx *ctx, const uint64_t *bsk, double *dst, hipS
 int slz_generic_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx,
                              const double *bskp, uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out,
                              uint32_t batch, hipStream_t s);
-// fused path for N = 4096 (slz_fused_n4096.hip)
-int slz_fused4096_supported(const slz_params *p);
-int slz_fused4096_init(slz_ctx *ctx);
-void slz_fused4096_destroy(slz_ctx *ctx);
-int slz_fused4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx,
-                               const double *bskp, uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch,
-                               hipStream_t s);
 // fused path for N = 512 (slz_fused_n512.hip)
 int slz_fused512_supported(const slz_params *p);
 int slz_fused512_init(slz_ctx *ctx);
@@ -125,14 +114,16 @@ int slz_fused1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint6
 // *dA [2][N/BS][64], *dB [2][N/BS][BS/64 - 1][64], device memory owned by the caller
 int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, bool inverse, double **dA, double **dB);
 
-// floating-point transforms for N = 512 (l = 2), 1024 and 2048 (slz_fft.hip: tables and key; slz_fft512.hip, slz_fft1024.hip,
-// slz_fft2048.hip: kernels); their key form follows the
+// floating-point transforms for N = 512 (l = 2), 1024, 2048 and 4096 (slz_fft.hip: tables and key; slz_fft512.hip, slz_fft1024.hip,
+// slz_fft2048.hip, slz_fft4096.hip: kernels); their key form follows the
 // residue form of every prepared key
 int slz_fft_supported(const slz_params *p);
 int slz_fft_init(slz_ctx *ctx);
 void slz_fft_destroy(slz_ctx *ctx);
 size_t slz_fft_key_bytes(const slz_params *p);
 int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s);
+int slz_fft4096_supported(const slz_params *p);
+int slz_fft4096_setup();
 int slz_fft2048_setup();
 int slz_fft1024_setup();
 int slz_fft512_setup();
@@ -141,6 +132,8 @@ int slz_fft512_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t
 int slz_fft1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
 int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                             uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+int slz_fft4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
 // large-N path (slz_bign.hip)
 int slz_bign_supported(const slz_params *p);

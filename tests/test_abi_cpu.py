@@ -206,6 +206,26 @@ def test_transform_error_bound_and_the_bases_it_admits():
         assert not supported(ctypes.byref(slz.make_params(q))), kw
 
 
+def test_transform_error_bound_of_n4096():
+    # N = 4096: forward a radix-2 layer on integers with the constant sqrt(1/2), radix 4, radix 8 twice (product, two additions, an addition
+    # whose odd part is a sum times the constant), radix 4; inverse 1, 2, 4, then radix 4 and radix 2 twice, 512, 1024 and the turn
+    L = slz.lib()
+    bound, supported = L._Z19slz_fft_error_boundjjj, L._Z21slz_fft4096_supportedPK10slz_params
+    bound.argtypes, bound.restype = [ctypes.c_uint32] * 3, ctypes.c_double
+    table, half = 26 * 2.0 ** -11, 0.5 ** 0.5
+    root = decimal.Context(prec=40).sqrt(decimal.Decimal("0.5"))
+    constant = float(abs(decimal.Decimal(half) / root - 1)) * 2.0 ** 53
+    radix4, radix8, radix2 = 4 + half + table, 2 + half + table + 2 + 2 + constant, 4 + table
+    units = 1 + constant + 2 * radix4 + 2 * radix8 + 3 + 1.05 + 2 + (2 + constant) + 2 * (radix4 + radix2) + 2 * radix2 + 1 + constant
+    for beta in range(1, 24):
+        want = units * 2.0 ** -53 * 2 * 4096 * 2.0 ** (beta - 1) * 2.0 ** 12
+        assert want <= bound(4096, 2, beta) <= 1.01 * want, beta
+        q = synth.CONFIGS[2].with_(N=4096, pbs_base_log=beta)
+        assert bool(supported(ctypes.byref(slz.make_params(q)))) == (want < 0.499) == (beta <= 22), beta
+    for kw in (dict(N=4096, pbs_level=2), dict(N=4096, k=2), dict(N=2048), dict(N=8192)):
+        assert not supported(ctypes.byref(slz.make_params(synth.CONFIGS[2].with_(pbs_base_log=8, **kw)))), kw
+
+
 @pytest.mark.parametrize("G,half", [(2, 512), (4, 256), (8, 128), (16, 64), (32, 32)])
 def test_large_n_lanes_are_cut_where_it_wins_and_keep_the_order_of_the_row_pass(G, half):
     # an internal host function, by its mangled name: ciphertexts of the first lane for a batch past half / 2, 0: not even

@@ -81,6 +81,44 @@ def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch
     assert np.array_equal(slz.to_host_u64(out)[sample], orc.pbs_batch(p, cts[sample], luts, idx[sample], bsk))
 
 
+# N = 4096: one ciphertext, all workgroups busy, a second round for one and for 44 of them; the largest base a context takes is 2^22
+@pytest.mark.parametrize("batch,beta,extreme", [(1, 22, False), (5, 22, True), (256, 1, False), (257, 22, True), (300, 13, True)])
+def test_fft4096_states_and_outputs_match_generic_path_and_oracle(slz, orc, batch, beta, extreme):
+    N, n = 4096, 2
+    p = synth.CONFIGS[2].with_(name="fft", N=N, n=n, pbs_base_log=beta, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", n * 4 * N)
+    luts = synth.raw_words(p, "misc", 2 * N).reshape(2, N)
+    cts = synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1)
+    if extreme:                                 # as above: pieces of the largest magnitude, digits at the ends, rotations by N
+        bsk[:2 * N] = np.uint64(0x7FFF7FFBFFDFFEFF)
+        bsk[2 * N:4 * N:2] = np.uint64(1 << 63)
+        bsk[4 * N:8 * N:3] = np.uint64(0xF001800C00600300)
+        luts[0] = np.uint64(1 << 62)
+        luts[1, 0::2] = np.uint64((1 << 63) - (1 << (63 - beta)))
+        luts[1, 1::2] = np.uint64(1 << 63)
+        cts[0::3] = np.uint64(1 << 63)
+        cts[1::3, 0] = np.uint64(1 << 63)
+    idx = (np.arange(batch) % 2).astype(np.uint32)
+    ctx = slz.Context(p, batch)
+    assert ctx.path == "fused_n4096"
+    assert ctx.bsk_prepared_bytes() == n * 2 * 4 * N * 8 + n * 5 * 4 * 8 * 4 * 64 * 16
+    bsk = bsk.reshape(n, 2, 1, 2, N)
+    d = [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy(idx.astype(np.int32)).cuda(), ctx.bsk_prepare(slz.to_device_u64(bsk))]
+    sample = np.unique(np.minimum([0, 1, 2, 255, 256, batch - 1], batch - 1))
+    got = {s: ctx.blind_rotate_batch(*d, s) for s in (0, 1, n)}
+    out, out0 = ctx.pbs_batch(*d), ctx.pbs_batch(d[0], d[1], None, d[3])
+    other = d[3].clone()
+    other[:bsk.size * 2] = 0                    # without the residue form: the transform kernel ran
+    assert torch.equal(ctx.pbs_batch(*d[:3], other), out)
+    ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)
+    for s, acc in got.items():
+        assert torch.equal(acc, ctx.blind_rotate_batch(*d, s)), s
+    want = orc.blind_rotate_batch(p, cts[sample], luts, idx[sample], bsk, n)
+    assert np.array_equal(slz.to_host_u64(got[n])[sample], want)
+    assert torch.equal(out, ctx.pbs_batch(*d))
+    assert torch.equal(out0, ctx.pbs_batch(d[0], d[1], None, d[3]))
+
+
 # N = 16384: one lane up to 32 ciphertexts, two even halves from 33 to 128, halves of 64 past that.  N = 8192: even lanes from 65 to 160
 # and from 208 to 256, a lane of 128 and the rest in between; N = 4096: even lanes from 129 to 320, then a lane of 256 and the rest.
 @pytest.mark.parametrize("N,batch", [(16384, 32), (16384, 33), (16384, 49), (16384, 128), (16384, 129), (8192, 66), (8192, 67), (8192, 161),
