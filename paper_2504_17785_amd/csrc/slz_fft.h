@@ -27,7 +27,17 @@
 #define FFT_LDS_TAB (FFT_I3_OFF + FFT_I3_LEN)          // everything up to here is staged in LDS
 #define FFT_F3_OFF FFT_LDS_TAB
 #define FFT_F3_LEN (2u * 6u * 64u)
-#define FFT_TAB_LEN (FFT_F3_OFF + FFT_F3_LEN)
+// eight waves per ciphertext (slz_fft2048_team.hip), offsets from FFT_T_OFF:
+//   T2 [3][4]        inverse half-sizes 4 and 8 as one radix-4 layer (v, v^2, v^3), by the two lowest position bits
+//   T3 [2][16], T4 [2][64]   half-sizes 16, 32 and 64, 128 as (cos, tan), by the four and six lowest position bits
+//   T5 [5][256]      256 as (cos, tan); 512: two (c1, c2) pairs as above
+#define FFT_T_OFF (FFT_F3_OFF + FFT_F3_LEN)
+#define FFT_T2_OFF 0u
+#define FFT_T3_OFF 12u
+#define FFT_T4_OFF 44u
+#define FFT_T5_OFF 172u
+#define FFT_T_LEN (FFT_T5_OFF + 5u * 256u)
+#define FFT_TAB_LEN (FFT_T_OFF + FFT_T_LEN)
 
 // complex entries of the transform-domain key of one step: [piece][half g][k][row, component][lane]
 #define FFT_KEY_STEP (SLZ_FFT_PIECES * 2u * 8u * 4u * 64u)

@@ -112,6 +112,22 @@ static void build_2048(std::vector<cpl> &t, double (&f1_out)[15][2]) {
             o[64 * (4 + 2 * q)] = cos_tan(-j / (2 * M) - j / 512);
         }
     }
+    cpl *tt = &t[FFT_T_OFF];                                        // eight waves per ciphertext
+    for (uint32_t l = 0; l < 4; l++)
+        for (uint32_t q = 0; q < 3; q++) tt[FFT_T2_OFF + 4 * q + l] = unit(-(long double)((q + 1) * l) / 8);
+    for (uint32_t q = 0; q < 2; q++) {
+        for (uint32_t l = 0; l < 16; l++) tt[FFT_T3_OFF + 16 * q + l] = cos_tan(-(long double)l / (16 << q));
+        for (uint32_t l = 0; l < 64; l++) tt[FFT_T4_OFF + 64 * q + l] = cos_tan(-(long double)l / (64 << q));
+    }
+    for (uint32_t l = 0; l < 256; l++) {
+        cpl *o = tt + FFT_T5_OFF + l;
+        o[0] = cos_tan(-(long double)l / 256);
+        for (uint32_t q = 0; q < 2; q++) {
+            const long double j = 256 * q + l;
+            o[256 * (1 + 2 * q)] = unit(-j / (2 * M));
+            o[256 * (2 + 2 * q)] = cos_tan(-j / (2 * M) - j / 512);
+        }
+    }
     cpl f1[15];
     three(f1, 1, 1, 0);
     for (uint32_t q = 0; q < 4; q++) three(f1 + 3 + 3 * q, 1, 4, q);

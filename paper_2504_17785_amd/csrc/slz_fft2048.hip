@@ -27,8 +27,7 @@
 // Two waves hide little of each other's LDS round trips, so loads are requested in groups ahead of the arithmetic, and results are
 // written while the next ones are computed.  Measured with 742 steps (in brackets: two residues on the same card): 1024 ciphertexts
 // 20.2 ms (31.5), 4096: 80.6 (126.6), 301: 12.9 (15.4).
-// Batches up to 256 leave three of a compute unit's four pairs idle, and a pair alone needs 12.9 ms; there all four work on one
-// ciphertext (WIDE): 256 ciphertexts 8.2 ms (9.7 with residues), one 8.9 ms (9.5).
+// Batches up to 256 go to slz_fft2048_team.hip.  From 257 to 512 a compute unit has two ciphertexts; two pairs work on each (SHARE = 2).
 #include "slz_fft.h"
 #include "slz_fft_wave.h"
 #include "slz_modarith.h"
@@ -36,14 +35,14 @@
 
 #define FFT_WAVES 8                                 // waves per workgroup: four ciphertexts share one copy of the tables
 #define FFT_PAIRS (FFT_WAVES / 2)
-#define FFT_WIDE_MAX 256                            // batches up to this take the shared form, one workgroup per ciphertext
+#define FFT_TEAM_MAX 256                            // batches up to this: slz_fft2048_team.hip; up to twice this: two pairs per ciphertext
 #define FFT_THREADS (64 * FFT_WAVES)
 #define FFT_BUF (4u * 272u * 16u)                   // bytes of a wave's exchange buffer: 1024 points, padded
 #define FFT_EARLY 4                                 // positions (of four key words each) requested during the last inverse stage: each of its
                                                     // eight butterflies frees the registers of half a position
 #define FFT_RING 4                                  // positions in registers at a time during the products
 #define FFT_FLAGS_OFF (FFT_WAVES * FFT_BUF + FFT_LDS_TAB * 16u)
-#define FFT_FLAGS 34u                               // done and free per wave; for WIDE: spectra written (2), read (8), sums written (8)
+#define FFT_FLAGS 40u                               // per wave: done and free; for shared ciphertexts also spectra written, read, sums written
 #define FFT_LDS_BYTES (FFT_FLAGS_OFF + 4u * FFT_FLAGS)
 
 struct fft_args {
@@ -58,12 +57,12 @@ struct fft_args {
     double f1[15][2];         // lane-uniform twiddles of the first two forward layers: (v, v^2, v^3) of block 0 and of the next four blocks
 };
 
-// WIDE = false: a workgroup's four pairs of waves take a ciphertext each.  WIDE = true, for batches of at most one ciphertext per
-// compute unit: all four pairs work on one.  Pair 0 owns the accumulator and runs step 1 and the forward transform; every pair reads
-// the spectra from pair 0's exchange buffers and takes one or two of the key pieces (its first piece's key words wait in registers
-// by then); the sums of the other pairs come back through their exchange buffers.
+// SHARE = 1: a workgroup's four pairs of waves take a ciphertext each.  SHARE = 2, for batches of at most two ciphertexts per
+// compute unit: two pairs work on each.  One owns the accumulator, runs step 1, the forward transform and two key pieces; the other
+// reads the spectra from the owner's exchange buffers and takes three pieces (its first piece's key words wait in registers by then); its sums
+// come back through its exchange buffers.  The owners of a workgroup's two ciphertexts sit on different SIMDs.
 // The base is an argument: an instance with 23 as a constant measured the same (256 ciphertexts 8.28 ms, 301: 12.95, 1024: 20.2).
-template <bool WIDE>
+template <int SHARE>
 __global__ void __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_fft_blind_rotate(fft_args A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -71,25 +70,29 @@ k_fft_blind_rotate(fft_args A) {
     const uint32_t beta = A.beta;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t h = wave & 1u, pair = wave >> 1;
+    constexpr bool SHARED = SHARE == 2;
+    constexpr uint32_t GROUPS = FFT_PAIRS / SHARE;                    // ciphertexts of a workgroup at a time
+    const uint32_t h = wave & 1u, pair = wave >> 1, group = pair / SHARE;
     const uint32_t T0 = lds + wave * FFT_BUF, Tp0 = lds + (wave & ~1u) * FFT_BUF;   // buffer of component h; of both components
     const uint32_t tab0 = lds + FFT_WAVES * FFT_BUF;
     const uint32_t flags = lds + FFT_FLAGS_OFF;
     const uint32_t my_done = flags + 4u * wave, my_free = my_done + 32u, his_done = flags + 4u * (wave ^ 1u), his_free = his_done + 32u;
     for (uint32_t i = threadIdx.x; i < FFT_LDS_TAB; i += FFT_THREADS) lds_put(tab0 + 16u * i, A.tab[i]);
     if (threadIdx.x < FFT_FLAGS) *(LDS_AS uint32_t *)(uintptr_t)(flags + 4u * threadIdx.x) = 0;
-    const uint32_t spectra_done = flags + 64u, spectra_read = flags + 72u, sums_done = flags + 104u;     // WIDE: counted in steps
+    // SHARE = 2, counted in steps: spectra written (per owner wave), spectra read, sums written (per wave of the group)
+    const uint32_t own = 6u * group;                                  // first wave of this group's owner pair
+    const uint32_t spectra_done = flags + 64u + 4u * own, spectra_read = flags + 96u + 8u * SHARE * group, sums_done = flags + 128u;
     __syncthreads();
 
     const double magic = 6755399441055744.0;                          // 1.5 * 2^52: adding it rounds to an integer
     uint32_t seq = 0;                                                 // exchanges of this pair so far
-    uint32_t tick = 0;                                                // WIDE: steps so far
-    // One loop per kind of wave, so that each keeps only its own values in registers.  ROLE: pair number, or FFT_PAIRS when the pair has
-    // the ciphertext to itself.
+    uint32_t tick = 0;                                                // SHARE = 2: steps so far
+    // One loop per kind of wave, so that each keeps only its own values in registers.  ROLE 0: owner, 1: helper, 2: the pair has the
+    // ciphertext to itself.
     auto rotate = [&](auto role) __attribute__((always_inline)) {
         constexpr int ROLE = decltype(role)::value;
-        constexpr bool owner = ROLE == 0 || ROLE == FFT_PAIRS;
-        for (uint32_t c = WIDE ? blockIdx.x : blockIdx.x + pair * gridDim.x; c < A.batch; c += (WIDE ? 1u : FFT_PAIRS) * gridDim.x) {
+        constexpr bool owner = ROLE != 1;
+        for (uint32_t c = blockIdx.x + group * gridDim.x; c < A.batch; c += GROUPS * gridDim.x) {
             const uint64_t *lwe = A.lwe_in + (size_t)c * (A.n + 1);
             uint64_t accr[16], acci[16];                                  // negated coefficients 64 e + lane and 1024 + 64 e + lane of component h
             const uint32_t li = fresh(lane);
@@ -124,7 +127,7 @@ k_fft_blind_rotate(fft_args A) {
                 asm volatile("s_mov_b32 %0, 0" : "=s"(z));
                 uint32_t T = T0 + z;
                 tick++;
-                if (!WIDE) {
+                if (!SHARED) {
                     // The SIMD serves its older wave first, which would let half of the ciphertexts of a compute unit run ahead and leave
                     // the SIMDs half empty at the end: of the two waves on a SIMD the one that is behind gets the priority.
                     if ((int32_t)(seq - (uint32_t)__builtin_amdgcn_readfirstlane(fft_peek(flags + 4u * (wave ^ 4u)))) > 0) __builtin_amdgcn_s_setprio(0);
@@ -219,8 +222,8 @@ k_fft_blind_rotate(fft_args A) {
                             for (int i = 4 * q; i < 4 * q + 4; i++)
                                 lds_put(o + 16 * 17 * (((i >> 3) & 1) * 8 + (i & 1) * 4 + ((i >> 2) & 1) * 2 + ((i >> 1) & 1)), x[i]);
                         }
-                        if (WIDE) {
-                            fft_signal(spectra_done + 4u * wave, tick);
+                        if (SHARED) {
+                            fft_signal(spectra_done + 4u * h, tick);
                         } else {
                             seq++;
                             fft_signal(my_done, seq);
@@ -235,7 +238,7 @@ k_fft_blind_rotate(fft_args A) {
                     for (int q = 0; q < 6; q++) f3[q] = lane_get(tabF3 + 64 * q, kl);
                     // key words of the first positions are requested one phase ahead of their use, here and at the end of every piece
                     if constexpr (!owner) {
-                        kp += ROLE * 4096u;                               // pairs 1, 2, 3 begin with pieces 1, 2, 3
+                        kp += 2u * 4096u;                                 // the helper begins with piece 2
 #pragma unroll
                         for (int k = 0; k < 8; k++) request(k);
                     } else {
@@ -243,19 +246,19 @@ k_fft_blind_rotate(fft_args A) {
                         for (int k = 0; k < FFT_EARLY; k++) request(k);
                     }
                     FFT_FENCE();
-                    if (WIDE) {
+                    if (SHARED) {
                         fft_wait(spectra_done, fft_peek(spectra_done), tick);
                         fft_wait(spectra_done + 4u, fft_peek(spectra_done + 4u), tick);
                     } else {
                         fft_wait(his_done, fft_peek(his_done), seq);
                     }
                     const uint32_t lr = fresh(lane);                                                        // b8 b7 b6 b5 b4 b3
-                    const uint32_t rd = (WIDE ? lds : Tp0) + z + h * 8704u + (lr >> 5) * 4352u + ((lr >> 2) & 1u) * 2176u + (lr & 3u) * 272u + ((lr >> 3) & 3u) * 64u;
+                    const uint32_t rd = (SHARED ? lds + own * FFT_BUF : Tp0) + z + h * 8704u + (lr >> 5) * 4352u + ((lr >> 2) & 1u) * 2176u + (lr & 3u) * 272u + ((lr >> 3) & 3u) * 64u;
 #pragma unroll
                     for (int cc = 0; cc < 2; cc++)
 #pragma unroll
                         for (int k = 0; k < 8; k++) D[cc][k] = lds_get(rd + cc * FFT_BUF + 16 * (68 * (k >> 2) + (k & 3)));
-                    if (WIDE) fft_signal(spectra_read + 4u * wave, tick);
+                    if (SHARED) fft_signal(spectra_read + 4u * (wave % (2u * SHARE)), tick);
                     else fft_signal(my_free, seq);
 #pragma unroll
                     for (int cc = 0; cc < 2; cc++)
@@ -293,9 +296,9 @@ k_fft_blind_rotate(fft_args A) {
 #pragma unroll
                     for (int k = 0; k < 8; k++) pin(S[0][k]);
                     fft_wait(his_free, free_seen, seq);                  // the other wave has read the previous exchange
-                    if (WIDE && piece == 0) {                            // pair 0 writes where all eight waves read the spectra
+                    if (SHARED && piece == 0) {                            // the owner writes where all waves of the group read the spectra
 #pragma unroll
-                        for (uint32_t q = 0; q < FFT_WAVES; q++) fft_wait(spectra_read + 4u * q, fft_peek(spectra_read + 4u * q), tick);
+                        for (uint32_t q = 0; q < 2 * SHARE; q++) fft_wait(spectra_read + 4u * q, fft_peek(spectra_read + 4u * q), tick);
                     }
                     {
                         const uint32_t ln = fresh(lane);                                                    // b8 b7 b6 b5 b4 b3
@@ -394,7 +397,7 @@ k_fft_blind_rotate(fft_args A) {
                                 accr[e + 8] -= 0x4338000000000000ull; acci[e + 8] -= 0x4338000000000000ull;
                             }
                             pin(accr[e]); pin(acci[e]); pin(accr[e + 8]); pin(acci[e + 8]);
-                            if (!WIDE && next < 0) { stage(e); stage(e + 8); }
+                            if (!SHARED && next < 0) { stage(e); stage(e + 8); }
                             if (next >= 0) {
                                 FFT_FENCE();
 #pragma unroll
@@ -407,29 +410,28 @@ k_fft_blind_rotate(fft_args A) {
                 fft_int<FFT_EARLY> first;
                 fft_int<8> all;
                 fft_int<-1> none;
-                if constexpr (!WIDE) {
+                if constexpr (!SHARED) {
                     run_piece(fft_int<0>(), first, fft_int<1>());
                     run_piece(fft_int<1>(), first, fft_int<2>());
                     run_piece(fft_int<2>(), first, fft_int<3>());
                     run_piece(fft_int<3>(), first, fft_int<4>());
                     run_piece(fft_int<4>(), first, none);
                 } else if constexpr (owner) {
-                    run_piece(fft_int<0>(), first, none);
-#pragma unroll 1
-                    for (uint32_t q = 1; q < FFT_PAIRS; q++) {
-                        const uint32_t flag = sums_done + 4u * (2 * q + h);
-                        fft_wait(flag, fft_peek(flag), tick);
-                        const LDS_AS uint64_t *S = (const LDS_AS uint64_t *)(uintptr_t)(T + 2u * q * FFT_BUF);
+                    run_piece(fft_int<0>(), first, fft_int<1>());
+                    run_piece(fft_int<1>(), first, none);
+                    const uint32_t flag = sums_done + 4u * (wave ^ 2u);
+                    fft_wait(flag, fft_peek(flag), tick);
+                    const LDS_AS uint64_t *S = (const LDS_AS uint64_t *)(uintptr_t)(lds + z + (wave ^ 2u) * FFT_BUF);
 #pragma unroll
-                        for (int e = 0; e < 16; e++) { accr[e] += S[64 * e + lane]; acci[e] += S[1024 + 64 * e + lane]; }
-                    }
+                    for (int e = 0; e < 16; e++) { accr[e] += S[64 * e + lane]; acci[e] += S[1024 + 64 * e + lane]; }
 #pragma unroll
                     for (int e = 0; e < 16; e++) stage(e);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 16; e++) accr[e] = acci[e] = 0;
-                    if constexpr (ROLE < 3) run_piece(fft_int<ROLE>(), all, none);
-                    else { run_piece(fft_int<3>(), all, fft_int<4>()); run_piece(fft_int<4>(), first, none); }
+                    run_piece(fft_int<2>(), all, fft_int<3>());
+                    run_piece(fft_int<3>(), first, fft_int<4>());
+                    run_piece(fft_int<4>(), first, none);
                     LDS_AS uint64_t *S = (LDS_AS uint64_t *)(uintptr_t)T;
 #pragma unroll
                     for (int e = 0; e < 16; e++) { S[64 * e + lane] = accr[e]; S[1024 + 64 * e + lane] = acci[e]; }
@@ -460,23 +462,24 @@ k_fft_blind_rotate(fft_args A) {
             }
         }
     };
-    if constexpr (!WIDE) rotate(fft_int<FFT_PAIRS>());
-    else if (pair == 0) rotate(fft_int<0>());
-    else if (pair == 1) rotate(fft_int<1>());
-    else if (pair == 2) rotate(fft_int<2>());
-    else rotate(fft_int<3>());
+    if constexpr (!SHARED) rotate(fft_int<2>());
+    else if ((pair & 1u) == group) rotate(fft_int<0>());
+    else rotate(fft_int<1>());
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------------
 
 int slz_fft2048_setup() {
-    const void *const kernels[2] = {(const void *)k_fft_blind_rotate<false>, (const void *)k_fft_blind_rotate<true>};
+    const void *const kernels[] = {(const void *)k_fft_blind_rotate<1>, (const void *)k_fft_blind_rotate<2>};
     for (const void *k : kernels) SLZ_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
-    return SLZ_OK;
+    return slz_fft2048_team_setup();
 }
 
 int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
+    // Up to one ciphertext per compute unit its eight waves take one together (742 steps: one 7.2 ms against 8.5 with two pairs on it, 256
+    // 8.3 against 8.6); from 257 on that needs a second round (301: 14.6 ms against 12.4).
+    if (batch <= FFT_TEAM_MAX) return slz_fft2048_team(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);
     fft_args A;
     A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;
     A.acc_out = acc_out; A.lwe_out = lwe_out;
@@ -485,10 +488,9 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
     const uint32_t grid = slz_fused_grid(batch, 1);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(FFT_THREADS), FFT_LDS_BYTES, s, A); };
-    // Up to one ciphertext per compute unit, its four pairs share the ciphertext's work: 8.2 ms for 256 ciphertexts and 742 steps,
-    // 12.9 ms with a pair for each.  From 257 on, the shared form needs a second round: 17.1 ms against 12.9 ms.
-    if (batch <= FFT_WIDE_MAX) launch(k_fft_blind_rotate<true>);
-    else launch(k_fft_blind_rotate<false>);
+    // From 257 to 512 ciphertexts two pairs share each: 301 12.4 ms against 12.9 with a pair for each (512: 12.5 and 13.1).
+    if (batch <= 2 * FFT_TEAM_MAX) launch(k_fft_blind_rotate<2>);
+    else launch(k_fft_blind_rotate<1>);
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;
 }

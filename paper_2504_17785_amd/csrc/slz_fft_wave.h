@@ -43,6 +43,16 @@ __device__ __forceinline__ void fwd2i(d2 &a, d2 &b, d2 ct) {
     a.x = __builtin_fma(ct.x, vr, a.x);
     a.y = __builtin_fma(ct.x, vi, a.y);
 }
+// inverse radix-4: half-sizes t and 2 t over (a0, a1, a2, a3) with v the twiddle of half-size 2 t and its powers
+__device__ __forceinline__ void inv4(d2 &a0, d2 &a1, d2 &a2, d2 &a3, d2 v, d2 v2, d2 v3) {
+    const d2 b1 = cmul(a1, v2), b2 = cmul(a2, v), b3 = cmul(a3, v3);
+    const d2 s = a0 + b1, d = a0 - b1, e = b2 + b3, f = b2 - b3;
+    a0 = s + e;
+    a2 = s - e;
+    a1.x = d.x + f.y; a1.y = d.y - f.x;
+    a3.x = d.x - f.y; a3.y = d.y + f.x;
+}
+
 // a +- b and a -+ i b
 __device__ __forceinline__ void add2(d2 &a, d2 &b) { const d2 t = b; b = a - t; a = a + t; }
 __device__ __forceinline__ void add2i(d2 &a, d2 &b) {                 // b <- a + i b, a <- a - i b  (twiddle -i)
@@ -115,6 +125,18 @@ __device__ __forceinline__ void fft_wait(uint32_t flag, uint32_t seen, uint32_t 
     while ((int32_t)((uint32_t)__builtin_amdgcn_readfirstlane(seen) - value) < 0) {
         __builtin_amdgcn_s_sleep(1);
         seen = fft_peek(flag);
+    }
+    asm volatile("" ::: "memory");
+}
+
+// Counters of the four waves of a component from `flags` on, one read for all of them.  As in fft_wait, every wave of the workgroup is
+// resident and takes the same sequence of exchanges, so every wait ends.
+__device__ __forceinline__ uint32_t peek_four(uint32_t flags, uint32_t lane) { return fft_peek(flags + 4u * (lane & 3u)); }
+__device__ __forceinline__ void wait_four(uint32_t flags, uint32_t lane, uint32_t seen, uint32_t value) {
+    asm volatile("" ::: "memory");
+    while (__builtin_amdgcn_ballot_w64((int32_t)(seen - value) < 0)) {
+        __builtin_amdgcn_s_sleep(1);
+        seen = peek_four(flags, lane);
     }
     asm volatile("" ::: "memory");
 }

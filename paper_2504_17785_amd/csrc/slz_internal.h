@@ -125,6 +125,9 @@ int slz_fft_prepare(slz_ctx *ctx, const uint64_t *bsk, void *dst, hipStream_t s)
 int slz_fft4096_supported(const slz_params *p);
 int slz_fft4096_setup();
 int slz_fft2048_setup();
+int slz_fft2048_team_setup();
+int slz_fft2048_team(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
 int slz_fft1024_setup();
 int slz_fft512_setup();
 int slz_fft512_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,

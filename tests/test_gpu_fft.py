@@ -81,6 +81,15 @@ def test_fft_states_and_outputs_match_generic_path_and_oracle(slz, orc, N, batch
     assert np.array_equal(slz.to_host_u64(out)[sample], orc.pbs_batch(p, cts[sample], luts, idx[sample], bsk))
 
 
+# N = 2048, 200 and 256 ciphertexts with eight waves on each, 257, 511 and 512 with four (an odd count leaves one half of a workgroup
+# idle), 513 with two: a ciphertext's result does not depend on which
+def test_fft2048_forms_agree(slz):
+    p, ctx, bsk, luts, cts, idx, d = _inputs(slz, 513, 23, n=4)
+    want = ctx.blind_rotate_batch(*d, p.n)
+    for count in (512, 511, 257, 256, 200, 1):
+        assert torch.equal(ctx.blind_rotate_batch(d[0][:count], d[1], d[2][:count], d[3], p.n), want[:count]), count
+
+
 # N = 4096: one ciphertext, all workgroups busy, a second round for one and for 44 of them; the largest base a context takes is 2^22
 @pytest.mark.parametrize("batch,beta,extreme", [(1, 22, False), (5, 22, True), (256, 1, False), (257, 22, True), (300, 13, True)])
 def test_fft4096_states_and_outputs_match_generic_path_and_oracle(slz, orc, batch, beta, extreme):
