@@ -90,7 +90,8 @@ k_keyswitch(const uint64_t *__restrict__ lwe_in, const uint64_t *__restrict__ ks
     }
 }
 
-void slz_ks_init_launch(const uint64_t *lwe_in, uint64_t *lwe_out, uint32_t kN, uint32_t n, uint32_t batch, hipStream_t s) {
+// out = (0, .., 0, b') for every ciphertext
+static void ks_init_launch(const uint64_t *lwe_in, uint64_t *lwe_out, uint32_t kN, uint32_t n, uint32_t batch, hipStream_t s) {
     const size_t total = (size_t)batch * (n + 1);
     hipLaunchKernelGGL(k_ks_init, dim3((unsigned)((total + KS_THREADS - 1) / KS_THREADS)), dim3(KS_THREADS), 0, s, lwe_in, lwe_out,
                        kN, n, batch);
@@ -110,7 +111,7 @@ int slz_keyswitch_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *k
         int rc = slz_ksm_launch(ctx, lwe_in, ksk, nullptr, lwe_out, batch, s);
         if (rc != SLZ_E_UNSUPPORTED) return rc;
     }
-    slz_ks_init_launch(lwe_in, lwe_out, kN, n, batch, s);
+    ks_init_launch(lwe_in, lwe_out, kN, n, batch, s);
     uint32_t xt = (n + 1 + KS_THREADS - 1) / KS_THREADS, ct = (batch + KS_TB - 1) / KS_TB;
     // enough segments of the mask index to give the 256 CUs several workgroups each
     uint32_t segs = 1;

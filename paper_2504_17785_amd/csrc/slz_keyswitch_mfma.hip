@@ -26,12 +26,14 @@
 // A workgroup takes 32 ciphertexts x 128 mask words: every wave reads whole 512-byte runs of a ciphertext, the digit bytes
 // are turned through LDS (rows of 128 + 16 bytes: the 16-byte reads of 8 neighbouring lanes then cover all banks), and
 // every store instruction writes one 1 KiB operand block.
+// init: where the contraction adds its segments up, the output's (0, b') is written here as well, a part of every ciphertext's words by
+// each workgroup of its tile (a launch of its own took 5 us of 110 at 1024 ciphertexts of configuration size kN = 2048, n = 742).
 #define KD_WORDS 128
 #define KD_PITCH (KD_WORDS + 16)
 #define KD_LEVELS 8                     // levels turned through LDS at a time
 __global__ void __launch_bounds__(256)
 k_ksm_digits(const uint64_t *__restrict__ lwe_in, v4i *__restrict__ dig, uint32_t kN, uint32_t beta, uint32_t l, uint32_t batch,
-             uint32_t n_kb) {
+             uint32_t n_kb, uint64_t *__restrict__ init, uint32_t n) {
     __shared__ __attribute__((aligned(16))) unsigned char L[KD_LEVELS * 32 * KD_PITCH];
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const uint32_t w0 = blockIdx.x * KD_WORDS, tile = blockIdx.y;
@@ -50,6 +52,14 @@ k_ksm_digits(const uint64_t *__restrict__ lwe_in, v4i *__restrict__ dig, uint32_
             const uint32_t w = w0 + 64 * h + lane;
             const uint64_t a = (c < batch && w < kN) ? lwe_in[(size_t)c * (kN + 1) + w] : 0ull;
             v[q][h] = slz_round_top_bits(a, bits) + H;
+        }
+    }
+    if (init) {
+        const uint32_t width = n + 1, part = (width + gridDim.x - 1) / gridDim.x, x0 = blockIdx.x * part, x1 = min(x0 + part, width);
+        for (uint32_t q = 0; q < 8; q++) {
+            const uint32_t c = tile * 32 + 8 * wave + q;
+            if (c >= batch) break;
+            for (uint32_t x = x0 + lane; x < x1; x += 64) init[(size_t)c * width + x] = x == n ? lwe_in[(size_t)c * (kN + 1) + kN] : 0ull;
         }
     }
     for (uint32_t j0 = 0; j0 < l; j0 += KD_LEVELS) {
@@ -331,9 +341,9 @@ static int ksm_run(const slz_params &p, void *dig, uint32_t max_tiles, const uin
         A.per_xcd = (A.total + 7) / 8;
         A.lwe_in = lwe_in + (size_t)c0 * (kN + 1);
         A.direct = segs == 1;
-        if (!A.direct) slz_ks_init_launch(A.lwe_in, A.out, kN, p.n, nb, s);
         hipLaunchKernelGGL(k_ksm_digits, dim3((kN + KD_WORDS - 1) / KD_WORDS, A.n_tiles), dim3(256), 0, s,
-                           lwe_in + (size_t)c0 * (kN + 1), (v4i *)dig, kN, p.ks_base_log, p.ks_level, nb, n_kb);
+                           lwe_in + (size_t)c0 * (kN + 1), (v4i *)dig, kN, p.ks_base_log, p.ks_level, nb, n_kb,
+                           A.direct ? nullptr : A.out, p.n);
         if (kskp) hipLaunchKernelGGL(k_ksm_main<true>, dim3(A.per_xcd * 8), dim3(KM_THREADS), 0, s, A);
         else hipLaunchKernelGGL(k_ksm_main<false>, dim3(A.per_xcd * 8), dim3(KM_THREADS), 0, s, A);
     }

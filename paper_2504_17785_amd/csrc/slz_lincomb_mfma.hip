@@ -7,7 +7,7 @@
 // s_b = byte b of (W + 0x80808080) - 128 for b < 4 and s_4 = (W + 0x80808080) >> 32; digit plane b multiplies the
 // ciphertext word shifted left by 8 b bits, so every digit plane is just more rows of the same contraction.  A first
 // kernel writes the digit planes in operand layout and records how many are non-zero anywhere (one, when every weight
-// fits a signed byte); the contraction reads that count from device memory, so no host synchronisation is needed.
+// fits a signed byte); the contraction reads the counts of its output tiles from device memory, so no host synchronisation is needed.
 #include "slz_internal.h"
 #include "slz_mfma_i8.h"
 
@@ -16,8 +16,7 @@
 // ---- weights -------------------------------------------------------------------------------------------------------
 // dig[otile][b][kb][lane] (16 bytes): A operand of lane `lane` for digit plane b, 32-row block kb of 32-output tile otile:
 // output 32 otile + lane % 32, inputs j = 32 kb + 16 (lane / 32) + t for byte t; zero past J or O.
-__global__ void k_lcm_clear(uint32_t *planes) { *planes = 1; }
-
+// planes[otile][kb]: digit planes that are not all zero there.
 __global__ void __launch_bounds__(64)
 k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint32_t *__restrict__ planes, uint32_t J, uint32_t O,
               uint32_t n_kb) {
@@ -50,7 +49,9 @@ k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint32_t *__
         v4i v = {(int)wd[b][0], (int)wd[b][1], (int)wd[b][2], (int)wd[b][3]};
         dig[(((size_t)otile * LM_MAX_PLANES + b) * n_kb + kb) * 64 + lane] = v;
     }
-    if (used > 1) atomicMax(planes, used);
+#pragma unroll
+    for (int d = 32; d; d >>= 1) used = max(used, (uint32_t)__shfl_xor((int)used, d));
+    if (lane == 0) planes[(size_t)otile * n_kb + kb] = used;
 }
 
 // ---- contraction ---------------------------------------------------------------------------------------------------
@@ -83,8 +84,6 @@ k_lcm_main(lcm_args A) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint32_t otile = og * W + wave;
     const bool tile_ok = otile < A.n_otiles;
-    const uint32_t planes = min(*A.planes, (uint32_t)LM_MAX_PLANES);
-    const uint32_t kb_end = planes * A.n_kb;
     const uint32_t width = A.width;
 
     const uint32_t xl = lane % 32;
@@ -101,9 +100,8 @@ k_lcm_main(lcm_args A) {
     uint64_t kw0[8], kw1[8];
     uint32_t sh0, sh1, nv0, nv1;        // shift of the stage's digit plane; rows of the stage that exist
     v4i an0[IT_KB], an1[IT_KB];
-    auto load_rows = [&](uint64_t (&kw)[8], uint32_t &sh, uint32_t &nv, uint32_t it) {
-        const bool ok = x_ok && (it + oct / 4 < kb_end);
-        nv = ok ? (j < A.J ? min(A.J - j, 8u) : 0u) : 0u;
+    auto load_rows = [&](uint64_t (&kw)[8], uint32_t &sh, uint32_t &nv) {
+        nv = x_ok && j < A.J ? min(A.J - j, 8u) : 0u;
         sh = 8 * b;
 #pragma unroll
         for (int t = 0; t < 8; t++) kw[t] = src[(size_t)min(j + t, A.J - 1) * width];
@@ -117,6 +115,7 @@ k_lcm_main(lcm_args A) {
         for (int q = 0; q < IT_KB; q++) an[q] = A.dig[(dig_base + min(it + q, dig_last)) * 64 + lane];
     };
 
+    uint32_t planes = 1;
     v16i acc[8];
 #pragma unroll
     for (int p = 0; p < 8; p++)
@@ -127,6 +126,7 @@ k_lcm_main(lcm_args A) {
     auto body = [&](uint64_t (&kw)[8], uint32_t &sh, uint32_t &nv, v4i (&an)[IT_KB], uint32_t it) {
         {
             uint64_t w[8], plane[8];
+            if (sh >= 8 * planes) nv = 0;                               // past the last digit plane in use
 #pragma unroll
             for (int t = 0; t < 8; t++) w[t] = (uint32_t)t < nv ? slz_signed_bytes(kw[t] << sh) : 0ull;
             slz_byte_planes(w, plane);
@@ -134,7 +134,7 @@ k_lcm_main(lcm_args A) {
 #pragma unroll
             for (int p = 0; p < 8; p++) dst[(size_t)p * 64] = plane[p];
         }
-        load_rows(kw, sh, nv, it + 2 * IT_KB);
+        load_rows(kw, sh, nv);
         __syncthreads();    // one barrier per iteration suffices with two buffers (see the keyswitch kernel)
         if (tile_ok) {
             const v4i *bsrc = lds + buf * BUF_V4 + (lane / 32) * (8 * 32) + xl;
@@ -157,10 +157,21 @@ k_lcm_main(lcm_args A) {
         load_dig(an, it + 2 * IT_KB);
         buf ^= 1;
     };
-    load_rows(kw0, sh0, nv0, 0);
+    load_rows(kw0, sh0, nv0);
     load_dig(an0, 0);
-    load_rows(kw1, sh1, nv1, IT_KB);
+    load_rows(kw1, sh1, nv1);
     load_dig(an1, IT_KB);
+    // digit planes in use in this workgroup's output tiles
+    __shared__ uint32_t wave_planes[W];
+    for (uint32_t t = lane; tile_ok && t < A.n_kb; t += 64) planes = max(planes, A.planes[(size_t)otile * A.n_kb + t]);
+#pragma unroll
+    for (int d = 32; d; d >>= 1) planes = max(planes, (uint32_t)__shfl_xor((int)planes, d));
+    if (lane == 0) wave_planes[wave] = planes;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < W; w++) planes = max(planes, wave_planes[w]);
+    planes = min(planes, (uint32_t)LM_MAX_PLANES);
+    const uint32_t kb_end = planes * A.n_kb;
     for (uint32_t it = 0; it < kb_end; it += 2 * IT_KB) {
         body(kw0, sh0, nv0, an0, it);
         body(kw1, sh1, nv1, an1, it + IT_KB);
@@ -192,7 +203,7 @@ int slz_lcm_launch(slz_ctx *ctx, const uint64_t *cts, const int32_t *w, uint64_t
     // int32 accumulators: at most 5 planes x 32 n_kb rows of |digit * byte| <= 2^14
     if ((uint64_t)LM_MAX_PLANES * 32 * n_kb >= (1u << 17)) return SLZ_E_UNSUPPORTED;
     const uint32_t n_otiles = (O + 31) / 32;
-    const size_t need = ((size_t)n_otiles * LM_MAX_PLANES * n_kb * 64 + 16) * 16;      // operands + the plane count
+    const size_t need = (size_t)n_otiles * n_kb * (LM_MAX_PLANES * 1024 + sizeof(uint32_t));    // operands and plane counts
     if (ctx->lc_dig_bytes < need) {
         // the previous buffer may still be read by work queued on another stream: wait before letting it go
         if (ctx->lc_dig) { SLZ_HIP(hipDeviceSynchronize()); (void)hipFree(ctx->lc_dig); ctx->lc_dig = nullptr; ctx->lc_dig_bytes = 0; }
@@ -202,7 +213,6 @@ int slz_lcm_launch(slz_ctx *ctx, const uint64_t *cts, const int32_t *w, uint64_t
     v4i *dig = (v4i *)ctx->lc_dig;
     uint32_t *planes = (uint32_t *)(dig + (size_t)n_otiles * LM_MAX_PLANES * n_kb * 64);
     if (n_otiles > 65535) return SLZ_E_UNSUPPORTED;
-    hipLaunchKernelGGL(k_lcm_clear, dim3(1), dim3(1), 0, s, planes);
     hipLaunchKernelGGL(k_lcm_weights, dim3(n_kb, n_otiles), dim3(64), 0, s, w, dig, planes, J, O, n_kb);
     lcm_args A;
     A.cts = cts; A.dig = dig; A.planes = planes; A.out = out;
