@@ -702,8 +702,8 @@ static bool block_fits(uint32_t N, uint32_t BS) {
     return N % BS == 0 && G >= 2 && G <= 32 && (G & (G - 1)) == 0;
 }
 
-// block-specific forward tables for blocks of BS = 64 * E coefficients (E = 32 or 16 per lane), or with `inverse` the inverses of
-// their entries: fwd[x] = psi^bitrev(x), so 1 / fwd[x] = -psi^(N - bitrev(x))
+// Block-specific forward tables of one prime for blocks of BS = 64 * E coefficients (E = 32 or 16 per lane), ra [G][64] and
+// rb [G][E - 1][64], or with `inverse` the inverses of their entries: fwd[x] = psi^bitrev(x), so 1 / fwd[x] = -psi^(N - bitrev(x)).
 static double inverse_entry(const std::vector<double> &nat, uint32_t x) {
     const uint32_t N = (uint32_t)nat.size();
     auto bitrev = [&](uint32_t v) {
@@ -713,33 +713,33 @@ static double inverse_entry(const std::vector<double> &nat, uint32_t x) {
     };
     return x ? -nat[bitrev(N - bitrev(x))] : 1.0;
 }
-int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, bool inverse, double **dA, double **dB) {
-    const uint32_t N = ctx->prm.N, G = N / BS, E = BS / 64;
+static void fill_block_tables(const std::vector<double> &nat, uint32_t BS, bool inverse, double *ra, double *rb) {
+    const uint32_t G = (uint32_t)nat.size() / BS, E = BS / 64;
     int late = 0;                                   // stages done after the transposition: log2 E
     for (uint32_t e = E; e > 1; e >>= 1) late++;
-    const uint32_t nB = E - 1;                      // per-lane twiddles of those stages
-    std::vector<double> nat(N), rowA((size_t)2 * G * 64), rowB((size_t)2 * G * nB * 64);
-    for (int q = 0; q < 2; q++) {
-        SLZ_HIP(hipMemcpy(nat.data(), ctx->tab[q].fwd, (size_t)N * sizeof(double), hipMemcpyDeviceToHost));
-        auto entry = [&](size_t x) { return inverse ? inverse_entry(nat, (uint32_t)x) : nat[x]; };
-        for (uint32_t row = 0; row < G; row++) {
-            // block `row` continues the transform with sub-block counts m' = 1, 2, ..., BS / 2; its sub-block blk at that
-            // stage is block (G + row) m' + blk of the whole transform: table entry fwd[(G + row) m' + blk]
-            double *ra = &rowA[((size_t)q * G + row) * 64];
-            ra[0] = 1.0;
-            for (uint32_t x = 1; x < 64; x++) {
-                uint32_t mp = 1;
-                while (mp * 2 <= x) mp *= 2;
-                ra[x] = entry((size_t)(G + row) * mp + (x - mp));
-            }
-            int kk = 0;
-            for (int s = 0; s < late; s++) {
-                const uint32_t t = (E / 2) >> s, mp = BS / (2 * t);
-                for (uint32_t blk = 0; blk < (1u << s); blk++, kk++)
-                    for (uint32_t l = 0; l < 64; l++)
-                        rowB[(((size_t)q * G + row) * nB + kk) * 64 + l] = entry((size_t)(G + row) * mp + (E * l) / (2 * t) + blk);
-            }
+    auto entry = [&](size_t x) { return inverse ? inverse_entry(nat, (uint32_t)x) : nat[x]; };
+    for (uint32_t row = 0; row < G; row++, ra += 64) {
+        // block `row` continues the transform with sub-block counts m' = 1, 2, ..., BS / 2; its sub-block blk at that
+        // stage is block (G + row) m' + blk of the whole transform: table entry fwd[(G + row) m' + blk]
+        ra[0] = 1.0;
+        for (uint32_t x = 1; x < 64; x++) {
+            uint32_t mp = 1;
+            while (mp * 2 <= x) mp *= 2;
+            ra[x] = entry((size_t)(G + row) * mp + (x - mp));
         }
+        for (int s = 0; s < late; s++) {
+            const uint32_t t = (E / 2) >> s, mp = BS / (2 * t);
+            for (uint32_t blk = 0; blk < (1u << s); blk++, rb += 64)
+                for (uint32_t l = 0; l < 64; l++) rb[l] = entry((size_t)(G + row) * mp + (E * l) / (2 * t) + blk);
+        }
+    }
+}
+int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB) {
+    const uint32_t N = ctx->prm.N, G = N / BS, nB = BS / 64 - 1;
+    std::vector<double> nat(N), rowA((size_t)2 * G * 64), rowB((size_t)2 * G * nB * 64);
+    for (size_t q = 0; q < 2; q++) {
+        SLZ_HIP(hipMemcpy(nat.data(), ctx->tab[q].fwd, (size_t)N * sizeof(double), hipMemcpyDeviceToHost));
+        fill_block_tables(nat, BS, false, &rowA[q * G * 64], &rowB[q * G * nB * 64]);
     }
     SLZ_HIP(hipMalloc((void **)dA, rowA.size() * sizeof(double)));
     SLZ_HIP(hipMalloc((void **)dB, rowB.size() * sizeof(double)));
@@ -748,18 +748,22 @@ int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, bool inverse, double **dA,
     return SLZ_OK;
 }
 
-// column constants of the mirrored inverse, [2][32]
-static int build_col_table(slz_ctx *ctx, uint32_t G) {
-    const uint32_t N = ctx->prm.N;
-    std::vector<double> nat(N), col(2 * 32, 0.0);
+// The tables of the 1024-block kernels in one piece of device memory, per prime: rowA [G][64], rowB [G][15][64], their inverses, and the
+// column constants of the mirrored inverse [32].
+#define BIG16_TAB(G) ((size_t)(G) * 64 * 32 + 32)
+static int build_tables16(slz_ctx *ctx) {
+    const uint32_t N = ctx->prm.N, G = N / 1024;
+    std::vector<double> nat(N), t(2 * BIG16_TAB(G), 0.0);
     for (int q = 0; q < 2; q++) {
+        double *o = &t[q * BIG16_TAB(G)], *col = o + (size_t)G * 64 * 32;
         SLZ_HIP(hipMemcpy(nat.data(), ctx->tab[q].fwd, (size_t)N * sizeof(double), hipMemcpyDeviceToHost));
-        for (uint32_t x = 2; x < G; x++) col[32 * q + x] = inverse_entry(nat, x);
-        for (uint32_t x = 0; x < 2; x++)             // the twist table holds psi^-j / N, and fwd[1] = psi^(N / 2)
-            SLZ_HIP(hipMemcpy(&col[32 * q + x], ctx->tab[q].post + x * (N / 2), sizeof(double), hipMemcpyDeviceToHost));
+        fill_block_tables(nat, 1024, false, o, o + (size_t)G * 64);
+        fill_block_tables(nat, 1024, true, o + (size_t)G * 64 * 16, o + (size_t)G * 64 * 17);
+        for (uint32_t x = 0; x < 2; x++) col[x] = ctx->mirror_last[q][x];
+        for (uint32_t x = 2; x < G; x++) col[x] = inverse_entry(nat, x);
     }
-    SLZ_HIP(hipMalloc((void **)&ctx->bign16_colI, col.size() * sizeof(double)));
-    SLZ_HIP(hipMemcpy(ctx->bign16_colI, col.data(), col.size() * sizeof(double), hipMemcpyHostToDevice));
+    SLZ_HIP(hipMalloc((void **)&ctx->bign16_tab, t.size() * sizeof(double)));
+    SLZ_HIP(hipMemcpy(ctx->bign16_tab, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
     return SLZ_OK;
 }
 
@@ -789,16 +793,14 @@ int slz_bign_init(slz_ctx *ctx) {
     ctx->bign_latency = 1;
     bool any = false;
     if (block_fits(N, 2048) && bounds_ok(N, 2048)) {
-        int rc = slz_build_block_tables(ctx, 2048, false, &ctx->bign_rowA, &ctx->bign_rowB);
+        int rc = slz_build_block_tables(ctx, 2048, &ctx->bign_rowA, &ctx->bign_rowB);
         if (rc != SLZ_OK) return rc;
         SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * TBUF * sizeof(double)));
         ctx->bign_block = 2048;
         any = true;
     }
     if (block_fits(N, 1024) && bounds_ok(N, 1024)) {
-        int rc = slz_build_block_tables(ctx, 1024, false, &ctx->bign16_rowA, &ctx->bign16_rowB);
-        if (rc == SLZ_OK) rc = slz_build_block_tables(ctx, 1024, true, &ctx->bign16_rowAi, &ctx->bign16_rowBi);
-        if (rc == SLZ_OK) rc = build_col_table(ctx, N / 1024);
+        int rc = build_tables16(ctx);
         if (rc != SLZ_OK) return rc;
         SLZ_HIP(hipFuncSetAttribute((const void *)k_big_rows16, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (TBUF16 + 1024) * sizeof(double)));
         const struct { const void *kernel; uint32_t rows; } team[] = {{(const void *)k_big_rows16_team<2>, 2}, {(const void *)k_big_rows16_team<4>, 4},
@@ -814,14 +816,9 @@ int slz_bign_init(slz_ctx *ctx) {
 void slz_bign_destroy(slz_ctx *ctx) {
     if (ctx->bign_rowA) (void)hipFree(ctx->bign_rowA);
     if (ctx->bign_rowB) (void)hipFree(ctx->bign_rowB);
-    if (ctx->bign16_rowA) (void)hipFree(ctx->bign16_rowA);
-    if (ctx->bign16_rowB) (void)hipFree(ctx->bign16_rowB);
-    if (ctx->bign16_rowAi) (void)hipFree(ctx->bign16_rowAi);
-    if (ctx->bign16_rowBi) (void)hipFree(ctx->bign16_rowBi);
-    if (ctx->bign16_colI) (void)hipFree(ctx->bign16_colI);
+    if (ctx->bign16_tab) (void)hipFree(ctx->bign16_tab);
     if (ctx->bign_spare) (void)hipFree(ctx->bign_spare);
-    ctx->bign_rowA = ctx->bign_rowB = ctx->bign16_rowA = ctx->bign16_rowB = nullptr;
-    ctx->bign16_rowAi = ctx->bign16_rowBi = ctx->bign16_colI = nullptr;
+    ctx->bign_rowA = ctx->bign_rowB = ctx->bign16_tab = nullptr;
     ctx->bign_spare = nullptr;
     for (int j = 0; j < 2; j++) {
         if (ctx->bign_lane_stream[j]) (void)hipStreamDestroy((hipStream_t)ctx->bign_lane_stream[j]);
@@ -993,11 +990,17 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
             a.n = p.n; a.N = N; a.logG = logG; a.beta = p.pbs_base_log; a.l = p.pbs_level; a.batch = nb;
             for (int q = 0; q < 2; q++) {
                 a.tab[q].fwd = ctx->tab[q].fwd;
-                a.tab[q].rowA = (BS == 2048 ? ctx->bign_rowA : ctx->bign16_rowA) + (size_t)q * G * 64;
-                a.tab[q].rowB = BS == 2048 ? ctx->bign_rowB + (size_t)q * G * 31 * 64 : ctx->bign16_rowB + (size_t)q * G * 15 * 64;
-                a.tab[q].rowAi = ctx->bign16_rowAi + (size_t)q * G * 64;
-                a.tab[q].rowBi = ctx->bign16_rowBi + (size_t)q * G * 15 * 64;
-                a.tab[q].colI = ctx->bign16_colI + 32 * q;
+                if (BS == 2048) {
+                    a.tab[q].rowA = ctx->bign_rowA + (size_t)q * G * 64;
+                    a.tab[q].rowB = ctx->bign_rowB + (size_t)q * G * 31 * 64;
+                } else {
+                    const double *t = ctx->bign16_tab + q * BIG16_TAB(G);
+                    a.tab[q].rowA = t;
+                    a.tab[q].rowB = t + (size_t)G * 64;
+                    a.tab[q].rowAi = t + (size_t)G * 64 * 16;
+                    a.tab[q].rowBi = t + (size_t)G * 64 * 17;
+                    a.tab[q].colI = t + (size_t)G * 64 * 32;
+                }
                 a.tab[q].inv = ctx->tab[q].inv;
                 a.tab[q].post = ctx->tab[q].post;
                 a.mod[q] = ctx->mod[q];

@@ -260,7 +260,7 @@ int slz_fused1024_init(slz_ctx *ctx) {
     // six forward stages on the digits, reduction, four more; two products summed; inverse 2 + 2 stages, reduction, six
     // stages, twist
     if (!slz_fused_schedule_ok(6, 4, 2, 2, 6)) return SLZ_E_UNSUPPORTED;
-    int rc = slz_build_block_tables(ctx, GN, false, &ctx->fused1024_rowA, &ctx->fused1024_rowB);
+    int rc = slz_build_block_tables(ctx, GN, &ctx->fused1024_rowA, &ctx->fused1024_rowB);
     if (rc != SLZ_OK) return rc;
     rc = slz_fused_load_inv_scalars(ctx);
     if (rc != SLZ_OK) return rc;

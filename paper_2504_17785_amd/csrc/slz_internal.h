@@ -63,9 +63,8 @@ struct slz_ctx {
     int bign_block;           // block size the large-N path uses: 1024 or 2048
     int bign_latency;         // 1: few ciphertexts take the latency-oriented kernels (two launches per step)
     uint64_t *bign_spare;     // their second accumulator [few ciphertexts][2][N], allocated at first use
-    double *bign16_rowA;      // [2][G'][64] as bign_rowA for 1024-blocks
-    double *bign16_rowAi, *bign16_rowBi, *bign16_colI;   // mirrored inverse on 1024-blocks: inverses of rowA, of rowB, column constants [2][32]
-    double *bign16_rowB;      // [2][G'][15][64] per-lane twiddles of the last four forward stages of a 1024-block
+    double *bign16_tab;       // tables of the large-N kernels on 1024-blocks (slz_bign.hip)
+    double mirror_last[2][2]; // per prime 1 / N and 1 / (N fwd[1])
     // scratch for the generic path, sized for max_batch
     uint64_t *acc;            // [max_batch][k+1][N]
     double *dig;              // [max_batch][(k+1)l][N]
@@ -110,9 +109,9 @@ void slz_fused1024_destroy(slz_ctx *ctx);
 int slz_fused1024_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx,
                                const double *bskp, uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch,
                                hipStream_t s);
-// forward twiddle tables (`inverse`: the inverses of their entries) of the blocks of size BS of the wave-level transforms (slz_bign.hip):
-// *dA [2][N/BS][64], *dB [2][N/BS][BS/64 - 1][64], device memory owned by the caller
-int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, bool inverse, double **dA, double **dB);
+// forward twiddle tables of the blocks of size BS of the wave-level transforms (slz_bign.hip): *dA [2][N/BS][64],
+// *dB [2][N/BS][BS/64 - 1][64], device memory owned by the caller
+int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB);
 
 // floating-point transforms for N = 512 (l = 2), 1024, 2048 and 4096 (slz_fft.hip: tables and key; slz_fft512.hip, slz_fft1024.hip,
 // slz_fft2048.hip, slz_fft4096.hip: kernels); their key form follows the

@@ -55,6 +55,8 @@ int slz_build_tables(slz_ctx *ctx) {
                 inv[t + j] = centred(pwi[(size_t)(N / t) * j], p);
             }
         for (uint32_t j = 0; j < N; j++) post[j] = centred(mulmod_u64(pwi[j], n_inv, p), p);
+        ctx->mirror_last[q][0] = post[0];
+        ctx->mirror_last[q][1] = post[N / 2];                       // fwd[1] = psi^(N / 2)
         double **dst[3] = {&ctx->tab[q].fwd, &ctx->tab[q].inv, &ctx->tab[q].post};
         std::vector<double> *src[3] = {&fwd, &inv, &post};
         for (int a = 0; a < 3; a++) {
