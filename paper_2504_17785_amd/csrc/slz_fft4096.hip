@@ -25,9 +25,10 @@
 // What bounds it: 3 130 vector instructions per wave and step, 27 k cycles of a SIMD's two waves, and 18 exchanges per step of about 800 LDS
 // cycles each; of 38 k cycles per step (256 ciphertexts) 73 % issue vector instructions, the rest is what the two waves of a SIMD do not
 // hide of each other's exchanges.  With a full chip the clock falls from 2.25 to 1.8 GHz.  One ciphertext per compute unit: the exchange
-// buffers and tables of two would not fit LDS, and eight waves on one ciphertext also give the lower latency.  Measured, us per step (in
-// brackets: two residues): 1 ciphertext 18.3 (26.7), 100: 18.8 (27.4), 256: 21.3 (29.7), 1024: 77 (115); a lookup of 100 with 800 steps
-// 14.5 ms (21.2).  Key words are requested one piece ahead of their use (64 registers).
+// buffers and tables of two would not fit LDS, and eight waves on one ciphertext also give the lower latency.  Of the two waves on a SIMD
+// the one behind gets the priority (20.2 us per step at 100 ciphertexts without, 18.8 with); key words are requested one piece ahead, four
+// loads at a time (18.8, 17.7); the twiddles of I2 stay in registers (1024 ciphertexts: 68.6, 67.6).  Measured, us per step (in brackets: two
+// residues): 1 ciphertext 16.8 (26.7), 100: 17.6 (27.4), 256: 19.9 (29.7), 1024: 68 to 70 (115); a lookup of 100 with 800 steps 13.3 ms (21.2).
 #include "slz_fft.h"
 #include "slz_fft_wave.h"
 #include "slz_modarith.h"
@@ -90,6 +91,14 @@ k_fft4096_blind_rotate(fft4096_args A) {
     if (threadIdx.x < 16) *(LDS_AS uint32_t *)(uintptr_t)(flags + 4u * threadIdx.x) = 0;
     __syncthreads();
 
+    // twiddles of I2, the same for every piece and step
+    d2 i2v, i2v2, i2v3, i2w0, i2w1;
+    {
+        const uint32_t t2 = tab0 + F12_I2_OFF * 16u + 16u * (lane & 7u);
+        i2v = lds_get(t2); i2v2 = lds_get(t2 + 128); i2v3 = lds_get(t2 + 256); i2w0 = lds_get(t2 + 384); i2w1 = lds_get(t2 + 512);
+        pin(i2v); pin(i2v2); pin(i2v3); pin(i2w0); pin(i2w1);
+    }
+
     const double magic = 6755399441055744.0, r2 = FFT_SQRT_HALF;      // 1.5 * 2^52: adding it rounds to an integer
     uint32_t ex = 0;                                                  // exchanges between waves so far
     for (uint32_t c = blockIdx.x; c < A.batch; c += gridDim.x) {
@@ -122,14 +131,19 @@ k_fft4096_blind_rotate(fft4096_args A) {
         uint64_t mask = lwe[0];
         d2 kb[8][2];                                                  // key words of the next piece
         const d2 *kp = A.key + (g * 8u * 4u + h) * 64u;               // [piece][quarter][k][row, component][lane]
-        auto request = [&](uint32_t kl) {
+        // four loads at a time, spread over the passes: more of them together would fill the memory pipeline's queue and hold the wave
+        auto request = [&](int part) __attribute__((always_inline)) {
+            const uint32_t kl = fresh(lane);
 #pragma unroll
-            for (int k = 0; k < 8; k++)
+            for (int k = 2 * part; k < 2 * part + 2; k++)
 #pragma unroll
                 for (int r = 0; r < 2; r++) kb[k][r] = lane_get(kp + (4 * k + 2 * r) * 64, kl);
-            kp += F12_KEY_STEP / SLZ_FFT_PIECES;                       // pieces and steps follow each other at the same distance
+            if (part == 3) kp += F12_KEY_STEP / SLZ_FFT_PIECES;        // pieces and steps follow each other at the same distance
+            FFT_FENCE();
         };
-        if (A.n_steps) request(lane);
+        if (A.n_steps)
+#pragma unroll
+            for (int part = 0; part < 4; part++) request(part);
         for (uint32_t step = 0; step < A.n_steps; step++) {
             // The SIMD serves its older wave first, here that of component 0, which would run ahead through the pieces and then wait for the
             // other's spectra while that one runs alone: of the two waves on a SIMD the one that is behind gets the priority.
@@ -270,8 +284,8 @@ k_fft4096_blind_rotate(fft4096_args A) {
                 }
                 FFT_FENCE();
                 // the next piece's key words (the next step's after the last piece, if there is one) arrive during this inverse transform
-                if (piece < SLZ_FFT_PIECES - 1 || step + 1 < A.n_steps) request(fresh(lane));
-                FFT_FENCE();
+                const bool more = piece < SLZ_FFT_PIECES - 1 || step + 1 < A.n_steps;
+                if (more) request(0);
                 inv8(S);                                              // I1: half-sizes 1, 2, 4
                 if (piece) wait_four(freed, lane, free_seen, ex);     // the waves that read this one's buffer have done so
                 else fft_wait(his_free, free_seen, ex);
@@ -281,22 +295,22 @@ k_fft4096_blind_rotate(fft4096_args A) {
 #pragma unroll
                     for (int k = 0; k < 8; k++) lds_put(w + 16 * k, S[k]);
                 }
+                if (more) request(1);
                 {   // I2: half-sizes 8, 16, 32; lane = b8 b7 b6 b2 b1 b0; register = b5 b4 b3
                     const uint32_t ln = fresh(lane);
-                    const uint32_t t2 = tb + F12_I2_OFF * 16u + 16u * (ln & 7u);
-                    const d2 v = lds_get(t2), v2 = lds_get(t2 + 128), v3 = lds_get(t2 + 256), w0 = lds_get(t2 + 384), w1 = lds_get(t2 + 512);
                     const uint32_t r0 = R + 16u * (17u * (16u * (ln >> 5) + 8u * ((ln >> 4) & 1u)) + 8u * ((ln >> 3) & 1u) + (ln & 7u));
 #pragma unroll
                     for (int m = 0; m < 8; m++) x[m] = lds_get(r0 + 16 * 17 * m);
                     FFT_FENCE();
-                    inv4(x[0], x[1], x[2], x[3], v, v2, v3);
-                    inv4(x[4], x[5], x[6], x[7], v, v2, v3);
-                    inv2<false>(x[0], x[4], w0); inv2<false>(x[1], x[5], w1);
-                    inv2<true>(x[2], x[6], w0); inv2<true>(x[3], x[7], w1);
+                    inv4(x[0], x[1], x[2], x[3], i2v, i2v2, i2v3);
+                    inv4(x[4], x[5], x[6], x[7], i2v, i2v2, i2v3);
+                    inv2<false>(x[0], x[4], i2w0); inv2<false>(x[1], x[5], i2w1);
+                    inv2<true>(x[2], x[6], i2w0); inv2<true>(x[3], x[7], i2w1);
                     const uint32_t w = R + 16u * (17u * (16u * (ln >> 5) + 4u * ((ln >> 4) & 1u) + 8u * ((ln >> 3) & 1u)) + (ln & 7u));
 #pragma unroll
                     for (int m = 0; m < 8; m++) lds_put(w + 16 * (17 * (m >> 1) + 8 * (m & 1)), x[m]);
                 }
+                if (more) request(2);
                 {   // I3: half-sizes 64, 128, 256; lane = b5..b0; register = b8 b7 b6
                     const uint32_t ln = fresh(lane);
                     const uint32_t t3 = tb + F12_I3_OFF * 16u + 16u * ln;
@@ -313,6 +327,7 @@ k_fft4096_blind_rotate(fft4096_args A) {
                     for (int m = 0; m < 8; m++) lds_put(r0 + 16 * 17 * 4 * m, x[m]);
                 }
                 fft_signal(my_done, ++ex);
+                if (more) request(3);
                 {   // I4: half-sizes 512 and 1024 with the twist; lane = b5..b0, wave = b7 b6; register = b10 b9 b8
                     const uint32_t ln = fresh(lane);
                     const uint32_t t4 = tb + F12_I4_OFF * 16u + 16u * (64u * g + ln);
