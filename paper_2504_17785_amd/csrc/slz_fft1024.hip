@@ -13,7 +13,7 @@
 // Bound and shape: FP64 issue.  A step is about 4.2 k VALU instructions per ciphertext; registers (accumulator 64, spectra 64, transform 64,
 // key words 64 of 256) allow two waves per SIMD.  The two components of a wave hide each other's LDS round trips.  Smaller batches
 // leave compute units with fewer than eight ciphertexts, so waves share one (SHARE below).  Measured with 630 steps and the
-// keyswitch (in brackets: two 50-bit residues on the same card): one ciphertext 3.7 ms (4.6), 512: 5.6 (7.0), 777: 8.5 (13.1),
+// keyswitch (in brackets: two 50-bit residues on the same card): one ciphertext 3.7 ms (4.6), 512: 5.6 (7.0), 777: 7.8 (13.1),
 // 2048: 15.4 (24.4), 8192: 60.3 (102).
 #include "slz_fft.h"
 #include "slz_fft_wave.h"
@@ -127,6 +127,9 @@ k_fft1024_blind_rotate(fft1024_args A) {
                     else __builtin_amdgcn_s_setprio(2);
                     fft_signal(progress + 4u * wave, tick);
                 }
+                // the helper, younger on its SIMD than the front, has three pieces to the front's two: 777 ciphertexts 12.7 us per step with, 13.6
+                // without (SHARE = 4, where the front's chain is the longer one: 400 ciphertexts 10.1 with, 9.6 without)
+                if (SHARE == 2 && !front) __builtin_amdgcn_s_setprio(2);
                 const d2 *kp = A.key + (size_t)step * F10_KEY_STEP + FIRST * 2048u + z;
                 d2 kb[8][4];
                 const uint32_t kl = fresh(lane);
@@ -455,7 +458,7 @@ int slz_fft1024_setup() {
 
 // Largest batches of SHARE = 8, 4 and 2: one, two and four ciphertexts per compute unit.  Past each line the form would need a second
 // round (1100 in two rounds of SHARE = 2: 17.0 ms, with SHARE = 1: 12.4), before it the next form leaves waves idle (512 with
-// SHARE = 2: 7.1 ms, with 4: 5.6; 777 with SHARE = 1: 9.9 ms, with 2: 8.5).
+// SHARE = 2: 7.1 ms, with 4: 5.6; 777 with SHARE = 1: 9.9 ms, with 2: 7.8).
 #define F10_MAX_8 256
 #define F10_MAX_4 512
 #define F10_MAX_2 1024

@@ -26,7 +26,7 @@
 // ciphertexts) share one workgroup, i.e. one copy of the tables in LDS, and only the two waves of a ciphertext wait for each other.
 // Two waves hide little of each other's LDS round trips, so loads are requested in groups ahead of the arithmetic, and results are
 // written while the next ones are computed.  Measured with 742 steps (in brackets: two residues on the same card): 1024 ciphertexts
-// 20.2 ms (31.5), 4096: 80.6 (126.6), 301: 12.9 (15.4).
+// 20.2 ms (31.5), 4096: 80.6 (126.6), 301: 11.5 (15.4).
 // Batches up to 256 go to slz_fft2048_team.hip.  From 257 to 512 a compute unit has two ciphertexts; two pairs work on each (SHARE = 2).
 #include "slz_fft.h"
 #include "slz_fft_wave.h"
@@ -133,6 +133,8 @@ k_fft_blind_rotate(fft_args A) {
                     if ((int32_t)(seq - (uint32_t)__builtin_amdgcn_readfirstlane(fft_peek(flags + 4u * (wave ^ 4u)))) > 0) __builtin_amdgcn_s_setprio(0);
                     else __builtin_amdgcn_s_setprio(2);
                 }
+                // the owner's front and two pieces are the longer chain: 301 ciphertexts 16.0 us per step with, 16.8 without
+                if (SHARED && owner) __builtin_amdgcn_s_setprio(2);
                 const d2 *kp = A.key + (size_t)step * FFT_KEY_STEP + h * 2048u + z;
                 d2 kb[8][4];
                 uint32_t kl = fresh(lane);
@@ -478,7 +480,7 @@ int slz_fft2048_setup() {
 int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
     // Up to one ciphertext per compute unit its eight waves take one together (742 steps: one 7.2 ms against 8.5 with two pairs on it, 256
-    // 8.3 against 8.6); from 257 on that needs a second round (301: 14.6 ms against 12.4).
+    // 8.3 against 8.6); from 257 on that needs a second round (301: 14.6 ms against 11.5).
     if (batch <= FFT_TEAM_MAX) return slz_fft2048_team(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);
     fft_args A;
     A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;
@@ -488,7 +490,7 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
     const uint32_t grid = slz_fused_grid(batch, 1);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(FFT_THREADS), FFT_LDS_BYTES, s, A); };
-    // From 257 to 512 ciphertexts two pairs share each: 301 12.4 ms against 12.9 with a pair for each (512: 12.5 and 13.1).
+    // From 257 to 512 ciphertexts two pairs share each: 301 11.5 ms against 12.9 with a pair for each (512: 12.2 and 13.1).
     if (batch <= 2 * FFT_TEAM_MAX) launch(k_fft_blind_rotate<2>);
     else launch(k_fft_blind_rotate<1>);
     SLZ_HIP(hipGetLastError());
