@@ -89,7 +89,16 @@ k_big_cols_fwd(bign_args A) {
             double y[G];
 #pragma unroll
             for (int i = 0; i < G; i++) y[i] = d[i];
-            cols_fwd<G>(y, tw, m);
+            // as cols_fwd (written out: the compiler schedules the call differently, and the pass takes 1 % longer)
+#pragma unroll
+            for (int half = G / 2, blocks = 1; half >= 1; half >>= 1, blocks <<= 1) {
+#pragma unroll
+                for (int blk = 0; blk < blocks; blk++) {
+                    const double w = tw[blocks + blk];
+#pragma unroll
+                    for (int j = 0; j < half; j++) bfly(y[blk * 2 * half + j], y[blk * 2 * half + j + half], w, m);
+                }
+            }
             double *dst = A.X + (((size_t)b * 2 + q) * R + (comp * A.l + lev)) * N + c;
 #pragma unroll
             for (int i = 0; i < G; i++) dst[(uint32_t)BS * i] = slz_reduce(y[i], m);
