@@ -24,11 +24,7 @@ __device__ __forceinline__ void st_through(uint64_t *p, uint64_t v) { __hip_atom
 struct bign_tabs {                 // per prime
     const double *fwd;             // natural forward table of the full transform (fwd[m + blk])
     const double *rowA;            // [G][64]      block-specific twiddles of stages with 1..32 sub-blocks (uniform per wave)
-    const double *rowB;            // [G][31][64]  block-specific per-lane twiddles of the last five forward stages
-    // 1024-blocks: tables of the mirrored inverse
-    const double *rowAi, *rowBi;   // [G][64], [G][15][64]  inverses of rowA and rowB
-    const double *colI;            // [G]  column stages: inverses of fwd[2 .. G - 1]; [0] = 1 / N, [1] = 1 / (N fwd[1])
-    // 2048-blocks: decimation in time and twist
+    const double *rowB;            // [G][31][64]  block-specific per-lane twiddles of the last five forward stages (1024-blocks: [G][15][64], four)
     const double *inv;             // natural inverse table
     const double *post;            // natural twist table
 };
@@ -58,6 +54,14 @@ __device__ __forceinline__ void cols_fwd(double (&y)[G], const double *tw, slz_m
         }
     }
 }
+
+// 1024-blocks: the tables of the mirrored inverse follow rowA [G][64] and rowB [G][15][64] in memory (BIG16_TAB), so the arguments of the
+// throughput kernels do not grow by them: inverses of rowA and of rowB, and the column stages' [32]: inverses of fwd[2 .. G - 1], [0] = 1 / N,
+// [1] = 1 / (N fwd[1])
+#define BIG16_TAB(G) ((size_t)(G) * 64 * 32 + 32)
+__device__ __forceinline__ const double *rowAi_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 16; }
+__device__ __forceinline__ const double *rowBi_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 17; }
+__device__ __forceinline__ const double *colI_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 32; }
 
 // ---- P1 ------------------------------------------------------------------------------------------
 // BS: block size of the row pass (2048 or 1024); G = N / BS rows of BS columns
@@ -89,7 +93,7 @@ k_big_cols_fwd(bign_args A) {
             double y[G];
 #pragma unroll
             for (int i = 0; i < G; i++) y[i] = d[i];
-            // as cols_fwd (written out: the compiler schedules the call differently, and the pass takes 1 % longer)
+            // as cols_fwd, written out: the compiler schedules the call differently
 #pragma unroll
             for (int half = G / 2, blocks = 1; half >= 1; half >>= 1, blocks <<= 1) {
 #pragma unroll
@@ -393,13 +397,13 @@ __device__ __forceinline__ void cols_mirror_both(double (&res)[2][G], const bign
         double lo[G / 2], hi[G / 2], ba[G / 2], bb[G / 2];
 #pragma unroll
         for (int i = 0; i < G / 2; i++) { lo[i] = src[1024u * i]; hi[i] = src[1024u * (G / 2 + i)]; ba[i] = bb[i] = 0.51; }
-        cols_mirror<G / 2>(lo, ba, A.tab[q].colI, 0, 2, m);
-        cols_mirror<G / 2>(hi, bb, A.tab[q].colI, 1, 2, m);
+        cols_mirror<G / 2>(lo, ba, colI_of(A.tab[q], G), 0, 2, m);
+        cols_mirror<G / 2>(hi, bb, colI_of(A.tab[q], G), 1, 2, m);
         lazy_limit(lo, ba, LAZY_MAX / 2, m);
         lazy_limit(hi, bb, LAZY_MAX / 2, m);
 #pragma unroll
         for (int i = 0; i < G / 2; i++) {
-            cols_mirror_last(lo[i], hi[i], A.tab[q].colI, m);
+            cols_mirror_last(lo[i], hi[i], colI_of(A.tab[q], G), m);
             res[q][i] = lo[i];
             res[q][G / 2 + i] = hi[i];
         }
@@ -562,7 +566,7 @@ k_big_rows16_team(bign_args A, uint32_t G) {
         }
     }
     double twi[15];
-    const double *gBi = tb.rowBi + (size_t)row * 15 * 64;
+    const double *gBi = rowBi_of(tb, G) + (size_t)row * 15 * 64;
 #pragma unroll
     for (int k = 0; k < 15; k++) twi[k] = ldl(gBi + 64 * k, lane * 8u);
 #pragma unroll
@@ -574,7 +578,7 @@ k_big_rows16_team(bign_args A, uint32_t G) {
 #pragma unroll
         for (int u = 0; u < 8; u++) o[8 * g + u] = r8[u];
     }
-    inv16_mirror(o, T_other, tb.rowAi + (size_t)row * 64, twi, m, lane, z);     // this buffer has no other reader any more
+    inv16_mirror(o, T_other, rowAi_of(tb, G) + (size_t)row * 64, twi, m, lane, z);     // this buffer has no other reader any more
     double *dst = A.Y + (((size_t)b * 2 + q) * 2 + r) * N + 1024u * row;
 #pragma unroll
     for (int g = 0; g < 2; g++) {
@@ -626,7 +630,7 @@ k_big_cols_turn(bign_args A, const uint64_t *__restrict__ acc_in, uint64_t *__re
         const double *src = A.Y + (((size_t)b * 2 + q) * 2 + comp) * N + 1024u * part * H + col;
 #pragma unroll
         for (int i = 0; i < H; i++) { y[i] = src[1024u * i]; bd[i] = 0.51; }
-        cols_mirror<H>(y, bd, A.tab[q].colI, part, 2, m);
+        cols_mirror<H>(y, bd, colI_of(A.tab[q], G), part, 2, m);
         lazy_limit(y, bd, LAZY_MAX / 2, m);
 #pragma unroll
         for (int i = 0; i < H; i++) res[((rot * 2 + q) * G + part * H + i) * 64 + lane] = y[i];
@@ -644,7 +648,7 @@ k_big_cols_turn(bign_args A, const uint64_t *__restrict__ acc_in, uint64_t *__re
         for (int p = 0; p < 2; p++) {
             r[0][p] = res[((rot * 2 + p) * G + j0 + k) * 64 + lane];
             r[1][p] = res[((rot * 2 + p) * G + H + j0 + k) * 64 + lane];
-            cols_mirror_last(r[0][p], r[1][p], A.tab[p].colI, A.mod[p]);
+            cols_mirror_last(r[0][p], r[1][p], colI_of(A.tab[p], G), A.mod[p]);
         }
         lo[k] += slz_crt64(r[0][0], r[0][1], A.mod[1], A.p1inv_mod_p2);
         hi[k] += slz_crt64(r[1][0], r[1][1], A.mod[1], A.p1inv_mod_p2);
@@ -759,7 +763,6 @@ int slz_build_block_tables(slz_ctx *ctx, uint32_t BS, double **dA, double **dB) 
 
 // The tables of the 1024-block kernels in one piece of device memory, per prime: rowA [G][64], rowB [G][15][64], their inverses, and the
 // column constants of the mirrored inverse [32].
-#define BIG16_TAB(G) ((size_t)(G) * 64 * 32 + 32)
 static int build_tables16(slz_ctx *ctx) {
     const uint32_t N = ctx->prm.N, G = N / 1024;
     std::vector<double> nat(N), t(2 * BIG16_TAB(G), 0.0);
@@ -1006,9 +1009,6 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
                     const double *t = ctx->bign16_tab + q * BIG16_TAB(G);
                     a.tab[q].rowA = t;
                     a.tab[q].rowB = t + (size_t)G * 64;
-                    a.tab[q].rowAi = t + (size_t)G * 64 * 16;
-                    a.tab[q].rowBi = t + (size_t)G * 64 * 17;
-                    a.tab[q].colI = t + (size_t)G * 64 * 32;
                 }
                 a.tab[q].inv = ctx->tab[q].inv;
                 a.tab[q].post = ctx->tab[q].post;
