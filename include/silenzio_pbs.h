@@ -82,7 +82,8 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
 #define SLZ_OPT_LARGE_N_LATENCY 5 /* value 1 (default) or 0: on the large-N path with 1024-blocks, calls with few ciphertexts (at most 32 at
                                      N = 32768, 56 at 16384, 96 at 8192, 512 / (N / 1024) below) run every CMux step as two launches of
                                      more, shorter threads instead of three (lower latency, identical results; their second accumulator
-                                     of (k+1) N words per such ciphertext is allocated by the first such call);
+                                     of (k+1) N words per such ciphertext is allocated by the context's first call of any batch size;
+                                     if there is no room for it then, the context keeps to three launches);
                                      0 keeps the throughput kernels at every batch size; SLZ_E_INVALID_ARG without a large-N path */
 
 #define SLZ_OPT_FUSED_PACING 6    /* values 0, 1 and 2, on the N = 2048 fused path: accepted and without effect.  They paced the workgroups of

@@ -214,6 +214,7 @@ static int ensure_generic_scratch(slz_ctx *ctx) {
     if (fresh[1]) ctx->dig = (double *)fresh[1];
     if (fresh[2]) ctx->xhat = (double *)fresh[2];
     if (fresh[3]) ctx->outhat = (double *)fresh[3];
+    if (ctx->has_bign) slz_bign_scratch(ctx);                       // optional: a call succeeds without it
     return SLZ_OK;
 }
 

@@ -940,6 +940,17 @@ uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half)
     return even && batch <= 2 * half ? batch - batch / 2 / unit * unit : 0;
 }
 
+// The second accumulator of the two-launch steps, asked for with the first scratch of a context and never again: a later call allocates
+// nothing, whatever its batch, and may be captured.  Without it a step runs as three launches at every batch size.
+void slz_bign_scratch(slz_ctx *ctx) {
+    if (!ctx->has_bign16 || ctx->bign_spare_asked) return;
+    ctx->bign_spare_asked = 1;
+    const uint32_t lat_max = latency_max_batch(ctx->prm.N / 1024);
+    const size_t cts = ctx->max_batch < lat_max ? ctx->max_batch : lat_max;
+    void *buf = nullptr;
+    if (slz_scratch_alloc(&buf, cts * 2 * ctx->prm.N * sizeof(uint64_t)) == SLZ_OK) ctx->bign_spare = (uint64_t *)buf;
+}
+
 // Runs steps [0, n_steps) on accumulators that the caller has initialised in `acc` ([batch][2][N]).
 int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc,
                         uint32_t batch, hipStream_t s) {
@@ -947,15 +958,9 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     const uint32_t N = p.N, BS = (uint32_t)ctx->bign_block, G = N / BS, R = 2 * p.pbs_level;
     uint32_t logG = 0;
     while ((1u << logG) < G) logG++;
-    // few ciphertexts: every step in two launches (1024-blocks only)
+    // few ciphertexts: every step in two launches (1024-blocks only, and where there was room for the second accumulator)
     const uint32_t lat_max = latency_max_batch(G);
-    const bool lat = ctx->bign_latency && BS == 1024 && batch <= lat_max;
-    if (lat && !ctx->bign_spare) {
-        const size_t cts = ctx->max_batch < lat_max ? ctx->max_batch : lat_max;
-        void *buf = nullptr;
-        if (slz_scratch_alloc(&buf, cts * 2 * N * sizeof(uint64_t)) != SLZ_OK) return SLZ_E_NOMEM;
-        ctx->bign_spare = (uint64_t *)buf;
-    }
+    const bool lat = ctx->bign_latency && BS == 1024 && batch <= lat_max && ctx->bign_spare;
     // Ciphertexts go through all steps in chunks whose workspace (X, Y, accumulators: (2R + 4 + 2) N doubles each) stays
     // in the 256 MB Infinity Cache; the key (read once per chunk and step) streams from HBM.
     const size_t per_ct = (size_t)(2 * R + 4 + 2) * N * 8;

@@ -62,7 +62,8 @@ struct slz_ctx {
     void *bign_lane_stream[2], *bign_lane_done[2], *bign_fork;   // hipStream_t / hipEvent_t of the lanes, created at first use
     int bign_block;           // block size the large-N path uses: 1024 or 2048
     int bign_latency;         // 1: few ciphertexts take the latency-oriented kernels (two launches per step)
-    uint64_t *bign_spare;     // their second accumulator [few ciphertexts][2][N], allocated at first use
+    uint64_t *bign_spare;     // their second accumulator [few ciphertexts][2][N], or null
+    int bign_spare_asked;     // its allocation has been tried
     double *bign16_tab;       // tables of the large-N kernels on 1024-blocks (slz_bign.hip)
     double mirror_last[2][2]; // per prime 1 / N and 1 / (N fwd[1])
     // scratch for the generic path, sized for max_batch
@@ -141,6 +142,7 @@ int slz_fft4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
 int slz_bign_supported(const slz_params *p);
 int slz_bign_init(slz_ctx *ctx);
 void slz_bign_destroy(slz_ctx *ctx);
+void slz_bign_scratch(slz_ctx *ctx);
 int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc,
                         uint32_t batch, hipStream_t s);
 // where a batch is cut between its two lanes (tested on the host)

@@ -986,3 +986,42 @@ def test_large_n_two_launch_steps_match_the_throughput_kernels(slz, orc, N, l, b
     for count in batches:
         got = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts[:count], case.d_luts, case.d_idx[:count], case.d_bsk))
         assert np.array_equal(got, want[:count]), count
+
+
+@pytest.mark.parametrize("N,largest,counts", [(32768, 40, [32, 17, 3]), (16384, 70, [56, 33]), (8192, 100, [96, 65])])
+def test_large_n_calls_after_the_first_allocate_nothing(slz, orc, N, largest, counts):
+    # the first call has a batch of the throughput kernels; smaller ones then take the two-launch steps without an allocation: with the next one
+    # forced to fail, and inside a graph capture
+    p = tiny(n=2, N=N, k=1, pbs_base_log=15, pbs_level=2)
+    case = Case(slz, orc, p, largest, raw_inputs=True)
+    all_cts = case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)
+    for count in counts:
+        d = (case.d_cts[:count].clone(), case.d_luts, case.d_idx[:count], case.d_bsk)
+        case.ctx.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, 0)
+        got = case.ctx.pbs_batch(*d)
+        case.ctx.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, -1)
+        assert torch.equal(got, all_cts[:count]), count
+        out = torch.empty_like(got)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            case.ctx.pbs_batch(*d, out=out)
+        for rep in range(3):
+            d[0].copy_(case.d_cts[rep:rep + count])
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, case.ctx.pbs_batch(*d)), (count, rep)
+        case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)
+
+
+def test_large_n_without_room_for_the_second_accumulator_runs_three_launches(slz, orc):
+    # the fourth allocation of the first call is the second accumulator: the call and those after it are served without, and it is not asked for again
+    p = tiny(n=2, N=4096, k=1, pbs_base_log=11, pbs_level=2)
+    case = Case(slz, orc, p, 3, raw_inputs=True)
+    want = orc.pbs_batch(p, case.cts, case.luts, case.lut_idx, case.keys.bsk)
+    for after in (3, 0):
+        case.ctx.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, after)
+        got = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
+        case.ctx.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, -1)
+        assert np.array_equal(got, want), after
