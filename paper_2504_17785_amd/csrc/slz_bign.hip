@@ -923,8 +923,8 @@ static uint32_t latency_max_batch(uint32_t G) { return G >= 32 ? 32u : G == 16 ?
 // From more than this many on they run as two even halves on the two lanes: N = 32768: 16: 44 either way, 24: 60 -> 57, 32: 75 -> 71;
 // N = 16384: 32: 40 either way, 48: 54 -> 53; N = 8192: 64: 41 -> 43.
 static uint32_t latency_one_lane_max(uint32_t G) { return G >= 16 ? 512u / G : 0xffffffffu; }
-// Ciphertexts of the first of two lanes for a batch past latency_max_batch (1024-blocks); 0: the lanes take chunks of `half`, or one
-// lane takes all.  `half` ciphertexts are 2048 row tasks or more: alone on the chip they fill it, so a smaller batch leaves the chip idle at
+// Ciphertexts of the first of two lanes of the three-launch steps (1024-blocks); 0: the lanes take chunks of `half`, or one
+// lane takes all, as up to 512 / G ciphertexts always (1024 row tasks, a wave for every SIMD).  `half` ciphertexts are 2048 row tasks or more: alone on the chip they fill it, so a smaller batch leaves the chip idle at
 // every hand-over between its launches, which a second lane fills; a batch a little larger would be a full lane and a small rest.  From a
 // quarter above `half` on (G = 2: an eighth) the rest is large enough to hide its launches behind the full lane, while two even halves are
 // one and a half rounds of row tasks each; G >= 16 and the upper part of G = 8 move so much memory per ciphertext that even lanes win.
@@ -937,7 +937,7 @@ static uint32_t latency_one_lane_max(uint32_t G) { return G >= 16 ? 512u / G : 0
 uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half) {
     const bool even = batch <= half + half / (G == 2 ? 8 : 4) || G >= 16 || (G == 8 && batch >= half + half * 5 / 8);
     const uint32_t unit = G == 4 || G == 8 ? 16 / G : 1;
-    return even && batch <= 2 * half ? batch - batch / 2 / unit * unit : 0;
+    return even && batch > 512 / G && batch <= 2 * half ? batch - batch / 2 / unit * unit : 0;
 }
 
 // The second accumulator of the two-launch steps, asked for with the first scratch of a context and never again: a later call allocates
@@ -979,7 +979,7 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     } else if (lanes >= 2) {
         uint32_t half = chunk / 2 / fill * fill;
         if (half < fill) half = fill;
-        const uint32_t first = BS == 1024 && batch > lat_max ? slz_bign_first_of_even_lanes(G, batch, half) : 0;
+        const uint32_t first = BS == 1024 ? slz_bign_first_of_even_lanes(G, batch, half) : 0;
         if (first) chunk = first;
         else if (batch > half) chunk = half;
         else lanes = 1;

@@ -231,6 +231,7 @@ def test_large_n_lanes_are_cut_where_it_wins_and_keep_the_order_of_the_row_pass(
     # an internal host function, by its mangled name: ciphertexts of the first lane for a batch past half / 2, 0: not even
     f = slz.lib()._Z28slz_bign_first_of_even_lanesjjj
     f.argtypes, f.restype = [ctypes.c_uint32] * 3, ctypes.c_uint32
+    assert not any(f(G, b, half) for b in range(1, 512 // G + 1)) and half // 2 == 512 // G
     unit = 16 // G if G in (4, 8) else 1                    # what the XCD-aware order takes: batch * 2 G a multiple of 32
     got = {b: f(G, b, half) for b in range(half // 2 + 1, 2 * half + 8)}
     for b, first in got.items():

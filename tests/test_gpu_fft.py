@@ -178,3 +178,36 @@ def test_large_n_graph_gets_both_lanes_whatever_the_context_ran_before(slz, batc
             torch.cuda.synchronize()
             assert torch.equal(out, ctx.pbs_batch(d_in, d_luts, None, d_key)), (warm, rep)
     assert nodes[20] == nodes[batch] >= 2 * 3 * p.n          # three kernels a step and lane, and the accumulators' start and extraction
+
+
+# Without the two-launch steps 33 to 56 ciphertexts of N = 16384 (and 17 to 32 of 32768, 65 to 96 of 8192) are two even halves on the two lanes
+@pytest.mark.parametrize("N,batch,lanes", [(16384, 32, 1), (16384, 33, 2), (16384, 49, 2), (32768, 17, 2), (8192, 66, 2)])
+def test_large_n_three_launch_steps_get_both_lanes_at_every_batch_that_had_them(slz, N, batch, lanes):
+    import ctypes
+    p = synth.CONFIGS[2].with_(name="halves", N=N, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", p.n * 8 * p.N).reshape(p.n, 2, 2, 2, p.N)
+    d_luts = slz.to_device_u64(synth.raw_words(p, "misc", p.N).reshape(1, p.N))
+    d_in = slz.to_device_u64(synth.raw_words(p, "raw_ct", batch * (p.n + 1)).reshape(batch, p.n + 1))
+    ctx = slz.Context(p, batch)
+    d_key = ctx.bsk_prepare(slz.to_device_u64(bsk))
+    want = ctx.pbs_batch(d_in, d_luts, None, d_key)
+    out = torch.empty_like(want)
+    ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
+    nodes = {}
+    for option in (1, 2):
+        ctx.set_option(slz.SLZ_OPT_LARGE_N_LANES, option)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            ctx.pbs_batch(d_in, d_luts, None, d_key, out=out)
+        count = ctypes.c_size_t(0)
+        assert slz.lib().hipGraphGetNodes(ctypes.c_void_p(int(graph.raw_cuda_graph())), None, ctypes.byref(count)) == 0
+        nodes[option] = count.value
+        graph.instantiate()
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+            assert torch.equal(ctx.pbs_batch(d_in, d_luts, None, d_key), want)
+    assert nodes[2] - nodes[1] == (lanes - 1) * 3 * p.n
