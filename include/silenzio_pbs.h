@@ -79,8 +79,8 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      overlaps the memory-bound column passes of the other; results are identical);
                                      SLZ_E_INVALID_ARG when the context has no large-N path */
 
-#define SLZ_OPT_LARGE_N_LATENCY 5 /* value 1 (default) or 0: on the large-N path with 1024-blocks, calls with few ciphertexts (at most 32 at
-                                     N = 32768, 56 at 16384, 96 at 8192, 512 / (N / 1024) below) run every CMux step as two launches of
+#define SLZ_OPT_LARGE_N_LATENCY 5 /* value 1 (default) or 0: on the large-N path with 1024-blocks, calls with few ciphertexts (pbs_level 2:
+                                     at most 32 at N = 32768, 56 at 16384, 96 at 8192, 512 / (N / 1024) below; fewer with more levels) run every CMux step as two launches of
                                      more, shorter threads instead of three (lower latency, identical results; their second accumulator
                                      of (k+1) N words per such ciphertext is allocated by the context's first call of any batch size;
                                      if there is no room for it then, the context keeps to three launches);

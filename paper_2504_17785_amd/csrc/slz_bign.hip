@@ -914,12 +914,25 @@ static int ensure_lanes(slz_ctx *ctx) {
     return SLZ_OK;
 }
 
-// Ciphertexts up to which a step runs as the two launches above.  us per CMux step, three launches per step -> two (l = 2 unless said):
-//   N = 32768: 1: 34 -> 22, 4: 39 -> 25, 8: 41 -> 33, 16: 53 -> 44, 24: 74 -> 57, 32: 79 -> 71, 48: 101 -> 103
-//   N = 16384: 8: 34 -> 21, 32: 50 -> 40, 48: 61 -> 53, 56: 64 -> 62, 64: 68 -> 69     N = 8192: 64: 50 -> 41, 96: 58 -> 56, 112: 60 -> 64; l = 1: 112: 48 -> 49
-//   N = 4096: 64: 32 -> 27, 128: 48 -> 38; l = 3: 64: 39 -> 36, 128: 60 -> 60          N = 2048: 256: 50 -> 38; l = 3: 192: 57 -> 47, 256: 63 -> 59
+// Ciphertexts up to which a step runs as the two launches above.  us per CMux step, three launches per step (as they were: with kernels of their
+// own for few ciphertexts, up to 512 / G) -> two; l = 2:
+//   N = 32768: 1: 34 -> 22, 4: 39 -> 25, 8: 41 -> 33, 16: 53 -> 44, 24: 73 -> 56, 32: 78 -> 70, 48: 101 -> 103
+//   N = 16384: 8: 34 -> 21, 32: 50 -> 40, 48: 61 -> 53, 56: 63 -> 59, 64: 68 -> 69     N = 8192: 64: 50 -> 41, 96: 57 -> 56, 112: 60 -> 64
+//   N = 4096: 64: 32 -> 27, 128: 48 -> 38     N = 2048: 256: 50 -> 38
 // Past that the column work done twice costs more than the launch and the accumulator's traffic that it saves.
-static uint32_t latency_max_batch(uint32_t G) { return G >= 32 ? 32u : G == 16 ? 56u : G == 8 ? 96u : 512u / G; }
+// l = 1: N = 32768: 32: 61 -> 50     N = 16384: 48: 47 -> 43, 49: 47 -> 43, 50: 46.4 -> 46.1 (three of today: 44.8 to 46.5), 56: 47.5 -> 48     N = 8192: 96: 46 -> 42.5, 112: 48 -> 49
+// l = 3, 4: a workgroup of the row pass is six or eight waves, of which a compute unit takes two or one, so the step grows by rounds of 512 or 256
+// workgroups, 2 G per ciphertext.  G <= 8: one round of l = 3 and three of l = 4 win, three launches of today / two:
+//   l = 3: N = 2048: 192: 43.9 / 46.1     N = 4096: 64: 44.9 / 35.3, 96: 46.3 / 47.0     N = 8192: 32: 45.9 / 38.0, 40: 46.4 / 48.2, 64: 49.8 / 62.9
+//   l = 4: N = 2048: 192: 51.7 / 52.6, 224: 53.5 / 64.7     N = 4096: 96: 54.8 / 53.1, 104: 56.3 / 64.9     N = 8192: 48: 55.7 / 54.7, 52: 56.1 / 67.0
+// G >= 16:
+//   l = 3: N = 16384: 24: 52 / 50, 32: 55 / 61, 33: 70.5 / 62, 40: 72.6 / 71.9, 42: 73 / 80     N = 32768: 16: 70 / 67, 20: 88 / 84, 22: 87 / 85, 24: 88 / 92
+//   l = 4: N = 16384: 24: 61 / 56, 32: 64 / 70, 33: 84 / 76, 40: 86 / 83, 42: 87 / 91     N = 32768: 16: 81 / 77, 20: 99 / 94, 22: 102.5 / 99.7, 24: 104 / 106
+uint32_t slz_bign_latency_max_batch(uint32_t G, uint32_t l) {
+    if (l <= 2) return G >= 32 ? 32u : G == 16 ? (l == 1 ? 49u : 56u) : G == 8 ? 96u : 512u / G;
+    if (G >= 16) return G == 16 ? 40u : 22u;
+    return (l == 3 ? 256u : 384u) / G;
+}
 // From more than this many on they run as two even halves on the two lanes: N = 32768: 16: 44 either way, 24: 60 -> 57, 32: 75 -> 71;
 // N = 16384: 32: 40 either way, 48: 54 -> 53; N = 8192: 64: 41 -> 43.
 static uint32_t latency_one_lane_max(uint32_t G) { return G >= 16 ? 512u / G : 0xffffffffu; }
@@ -945,7 +958,7 @@ uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half)
 void slz_bign_scratch(slz_ctx *ctx) {
     if (!ctx->has_bign16 || ctx->bign_spare_asked) return;
     ctx->bign_spare_asked = 1;
-    const uint32_t lat_max = latency_max_batch(ctx->prm.N / 1024);
+    const uint32_t lat_max = slz_bign_latency_max_batch(ctx->prm.N / 1024, ctx->prm.pbs_level);
     const size_t cts = ctx->max_batch < lat_max ? ctx->max_batch : lat_max;
     void *buf = nullptr;
     if (slz_scratch_alloc(&buf, cts * 2 * ctx->prm.N * sizeof(uint64_t)) == SLZ_OK) ctx->bign_spare = (uint64_t *)buf;
@@ -959,8 +972,7 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     uint32_t logG = 0;
     while ((1u << logG) < G) logG++;
     // few ciphertexts: every step in two launches (1024-blocks only, and where there was room for the second accumulator)
-    const uint32_t lat_max = latency_max_batch(G);
-    const bool lat = ctx->bign_latency && BS == 1024 && batch <= lat_max && ctx->bign_spare;
+    const bool lat = ctx->bign_latency && BS == 1024 && batch <= slz_bign_latency_max_batch(G, p.pbs_level) && ctx->bign_spare;
     // Ciphertexts go through all steps in chunks whose workspace (X, Y, accumulators: (2R + 4 + 2) N doubles each) stays
     // in the 256 MB Infinity Cache; the key (read once per chunk and step) streams from HBM.
     const size_t per_ct = (size_t)(2 * R + 4 + 2) * N * 8;

@@ -145,7 +145,8 @@ void slz_bign_destroy(slz_ctx *ctx);
 void slz_bign_scratch(slz_ctx *ctx);
 int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc,
                         uint32_t batch, hipStream_t s);
-// where a batch is cut between its two lanes (tested on the host)
+// largest batch of the two-launch steps, and where a batch is cut between its two lanes (tested on the host)
+uint32_t slz_bign_latency_max_batch(uint32_t G, uint32_t l);
 uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half);
 // keyswitch / lincomb (slz_keyswitch.hip)
 int slz_keyswitch_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *ksk, uint64_t *lwe_out,

@@ -251,6 +251,15 @@ def test_large_n_lanes_are_cut_where_it_wins_and_keep_the_order_of_the_row_pass(
     assert not any(got[b] for b in got if b > 2 * half)
 
 
+def test_large_n_two_launch_steps_end_where_they_stop_winning():
+    # by G = N / 1024 and levels; a step of more levels has fewer and larger workgroups, which stop winning earlier
+    f = slz.lib()._Z26slz_bign_latency_max_batchjj
+    f.argtypes, f.restype = [ctypes.c_uint32] * 2, ctypes.c_uint32
+    want = {1: {8: 96, 16: 49, 32: 32}, 2: {2: 256, 4: 128, 8: 96, 16: 56, 32: 32}, 3: {2: 128, 4: 64, 8: 32, 16: 40, 32: 22},
+            4: {2: 192, 4: 96, 8: 48, 16: 40, 32: 22}}
+    assert {l: {G: f(G, l) for G in row} for l, row in want.items()} == want
+
+
 def test_bench_counts_the_key_form_and_the_operations_of_the_path_that_runs():
     import sys
     sys.path.insert(0, ROOT)

@@ -211,3 +211,34 @@ def test_large_n_three_launch_steps_get_both_lanes_at_every_batch_that_had_them(
             assert torch.equal(out, want)
             assert torch.equal(ctx.pbs_batch(d_in, d_luts, None, d_key), want)
     assert nodes[2] - nodes[1] == (lanes - 1) * 3 * p.n
+
+
+# The largest batch of the two-launch steps and one past it, by the kernels of a captured call: 2 n + 1 a lane against 3 n, and the accumulators'
+# start and extraction
+@pytest.mark.parametrize("N,l,beta,last,lanes", [(2048, 3, 12, 128, 1), (2048, 4, 12, 192, 1), (4096, 3, 12, 64, 1), (4096, 4, 12, 96, 1), (8192, 1, 20, 96, 1),
+                                                 (8192, 3, 12, 32, 1), (8192, 4, 10, 48, 1), (16384, 1, 20, 49, 2), (16384, 2, 15, 56, 2), (16384, 3, 12, 40, 2),
+                                                 (32768, 3, 12, 22, 2), (32768, 4, 10, 22, 2)])
+def test_large_n_two_launch_steps_up_to_their_line(slz, N, l, beta, last, lanes):
+    import ctypes
+    n, batch = 3, last + 1
+    p = synth.CONFIGS[2].with_(name="line", N=N, n=n, pbs_level=l, pbs_base_log=beta, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", n * 4 * l * N).reshape(n, 2, l, 2, N)
+    d_luts = slz.to_device_u64(synth.raw_words(p, "misc", N).reshape(1, N))
+    d_in = slz.to_device_u64(synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1))
+    ctx = slz.Context(p, batch)
+    d_key = ctx.bsk_prepare(slz.to_device_u64(bsk))
+    ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)
+    want = ctx.pbs_batch(d_in, d_luts, None, d_key)
+    ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 0)
+    past = 2 if batch > 512 // (N // 1024) else 1                      # lanes of the three-launch steps
+    for count, kernels in ((last, lanes * (2 * n + 1)), (last + 1, past * 3 * n)):
+        out = torch.empty((count, N + 1), dtype=torch.int64, device="cuda")
+        ctx.pbs_batch(d_in[:count], d_luts, None, d_key, out=out)
+        assert torch.equal(out, want[:count]), count
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            ctx.pbs_batch(d_in[:count], d_luts, None, d_key, out=out)
+        nodes = ctypes.c_size_t(0)
+        assert slz.lib().hipGraphGetNodes(ctypes.c_void_p(int(graph.raw_cuda_graph())), None, ctypes.byref(nodes)) == 0
+        assert nodes.value == kernels + 2, count

@@ -968,7 +968,7 @@ def test_lookup_replays_from_a_hip_graph(slz, orc, shape, batch):
 @pytest.mark.parametrize("N,l,beta,n,batches", [
     (2048, 2, 12, 1, [1, 256]),             # G = 2, a thread per column; one step: no column pass between two row passes
     (2048, 4, 7, 2, [3]),                   # eight GGSW rows per team
-    (4096, 3, 11, 3, [2, 128]),             # G = 4, six rows
+    (4096, 3, 11, 3, [2, 64]),              # G = 4, six rows
     (8192, 1, 20, 2, [1, 5, 96]),           # G = 8, eight waves per 64 columns, two rows; five ciphertexts: pairs split over the XCDs
     (8192, 3, 12, 3, [4]),                  # three levels over eight waves
     (16384, 2, 15, 3, [3, 32, 33, 56]),     # G = 16; one lane up to 32
