@@ -128,9 +128,10 @@ def test_fft4096_states_and_outputs_match_generic_path_and_oracle(slz, orc, batc
     assert torch.equal(out0, ctx.pbs_batch(d[0], d[1], None, d[3]))
 
 
-# N = 16384: one lane up to 32 ciphertexts, two even halves from 33 to 128, halves of 64 past that.  N = 8192: even lanes from 65 to 160
-# and from 208 to 256, a lane of 128 and the rest in between; N = 4096: even lanes from 129 to 320, then a lane of 256 and the rest.
-@pytest.mark.parametrize("N,batch", [(16384, 32), (16384, 33), (16384, 49), (16384, 128), (16384, 129), (8192, 66), (8192, 67), (8192, 161),
+# Three launches per step.  N = 16384: one lane up to 32 ciphertexts, two even halves from 33 to 128, halves of 64 past that.  N = 8192: even
+# lanes from 65 to 160 and from 208 to 256, a lane of 128 and the rest in between; N = 4096: even lanes from 129 to 320, then a lane of 256 and
+# the rest.  By default up to 56 ciphertexts of N = 16384 and 96 of N = 8192 take two launches per step, so every size runs without them as well.
+@pytest.mark.parametrize("N,batch", [(16384, 32), (16384, 33), (16384, 49), (16384, 128), (16384, 129), (8192, 66), (8192, 67), (8192, 98), (8192, 99), (8192, 161),
                                      (8192, 208), (4096, 129), (4096, 134), (4096, 321)])
 def test_large_n_halves_match_one_lane_and_oracle(slz, orc, N, batch):
     p = synth.CONFIGS[2].with_(name="halves", N=N, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
@@ -141,17 +142,19 @@ def test_large_n_halves_match_one_lane_and_oracle(slz, orc, N, batch):
     assert ctx.path == "three_pass_large_n"
     d = [slz.to_device_u64(cts), slz.to_device_u64(luts), None, ctx.bsk_prepare(slz.to_device_u64(bsk))]
     got = [ctx.pbs_batch(*d) for _ in range(3)]
-    ctx.set_option(slz.SLZ_OPT_LARGE_N_LANES, 1)
     ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
+    got += [ctx.pbs_batch(*d) for _ in range(3)]
+    ctx.set_option(slz.SLZ_OPT_LARGE_N_LANES, 1)
     want = ctx.pbs_batch(*d)
     assert all(torch.equal(g, want) for g in got)
     idx = np.array([0, batch // 2 - 1, (batch + 1) // 2, batch - 1])
     assert np.array_equal(slz.to_host_u64(want)[idx], orc.pbs_batch(p, cts[idx], luts, np.zeros(4, np.uint32), bsk))
 
 
-# One lane up to 32 ciphertexts, so a context that has only seen 20 has no lane streams when the capture begins
-@pytest.mark.parametrize("batch", [49, 65])
-def test_large_n_graph_gets_both_lanes_whatever_the_context_ran_before(slz, batch):
+# One lane up to 32 ciphertexts, so a context that has only seen 20 has no lane streams when the capture begins.  Kernels a lane: 49 ciphertexts
+# take two a step and one at the end, 65 three a step.
+@pytest.mark.parametrize("batch,kernels", [(49, 5), (65, 6)])
+def test_large_n_graph_gets_both_lanes_whatever_the_context_ran_before(slz, batch, kernels):
     import ctypes
     p = synth.CONFIGS[2].with_(name="halves", N=16384, n=2, pbs_level=2, pbs_base_log=15, msg_bits=3, batch=batch)
     bsk = synth.raw_words(p, "raw_bsk", p.n * 8 * p.N).reshape(p.n, 2, 2, 2, p.N)
@@ -177,7 +180,7 @@ def test_large_n_graph_gets_both_lanes_whatever_the_context_ran_before(slz, batc
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(out, ctx.pbs_batch(d_in, d_luts, None, d_key)), (warm, rep)
-    assert nodes[20] == nodes[batch] >= 2 * 3 * p.n          # three kernels a step and lane, and the accumulators' start and extraction
+    assert nodes[20] == nodes[batch] == 2 * kernels + 2      # two lanes, the accumulators' start and extraction
 
 
 # Without the two-launch steps 33 to 56 ciphertexts of N = 16384 (and 17 to 32 of 32768, 65 to 96 of 8192) are two even halves on the two lanes

@@ -738,8 +738,8 @@ def test_large_n_path_matches_oracle_and_generic(slz, orc, shape, block):
     want = orc.pbs_batch(p, case.cts, case.luts, case.lut_idx, case.keys.bsk)
     got = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
     assert np.array_equal(got, want)
-    # five ciphertexts on 1024-blocks took the latency-oriented kernels (four launches per step); the same call on the
-    # throughput kernels, after one more step count on them
+    # five ciphertexts on 1024-blocks took the two-launch steps; the same call on the throughput kernels, after one more
+    # step count on them
     case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
     assert np.array_equal(slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)), want)
     one = slz.to_host_u64(case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, 1))
@@ -749,19 +749,19 @@ def test_large_n_path_matches_oracle_and_generic(slz, orc, shape, block):
     assert np.array_equal(gen, want)
 
 
-def test_large_n_latency_kernels_at_their_largest_batch_and_one_past_it(slz, orc):
-    # N = 8192 on 1024-blocks: up to 1024 / 16 = 64 ciphertexts take the latency-oriented kernels (up to 16 with the row pass
-    # in two launches, above that in one launch of one-component tasks), 65 the throughput ones; a ciphertext's result must
-    # not depend on which
-    p = tiny(n=2, N=8192, k=1, pbs_base_log=15, pbs_level=2)
-    case = Case(slz, orc, p, 65, raw_inputs=True)
+@pytest.mark.parametrize("N,last", [(8192, 96), (16384, 56)])
+def test_large_n_latency_kernels_at_their_largest_batch_and_one_past_it(slz, orc, N, last):
+    # two levels on 1024-blocks: up to 96 ciphertexts of N = 8192 and 56 of N = 16384 take the two-launch steps (N = 16384: one lane up to 32, two
+    # above), one more the throughput kernels; a ciphertext's result must not depend on which
+    p = tiny(n=2, N=N, k=1, pbs_base_log=15, pbs_level=2)
+    case = Case(slz, orc, p, last + 1, raw_inputs=True)
     assert case.ctx.path == "three_pass_large_n"
-    all65 = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
-    for count in (64, 17, 16, 1):
+    every = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
+    for count in (last, 33, 32, 17, 1):
         part = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts[:count], case.d_luts, case.d_idx[:count], case.d_bsk))
-        assert np.array_equal(part, all65[:count]), count
-    idx = np.array([0, 15, 16, 63, 64])
-    assert np.array_equal(all65[idx], orc.pbs_batch(p, case.cts[idx], case.luts, case.lut_idx[idx], case.keys.bsk))
+        assert np.array_equal(part, every[:count]), count
+    idx = np.array([0, 31, 32, last - 1, last])
+    assert np.array_equal(every[idx], orc.pbs_batch(p, case.cts[idx], case.luts, case.lut_idx[idx], case.keys.bsk))
     with pytest.raises(slz.SlzError):
         case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 2)
 
