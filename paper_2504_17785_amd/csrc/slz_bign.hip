@@ -794,7 +794,11 @@ static bool bounds_ok(uint32_t N, uint32_t BS) {
     if (0.5 + 4.0 * slz_mulmod_bound(a) > 7.5) return false;
     a = 0.5 + 1e-9;
     for (uint32_t g = G; g > 1; g >>= 1) a += slz_mulmod_bound(a);
-    return slz_mulmod_bound(a) <= 1.95;
+    if (slz_mulmod_bound(a) > 1.95) return false;
+    // 1024-blocks: the mirrored inverse counts products by a constant form of the bound (slz_wave_ntt.h)
+    for (double s = 0.5; BS == 1024 && s < LAZY_MAX; s += 0.1)
+        if (slz_mulmod_bound(s) > LAZY_PRODUCT(s)) return false;
+    return true;
 }
 
 int slz_bign_init(slz_ctx *ctx) {

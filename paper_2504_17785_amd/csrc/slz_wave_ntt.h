@@ -433,12 +433,16 @@ __device__ __forceinline__ void inv16(double (&x)[16], double *T, const double *
 }
 
 // ---- the mirrored inverse ----------------------------------------------------------------------------------------------
-// Inverse as the forward transform run backwards: (a, b) -> (a + b, (a - b) / w) with the twiddle w of the forward butterfly, N times
+// Inverse as the forward transform run backwards, by Gentleman-Sande butterflies: (a, b) -> (a + b, (a - b) / w) with the twiddle w of the forward butterfly, N times
 // the inverse in all.  Its twiddles depend on the block and not on the position inside it, so the column passes of the large-N path need a
 // handful of uniform constants and no twist, where the decimation-in-time form above reads 63 table words per column of 32.
 // Sums grow by doubling: every value carries a bound (in units of p; constants once the loops are unrolled), and a pair is reduced
 // where its sum could pass LAZY_MAX.
 #define LAZY_MAX 7.4
+#define LAZY_PRODUCT(s) (0.5 + 0.1875 * (s) + 1e-9)                // slz_mulmod_bound as a constant: 1.5 p 2^-53 < 0.1875 for p < 2^50
+static_assert(SLZ_P1_U64 < (1ull << 50) && SLZ_P2_U64 < (1ull << 50), "LAZY_PRODUCT");
+static_assert(LAZY_MAX <= 7.5, "integers stay below 2^53");
+static_assert(LAZY_PRODUCT(LAZY_MAX) <= 1.95, "the lift takes the products of the last column stage");
 // K independent pairs, interleaved like bfly_k
 template <int K>
 __device__ __forceinline__ void gs_k(double *(&a)[K], double *(&b)[K], double *(&ba)[K], double *(&bb)[K], const double (&w)[K], slz_mod m) {
@@ -450,7 +454,7 @@ __device__ __forceinline__ void gs_k(double *(&a)[K], double *(&b)[K], double *(
         if (*ba[i] + *bb[i] > LAZY_MAX) { *a[i] = slz_reduce(*a[i], m); *ba[i] = 0.5 + 1e-9; }
         const double s = *ba[i] + *bb[i];
         *ba[i] = s;
-        *bb[i] = 0.5 + 0.1875 * s + 1e-9;                          // slz_mulmod_bound
+        *bb[i] = LAZY_PRODUCT(s);
     }
 #pragma unroll
     for (int i = 0; i < K; i++) d[i] = *a[i] - *b[i];
@@ -469,7 +473,7 @@ __device__ __forceinline__ void gs_k(double *(&a)[K], double *(&b)[K], double *(
 #pragma unroll
     for (int i = 0; i < K; i++) *b[i] = h[i] + l[i];
 }
-// eight values stay below `limit` (units of p) from here on
+// K values stay below `limit` (units of p) from here on
 template <int K>
 __device__ __forceinline__ void lazy_limit(double (&x)[K], double (&bd)[K], double limit, slz_mod m) {
 #pragma unroll
