@@ -35,7 +35,7 @@ struct bign_args {
     double *X;                     // [batch][2 primes][R][N]
     double *Y;                     // [batch][2 primes][2][N]
     const double *bskp_step;       // prepared GGSW of this step: [2][R][2][N]
-    uint32_t n, step, N, logG, beta, l, batch;
+    uint32_t n, step, N, beta, l, batch;
     bign_tabs tab[2];
     slz_mod mod[2];
     double p1inv_mod_p2;
@@ -55,8 +55,8 @@ __device__ __forceinline__ void cols_fwd(double (&y)[G], const double *tw, slz_m
     }
 }
 
-// 1024-blocks: the tables of the mirrored inverse follow rowA [G][64] and rowB [G][15][64] in memory (BIG16_TAB), so the arguments of the
-// throughput kernels do not grow by them: inverses of rowA and of rowB, and the column stages' [32]: inverses of fwd[2 .. G - 1], [0] = 1 / N,
+// 1024-blocks: the tables of the mirrored inverse follow rowA [G][64] and rowB [G][15][64] in memory (BIG16_TAB), one allocation
+// and one copy for all: inverses of rowA and of rowB, and the column stages' [32]: inverses of fwd[2 .. G - 1], [0] = 1 / N,
 // [1] = 1 / (N fwd[1])
 #define BIG16_TAB(G) ((size_t)(G) * 64 * 32 + 32)
 __device__ __forceinline__ const double *rowAi_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 16; }
@@ -93,7 +93,8 @@ k_big_cols_fwd(bign_args A) {
             double y[G];
 #pragma unroll
             for (int i = 0; i < G; i++) y[i] = d[i];
-            // as cols_fwd, written out: the compiler schedules the call differently
+            // as cols_fwd, written out: with the call the compiler orders the stages' instructions differently, N = 32768, 256 ciphertexts 506.7 to
+            // 507.9 us per step against 504.3 to 507.0, 64: 127.2 to 128.3 against 127.0 to 128.0
 #pragma unroll
             for (int half = G / 2, blocks = 1; half >= 1; half >>= 1, blocks <<= 1) {
 #pragma unroll
@@ -973,8 +974,6 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
                         uint32_t batch, hipStream_t s) {
     const slz_params &p = ctx->prm;
     const uint32_t N = p.N, BS = (uint32_t)ctx->bign_block, G = N / BS, R = 2 * p.pbs_level;
-    uint32_t logG = 0;
-    while ((1u << logG) < G) logG++;
     // few ciphertexts: every step in two launches (1024-blocks only, and where there was room for the second accumulator)
     const bool lat = ctx->bign_latency && BS == 1024 && batch <= slz_bign_latency_max_batch(G, p.pbs_level) && ctx->bign_spare;
     // Ciphertexts go through all steps in chunks whose workspace (X, Y, accumulators: (2R + 4 + 2) N doubles each) stays
@@ -1020,7 +1019,7 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
             a.acc = acc + (size_t)c0 * 2 * N;
             a.X = ctx->xhat + (size_t)j * chunk * 2 * R * N;
             a.Y = ctx->outhat + (size_t)j * chunk * 2 * 2 * N;
-            a.n = p.n; a.N = N; a.logG = logG; a.beta = p.pbs_base_log; a.l = p.pbs_level; a.batch = nb;
+            a.n = p.n; a.N = N; a.beta = p.pbs_base_log; a.l = p.pbs_level; a.batch = nb;
             for (int q = 0; q < 2; q++) {
                 a.tab[q].fwd = ctx->tab[q].fwd;
                 if (BS == 2048) {

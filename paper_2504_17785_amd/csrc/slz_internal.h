@@ -151,7 +151,7 @@ uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half)
 // keyswitch / lincomb (slz_keyswitch.hip)
 int slz_keyswitch_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *ksk, uint64_t *lwe_out,
                          uint32_t batch, hipStream_t s);
-// matrix-core keyswitch (slz_keyswitch_mfma.hip); lwe_out must already hold (0, .., 0, b')
+// matrix-core keyswitch (slz_keyswitch_mfma.hip); slz_ksm_launch writes every word of lwe_out
 int slz_ksm_supported(const slz_params *p);
 void slz_ksm_destroy(slz_ctx *ctx);
 int slz_ksm_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *ksk, const void *kskp, uint64_t *lwe_out, uint32_t batch,
