@@ -25,6 +25,8 @@
 //  same with a already multiplied by a plain complex factor (2.71 u, not above the 3 u of the other operand), and the second
 //  half of its outputs is turned by 45 degrees: an addition and the constant sqrt(1/2) (1.61 u; the product itself is inside the
 //  fused rounding add).  1 + 1 + 2.61 + 6 * 4 + 4 + 1.61 = 34.22 u, and TABLE for each of the seven stages with table twiddles.
+//  With eight waves per ciphertext (slz_fft2048_team.hip) the forward layers are the same, and half-sizes 4 and 8 are one radix-4 layer
+//  (on a path one product, 2.7072 u and TABLE, and two additions): 1 + 1 + 4.7072 + 6 * 4 + 1.61 = 32.32 u and seven times TABLE, below.
 //  Second-order terms are covered by the factor 1 + 2^-40.
 // Every row r contributes ||d_r|| ||K_(r,j)||.  The chain of four constants above is for two rows.
 // N = 1024, M = 512: the forward layers are radix-2 butterflies of the inverse's form, at most 4 u and TABLE each relative to the 2-norm

@@ -1,5 +1,6 @@
 // Blind rotation for N = 2048, k = 1, l = 1 with eight waves on one ciphertext, for batches of a few ciphertexts per compute unit
-// (slz_fft2048.hip: one pair of waves per ciphertext).  Key, error bound and arithmetic are those of slz_fft2048.hip.
+// (slz_fft2048.hip: one pair of waves per ciphertext).  Key and arithmetic are those of slz_fft2048.hip; its
+// inverse rounds less (slz_fft.hip), so the error bound of that kernel covers it.
 //
 // Four waves share each component: wave (h, g) keeps a quarter of component h of the accumulator (four points, eight words per lane) and
 // transforms it together with the other three; between the transforms it holds the spectra of both components at quarter g of the
