@@ -127,8 +127,8 @@ k_fft1024_blind_rotate(fft1024_args A) {
                     else __builtin_amdgcn_s_setprio(2);
                     fft_signal(progress + 4u * wave, tick);
                 }
-                // the helper, younger on its SIMD than the front, has three pieces to the front's two: 777 ciphertexts 12.7 us per step with, 13.6
-                // without (SHARE = 4, where the front's chain is the longer one: 400 ciphertexts 10.1 with, 9.6 without)
+                // the helper, younger on its SIMD than the front, has three pieces to the front's two: 630 steps of 513 ciphertexts 7.4 ms with,
+                // 8.5 without, 777: 7.7 and 8.5, 1024: 8.3 and 8.6 (SHARE = 4, where the front's chain is the longer one: 400 ciphertexts 10.1 with, 9.6 without)
                 if (SHARE == 2 && !front) __builtin_amdgcn_s_setprio(2);
                 const d2 *kp = A.key + (size_t)step * F10_KEY_STEP + FIRST * 2048u + z;
                 d2 kb[8][4];

@@ -133,7 +133,8 @@ k_fft_blind_rotate(fft_args A) {
                     if ((int32_t)(seq - (uint32_t)__builtin_amdgcn_readfirstlane(fft_peek(flags + 4u * (wave ^ 4u)))) > 0) __builtin_amdgcn_s_setprio(0);
                     else __builtin_amdgcn_s_setprio(2);
                 }
-                // the owner's front and two pieces are the longer chain: 301 ciphertexts 16.0 us per step with, 16.8 without
+                // the owner's front and two pieces are the longer chain: 742 steps of 257 ciphertexts 11.5 ms with, 12.4 without, 301: 11.4 and
+                // 12.3, 512: 11.6 and 12.6
                 if (SHARED && owner) __builtin_amdgcn_s_setprio(2);
                 const d2 *kp = A.key + (size_t)step * FFT_KEY_STEP + h * 2048u + z;
                 d2 kb[8][4];

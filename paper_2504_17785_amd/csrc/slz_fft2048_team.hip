@@ -11,11 +11,11 @@
 //   F1, I5: b9 b8 / b5..b0 / b7 b6          F2, I4: b7 b6 / b5..b0 / b9 b8                   F3, I3: b5 b4 / b7 b6 b3 b2 b1 b0 / b9 b8
 //   F4, I2: b3 b2 / b7 b6 b5 b4 b1 b0 / b9 b8     F5, I1: b1 b0 / b7..b2 / b9 b8
 // Only F1 -> F2, F4 -> F5 (across the components) and I4 -> I5 cross waves.  A wave's buffer holds the 256 points with the same b9 b8; a
-// point sits at 17 * A + B (16-byte slots) with four bits each, so that 16 neighbouring lanes touch 16 different columns when writing and
-// when reading:
+// point sits at 17 * A + B (16-byte slots) with four bits each, by which 16 neighbouring lanes touch 16 different columns when writing and
+// when reading (the counter still shows conflicts, see below):
 //   F4 -> F5, I1 -> I2: A = b7 b6 b3 b2, B = b5 b4 b1 b0            all others: A = b5 b4 b7 b6, B = b3 b2 b1 b0
-// What bounds it: of 20 k cycles per step 12.5 k issue vector instructions on every SIMD (1 490 per wave), and the LDS needs about 13 k for
-// 88 writes (13 cycles each) and 120 reads per wave; key words (320 KiB per step and ciphertext) stream in four loads at a time, because more
+// What bounds it: of 22 k cycles per step 13 k issue vector instructions on every SIMD (1 475 per wave), and the LDS is busy for 14 k with 251
+// instructions per wave, 3.3 k of them counted as bank conflicts (of which accesses is not known); key words (320 KiB per step and ciphertext) stream in four loads at a time, because more
 // of them together hold the wave (10.5 us per step with 24 at once, 9.8 spread out).  Twiddles of three passes stay in registers (9.7 -> 9.5);
 // of the two waves on a SIMD the one behind gets the priority (10.3 without).  Measured, us per step (in brackets: two pairs of waves doing
 // the front and the pieces in turn, which is where 257 to 512 ciphertexts still are): 1 ciphertext 9.5 (11.4), 100: 10.1 (11.4), 256: 10.9 (11.6);

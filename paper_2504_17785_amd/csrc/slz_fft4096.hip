@@ -17,14 +17,16 @@
 //   F1, I4: b10 b9 b8 / b5..b0 / b7 b6     F2: b7 b6 b5 / b8 b4 b3 b2 b1 b0 / b10 b9     F3: b4 b3 b2 / b8 b7 b6 b5 b1 b0 / b10 b9
 //   F4, I1: b2 b1 b0 / b8..b3 / b10 b9     I2: b5 b4 b3 / b8 b7 b6 b2 b1 b0 / b10 b9     I3: b8 b7 b6 / b5..b0 / b10 b9
 // so that only F1 -> F2, F3 -> F4 (across the components) and I3 -> I4 cross waves.  A wave's buffer holds the 512 points with the same
-// b10 b9; an exchange places a point at 17 * A + B (16-byte slots) with five bits in A and four in B, chosen so that 16 neighbouring
-// lanes touch 16 different columns when writing and when reading, and every register is one lane base plus an immediate:
+// b10 b9; an exchange places a point at 17 * A + B (16-byte slots) with five bits in A and four in B, by which 16 neighbouring
+// lanes touch 16 different columns when writing and when reading (the counter still shows conflicts, see below), and every register is one lane
+// base plus an immediate:
 //   F1 -> F2, F2 -> F3: A = b8 b6 b5 b4 b7, B = b3 b2 b1 b0     F3 -> F4: A = b8 b7 b2 b4 b3, B = b6 b5 b1 b0
 //   I1 -> I2: A = b8 b7 b5 b4 b3, B = b6 b2 b1 b0               I2 -> I3: A = b8 b6 b7 b5 b4, B = b3 b2 b1 b0
 //   I3 -> I4: A = b8 b7 b6 b5 b4, B = b3 b2 b1 b0
-// What bounds it: 3 130 vector instructions per wave and step, 27 k cycles of a SIMD's two waves, and 18 exchanges per step of about 800 LDS
-// cycles each; of 38 k cycles per step (256 ciphertexts) 73 % issue vector instructions, the rest is what the two waves of a SIMD do not
-// hide of each other's exchanges.  With a full chip the clock falls from 2.25 to 1.8 GHz.  One ciphertext per compute unit: the exchange
+// What bounds it: 3 096 vector instructions per wave and step, 27.5 k cycles of a SIMD's two waves, and 18 exchanges per step, which keep the
+// LDS busy for 23 k cycles, 4.9 k of them counted as bank conflicts (of which accesses is not known); of 39.6 k cycles per step (100 and 256
+// ciphertexts alike) 70 % issue vector instructions, the rest is what the two waves of a SIMD do not hide of each other's exchanges.  With a full
+// chip the clock falls from 2.35 to 2.0 GHz.  One ciphertext per compute unit: the exchange
 // buffers and tables of two would not fit LDS, and eight waves on one ciphertext also give the lower latency.  Of the two waves on a SIMD
 // the one behind gets the priority (20.2 us per step at 100 ciphertexts without, 18.8 with); key words are requested one piece ahead, four
 // loads at a time (18.8, 17.7); the twiddles of I2 stay in registers (1024 ciphertexts: 68.6, 67.6).  Measured, us per step (in brackets: two
