@@ -6,8 +6,8 @@
 // keyswitch does with its key.  An int32 weight W is recoded into five signed bytes, W = sum_b s_b 2^(8b) with
 // s_b = byte b of (W + 0x80808080) - 128 for b < 4 and s_4 = (W + 0x80808080) >> 32; digit plane b multiplies the
 // ciphertext word shifted left by 8 b bits, so every digit plane is just more rows of the same contraction.  A first
-// kernel writes the digit planes in operand layout and records how many are non-zero anywhere (one, when every weight
-// fits a signed byte); the contraction reads the counts of its output tiles from device memory, so no host synchronisation is needed.
+// kernel writes the digit planes in operand layout and records where they are non-zero (plane 0 alone, when every weight
+// fits a signed byte); the contraction reads the records of its output tiles from device memory, so no host synchronisation is needed.
 #include "slz_internal.h"
 #include "slz_mfma_i8.h"
 
@@ -16,9 +16,9 @@
 // ---- weights -------------------------------------------------------------------------------------------------------
 // dig[otile][b][kb][lane] (16 bytes): A operand of lane `lane` for digit plane b, 32-row block kb of 32-output tile otile:
 // output 32 otile + lane % 32, inputs j = 32 kb + 16 (lane / 32) + t for byte t; zero past J or O.
-// planes[otile][kb]: digit planes that are not all zero there.
+// planes[otile][kb] (bytes): bit b is set where digit plane b is not all zero there.
 __global__ void __launch_bounds__(64)
-k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint32_t *__restrict__ planes, uint32_t J, uint32_t O,
+k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint8_t *__restrict__ planes, uint32_t J, uint32_t O,
               uint32_t n_kb) {
     const uint32_t lane = threadIdx.x, kb = blockIdx.x, otile = blockIdx.y;
     const uint32_t o = otile * 32 + lane % 32;
@@ -28,7 +28,7 @@ k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint32_t *__
     for (int b = 0; b < LM_MAX_PLANES; b++)
 #pragma unroll
         for (int q = 0; q < 4; q++) wd[b][q] = 0;
-    uint32_t used = 1;
+    uint32_t used = 0;
 #pragma unroll
     for (int t = 0; t < 16; t++) {
         const uint32_t j = j0 + t;
@@ -38,27 +38,28 @@ k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint32_t *__
         for (int b = 0; b < 4; b++) {
             const uint32_t s = (((uint32_t)(T >> (8 * b)) & 0xffu) - 128u) & 0xffu;
             wd[b][t / 4] |= s << (8 * (t % 4));
-            if (s) used = max(used, (uint32_t)b + 1);
+            if (s) used |= 1u << b;
         }
         const uint32_t s4 = (uint32_t)(T >> 32) & 0xffu;
         wd[4][t / 4] |= s4 << (8 * (t % 4));
-        if (s4) used = 5;
+        if (s4) used |= 1u << 4;
     }
 #pragma unroll
     for (int b = 0; b < LM_MAX_PLANES; b++) {
         v4i v = {(int)wd[b][0], (int)wd[b][1], (int)wd[b][2], (int)wd[b][3]};
         dig[(((size_t)otile * LM_MAX_PLANES + b) * n_kb + kb) * 64 + lane] = v;
     }
+    uint32_t any = 0;
 #pragma unroll
-    for (int d = 32; d; d >>= 1) used = max(used, (uint32_t)__shfl_xor((int)used, d));
-    if (lane == 0) planes[(size_t)otile * n_kb + kb] = used;
+    for (int b = 0; b < LM_MAX_PLANES; b++) any |= __builtin_amdgcn_ballot_w64(used >> b & 1u) ? 1u << b : 0u;
+    if (lane == 0) planes[(size_t)otile * n_kb + kb] = (uint8_t)any;
 }
 
 // ---- contraction ---------------------------------------------------------------------------------------------------
 struct lcm_args {
     const uint64_t *cts;    // [G][J][width]
     const v4i *dig;
-    const uint32_t *planes;
+    const uint8_t *planes;
     uint64_t *out;          // [G][O][width]
     uint32_t J, O, width;
     uint32_t n_kb;          // 32-row blocks per digit plane (ceil(J / 32))
@@ -71,6 +72,9 @@ template <int W>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_lcm_main(lcm_args A) {
     constexpr int IT_KB = W / 2;
+    // rows past the last digit plane in use are zeroed when they are used or, eight waves, when they are requested: 10 000 x 300 144.5 us against 152.5,
+    // but 10 000 x 8 (two waves) 177.6 against 174.4 and 10 000 x 128 (four) 143 against 141
+    constexpr bool MASK_LATE = W < 8;
     constexpr int BUF_V4 = IT_KB * 2 * 8 * 32;                      // 16-byte slots per LDS buffer: [block][half][plane][x]
     __shared__ v4i lds[2 * BUF_V4];
     // one XCD (workgroups b, b+8, ...) walks a contiguous range of work items: neighbouring word tiles of one group share
@@ -100,8 +104,9 @@ k_lcm_main(lcm_args A) {
     uint64_t kw0[8], kw1[8];
     uint32_t sh0, sh1, nv0, nv1;        // shift of the stage's digit plane; rows of the stage that exist
     v4i an0[IT_KB], an1[IT_KB];
+    uint32_t planes = LM_MAX_PLANES;                                // known after the first requests
     auto load_rows = [&](uint64_t (&kw)[8], uint32_t &sh, uint32_t &nv) {
-        nv = x_ok && j < A.J ? min(A.J - j, 8u) : 0u;
+        nv = x_ok && (MASK_LATE || b < planes) && j < A.J ? min(A.J - j, 8u) : 0u;
         sh = 8 * b;
 #pragma unroll
         for (int t = 0; t < 8; t++) kw[t] = src[(size_t)min(j + t, A.J - 1) * width];
@@ -115,18 +120,47 @@ k_lcm_main(lcm_args A) {
         for (int q = 0; q < IT_KB; q++) an[q] = A.dig[(dig_base + min(it + q, dig_last)) * 64 + lane];
     };
 
-    uint32_t planes = 1;
     v16i acc[8];
 #pragma unroll
     for (int p = 0; p < 8; p++)
 #pragma unroll
         for (int r = 0; r < 16; r++) acc[p][r] = 0;
 
+    // Digit planes in use in this workgroup's output tiles.  Their records (W n_kb bytes in a row, from a multiple of four on: og is 0 below W = 8) are
+    // requested among the first loads and arrive in their order; each wave takes all of them, and nothing waits for them but the first iteration.
+    // Read behind all first loads and exchanged between the waves they cost a workgroup of eight waves, alone on its compute unit, over a microsecond
+    // (32 groups, 15 x 300 at n = 742 60.6 us against 55, 784 x 300 126 against 120; 784 x 128 48.3 against 46.8).  Eight waves request them behind
+    // the first rows (15 x 300 at n = 1024 77.9 us before them, 76.0 behind), fewer before (784 x 128 46.8 us, 47.2).
+    const uint32_t n_bytes = min((uint32_t)W, A.n_otiles - og * W) * A.n_kb, n_words = (n_bytes + 3) / 4;
+    const uint32_t *records = reinterpret_cast<const uint32_t *>(A.planes + (size_t)og * W * A.n_kb);
+    uint32_t used = 0, rec[4];
+    auto valid = [&](uint32_t t, uint32_t r) { return 4 * t + 4 > n_bytes ? r & ((1u << 8 * (n_bytes & 3u)) - 1u) : r; };     // t < n_words
+    auto load_records = [&]() {
+#pragma unroll
+        for (uint32_t t = 0; t < 4; t++) rec[t] = records[min(64 * t + lane, n_words - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (W < 8) load_records();
+    load_rows(kw0, sh0, nv0);
+    if (W == 8) { __builtin_amdgcn_sched_barrier(0); load_records(); }
+    load_dig(an0, 0);
+    load_rows(kw1, sh1, nv1);
+    load_dig(an1, IT_KB);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (uint32_t t = 0; t < 4; t++) used |= valid(min(64 * t + lane, n_words - 1), rec[t]);
+    for (uint32_t t = 256 + lane; t < n_words; t += 64) used |= valid(t, records[t]);
+    planes = 1;
+#pragma unroll
+    for (uint32_t b = 1; b < LM_MAX_PLANES; b++) planes = __builtin_amdgcn_ballot_w64(used & 0x01010101u << b) ? b + 1 : planes;
+    if (!MASK_LATE && sh0 >= 8 * planes) nv0 = 0;
+    if (!MASK_LATE && sh1 >= 8 * planes) nv1 = 0;
+
     uint32_t buf = 0;
     auto body = [&](uint64_t (&kw)[8], uint32_t &sh, uint32_t &nv, v4i (&an)[IT_KB], uint32_t it) {
         {
             uint64_t w[8], plane[8];
-            if (sh >= 8 * planes) nv = 0;                               // past the last digit plane in use
+            if (MASK_LATE && sh >= 8 * planes) nv = 0;
 #pragma unroll
             for (int t = 0; t < 8; t++) w[t] = (uint32_t)t < nv ? slz_signed_bytes(kw[t] << sh) : 0ull;
             slz_byte_planes(w, plane);
@@ -157,20 +191,6 @@ k_lcm_main(lcm_args A) {
         load_dig(an, it + 2 * IT_KB);
         buf ^= 1;
     };
-    load_rows(kw0, sh0, nv0);
-    load_dig(an0, 0);
-    load_rows(kw1, sh1, nv1);
-    load_dig(an1, IT_KB);
-    // digit planes in use in this workgroup's output tiles
-    __shared__ uint32_t wave_planes[W];
-    for (uint32_t t = lane; tile_ok && t < A.n_kb; t += 64) planes = max(planes, A.planes[(size_t)otile * A.n_kb + t]);
-#pragma unroll
-    for (int d = 32; d; d >>= 1) planes = max(planes, (uint32_t)__shfl_xor((int)planes, d));
-    if (lane == 0) wave_planes[wave] = planes;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < W; w++) planes = max(planes, wave_planes[w]);
-    planes = min(planes, (uint32_t)LM_MAX_PLANES);
     const uint32_t kb_end = planes * A.n_kb;
     for (uint32_t it = 0; it < kb_end; it += 2 * IT_KB) {
         body(kw0, sh0, nv0, an0, it);
@@ -203,7 +223,7 @@ int slz_lcm_launch(slz_ctx *ctx, const uint64_t *cts, const int32_t *w, uint64_t
     // int32 accumulators: at most 5 planes x 32 n_kb rows of |digit * byte| <= 2^14
     if ((uint64_t)LM_MAX_PLANES * 32 * n_kb >= (1u << 17)) return SLZ_E_UNSUPPORTED;
     const uint32_t n_otiles = (O + 31) / 32;
-    const size_t need = (size_t)n_otiles * n_kb * (LM_MAX_PLANES * 1024 + sizeof(uint32_t));    // operands and plane counts
+    const size_t need = (size_t)n_otiles * n_kb * (LM_MAX_PLANES * 1024 + 1) + 3;     // operands and plane records, read as whole words
     if (ctx->lc_dig_bytes < need) {
         // the previous buffer may still be read by work queued on another stream: wait before letting it go
         if (ctx->lc_dig) { SLZ_HIP(hipDeviceSynchronize()); (void)hipFree(ctx->lc_dig); ctx->lc_dig = nullptr; ctx->lc_dig_bytes = 0; }
@@ -211,7 +231,7 @@ int slz_lcm_launch(slz_ctx *ctx, const uint64_t *cts, const int32_t *w, uint64_t
         ctx->lc_dig_bytes = need;
     }
     v4i *dig = (v4i *)ctx->lc_dig;
-    uint32_t *planes = (uint32_t *)(dig + (size_t)n_otiles * LM_MAX_PLANES * n_kb * 64);
+    uint8_t *planes = (uint8_t *)(dig + (size_t)n_otiles * LM_MAX_PLANES * n_kb * 64);
     if (n_otiles > 65535) return SLZ_E_UNSUPPORTED;
     hipLaunchKernelGGL(k_lcm_weights, dim3(n_kb, n_otiles), dim3(64), 0, s, w, dig, planes, J, O, n_kb);
     lcm_args A;

@@ -239,6 +239,19 @@ def test_lincomb_matches_oracle(slz, orc, G, J, O, n, kind):
     assert np.array_equal(slz.to_host_u64(ctx.lwe_lincomb_batch(d_cts, d_w)), want)
 
 
+@pytest.mark.parametrize("J,O,at", [(4200, 300, (4195, 250)), (1100, 300, (3, 299)), (8300, 100, (8295, 99)), (16500, 40, (16490, 39)), (784, 300, (700, 31))])
+def test_lincomb_finds_the_one_wide_weight(slz, orc, J, O, at):
+    # workgroups of 8, 4 and 2 waves; one weight of the whole matrix needs all five digit planes, in the last or the first of the records that a
+    # workgroup goes through (more than it holds in registers where J is over 4096, 8192 and 16384)
+    p = tiny(n=20)
+    cts = synth.raw_words(p, "raw_ct", 2 * J * (p.n + 1)).reshape(2, J, p.n + 1)
+    w = (_lincomb_weights(p, J, O, "small") % 13).astype(np.int32)
+    w[at] = -2 ** 31 + 12345
+    ctx = slz.Context(p, 1)
+    got = slz.to_host_u64(ctx.lwe_lincomb_batch(slz.to_device_u64(cts), torch.from_numpy(w).cuda()))
+    assert np.array_equal(got, orc.lwe_lincomb_batch(cts, w))
+
+
 def test_config1_full_pipeline_bit_exact_and_decrypts(slz, orc):
     p = synth.CONFIGS[1]
     case = Case(slz, orc, p, p.batch, n_tables=1, msgs=synth.config_messages(1))
