@@ -26,8 +26,9 @@
 // A workgroup takes 32 ciphertexts x 128 mask words: every wave reads whole 512-byte runs of a ciphertext, the digit bytes
 // are turned through LDS (rows of 128 + 16 bytes: the 16-byte reads of 8 neighbouring lanes then cover all banks), and
 // every store instruction writes one 1 KiB operand block.
-// init: where the contraction adds its segments up, the output's (0, b') is written here as well, a part of every ciphertext's words by
-// each workgroup of its tile (a launch of its own took 5 us of 110 at 1024 ciphertexts of configuration size kN = 2048, n = 742).
+// init: where the contraction adds its segments up, the output's (0, b') is written here as well, a run of the tile's 32 (n + 1) consecutive words by
+// each workgroup of it (a launch of its own took 5 us of 110 at 1024 ciphertexts of kN = 2048, n = 742; as a part of every ciphertext's
+// words, 26 of 801 at kN = 4096, 8 ciphertexts of that size took 39.4 us against 38.6 with the launch, now 37.2; 4096: 706 against 705, now 698).
 #define KD_WORDS 128
 #define KD_PITCH (KD_WORDS + 16)
 #define KD_LEVELS 8                     // levels turned through LDS at a time
@@ -55,11 +56,12 @@ k_ksm_digits(const uint64_t *__restrict__ lwe_in, v4i *__restrict__ dig, uint32_
         }
     }
     if (init) {
-        const uint32_t width = n + 1, part = (width + gridDim.x - 1) / gridDim.x, x0 = blockIdx.x * part, x1 = min(x0 + part, width);
-        for (uint32_t q = 0; q < 8; q++) {
-            const uint32_t c = tile * 32 + 8 * wave + q;
-            if (c >= batch) break;
-            for (uint32_t x = x0 + lane; x < x1; x += 64) init[(size_t)c * width + x] = x == n ? lwe_in[(size_t)c * (kN + 1) + kN] : 0ull;
+        const uint32_t width = n + 1, total = min(32u, batch - 32 * tile) * width, part = (total + gridDim.x - 1) / gridDim.x;
+        const uint32_t end = min(total, (blockIdx.x + 1) * part);
+        uint64_t *dst = init + (size_t)tile * 32 * width;
+        for (uint32_t i = blockIdx.x * part + threadIdx.x; i < end; i += 256) {
+            const uint32_t c = i / width, x = i - c * width;
+            dst[i] = x == n ? lwe_in[(size_t)(32 * tile + c) * (kN + 1) + kN] : 0ull;
         }
     }
     for (uint32_t j0 = 0; j0 < l; j0 += KD_LEVELS) {
