@@ -28,7 +28,8 @@
 // every store instruction writes one 1 KiB operand block.
 // init: where the contraction adds its segments up, the output's (0, b') is written here as well, a run of the tile's 32 (n + 1) consecutive words by
 // each workgroup of it (a launch of its own took 5 us of 110 at 1024 ciphertexts of kN = 2048, n = 742; as a part of every ciphertext's
-// words, 26 of 801 at kN = 4096, 8 ciphertexts of that size took 39.4 us against 38.6 with the launch, now 37.2; 4096: 706 against 705, now 698).
+// words, 26 of 801 at kN = 4096, 33 ciphertexts of that size took 42.2 us against 42.0 with the launch, now 40.1, and 4096 675 against 665, now 670;
+// 1024 of kN = 2048, n = 742: 107.1 against 108.9, now 106.2).
 #define KD_WORDS 128
 #define KD_PITCH (KD_WORDS + 16)
 #define KD_LEVELS 8                     // levels turned through LDS at a time
@@ -59,8 +60,9 @@ k_ksm_digits(const uint64_t *__restrict__ lwe_in, v4i *__restrict__ dig, uint32_
         const uint32_t width = n + 1, total = min(32u, batch - 32 * tile) * width, part = (total + gridDim.x - 1) / gridDim.x;
         const uint32_t end = min(total, (blockIdx.x + 1) * part);
         uint64_t *dst = init + (size_t)tile * 32 * width;
-        for (uint32_t i = blockIdx.x * part + threadIdx.x; i < end; i += 256) {
-            const uint32_t c = i / width, x = i - c * width;
+        uint32_t c = blockIdx.x * part / width, x = blockIdx.x * part - c * width + threadIdx.x;
+        for (uint32_t i = blockIdx.x * part + threadIdx.x; i < end; i += 256, x += 256) {
+            while (x >= width) { x -= width; c++; }
             dst[i] = x == n ? lwe_in[(size_t)(32 * tile + c) * (kN + 1) + kN] : 0ull;
         }
     }
