@@ -147,23 +147,29 @@ k_big_rows(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
 #pragma unroll
         for (int e = 0; e < 32; e++) x[e] = ldl(src + 64 * e, lane * 8u);
         fused_fwd(x, T, tw6, twA, fwdB, m, lane, z);
-        // multiply-accumulate with the key polynomials of GGSW row r (both components); spectrum index of x[i] is
-        // 2048 row + 32 lane + i, stored at position i * (N/32) + 64 row + lane of the prepared polynomial
-        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + 0) * N + 64u * row + z;
+        // multiply-accumulate with the key polynomials of GGSW row r (both components); spectrum index of x[i] is 2048 row + 32 lane + i:
+        // the words of x[i], x[i + 1], x[i + 16] and x[i + 17] are consecutive in the prepared polynomial for even i (slz_prep_pos)
+        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + 0) * N + 2048u * row + z;
         const double *k1 = k0 + N;
-        const uint32_t stride = N / 32;
+        const uint32_t key_lane = hh * 1024u + (lane & 31u) * 4u;
 #pragma unroll
         for (int g = 0; g < 8; g++) {
-            double kk0[4], kk1[4], r0[4], r1[4];
+            double2 ka[2], kb[2];
 #pragma unroll
-            for (int u = 0; u < 4; u++) { kk0[u] = ldl(k0 + (size_t)(4 * g + u) * stride, lane * 8u); kk1[u] = ldl(k1 + (size_t)(4 * g + u) * stride, lane * 8u); }
-            const double x4[4] = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+            for (int h = 0; h < 2; h++) {
+                ka[h] = *reinterpret_cast<const double2 *>(k0 + 128 * g + 2 * h + key_lane);
+                kb[h] = *reinterpret_cast<const double2 *>(k1 + 128 * g + 2 * h + key_lane);
+            }
+            const int at[4] = {2 * g, 2 * g + 1, 2 * g + 16, 2 * g + 17};
+            const double kk0[4] = {ka[0].x, ka[0].y, ka[1].x, ka[1].y}, kk1[4] = {kb[0].x, kb[0].y, kb[1].x, kb[1].y};
+            const double x4[4] = {x[at[0]], x[at[1]], x[at[2]], x[at[3]]};
+            double r0[4], r1[4];
             mulmod_k<4>(r0, x4, kk0, m);
             mulmod_k<4>(r1, x4, kk1, m);
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                o0[4 * g + u] = (r == 0) ? r0[u] : o0[4 * g + u] + r0[u];
-                o1[4 * g + u] = (r == 0) ? r1[u] : o1[4 * g + u] + r1[u];
+                o0[at[u]] = (r == 0) ? r0[u] : o0[at[u]] + r0[u];
+                o1[at[u]] = (r == 0) ? r1[u] : o1[at[u]] + r1[u];
             }
         }
         if ((r & 3u) == 3u && r + 1 < R) {                       // more than four rows: keep the running sums below 8 p
@@ -238,10 +244,7 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
         for (int k = 0; k < 15; k++) twB[64 * k + lane] = gB[64 * k + lane];
         wave_sync();
     }
-    // spectrum index of x[i] is 1024 row + 16 lane + i, stored at position (idx % 32) (N/32) + idx / 32 of the prepared
-    // polynomial: register i of lane l sits at i (N/32) + [16 (l & 1) (N/32) + 32 row + l / 2]
-    const uint32_t stride = N / 32;
-    const uint32_t key_lane_off = (16u * (lane & 1u) * stride + (lane >> 1)) * 8u;
+    // spectrum index of x[i] is 1024 row + 16 lane + i, stored in pairs of registers, lane-minor, from position 1024 row of the prepared polynomial on
     double o0[16], o1[16];
     double xn[16];                                               // the next GGSW row's block, requested one row ahead
     {
@@ -257,13 +260,14 @@ k_big_rows16(bign_args A, uint32_t G, uint32_t n_tasks, int xcd_aware) {
         for (int e = 0; e < 16; e++) x[e] = xn[e];
         // the key words of this row and then the next row's block are requested here (vector memory completes in issue
         // order) and arrive while the transform runs
-        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + 0) * N + 32u * row + z;
+        const double *k0 = A.bskp_step + (((size_t)q * R + r) * 2 + 0) * N + 1024u * row + z;
         const double *k1 = k0 + N;
         double kk0[16], kk1[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
-            kk0[i] = ldl(k0 + (size_t)i * stride, key_lane_off);
-            kk1[i] = ldl(k1 + (size_t)i * stride, key_lane_off);
+        for (int i = 0; i < 16; i += 2) {
+            const double2 a = ldl2(k0 + 64 * i, lane * 16u), b = ldl2(k1 + 64 * i, lane * 16u);
+            kk0[i] = a.x; kk0[i + 1] = a.y;
+            kk1[i] = b.x; kk1[i + 1] = b.y;
         }
         {
             const double *nxt = A.X + (((size_t)b * 2 + q) * R + (r + 1 < R ? r + 1 : r)) * N + 1024u * row + z;
@@ -503,8 +507,6 @@ k_big_rows16_team(bign_args A, uint32_t G) {
     const uint32_t N = A.N;
     const slz_mod m = A.mod[q];
     const bign_tabs tb = A.tab[q];
-    const uint32_t stride = N / 32;
-    const uint32_t key_lane_off = (16u * (lane & 1u) * stride + (lane >> 1)) * 8u;
     int z;
     asm volatile("s_mov_b32 %0, 0" : "=s"(z));
     double x[16], kk[2][16];
@@ -520,11 +522,15 @@ k_big_rows16_team(bign_args A, uint32_t G) {
         const double *src = A.X + (((size_t)b * 2 + q) * R + r) * N + 1024u * row;
 #pragma unroll
         for (int e = 0; e < 16; e++) x[e] = ldl(src + 64 * e, lane * 8u);
-        const double *key = A.bskp_step + (((size_t)q * R + r) * 2) * N + 32u * row;
+        const double *key = A.bskp_step + (((size_t)q * R + r) * 2) * N + 1024u * row;
 #pragma unroll
-        for (int i = 0; i < 16; i++)
+        for (int i = 0; i < 16; i += 2)
 #pragma unroll
-            for (int c = 0; c < 2; c++) kk[c][i] = ldl(key + (size_t)c * N + (size_t)i * stride, key_lane_off);
+            for (int c = 0; c < 2; c++) {
+                const double2 w = ldl2(key + (size_t)c * N + 64 * i, lane * 16u);
+                kk[c][i] = w.x;
+                kk[c][i + 1] = w.y;
+            }
 #pragma unroll
         for (uint32_t i = 0; i < TAB; i++) if (i * 64 * R + threadIdx.x < 1024u) twA[i * 64 * R + threadIdx.x] = tab[i];
     }

@@ -22,9 +22,12 @@ struct slz_mod {          // one transform prime, passed to kernels by value
 };
 
 // Position of transform-domain coefficient `idx` (index in the bit-reversed output order of the
-// forward transform) inside a prepared polynomial.  The fused kernels hold 32 consecutive outputs per
-// lane, so the prepared key is stored register-major / lane-minor to make their loads coalesced.
+// forward transform) inside a prepared polynomial: register-major / lane-minor, so that a wave's loads are consecutive.
+// N <= 1024: register idx % 32 of lane idx / 32 (the fused kernels take two lanes of 16 from it).  Larger: blocks of 1024, register
+// idx % 16 of lane (idx / 16) % 64, a lane's registers in pairs: a wave of the large-N row pass reads its 8 KiB of a polynomial from
+// consecutive addresses, 16 bytes per lane.  With the order of small N over the whole polynomial they were 32 runs of 256 bytes, N / 4 bytes apart.
 __host__ __device__ static inline uint32_t slz_prep_pos(uint32_t idx, uint32_t N) {
+    if (N > 1024) return (idx & ~1023u) + ((idx & 14u) << 6) + ((idx >> 3) & 126u) + (idx & 1u);
     uint32_t E = N < 32 ? N : 32;
     return (idx % E) * (N / E) + idx / E;
 }

@@ -21,6 +21,10 @@ __device__ __forceinline__ double ldl(const double *uniform_base, uint32_t lane_
     return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(uniform_base) + lane_byte_off);
 }
 
+__device__ __forceinline__ double2 ldl2(const double *uniform_base, uint32_t lane_byte_off) {
+    return *reinterpret_cast<const double2 *>(reinterpret_cast<const char *>(uniform_base) + lane_byte_off);
+}
+
 __device__ __forceinline__ void wave_sync() {
     // orders this wave's LDS writes before its later LDS reads of other lanes' data
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
