@@ -316,7 +316,7 @@ def bench_loss(args):
 PATH_SOURCES = {       # sources of the dominant kernel of each path (for the check that a stored traffic figure is current)
     "fused_n2048": ("slz_fft2048.hip", "slz_fft.h", "slz_fft_wave.h", "slz_modarith.h"),
     "fused_n512": ("slz_fft512.hip", "slz_fft.h", "slz_fft_wave.h", "slz_modarith.h"),
-    "three_pass_large_n": ("slz_bign.hip", "slz_wave_ntt.h", "slz_modarith.h"),
+    "three_pass_large_n": ("slz_bign.hip", "slz_bign.h", "slz_wave_ntt.h", "slz_modarith.h"),
 }
 
 

@@ -83,7 +83,8 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      at most 32 at N = 32768, 56 at 16384, 96 at 8192, 512 / (N / 1024) below; fewer with more levels) run every CMux step as two launches of
                                      more, shorter threads instead of three (lower latency, identical results; their second accumulator
                                      of (k+1) N words per such ciphertext is allocated by the context's first call of any batch size;
-                                     if there is no room for it then, the context keeps to three launches);
+                                     if there is no room for it then, the context keeps to three launches).  At N = 32768 with pbs_level 2
+                                     batches of up to 16, 22 to 24 and 31 to 40 run all steps in one launch, identical results again.
                                      0 keeps the throughput kernels at every batch size; SLZ_E_INVALID_ARG without a large-N path */
 
 #define SLZ_OPT_FUSED_PACING 6    /* values 0, 1 and 2, on the N = 2048 fused path: accepted and without effect.  They paced the workgroups of

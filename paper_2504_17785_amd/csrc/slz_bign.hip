@@ -9,9 +9,7 @@
 //                           coefficients per lane, block-specific twiddles), multiply-accumulate with the prepared
 //                           key over all GGSW rows, the same number of inverse stages.
 //   P3 "columns, inverse":  the last log2(G) inverse stages per column, the psi^-j / N twist, CRT lift, accumulate.
-#include "slz_internal.h"
-#include "slz_modarith.h"
-#include "slz_wave_ntt.h"
+#include "slz_bign.h"
 #include <vector>
 
 #define BIG_MAX_L 4
@@ -20,49 +18,6 @@
 // a launch, before the next one may start.
 __device__ __forceinline__ void st_through(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void st_through(uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-struct bign_tabs {                 // per prime
-    const double *fwd;             // natural forward table of the full transform (fwd[m + blk])
-    const double *rowA;            // [G][64]      block-specific twiddles of stages with 1..32 sub-blocks (uniform per wave)
-    const double *rowB;            // [G][31][64]  block-specific per-lane twiddles of the last five forward stages (1024-blocks: [G][15][64], four)
-    const double *inv;             // natural inverse table
-    const double *post;            // natural twist table
-};
-
-struct bign_args {
-    const uint64_t *lwe_in;
-    uint64_t *acc;                 // [batch][2][N]
-    double *X;                     // [batch][2 primes][R][N]
-    double *Y;                     // [batch][2 primes][2][N]
-    const double *bskp_step;       // prepared GGSW of this step: [2][R][2][N]
-    uint32_t n, step, N, pad, beta, l, batch;    // pad: not read.  Without it the arguments are 184 bytes and 8 ciphertexts of N = 32768 (1024 steps)
-                                   // take 33.76 ms, in every order of these words tried, against 33.59; with a word more (200 bytes) 33.87
-    bign_tabs tab[2];
-    slz_mod mod[2];
-    double p1inv_mod_p2;
-};
-
-// forward column stages (strides N/2 .. BS) on a column of G rows: pairs of rows, twiddle by block of rows (uniform)
-template <int G>
-__device__ __forceinline__ void cols_fwd(double (&y)[G], const double *tw, slz_mod m) {
-#pragma unroll
-    for (int half = G / 2, blocks = 1; half >= 1; half >>= 1, blocks <<= 1) {
-#pragma unroll
-        for (int blk = 0; blk < blocks; blk++) {
-            const double w = tw[blocks + blk];
-#pragma unroll
-            for (int j = 0; j < half; j++) bfly(y[blk * 2 * half + j], y[blk * 2 * half + j + half], w, m);
-        }
-    }
-}
-
-// 1024-blocks: the tables of the mirrored inverse follow rowA [G][64] and rowB [G][15][64] in memory (BIG16_TAB), one allocation
-// and one copy for all: inverses of rowA and of rowB, and the column stages' [32]: inverses of fwd[2 .. G - 1], [0] = 1 / N,
-// [1] = 1 / (N fwd[1])
-#define BIG16_TAB(G) ((size_t)(G) * 64 * 32 + 32)
-__device__ __forceinline__ const double *rowAi_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 16; }
-__device__ __forceinline__ const double *rowBi_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 17; }
-__device__ __forceinline__ const double *colI_of(const bign_tabs &t, uint32_t G) { return t.rowA + (size_t)G * 64 * 32; }
 
 // ---- P1 ------------------------------------------------------------------------------------------
 // BS: block size of the row pass (2048 or 1024); G = N / BS rows of BS columns
@@ -365,32 +320,6 @@ k_big_cols_inv(bign_args A) {
     uint64_t *poly = A.acc + ((size_t)b * 2 + comp) * N + c;
 #pragma unroll
     for (int i = 0; i < G; i++) poly[(uint32_t)BS * i] += slz_crt64(res[0][i], res[1][i], A.mod[1], A.p1inv_mod_p2);
-}
-
-// Column stages of the mirrored inverse inside a part of K rows (1024-blocks): block `first` .. of the forward stage with
-// the same strides.  bd: bounds in units of p.
-template <int K>
-__device__ __forceinline__ void cols_mirror(double (&x)[K], double (&bd)[K], const double *colI, uint32_t part, uint32_t parts, slz_mod m) {
-#pragma unroll
-    for (int half = 1; half < K; half <<= 1) {
-#pragma unroll
-        for (int blk = 0; blk < K / (2 * half); blk++) {
-            const double w = colI[(parts + part) * (K / (2 * half)) + blk];
-#pragma unroll
-            for (int j = 0; j < half; j++) {
-                double *pa[1] = {&x[blk * 2 * half + j]}, *pb[1] = {&x[blk * 2 * half + j + half]};
-                double *ua[1] = {&bd[blk * 2 * half + j]}, *ub[1] = {&bd[blk * 2 * half + j + half]};
-                const double pw[1] = {w};
-                gs_k<1>(pa, pb, ua, ub, pw, m);
-            }
-        }
-    }
-}
-// the last stage with the factor 1 / N: f, g <- (f + g) / N, (f - g) / (N w)
-__device__ __forceinline__ void cols_mirror_last(double &f, double &g, const double *colI, slz_mod m) {
-    const double s = f + g, d = f - g;
-    f = slz_mulmod(s, colI[0], m);
-    g = slz_mulmod(d, colI[1], m);
 }
 
 // both residues of column c of one component after the mirrored inverse
@@ -830,6 +759,7 @@ int slz_bign_init(slz_ctx *ctx) {
         const struct { const void *kernel; uint32_t rows; } team[] = {{(const void *)k_big_rows16_team<2>, 2}, {(const void *)k_big_rows16_team<4>, 4},
                                                                       {(const void *)k_big_rows16_team<6>, 6}, {(const void *)k_big_rows16_team<8>, 8}};
         for (const auto &t : team) SLZ_HIP(hipFuncSetAttribute(t.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)TEAM_LDS(t.rows)));
+        if (slz_bign_xcd_setup() != SLZ_OK) return SLZ_E_HIP;
         ctx->has_bign16 = 1;
         ctx->bign_block = 1024;                                  // preferred: two waves per SIMD in the row pass
         any = true;
@@ -928,7 +858,7 @@ static int ensure_lanes(slz_ctx *ctx) {
 
 // Ciphertexts up to which a step runs as the two launches above.  us per CMux step, three launches per step (as they were: with kernels of their
 // own for few ciphertexts, up to 512 / G) -> two; l = 2:
-//   N = 32768: 1: 34 -> 22, 4: 39 -> 25, 8: 41 -> 33, 16: 53 -> 44, 24: 73 -> 56, 32: 78 -> 70, 48: 101 -> 103
+//   N = 32768: 1: 34 -> 22, 4: 39 -> 25, 8: 41 -> 33, 16: 53 -> 44, 24: 73 -> 56, 32: 78 -> 70, 48: 101 -> 103 (most of these run as one launch: slz_bign_xcd_takes)
 //   N = 16384: 8: 34 -> 21, 32: 50 -> 40, 48: 61 -> 53, 56: 63 -> 59, 64: 68 -> 69     N = 8192: 64: 50 -> 41, 96: 57 -> 56, 112: 60 -> 64
 //   N = 4096: 64: 32 -> 27, 128: 48 -> 38     N = 2048: 256: 50 -> 38
 // Past that the column work done twice costs more than the launch and the accumulator's traffic that it saves.
@@ -965,15 +895,63 @@ uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half)
     return even && batch > 512 / G && batch <= 2 * half ? batch - batch / 2 / unit * unit : 0;
 }
 
-// The second accumulator of the two-launch steps, asked for with the first scratch of a context and never again: a later call allocates
-// nothing, whatever its batch, and may be captured.  Without it a step runs as three launches at every batch size.
+// The second accumulator of the two-launch steps, and behind it the control words of the one launch, asked for with the first scratch of a
+// context and never again: a later call allocates nothing, whatever its batch, and may be captured.  Without them a step runs as three launches at every batch size.
 void slz_bign_scratch(slz_ctx *ctx) {
     if (!ctx->has_bign16 || ctx->bign_spare_asked) return;
     ctx->bign_spare_asked = 1;
     const uint32_t lat_max = slz_bign_latency_max_batch(ctx->prm.N / 1024, ctx->prm.pbs_level);
     const size_t cts = ctx->max_batch < lat_max ? ctx->max_batch : lat_max;
     void *buf = nullptr;
-    if (slz_scratch_alloc(&buf, cts * 2 * ctx->prm.N * sizeof(uint64_t)) == SLZ_OK) ctx->bign_spare = (uint64_t *)buf;
+    if (slz_scratch_alloc(&buf, cts * 2 * ctx->prm.N * sizeof(uint64_t) + slz_bign_xcd_ctl_bytes()) != SLZ_OK) return;
+    ctx->bign_spare = (uint64_t *)buf;
+    ctx->bign_ctl = (uint32_t *)(ctx->bign_spare + cts * 2 * ctx->prm.N);
+}
+
+// Arguments of the kernels for `batch` ciphertexts whose workspace starts `first` ciphertexts into the context's; step and key are the caller's.
+static bign_args args_of(const slz_ctx *ctx, uint32_t BS, const uint64_t *lwe_in, uint64_t *acc, size_t first, uint32_t batch) {
+    const slz_params &p = ctx->prm;
+    const uint32_t N = p.N, G = N / BS, R = 2 * p.pbs_level;
+    bign_args a;
+    a.lwe_in = lwe_in;
+    a.acc = acc;
+    a.X = ctx->xhat + first * 2 * R * N;
+    a.Y = ctx->outhat + first * 2 * 2 * N;
+    a.bskp_step = nullptr;
+    a.n = p.n; a.step = 0; a.N = N; a.pad = 0; a.beta = p.pbs_base_log; a.l = p.pbs_level; a.batch = batch;
+    for (int q = 0; q < 2; q++) {
+        a.tab[q].fwd = ctx->tab[q].fwd;
+        if (BS == 2048) {
+            a.tab[q].rowA = ctx->bign_rowA + (size_t)q * G * 64;
+            a.tab[q].rowB = ctx->bign_rowB + (size_t)q * G * 31 * 64;
+        } else {
+            const double *t = ctx->bign16_tab + q * BIG16_TAB(G);
+            a.tab[q].rowA = t;
+            a.tab[q].rowB = t + (size_t)G * 64;
+        }
+        a.tab[q].inv = ctx->tab[q].inv;
+        a.tab[q].post = ctx->tab[q].post;
+        a.mod[q] = ctx->mod[q];
+    }
+    a.p1inv_mod_p2 = ctx->p1inv_mod_p2;
+    return a;
+}
+
+// Batches that run all steps in one launch (slz_bign_xcd.hip): N = 32768 with two levels, rounds of eight ciphertexts, 15.7 (1024 steps) to 16.8 us (256
+// steps) per step and round whether it is full or not.  us per step of the launches below it (two up to 32 ciphertexts, then three): 1: 21.7, 4: 25, 8: 31.5,
+// 9: 37.9, 16: 42.9, 17: 41.4, 18: 48.4, 20: 47.6, 21: 47.9, 24: 52.7, 25: 54.8, 28: 62, 32: 67.6, 33: 81, 36: 85.4, 40: 85.5, 48: 94.9, 64: 121: they win at the
+// beginning of the third and fourth round and from the sixth on.
+uint32_t slz_bign_xcd_takes(uint32_t G, uint32_t l, uint32_t batch) {
+    if (G != 32 || l != 2) return 0;
+    return batch <= 16 || (batch >= 22 && batch <= 24) || (batch >= 31 && batch <= 40);
+}
+
+// The one launch on `workgroups` workgroups; any number of them goes through all steps (tests run fewer), SLZ_XCD_WORKGROUPS are one per slot.
+int slz_bign_xcd_run(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc, uint32_t batch, uint32_t workgroups,
+                     hipStream_t s) {
+    bign_args a = args_of(ctx, 1024, lwe_in, acc, 0, batch);
+    a.bskp_step = bskp;
+    return slz_bign_xcd_launch(a, ctx->bign_ctl, n_steps, workgroups, s);
 }
 
 // Runs steps [0, n_steps) on accumulators that the caller has initialised in `acc` ([batch][2][N]).
@@ -981,7 +959,10 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
                         uint32_t batch, hipStream_t s) {
     const slz_params &p = ctx->prm;
     const uint32_t N = p.N, BS = (uint32_t)ctx->bign_block, G = N / BS, R = 2 * p.pbs_level;
-    // few ciphertexts: every step in two launches (1024-blocks only, and where there was room for the second accumulator)
+    if (n_steps == 0) return SLZ_OK;
+    if (ctx->bign_latency && BS == 1024 && ctx->bign_ctl && slz_bign_xcd_takes(G, p.pbs_level, batch))
+        return slz_bign_xcd_run(ctx, lwe_in, bskp, n_steps, acc, batch, SLZ_XCD_WORKGROUPS, s);
+    // few ciphertexts otherwise: every step in two launches (1024-blocks only, and where there was room for the second accumulator)
     const bool lat = ctx->bign_latency && BS == 1024 && batch <= slz_bign_latency_max_batch(G, p.pbs_level) && ctx->bign_spare;
     // Ciphertexts go through all steps in chunks whose workspace (X, Y, accumulators: (2R + 4 + 2) N doubles each) stays
     // in the 256 MB Infinity Cache; the key (read once per chunk and step) streams from HBM.
@@ -1021,27 +1002,7 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
             const uint32_t c0 = g0 + j * chunk;
             if (c0 >= batch) break;
             const uint32_t nb = (batch - c0 < chunk) ? batch - c0 : chunk;
-            bign_args &a = A[j];
-            a.lwe_in = lwe_in + (size_t)c0 * (p.n + 1);
-            a.acc = acc + (size_t)c0 * 2 * N;
-            a.X = ctx->xhat + (size_t)j * chunk * 2 * R * N;
-            a.Y = ctx->outhat + (size_t)j * chunk * 2 * 2 * N;
-            a.n = p.n; a.N = N; a.beta = p.pbs_base_log; a.l = p.pbs_level; a.batch = nb;
-            for (int q = 0; q < 2; q++) {
-                a.tab[q].fwd = ctx->tab[q].fwd;
-                if (BS == 2048) {
-                    a.tab[q].rowA = ctx->bign_rowA + (size_t)q * G * 64;
-                    a.tab[q].rowB = ctx->bign_rowB + (size_t)q * G * 31 * 64;
-                } else {
-                    const double *t = ctx->bign16_tab + q * BIG16_TAB(G);
-                    a.tab[q].rowA = t;
-                    a.tab[q].rowB = t + (size_t)G * 64;
-                }
-                a.tab[q].inv = ctx->tab[q].inv;
-                a.tab[q].post = ctx->tab[q].post;
-                a.mod[q] = ctx->mod[q];
-            }
-            a.p1inv_mod_p2 = ctx->p1inv_mod_p2;
+            A[j] = args_of(ctx, BS, lwe_in + (size_t)c0 * (p.n + 1), acc + (size_t)c0 * 2 * N, (size_t)j * chunk, nb);
             n_tasks[j] = nb * 2 * G;
             nbs[j] = nb;
             st[j] = lanes >= 2 ? (hipStream_t)ctx->bign_lane_stream[j] : s;

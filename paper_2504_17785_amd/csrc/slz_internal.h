@@ -66,6 +66,7 @@ struct slz_ctx {
     int bign_block;           // block size the large-N path uses: 1024 or 2048
     int bign_latency;         // 1: few ciphertexts take the latency-oriented kernels (two launches per step)
     uint64_t *bign_spare;     // their second accumulator [few ciphertexts][2][N], or null
+    uint32_t *bign_ctl;       // control words of the one-launch kernel (slz_bign_xcd.hip), behind the second accumulator, or null
     int bign_spare_asked;     // its allocation has been tried
     double *bign16_tab;       // tables of the large-N kernels on 1024-blocks (slz_bign.hip)
     double mirror_last[2][2]; // per prime 1 / N and 1 / (N fwd[1])
@@ -148,7 +149,10 @@ void slz_bign_destroy(slz_ctx *ctx);
 void slz_bign_scratch(slz_ctx *ctx);
 int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc,
                         uint32_t batch, hipStream_t s);
-// largest batch of the two-launch steps, and where a batch is cut between its two lanes (tested on the host)
+// batches of the one launch, its driver for any number of workgroups (tests), largest batch of the two-launch steps, and where a batch is cut between its two lanes (tested on the host)
+uint32_t slz_bign_xcd_takes(uint32_t G, uint32_t l, uint32_t batch);
+int slz_bign_xcd_run(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc, uint32_t batch, uint32_t workgroups,
+                     hipStream_t s);
 uint32_t slz_bign_latency_max_batch(uint32_t G, uint32_t l);
 uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half);
 // keyswitch / lincomb (slz_keyswitch.hip)

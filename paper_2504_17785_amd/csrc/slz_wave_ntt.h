@@ -287,9 +287,14 @@ __device__ __forceinline__ void swap16(double &a, double &b) {
 // twB_tab: [15][64] per-lane twiddles of the last four stages.  Bounds: six stages 0.5 -> 4.81 p, reduction, four more -> 3.63 p.
 // PAIR: the 16 x 64 values are two independent 512-point polynomials (registers 0..7 and 8..15 on the way in, lanes
 // 0..31 and 32..63 on the way out): the stage that would pair them is left out and the tables carry each half's twiddles.
-template <bool PAIR = false>
+// DENSE: T is 1024 doubles without padding, a lane's 16 words turned by pairs (dense16_at).
+// Place of word j of lane l: 8 lanes' 16-byte reads of the same word cover all banks, as do 16 lanes' 8-byte writes to one lane's words.
+__device__ __forceinline__ uint32_t dense16_at(uint32_t l, uint32_t j) { return 16u * l + (j ^ (2u * (l & 7u))); }
+// between(0 .. 4): called between the stages, for loads that the caller spreads over the transform.
+struct nothing16 { __device__ __forceinline__ void operator()(int) const {} };
+template <bool PAIR = false, bool DENSE = false, class Between = nothing16>
 __device__ __forceinline__ void fwd16(double (&x)[16], double *T, const double *twA, const double *twB_tab, slz_mod m, uint32_t lane,
-                                      int z) {
+                                      int z, Between between = Between()) {
     const uint32_t hh = lane >> 5, v = (lane >> 4) & 1u, j = lane & 15u;
     // twA and twB_tab are expected in LDS (the kernel stages its block's tables there once): their reads do not queue
     // behind the kernel's global loads and need no registers until the stage that uses them
@@ -303,6 +308,8 @@ __device__ __forceinline__ void fwd16(double (&x)[16], double *T, const double *
             BF4(FA16_I(4 * g), FA16_I(4 * g) + half, FA16_W(4 * g), FA16_I(4 * g + 1), FA16_I(4 * g + 1) + half, FA16_W(4 * g + 1),
                 FA16_I(4 * g + 2), FA16_I(4 * g + 2) + half, FA16_W(4 * g + 2), FA16_I(4 * g + 3), FA16_I(4 * g + 3) + half, FA16_W(4 * g + 3));
         }
+        if (s == 1) between(0);
+        if (s == 3) between(1);
     }
 #pragma unroll
     for (int g = 0; g < 2; g++) {                                           // stride 32: partner 32 lanes away
@@ -312,7 +319,8 @@ __device__ __forceinline__ void fwd16(double (&x)[16], double *T, const double *
         BF4(8 * g, 8 * g + 1, TW5(4 * g), 8 * g + 2, 8 * g + 3, TW5(4 * g + 1), 8 * g + 4, 8 * g + 5, TW5(4 * g + 2), 8 * g + 6, 8 * g + 7,
             TW5(4 * g + 3));
     }
-    double *wb = T + 72u * hh + 36u * v + j;
+    double *wb = DENSE ? T + dense16_at(4u * hh + 2u * v, j) : T + 72u * hh + 36u * v + j, *wb1 = DENSE ? T + dense16_at(4u * hh + 2u * v + 1u, j) : wb + 18;
+    between(2);
 #pragma unroll
     for (int g = 0; g < 2; g++) {                                           // stride 16: partner 16 lanes away
 #pragma unroll
@@ -325,15 +333,16 @@ __device__ __forceinline__ void fwd16(double (&x)[16], double *T, const double *
         reduce_k<8>(r8, x8, m);
 #pragma unroll
         for (int u = 0; u < 4; u++) {                                       // registers 2 mm, 2 mm + 1 with mm = 4 g + u
-            wb[144 * (4 * g + u)] = r8[2 * u];
-            wb[144 * (4 * g + u) + 18] = r8[2 * u + 1];
+            wb[(DENSE ? 128 : 144) * (4 * g + u)] = r8[2 * u];
+            wb1[(DENSE ? 128 : 144) * (4 * g + u)] = r8[2 * u + 1];
         }
     }
     wave_sync();
     const double *rb = T + 18u * lane;
+    const uint32_t dense = dense16_at(lane, 0);
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
-        const double2 t2 = *reinterpret_cast<const double2 *>(rb + i);
+        const double2 t2 = *reinterpret_cast<const double2 *>(DENSE ? T + (dense ^ (uint32_t)i) : rb + i);
         x[i] = t2.x;
         x[i + 1] = t2.y;
     }
@@ -347,6 +356,8 @@ __device__ __forceinline__ void fwd16(double (&x)[16], double *T, const double *
             BF4(FB16_I(4 * g), FB16_I(4 * g) + t, FB16_W(4 * g), FB16_I(4 * g + 1), FB16_I(4 * g + 1) + t, FB16_W(4 * g + 1),
                 FB16_I(4 * g + 2), FB16_I(4 * g + 2) + t, FB16_W(4 * g + 2), FB16_I(4 * g + 3), FB16_I(4 * g + 3) + t, FB16_W(4 * g + 3));
         }
+        if (s == 0) between(3);
+        if (s == 2) between(4);
     }
 }
 
@@ -447,8 +458,8 @@ __device__ __forceinline__ void inv16(double (&x)[16], double *T, const double *
 static_assert(SLZ_P1_U64 < (1ull << 50) && SLZ_P2_U64 < (1ull << 50), "LAZY_PRODUCT");
 static_assert(LAZY_MAX <= 7.5, "integers stay below 2^53");
 static_assert(LAZY_PRODUCT(LAZY_MAX) <= 1.95, "the lift takes the products of the last column stage");
-// K independent pairs, interleaved like bfly_k
-template <int K>
+// K independent pairs, interleaved like bfly_k; NEG: w holds the negatives of the twiddles
+template <int K, bool NEG = false>
 __device__ __forceinline__ void gs_k(double *(&a)[K], double *(&b)[K], double *(&ba)[K], double *(&bb)[K], const double (&w)[K], slz_mod m) {
     double h[K], l[K], q[K], d[K];
 #pragma unroll
@@ -461,7 +472,7 @@ __device__ __forceinline__ void gs_k(double *(&a)[K], double *(&b)[K], double *(
         *bb[i] = LAZY_PRODUCT(s);
     }
 #pragma unroll
-    for (int i = 0; i < K; i++) d[i] = *a[i] - *b[i];
+    for (int i = 0; i < K; i++) d[i] = NEG ? *b[i] - *a[i] : *a[i] - *b[i];
 #pragma unroll
     for (int i = 0; i < K; i++) h[i] = d[i] * w[i];
 #pragma unroll
@@ -487,11 +498,15 @@ __device__ __forceinline__ void lazy_limit(double (&x)[K], double (&bd)[K], doub
 #define GS4(i0, j0, w0, i1, j1, w1, i2, j2, w2, i3, j3, w3) do { \
     double *pa_[4] = {&x[i0], &x[i1], &x[i2], &x[i3]}; double *pb_[4] = {&x[j0], &x[j1], &x[j2], &x[j3]}; \
     double *ua_[4] = {&bd[i0], &bd[i1], &bd[i2], &bd[i3]}; double *ub_[4] = {&bd[j0], &bd[j1], &bd[j2], &bd[j3]}; \
-    const double pw_[4] = {w0, w1, w2, w3}; gs_k<4>(pa_, pb_, ua_, ub_, pw_, m); } while (0)
+    const double pw_[4] = {w0, w1, w2, w3}; gs_k<4, DENSE>(pa_, pb_, ua_, ub_, pw_, m); } while (0)
 
 // 1024 points.  In: layout B, |x| <= 0.51 p.  Out: layout A, |x| <= LAZY_MAX p.  twB: the 15 per-lane twiddles of the first four stages
 // (inverses of the entries fwd16 takes from twB_tab), twA: the block's 64 lane-uniform ones (inverses of fwd16's twA).
-__device__ __forceinline__ void inv16_mirror(double (&x)[16], double *T, const double *twA, const double (&twB)[15], slz_mod m, uint32_t lane, int z) {
+// DENSE: T as in fwd16, and no tables of inverses: fwd[m + i] is psi to an odd multiple of N / m times its bit-reversed i, so
+// 1 / fwd[m + i] = -fwd[m + (m - 1 - i)], and the last block's tables read backwards are the first one's inverses, up to the sign.  twA: the
+// forward ones of block G - 1 - row; twB: its entries mirrored by the caller (lane 63 - lane, entry 2^(s + 1) - 2 - blk for 2^s - 1 + blk).
+template <bool DENSE = false, class Between = nothing16>
+__device__ __forceinline__ void inv16_mirror(double (&x)[16], double *T, const double *twA, const double (&twB)[15], slz_mod m, uint32_t lane, int z, Between between = Between()) {
     const uint32_t hh = lane >> 5, v = (lane >> 4) & 1u, j = lane & 15u;
     double bd[16];
 #pragma unroll
@@ -506,29 +521,32 @@ __device__ __forceinline__ void inv16_mirror(double (&x)[16], double *T, const d
             GS4(GB16_I(4 * g), GB16_I(4 * g) + t, GB16_W(4 * g), GB16_I(4 * g + 1), GB16_I(4 * g + 1) + t, GB16_W(4 * g + 1),
                 GB16_I(4 * g + 2), GB16_I(4 * g + 2) + t, GB16_W(4 * g + 2), GB16_I(4 * g + 3), GB16_I(4 * g + 3) + t, GB16_W(4 * g + 3));
         }
+        if (s == 2) between(0);
+        if (s == 0) between(1);
     }
     lazy_limit(x, bd, 0.6, m);
     wave_sync();                                                            // earlier reads of T are done
     double *wb = T + 18u * lane;
+    const uint32_t dense = dense16_at(lane, 0);
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
         double2 t2;
         t2.x = x[i];
         t2.y = x[i + 1];
-        *reinterpret_cast<double2 *>(wb + i) = t2;
+        *reinterpret_cast<double2 *>(DENSE ? T + (dense ^ (uint32_t)i) : wb + i) = t2;
     }
     wave_sync();
-    const double *rb = T + 72u * hh + 36u * v + j;
+    const double *rb = DENSE ? T + dense16_at(4u * hh + 2u * v, j) : T + 72u * hh + 36u * v + j, *rb1 = DENSE ? T + dense16_at(4u * hh + 2u * v + 1u, j) : rb + 18;
 #pragma unroll
     for (int mm = 0; mm < 8; mm++) {
-        x[2 * mm] = rb[144 * mm];
-        x[2 * mm + 1] = rb[144 * mm + 18];
+        x[2 * mm] = rb[(DENSE ? 128 : 144) * mm];
+        x[2 * mm + 1] = rb1[(DENSE ? 128 : 144) * mm];
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) bd[i] = 0.6;
 #pragma unroll
     for (int g = 0; g < 2; g++) {                                           // t = 16: block 4 mm + 2 hh + v of 32
-#define GW6(mm) ldl(twA + 32 + 4 * (mm) + z, (lane >> 4) * 8u)
+#define GW6(mm) (DENSE ? ldl(twA + 60 - 4 * (mm) + z, (3u - (lane >> 4)) * 8u) : ldl(twA + 32 + 4 * (mm) + z, (lane >> 4) * 8u))
         GS4(8 * g, 8 * g + 1, GW6(4 * g), 8 * g + 2, 8 * g + 3, GW6(4 * g + 1), 8 * g + 4, 8 * g + 5, GW6(4 * g + 2), 8 * g + 6, 8 * g + 7,
             GW6(4 * g + 3));
 #pragma unroll
@@ -537,9 +555,10 @@ __device__ __forceinline__ void inv16_mirror(double (&x)[16], double *T, const d
             bd[2 * mm] = bd[2 * mm + 1] = bd[2 * mm] > bd[2 * mm + 1] ? bd[2 * mm] : bd[2 * mm + 1];
         }
     }
+    between(2);
 #pragma unroll
     for (int g = 0; g < 2; g++) {                                           // t = 32: block 2 mm + hh of 16
-#define GW5(mm) ldl(twA + 16 + 2 * (mm) + z, hh * 8u)
+#define GW5(mm) (DENSE ? ldl(twA + 30 - 2 * (mm) + z, (1u - hh) * 8u) : ldl(twA + 16 + 2 * (mm) + z, hh * 8u))
         GS4(8 * g, 8 * g + 1, GW5(4 * g), 8 * g + 2, 8 * g + 3, GW5(4 * g + 1), 8 * g + 4, 8 * g + 5, GW5(4 * g + 2), 8 * g + 6, 8 * g + 7,
             GW5(4 * g + 3));
 #pragma unroll
@@ -554,9 +573,11 @@ __device__ __forceinline__ void inv16_mirror(double (&x)[16], double *T, const d
 #pragma unroll
         for (int g = 0; g < 2; g++) {
 #define GA16_I(b) (((b) / half) * 2 * half + (b) % half)
-#define GA16_W(b) twA[(1 << s) + (b) / half + z]
+#define GA16_W(b) twA[(DENSE ? (2 << s) - 1 - (b) / half : (1 << s) + (b) / half) + z]
             GS4(GA16_I(4 * g), GA16_I(4 * g) + half, GA16_W(4 * g), GA16_I(4 * g + 1), GA16_I(4 * g + 1) + half, GA16_W(4 * g + 1),
                 GA16_I(4 * g + 2), GA16_I(4 * g + 2) + half, GA16_W(4 * g + 2), GA16_I(4 * g + 3), GA16_I(4 * g + 3) + half, GA16_W(4 * g + 3));
         }
+        if (s == 3) between(3);
+        if (s == 1) between(4);
     }
 }

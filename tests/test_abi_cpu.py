@@ -264,6 +264,14 @@ def test_large_n_two_launch_steps_end_where_they_stop_winning():
     assert {l: {G: f(G, l) for G in row} for l, row in want.items()} == want
 
 
+def test_large_n_one_launch_is_taken_where_it_wins():
+    # rounds of eight ciphertexts: the first two, and the fuller part of the next three
+    f = slz.lib()._Z18slz_bign_xcd_takesjjj
+    f.argtypes, f.restype = [ctypes.c_uint32] * 3, ctypes.c_uint32
+    assert [b for b in range(1, 300) if f(32, 2, b)] == list(range(1, 17)) + list(range(22, 25)) + list(range(31, 41))
+    assert not any(f(G, l, b) for G in (2, 4, 8, 16, 32, 64) for l in (1, 2, 3, 4) for b in range(1, 65) if (G, l) != (32, 2))
+
+
 def test_bench_counts_the_key_form_and_the_operations_of_the_path_that_runs():
     import sys
     sys.path.insert(0, ROOT)

@@ -1038,3 +1038,35 @@ def test_large_n_without_room_for_the_second_accumulator_runs_three_launches(slz
         got = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
         case.ctx.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, -1)
         assert np.array_equal(got, want), after
+
+
+def test_large_n_one_launch_matches_the_throughput_kernels(slz, orc):
+    # N = 32768 with two levels: lists of one, two, three and five ciphertexts, odd and even counts of them; the throughput kernels are compared with
+    # the oracle elsewhere
+    p = tiny(n=3, N=32768, k=1, pbs_base_log=15, pbs_level=2)
+    case = Case(slz, orc, p, 40, raw_inputs=True)
+    for steps in (1, 2, p.n):
+        case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
+        want = case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, steps)
+        case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 1)
+        for count in (1, 7, 8, 9, 16, 23, 40):
+            got = case.ctx.blind_rotate_batch(case.d_cts[:count], case.d_luts, case.d_idx[:count], case.d_bsk, steps)
+            assert torch.equal(got, want[:count]), (steps, count)
+
+
+@pytest.mark.parametrize("count", [1, 9])
+def test_large_n_one_launch_needs_no_number_of_workgroups(slz, orc, count):
+    # the launch's driver (an internal function, by its mangled name) with fewer workgroups than slots, so that slots and whole lists are
+    # taken over, and with more
+    p = tiny(n=3, N=32768, k=1, pbs_base_log=15, pbs_level=2)
+    case = Case(slz, orc, p, count, raw_inputs=True)
+    want = case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, p.n)
+    start = case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, 0)
+    run = slz.lib()._Z16slz_bign_xcd_runP7slz_ctxPKmPKdjPmjjP12ihipStream_t
+    run.argtypes, run.restype = [ctypes.c_void_p] * 3 + [ctypes.c_uint32, ctypes.c_void_p] + [ctypes.c_uint32] * 2 + [ctypes.c_void_p], ctypes.c_int
+    for workgroups in (1, 2, 13, 200, 255, 300):
+        acc = start.clone()
+        torch.cuda.synchronize()
+        assert run(case.ctx._h, case.d_cts.data_ptr(), case.d_bsk.data_ptr(), p.n, acc.data_ptr(), count, workgroups, None) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(acc, want), workgroups
