@@ -100,6 +100,10 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
  * no larger than max_batch record only kernels and event edges on the given stream and may be captured into a HIP graph
  * (warm up once outside the capture). */
 
+/* Streams: at N = 2048 and N = 4096 (k = l = 1) a call with up to 128 ciphertexts uses memory of its context, allocated with it.  Calls of one
+ * context on several streams may overlap all the same: one that finds that memory in use by another stream, and one that is being captured,
+ * runs the kernel without (same results, 1.1 to 1.4 times the time). */
+
 /* Creates a context on the current device.  Allocates transform tables and scratch sized for
  * `max_batch` ciphertexts.  Fails with SLZ_E_UNSUPPORTED when the exactness bound
  * 4 * (k+1) * l * N * 2^(beta-1) * 2^63 <= p1 * p2 (the two ~2^50 transform primes) does not hold. */

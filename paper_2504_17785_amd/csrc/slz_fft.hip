@@ -1,4 +1,5 @@
 // Host side and key preparation of the floating-point transform path (see slz_fft.h): error bound, tables, key spectra.
+#include "slz_xcd.h"
 #include "slz_fft.h"
 #include <cmath>
 #include <cstring>
@@ -263,6 +264,50 @@ static const host_tables &tables(uint32_t N) {
     return t512;
 }
 
+// ---- pairs of workgroups (slz_xcd.h) ------------------------------------------------------------------------------------
+
+// Their words and mail: 32 bytes per coefficient and pair, for as many pairs as a launch makes.  A context without them (no room) runs
+// every batch with one workgroup per ciphertext.
+static void pairs_init(slz_ctx *ctx) {
+    const uint32_t N = ctx->prm.N;
+    if (N != 2048 && N != 4096) return;
+    const uint32_t most = ctx->max_batch < SLZ_PAIR_MAX ? ctx->max_batch : SLZ_PAIR_MAX, pairs = slz_pairs_grid(most) / 2;
+    const size_t words = (SLZ_PAIR_WORDS * sizeof(uint32_t) + 255) & ~(size_t)255;
+    void *buf = nullptr;
+    hipEvent_t ev;
+    if (hipMalloc(&buf, words + (size_t)pairs * 2 * 2 * (N / 2) * 16) != hipSuccess) { (void)hipGetLastError(); return; }
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(buf); return; }
+    ctx->pair_ctl = (uint32_t *)buf;
+    ctx->pair_mail = (char *)buf + words;
+    ctx->pair_done = ev;
+}
+
+// The context's words and mail for a launch on s, or 0: calls of one context on several streams may overlap, and a captured call may be
+// replayed at any time, so those that could meet an earlier launch's use of them keep to the kernels that need none.
+int slz_pairs_acquire(slz_ctx *ctx, uint32_t batch, hipStream_t s) {
+    if (!ctx->pair_ctl || batch > SLZ_PAIR_MAX) return 0;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return 0; }
+    if (!ctx->pair_used) return 1;
+    if (ctx->pair_stream != s && hipEventQuery((hipEvent_t)ctx->pair_done) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    // the same stream's earlier launches come first anyway, unless the handle has passed on to a new stream
+    return hipStreamWaitEvent(s, (hipEvent_t)ctx->pair_done, 0) == hipSuccess;
+}
+int slz_pairs_release(slz_ctx *ctx, hipStream_t s) {
+    SLZ_HIP(hipEventRecord((hipEvent_t)ctx->pair_done, s));
+    ctx->pair_used = 1;
+    ctx->pair_stream = s;
+    return SLZ_OK;
+}
+slz_pairs slz_pairs_of(const slz_ctx *ctx) { return slz_pairs{ctx->pair_ctl}; }
+__global__ void __launch_bounds__(256) k_pairs_clear(uint32_t *ctl) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < SLZ_PAIR_WORDS) ctl[i] = 0;
+}
+void slz_pairs_clear(slz_ctx *ctx, hipStream_t s) {
+    hipLaunchKernelGGL(k_pairs_clear, dim3((SLZ_PAIR_WORDS + 255) / 256), dim3(256), 0, s, ctx->pair_ctl);
+}
+
 int slz_fft_init(slz_ctx *ctx) {
     const host_tables &h = tables(ctx->prm.N);
     std::memcpy(ctx->fft_f1, h.f1, sizeof(h.f1));
@@ -270,10 +315,15 @@ int slz_fft_init(slz_ctx *ctx) {
     SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, h.w.size() * sizeof(double)));
     SLZ_HIP(hipMemcpy(ctx->fft_tab, h.t.data(), h.t.size() * sizeof(cpl), hipMemcpyHostToDevice));
     SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, h.w.data(), h.w.size() * sizeof(double), hipMemcpyHostToDevice));
+    pairs_init(ctx);
     return ctx->prm.N == 4096 ? slz_fft4096_setup() : ctx->prm.N == 2048 ? slz_fft2048_setup() : ctx->prm.N == 1024 ? slz_fft1024_setup() : slz_fft512_setup();
 }
 
 void slz_fft_destroy(slz_ctx *ctx) {
+    if (ctx->pair_done) (void)hipEventDestroy((hipEvent_t)ctx->pair_done);
+    if (ctx->pair_ctl) (void)hipFree(ctx->pair_ctl);
+    ctx->pair_done = ctx->pair_mail = nullptr;
+    ctx->pair_ctl = nullptr;
     if (ctx->fft_tab) (void)hipFree(ctx->fft_tab);
     if (ctx->fft_prep_tab) (void)hipFree(ctx->fft_prep_tab);
     ctx->fft_tab = nullptr;

@@ -27,7 +27,7 @@
 // Two waves hide little of each other's LDS round trips, so loads are requested in groups ahead of the arithmetic, and results are
 // written while the next ones are computed.  Measured with 742 steps (in brackets: two residues on the same card): 1024 ciphertexts
 // 20.2 ms (31.5), 4096: 80.6 (126.6), 301: 11.5 (15.4).
-// Batches up to 256 go to slz_fft2048_team.hip.  From 257 to 512 a compute unit has two ciphertexts; two pairs work on each (SHARE = 2).
+// Batches up to 128 go to slz_fft2048_pair.hip, up to 256 to slz_fft2048_team.hip.  From 257 to 512 a compute unit has two ciphertexts; two pairs work on each (SHARE = 2).
 #include "slz_fft.h"
 #include "slz_fft_wave.h"
 #include "slz_modarith.h"
@@ -475,6 +475,7 @@ k_fft_blind_rotate(fft_args A) {
 int slz_fft2048_setup() {
     const void *const kernels[] = {(const void *)k_fft_blind_rotate<1>, (const void *)k_fft_blind_rotate<2>};
     for (const void *k : kernels) SLZ_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FFT_LDS_BYTES));
+    if (slz_fft2048_pair_setup() != SLZ_OK) return SLZ_E_HIP;
     return slz_fft2048_team_setup();
 }
 
@@ -482,6 +483,12 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
     // Up to one ciphertext per compute unit its eight waves take one together (742 steps: one 7.2 ms against 8.5 with two pairs on it, 256
     // 8.3 against 8.6); from 257 on that needs a second round (301: 14.6 ms against 11.5).
+    // Up to 128 ciphertexts two workgroups take each (6.4 to 6.6 us per step against 9.2 to 9.3 with one), unless an overlapping or captured call needs the
+    // kernel without memory of its own.
+    if (n_steps && slz_pairs_acquire(ctx, batch, s)) {
+        const int rc = slz_fft2048_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);
+        return rc == SLZ_OK ? slz_pairs_release(ctx, s) : rc;
+    }
     if (batch <= FFT_TEAM_MAX) return slz_fft2048_team(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);
     fft_args A;
     A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;

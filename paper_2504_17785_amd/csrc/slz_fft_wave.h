@@ -16,6 +16,12 @@ __device__ __forceinline__ d2 lane_get(const d2 *uniform_base, uint32_t lane) {
     return *reinterpret_cast<const d2 *>(reinterpret_cast<const char *>(uniform_base) + lane * 16u);
 }
 
+__device__ __forceinline__ void lane_put(d2 *uniform_base, uint32_t lane, d2 v) {
+    *reinterpret_cast<d2 *>(reinterpret_cast<char *>(uniform_base) + lane * 16u) = v;
+}
+
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
 template <int V> struct fft_int { static constexpr int value = V; };
 
 // x w for a plain complex factor
@@ -91,6 +97,30 @@ __device__ __forceinline__ void inv8(d2 *s) {
         s[7].x = __builtin_fma(-r2, p, s[3].x); s[7].y = __builtin_fma(r2, q, s[3].y);
         s[3].x = __builtin_fma(r2, p, s[3].x); s[3].y = __builtin_fma(-r2, q, s[3].y);
     }
+}
+
+// forward radix-8 with u .. u^7: the values of sum_k x_k (u z)^k at z = 1, -1, i, -i, w, -w, iw, -iw, w = (1 + i) / sqrt(2)
+__device__ __forceinline__ void fwd8(d2 *x, const d2 *u) {
+    const double r2 = FFT_SQRT_HALF;
+#pragma unroll
+    for (int k = 1; k < 8; k++) x[k] = cmul(x[k], u[k - 1]);
+    const d2 s04 = x[0] + x[4], d04 = x[0] - x[4], s26 = x[2] + x[6], d26 = x[2] - x[6];
+    const d2 s15 = x[1] + x[5], d15 = x[1] - x[5], s37 = x[3] + x[7], d37 = x[3] - x[7];
+    const d2 e0 = s04 + s26, e1 = s04 - s26, o0 = s15 + s37, o1 = s15 - s37;
+    d2 e2, e3, o2, o3;
+    e2.x = d04.x - d26.y; e2.y = d04.y + d26.x;
+    e3.x = d04.x + d26.y; e3.y = d04.y - d26.x;
+    o2.x = d15.x - d37.y; o2.y = d15.y + d37.x;
+    o3.x = d15.x + d37.y; o3.y = d15.y - d37.x;
+    x[0] = e0 + o0;
+    x[1] = e0 - o0;
+    x[2].x = e1.x - o1.y; x[2].y = e1.y + o1.x;
+    x[3].x = e1.x + o1.y; x[3].y = e1.y - o1.x;
+    const double p2 = o2.x - o2.y, q2 = o2.x + o2.y, p3 = o3.x - o3.y, q3 = o3.x + o3.y;
+    x[4].x = __builtin_fma(r2, p2, e2.x); x[4].y = __builtin_fma(r2, q2, e2.y);
+    x[5].x = __builtin_fma(-r2, p2, e2.x); x[5].y = __builtin_fma(-r2, q2, e2.y);
+    x[6].x = __builtin_fma(-r2, q3, e3.x); x[6].y = __builtin_fma(r2, p3, e3.y);
+    x[7].x = __builtin_fma(r2, q3, e3.x); x[7].y = __builtin_fma(-r2, p3, e3.y);
 }
 
 // acc += y 2^s for the bits y of (integer + 1.5 * 2^52): the bits of that constant lie above bit 50, so they leave the word with any

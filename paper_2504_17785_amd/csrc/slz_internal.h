@@ -57,6 +57,11 @@ struct slz_ctx {
     void *fft_tab;            // its tables (slz_fft.h)
     double *fft_prep_tab;     // double-double twiddles of the key preparation
     double fft_f1[15][2];     // host copy of its lane-uniform twiddles
+    uint32_t *pair_ctl;       // N = 2048, 4096, few ciphertexts: control words of the pairs of workgroups (slz_xcd.h), behind them their mail; or null
+    void *pair_mail;
+    void *pair_done;          // hipEvent_t: behind the last launch that used them
+    int pair_used;            // there has been one
+    void *pair_stream;        // its stream
     int has_bign;             // large-N three-pass path available (N = 2048 G, k = 1)
     double *bign_rowA;        // [2][G][64] block-specific lane-uniform forward twiddles
     double *bign_rowB;        // [2][G][31][64] block-specific per-lane forward twiddles
@@ -132,6 +137,14 @@ int slz_fft2048_setup();
 int slz_fft2048_team_setup();
 int slz_fft2048_team(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                      uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+int slz_fft2048_pair_setup();
+int slz_fft2048_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+int slz_fft4096_pair_setup();
+int slz_fft4096_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+int slz_pairs_acquire(slz_ctx *ctx, uint32_t batch, hipStream_t s);
+int slz_pairs_release(slz_ctx *ctx, hipStream_t s);
 int slz_fft1024_setup();
 int slz_fft512_setup();
 int slz_fft512_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,

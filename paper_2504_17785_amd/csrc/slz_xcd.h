@@ -1,0 +1,88 @@
+// Workgroups of one XCD that work together through its L2, and pairs of them.
+//
+// Memory order.  The vector L1 caches are not coherent; an XCD's L2 is shared by all its compute units.  What one workgroup writes for another goes
+// to the L2 by plain stores (the L1 writes through, s_waitcnt vmcnt(0) waits for the L2's acknowledgement), and is read by agent-scope loads, which
+// pass the L1.  This holds inside one XCD only, so workgroups find each other by the XCC_ID they run on; words that workgroups of
+// different XCDs share are written and read by agent-scope atomics alone.
+#pragma once
+#include "slz_internal.h"
+#include "slz_fft_wave.h"
+
+__device__ __forceinline__ uint32_t slz_xcc_id() {
+    uint32_t v;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
+    return v & 15u;
+}
+__device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// This wave's stores have reached the L2; then the word is written there.
+__device__ __forceinline__ void slz_xcd_report(uint32_t *word, uint32_t value) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if ((threadIdx.x & 63u) == 0) __hip_atomic_store(word, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Waits for a workgroup that runs and takes the same sequence of steps, so it ends.
+__device__ __forceinline__ void slz_xcd_await(const uint32_t *word, uint32_t value) {
+    asm volatile("" ::: "memory");
+    while ((int32_t)(__builtin_amdgcn_readfirstlane(ld_agent(word)) - value) < 0) {}
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ d2 lane_get_l2(const d2 *uniform_base, uint32_t lane) {
+    const double *p = reinterpret_cast<const double *>(reinterpret_cast<const char *>(uniform_base) + lane * 16u);
+    d2 r;
+    r.x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    r.y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return r;
+}
+
+// Pairs.  A workgroup takes a number on its XCD; two with successive numbers are a pair, the second of which asks for ciphertexts for both until
+// there are none left.  The first waits for the second to start.  It ends: the second is a workgroup of the same launch (or, where the launch
+// has none left, all ciphertexts get taken by other pairs and the first sees that), which starts as soon as a place is free; places are held by pairs, which
+// wait for nobody else, by kernels that do not wait, and by at most one such first workgroup per XCD and launch in flight, of which
+// there are fewer (hardware queues) than an XCD has compute units.
+#define SLZ_PAIR_MAX 128u                           // pairs of a launch: 256 workgroups
+#define SLZ_PAIR_NONE 0xffffffffu
+struct slz_pairs {
+    uint32_t *ctl;            // words, zero at the start: [0] ciphertexts taken, [32] pairs, [64 + 32 x] numbers of XCD x, then [16][128] pair + 1 by
+};                            // XCD and number / 2, then a line of 32 words per pair: [8] progress of its waves, [8] the ciphertext at hand
+#define SLZ_PAIR_MET 576u
+#define SLZ_PAIR_LINES (SLZ_PAIR_MET + 16u * 128u)
+#define SLZ_PAIR_WORDS (SLZ_PAIR_LINES + 32u * SLZ_PAIR_MAX)
+__device__ __forceinline__ uint32_t *slz_pair_line(slz_pairs P, uint32_t pair) { return P.ctl + SLZ_PAIR_LINES + 32u * pair; }
+
+// One thread: 2 pair + (0 first, 1 second), or SLZ_PAIR_NONE
+__device__ __forceinline__ uint32_t slz_pair_join(slz_pairs P, uint32_t batch) {
+    const uint32_t x = slz_xcc_id();
+    const uint32_t number = __hip_atomic_fetch_add(P.ctl + 64 + 32 * x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t *met = P.ctl + SLZ_PAIR_MET + 128 * x + number / 2;
+    if (number & 1u) {
+        const uint32_t pair = __hip_atomic_fetch_add(P.ctl + 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // in the L2 before a ciphertext is taken: a first workgroup that sees the last one taken sees this too
+        __hip_atomic_store(met, pair + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return 2 * pair + 1;
+    }
+    for (;;) {
+        const bool over = ld_agent(P.ctl) >= batch;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // seen before the next look at the other word
+        const uint32_t pair = ld_agent(met);
+        if (pair) return 2 * (pair - 1);
+        if (over) return SLZ_PAIR_NONE;
+    }
+}
+// One thread of either workgroup: the pair's ciphertext of this round, or one past the last
+__device__ __forceinline__ uint32_t slz_pair_next(slz_pairs P, uint32_t pair, uint32_t second, uint32_t round) {
+    uint32_t *word = slz_pair_line(P, pair) + 8;
+    if (second) {
+        const uint32_t c = __hip_atomic_fetch_add(P.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(word, ((round + 1) << 16) | c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return c;
+    }
+    for (;;) {
+        const uint32_t w = ld_agent(word);
+        if (w >> 16 == round + 1) return w & 0xffffu;
+    }
+}
+
+// host (slz_fft.hip)
+static inline uint32_t slz_pairs_grid(uint32_t batch) { return 16u * ((batch + 7) / 8); }      // two workgroups per ciphertext of every XCD's share
+slz_pairs slz_pairs_of(const slz_ctx *ctx);
+void slz_pairs_clear(slz_ctx *ctx, hipStream_t s);

@@ -1,0 +1,67 @@
+"""N = 2048 and 4096 with few ciphertexts, where two workgroups share each: against the kernels with one workgroup per ciphertext (which larger
+batches, captured calls and calls beside another stream's take) bit for bit; those are compared with the oracle elsewhere."""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slz():
+    import paper_2504_17785_amd as m
+    return m
+
+
+def _case(slz, N, batch, n):
+    p = synth.CONFIGS[2].with_(name="pairs", N=N, n=n, pbs_level=1, pbs_base_log=22, msg_bits=3, batch=batch)
+    bsk = synth.raw_words(p, "raw_bsk", n * 4 * N).reshape(n, 2, 1, 2, N)
+    luts = synth.raw_words(p, "misc", 2 * N).reshape(2, N)
+    cts = synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1)
+    ctx = slz.Context(p, batch)
+    d_bsk = ctx.bsk_prepare(slz.to_device_u64(bsk))
+    return ctx, [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy((np.arange(batch) % 2).astype(np.int32)).cuda(), d_bsk]
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
+def test_pairs_of_workgroups_match_one_workgroup(slz, N):
+    # 129 ciphertexts are one past the pairs' last; 8 and 9: one pair per XCD and a second on each; one step and an odd and an even number of them
+    ctx, d = _case(slz, N, 129, 6)
+    for steps in (1, 5, 6):
+        every = ctx.blind_rotate_batch(*d, steps)
+        for count in (1, 2, 8, 9, 63, 127, 128):
+            part = ctx.blind_rotate_batch(d[0][:count], d[1], d[2][:count], d[3], steps)
+            assert torch.equal(part, every[:count]), (steps, count)
+    every = ctx.pbs_batch(*d)
+    for _ in range(3):
+        assert torch.equal(ctx.pbs_batch(d[0][:100], d[1], d[2][:100], d[3]), every[:100])
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
+def test_pairs_of_workgroups_beside_other_streams_and_in_graphs(slz, N):
+    ctx, d = _case(slz, N, 129, 40)
+    every = ctx.pbs_batch(*d)
+    count = 100
+    few = [d[0][:count].clone(), d[1], d[2][:count].clone(), d[3]]
+    outs = [torch.empty_like(every[:count]) for _ in range(6)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):                      # calls of one context on two streams at once
+        with torch.cuda.stream(streams[i % 2]):
+            ctx.pbs_batch(*few, out=out)
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        assert torch.equal(out, every[:count]), i
+    graph, out = torch.cuda.CUDAGraph(), torch.empty_like(outs[0])
+    with torch.cuda.graph(graph):
+        ctx.pbs_batch(*few, out=out)
+    for rep in range(3):                                # replays beside eager calls on another stream
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        with torch.cuda.stream(streams[0]):
+            ctx.pbs_batch(*few, out=outs[0])
+        torch.cuda.synchronize()
+        assert torch.equal(out, every[:count]) and torch.equal(outs[0], every[:count]), rep
