@@ -100,7 +100,7 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
  * no larger than max_batch record only kernels and event edges on the given stream and may be captured into a HIP graph
  * (warm up once outside the capture). */
 
-/* Streams: at N = 2048 and N = 4096 (k = l = 1) a call with up to 128 ciphertexts uses memory of its context, allocated with it.  Calls of one
+/* Streams: at N = 2048 and N = 4096 (k = l = 1) a call with up to 128 ciphertexts uses memory of its context, allocated by the first such call.  Calls of one
  * context on several streams may overlap all the same: one that finds that memory in use by another stream, and one that is being captured,
  * runs the kernel without (same results, 1.1 to 1.4 times the time). */
 

@@ -266,11 +266,11 @@ static const host_tables &tables(uint32_t N) {
 
 // ---- pairs of workgroups (slz_xcd.h) ------------------------------------------------------------------------------------
 
-// Their words and mail: 32 bytes per coefficient and pair, for as many pairs as a launch makes.  A context without them (no room) runs
-// every batch with one workgroup per ciphertext.
+// Their words and mail: 32 bytes per coefficient and pair, for as many pairs as a launch makes; asked for once, by
+// the first call that could use them.  A context without them (no room) runs every batch with one workgroup per ciphertext.
 static void pairs_init(slz_ctx *ctx) {
     const uint32_t N = ctx->prm.N;
-    if (N != 2048 && N != 4096) return;
+    ctx->pair_asked = 1;
     const uint32_t most = ctx->max_batch < SLZ_PAIR_MAX ? ctx->max_batch : SLZ_PAIR_MAX, pairs = slz_pairs_grid(most) / 2;
     const size_t words = (SLZ_PAIR_WORDS * sizeof(uint32_t) + 255) & ~(size_t)255;
     void *buf = nullptr;
@@ -285,9 +285,11 @@ static void pairs_init(slz_ctx *ctx) {
 // The context's words and mail for a launch on s, or 0: calls of one context on several streams may overlap, and a captured call may be
 // replayed at any time, so those that could meet an earlier launch's use of them keep to the kernels that need none.
 int slz_pairs_acquire(slz_ctx *ctx, uint32_t batch, hipStream_t s) {
-    if (!ctx->pair_ctl || batch > SLZ_PAIR_MAX) return 0;
+    if (batch > SLZ_PAIR_MAX) return 0;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return 0; }
+    if (!ctx->pair_asked) pairs_init(ctx);
+    if (!ctx->pair_ctl) return 0;
     if (!ctx->pair_used) return 1;
     if (ctx->pair_stream != s && hipEventQuery((hipEvent_t)ctx->pair_done) != hipSuccess) { (void)hipGetLastError(); return 0; }
     // the same stream's earlier launches come first anyway, unless the handle has passed on to a new stream
@@ -315,7 +317,6 @@ int slz_fft_init(slz_ctx *ctx) {
     SLZ_HIP(hipMalloc((void **)&ctx->fft_prep_tab, h.w.size() * sizeof(double)));
     SLZ_HIP(hipMemcpy(ctx->fft_tab, h.t.data(), h.t.size() * sizeof(cpl), hipMemcpyHostToDevice));
     SLZ_HIP(hipMemcpy(ctx->fft_prep_tab, h.w.data(), h.w.size() * sizeof(double), hipMemcpyHostToDevice));
-    pairs_init(ctx);
     return ctx->prm.N == 4096 ? slz_fft4096_setup() : ctx->prm.N == 2048 ? slz_fft2048_setup() : ctx->prm.N == 1024 ? slz_fft1024_setup() : slz_fft512_setup();
 }
 

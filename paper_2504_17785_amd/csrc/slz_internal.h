@@ -60,7 +60,8 @@ struct slz_ctx {
     uint32_t *pair_ctl;       // N = 2048, 4096, few ciphertexts: control words of the pairs of workgroups (slz_xcd.h), behind them their mail; or null
     void *pair_mail;
     void *pair_done;          // hipEvent_t: behind the last launch that used them
-    int pair_used;            // there has been one
+    int pair_asked;           // their allocation has been tried
+    int pair_used;            // there has been such a launch
     void *pair_stream;        // its stream
     int has_bign;             // large-N three-pass path available (N = 2048 G, k = 1)
     double *bign_rowA;        // [2][G][64] block-specific lane-uniform forward twiddles
