@@ -28,11 +28,15 @@ k_lcm_weights(const int32_t *__restrict__ w, v4i *__restrict__ dig, uint8_t *__r
     for (int b = 0; b < LM_MAX_PLANES; b++)
 #pragma unroll
         for (int q = 0; q < 4; q++) wd[b][q] = 0;
+    // unconditional, of the nearest weight that exists: sixteen loads behind conditions of their own were sixteen round trips (7.5 us for 784 x 128
+    // weights in front of 42 us of contraction)
+    int32_t w16[16];
+#pragma unroll
+    for (int t = 0; t < 16; t++) w16[t] = w[(size_t)min(j0 + t, J - 1) * O + min(o, O - 1)];
     uint32_t used = 0;
 #pragma unroll
     for (int t = 0; t < 16; t++) {
-        const uint32_t j = j0 + t;
-        const int64_t W = (o < O && j < J) ? (int64_t)w[(size_t)j * O + o] : 0;
+        const int64_t W = (o < O && j0 + t < J) ? (int64_t)w16[t] : 0;
         const int64_t T = W + 0x80808080ll;
 #pragma unroll
         for (int b = 0; b < 4; b++) {
