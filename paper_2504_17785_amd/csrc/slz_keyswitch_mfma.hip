@@ -5,7 +5,8 @@
 // is recoded into eight signed bytes s_p in [-128, 128) with w = sum_p s_p 2^(8p) (mod 2^64): s_p is byte p of
 // (w + 0x80..80) with its top bit flipped.  Each byte plane is one int8 x int8 -> int32 contraction; the eight plane sums
 // are recombined with shifts at the end.  Products are at most 2^14 in magnitude, so an int32 accumulator is exact for
-// fewer than 2^17 key rows; the host keeps every segment of the row index below that.
+// fewer than 2^17 key rows; the host keeps every segment of the row index below that, and a workgroup that takes a range
+// adds its sums to the output before it gets there.
 //
 // Row order inside the contraction is level-major, rho = j * kN + i, so that 16 consecutive rows are 16 consecutive mask
 // words at one level (kN must be a multiple of 32).
@@ -17,6 +18,8 @@
 #define KM_THREADS (64 * KM_WAVES)
 #define KM_IT_KB (KM_WAVES / 2)         // 32-row blocks per iteration: each thread brings in 8 rows of one output word
 #define KM_TARGET_WGS 768               // workgroups aimed for when the row index is cut into segments (three per CU)
+#define KM_RANGES_GROUPS_PREP 16        // ciphertext groups up to which workgroups take ranges of rows across x tiles: operand form,
+#define KM_RANGES_GROUPS_STD 8          // standard key
 #define KM_BUF_V4 (KM_IT_KB * 2 * 8 * 32)   // 16-byte slots per LDS buffer: [block][half][plane][x]
 
 // ---- digits --------------------------------------------------------------------------------------------------------
@@ -137,53 +140,70 @@ struct ksm_args {
     uint32_t kN, n, l, batch;
     uint32_t n_tiles;       // 32-ciphertext tiles in dig
     uint32_t n_kb;          // 32-row blocks in total (l kN / 32)
-    uint32_t kb_per_seg;    // multiple of 2 KM_IT_KB
-    uint32_t x_tiles, ct_groups, total;   // work items: (segment, x tile, ciphertext group), group fastest
-    uint32_t per_xcd;
+    uint32_t kb_cap;        // most blocks between two flushes of the accumulators (int32)
+    uint32_t x_tiles, ct_groups;
+    // Which blocks of which x tile a workgroup takes, as a range of positions x tile * padded blocks + block (multiples of 2 KM_IT_KB):
+    // by segments, work items (segment, x tile, ciphertext group), group fastest;
+    uint32_t kb_per_seg, total, per_xcd;
+    // by ranges: the positions are cut into 8 ranges_per_xcd equal ones, each taken by ct_groups workgroups
+    uint32_t ranges_per_xcd, range;
 };
 
 // PREP: the key comes in operand form (A.kskp) and goes from global memory to LDS as it is; otherwise every thread recodes
 // eight words of the standard key per iteration.
-template <bool PREP>
+template <bool PREP, bool RANGES>
 __global__ void __launch_bounds__(KM_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_ksm_main(ksm_args A) {
     __shared__ v4i lds[2 * KM_BUF_V4];                              // 64 KiB
-    // work items are dealt so that one XCD (workgroups b, b+8, ...) walks a contiguous range: the workgroups resident on
-    // it share a segment of the key and neighbouring output words, which its L2 then serves
-    const uint32_t item = (blockIdx.x % 8) * A.per_xcd + blockIdx.x / 8;
-    if (blockIdx.x / 8 >= A.per_xcd || item >= A.total) return;
-    // inside a segment the order is (block of 8 ciphertext groups, x tile, group in the block): the 64 workgroups resident on
-    // an XCD are then about 8 groups x 8 x tiles, and its L2 sees each of their digit and key streams once instead of the
-    // digits of 64 groups against one x tile (the digit operands are the larger stream)
-    const uint32_t per_seg = A.ct_groups * A.x_tiles;
-    const uint32_t seg = item / per_seg, r = item % per_seg;
-    const uint32_t n_full = A.ct_groups / 8, blk = 8 * A.x_tiles;
-    uint32_t cg, xt;
-    if (r < n_full * blk) {
-        cg = (r / blk) * 8 + r % 8;
-        xt = (r % blk) / 8;
-    } else {                                                        // the last, narrower block
-        const uint32_t rr = r - n_full * blk, w = A.ct_groups - n_full * 8;
-        cg = n_full * 8 + rr % w;
-        xt = rr / w;
+    const uint32_t kb_pad = ksm_padded_blocks(A.n_kb);
+    uint32_t cg, begin, end;
+    if (RANGES) {
+        // The workgroups of an XCD take consecutive ranges, ct_groups of them the same one: they read the same key words at the same time, and the digits
+        // of a range are read by the x tiles that share it.
+        const uint32_t r = blockIdx.x / 8, range = (blockIdx.x % 8) * A.ranges_per_xcd + r / A.ct_groups;
+        cg = r % A.ct_groups;
+        begin = range * A.range;
+        end = min(begin + A.range, A.x_tiles * kb_pad);
+        if (begin >= end) return;
+    } else {
+        // work items are dealt so that one XCD (workgroups b, b+8, ...) walks a contiguous range: the workgroups resident on
+        // it share a segment of the key and neighbouring output words, which its L2 then serves
+        const uint32_t item = (blockIdx.x % 8) * A.per_xcd + blockIdx.x / 8;
+        if (blockIdx.x / 8 >= A.per_xcd || item >= A.total) return;
+        // inside a segment the order is (block of 8 ciphertext groups, x tile, group in the block): the 64 workgroups resident on
+        // an XCD are then about 8 groups x 8 x tiles, and its L2 sees each of their digit and key streams once instead of the
+        // digits of 64 groups against one x tile (the digit operands are the larger stream)
+        const uint32_t per_seg = A.ct_groups * A.x_tiles;
+        const uint32_t seg = item / per_seg, r = item % per_seg;
+        const uint32_t n_full = A.ct_groups / 8, blk = 8 * A.x_tiles;
+        uint32_t xt;
+        if (r < n_full * blk) {
+            cg = (r / blk) * 8 + r % 8;
+            xt = (r % blk) / 8;
+        } else {                                                    // the last, narrower block
+            const uint32_t rr = r - n_full * blk, w = A.ct_groups - n_full * 8;
+            cg = n_full * 8 + rr % w;
+            xt = rr / w;
+        }
+        begin = xt * kb_pad + seg * A.kb_per_seg;
+        end = min(begin + A.kb_per_seg, (xt + 1) * kb_pad);
     }
     const uint32_t lane = threadIdx.x % 64;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint32_t tile = cg * KM_WAVES + wave;
     const bool tile_ok = tile < A.n_tiles;
-    const uint32_t kb_begin = seg * A.kb_per_seg;
-    const uint32_t kb_end = min(A.n_kb, kb_begin + A.kb_per_seg);
     const uint32_t width = A.n + 1;
 
     // key-loading role: output word x, rows 8 oct .. 8 oct + 7 of the iteration's 32 KM_IT_KB rows
     const uint32_t xl = lane % 32;
-    const uint32_t x = xt * 32 + xl;
     const uint32_t oct = 2 * wave + lane / 32;
-    const bool x_ok = x < width;
     const size_t row_stride = (size_t)A.l * width;                  // words between consecutive mask indices at one level
-    // level j and mask index i of this thread's first row; both advance by 32 KM_IT_KB rows per iteration
-    uint32_t rho = kb_begin * 32 + 8 * oct;
-    uint32_t j = rho / A.kN, i = rho % A.kN;
+    // where the next requests are: x tile and block, level j and mask index i of this thread's first row; they advance by 32 KM_IT_KB rows per
+    // iteration, from the last block of an x tile to the first of the next one
+    uint32_t req_at = begin, req_xt = begin / kb_pad, req_kb = begin % kb_pad;
+    const uint32_t req_end = RANGES ? A.n_kb : min(A.n_kb, req_kb + (end - begin));
+    bool req_ok = req_xt * 32 + xl < width;
+    uint32_t j = (req_kb * 32 + 8 * oct) / A.kN, i = (req_kb * 32 + 8 * oct) % A.kN;
     const uint32_t lds_w = ((((oct / 4) * 2 + (oct / 2) % 2) * 8) * 32 + xl) * 2 + (oct & 1);   // in 8-byte units, plane 0
 
     // Two register stages of key words and digit operands: what iteration t consumes was requested during iteration t-2,
@@ -194,13 +214,13 @@ k_ksm_main(ksm_args A) {
     v4i an0[KM_IT_KB], an1[KM_IT_KB];
     // operand form: the iteration's KM_BUF_V4 entries are consecutive; a thread moves entries tid + KM_THREADS u (the same
     // eight registers hold them as four 16-byte values)
-    const uint32_t kb_pad = ksm_padded_blocks(A.n_kb);
-    const v4i *pkey = PREP ? A.kskp + (size_t)xt * kb_pad * (2 * 8 * 32) + threadIdx.x : nullptr;
-    auto load_key = [&](uint64_t (&kw)[8], bool &ok, uint32_t it) {
+    uint32_t dig_kb;                                                // block of the last key request: its digits are requested next
+    auto load_key = [&](uint64_t (&kw)[8], bool &ok) {
+        dig_kb = req_kb;
         if (PREP) {
-            // blocks up to the padded count exist (zero past the last row); past that the read is clamped and unused
-            const uint32_t itc = min(it, kb_pad - KM_IT_KB);
-            const v4i *src = pkey + (size_t)itc * (2 * 8 * 32);
+            // blocks up to the padded count exist (zero past the last row)
+            const uint32_t kbc = RANGES ? req_kb : min(req_kb, kb_pad - KM_IT_KB);
+            const v4i *src = A.kskp + ((size_t)req_xt * kb_pad + kbc) * (2 * 8 * 32) + threadIdx.x;
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const v4i v = src[u * KM_THREADS];
@@ -208,20 +228,37 @@ k_ksm_main(ksm_args A) {
                 kw[2 * u + 1] = (uint64_t)(uint32_t)v[2] | ((uint64_t)(uint32_t)v[3] << 32);
             }
             ok = true;
+        } else {
+            ok = req_ok && req_kb + oct / 4 < req_end;
+            const uint64_t *src = A.ksk + (ok ? ((size_t)i * A.l + j) * width + req_xt * 32 + xl : (size_t)0);
+#pragma unroll
+            for (int t = 0; t < 8; t++) kw[t] = src[(size_t)t * row_stride];
+            i += 32 * KM_IT_KB;
+            while (i >= A.kN) { i -= A.kN; j++; }
+        }
+        if (!RANGES) {                                              // past the end: clamped, or one line, and unused
+            req_kb += KM_IT_KB;
             return;
         }
-        ok = x_ok && (it + oct / 4 < kb_end);
-        const uint64_t *src = A.ksk + (ok ? ((size_t)i * A.l + j) * width + x : (size_t)0);
-#pragma unroll
-        for (int t = 0; t < 8; t++) kw[t] = src[(size_t)t * row_stride];
-        i += 32 * KM_IT_KB;
-        while (i >= A.kN) { i -= A.kN; j++; }
+        req_at += KM_IT_KB;
+        if (req_at >= end) {                                        // past the end: the last entries, or one line, again
+            req_ok = false;
+            return;
+        }
+        req_kb += KM_IT_KB;
+        if (req_kb == kb_pad) {
+            req_kb = 0;
+            req_xt++;
+            req_ok = req_xt * 32 + xl < width;
+            j = 8 * oct / A.kN;
+            i = 8 * oct % A.kN;
+        }
     };
     const size_t dig_base = (size_t)(tile_ok ? tile : 0) * A.n_kb;
-    auto load_dig = [&](v4i (&an)[KM_IT_KB], uint32_t it) {
-        // blocks past the end of the segment meet zero key bytes, so their digits need no masking
+    auto load_dig = [&](v4i (&an)[KM_IT_KB]) {
+        // blocks past the last row meet zero key bytes, so their digits need no masking
 #pragma unroll
-        for (int q = 0; q < KM_IT_KB; q++) an[q] = A.dig[(dig_base + min(it + q, A.n_kb - 1)) * 64 + lane];
+        for (int q = 0; q < KM_IT_KB; q++) an[q] = A.dig[(dig_base + min(dig_kb + q, A.n_kb - 1)) * 64 + lane];
     };
 
     v16i acc[8];
@@ -231,7 +268,7 @@ k_ksm_main(ksm_args A) {
         for (int r = 0; r < 16; r++) acc[p][r] = 0;
 
     uint32_t buf = 0;
-    auto body = [&](uint64_t (&kw)[8], bool &ok, v4i (&an)[KM_IT_KB], uint32_t it) {
+    auto body = [&](uint64_t (&kw)[8], bool &ok, v4i (&an)[KM_IT_KB]) {
         // recode to signed bytes, transpose 8 rows x 8 planes, park the plane operands in LDS
         if (PREP) {
             uint64_t *dst = reinterpret_cast<uint64_t *>(lds + buf * KM_BUF_V4 + threadIdx.x);
@@ -249,7 +286,7 @@ k_ksm_main(ksm_args A) {
 #pragma unroll
             for (int p = 0; p < 8; p++) dst[(size_t)p * 64] = plane[p];
         }
-        load_key(kw, ok, it + 2 * KM_IT_KB);
+        load_key(kw, ok);
         __syncthreads();
         // one barrier per iteration is enough with two buffers: a wave reaches the barrier of iteration t only after it
         // has read everything of iteration t-1, and buffer (t+1)%2 is not written before that barrier
@@ -272,34 +309,53 @@ k_ksm_main(ksm_args A) {
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        load_dig(an, it + 2 * KM_IT_KB);
+        load_dig(an);
         buf ^= 1;
     };
-    load_key(kw0, ok0, kb_begin);
-    load_dig(an0, kb_begin);
-    load_key(kw1, ok1, kb_begin + KM_IT_KB);
-    load_dig(an1, kb_begin + KM_IT_KB);
-    for (uint32_t it = kb_begin; it < kb_end; it += 2 * KM_IT_KB) {  // kb_per_seg is a multiple of 2 KM_IT_KB
-        body(kw0, ok0, an0, it);
-        body(kw1, ok1, an1, it + KM_IT_KB);
-    }
-    if (!tile_ok || !x_ok) return;
-    // accumulator register r of a lane is ciphertext 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile, output word x
+    load_key(kw0, ok0);
+    load_dig(an0);
+    load_key(kw1, ok1);
+    load_dig(an1);
+    auto add_up = [&](uint32_t xt) {
+        uint32_t ln = lane;
+        if (RANGES) asm volatile("" : "+v"(ln));                    // the addresses below are made here and not kept through the iterations
+        const uint32_t x = xt * 32 + ln % 32;
+        if (!tile_ok || x >= width) return;
+        // accumulator register r of a lane is ciphertext 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile, output word x
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        const uint32_t c = tile * 32 + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
-        if (c < A.batch) {
-            uint64_t val = 0;
+        for (int r = 0; r < 16; r++) {
+            const uint32_t c = tile * 32 + 8 * (r / 4) + 4 * (ln / 32) + (r % 4);
+            if (c < A.batch) {
+                uint64_t val = 0;
 #pragma unroll
-            for (int p = 0; p < 8; p++) val += (uint64_t)(int64_t)acc[p][r] << (8 * p);
-            if (A.direct) {
-                const uint64_t base = x == A.n ? A.lwe_in[(size_t)c * (A.kN + 1) + A.kN] : 0ull;
-                A.out[(size_t)c * width + x] = base - val;
-            } else {
-                atomicAdd((unsigned long long *)&A.out[(size_t)c * width + x], (unsigned long long)(0 - val));
+                for (int p = 0; p < 8; p++) val += (uint64_t)(int64_t)acc[p][r] << (8 * p);
+                if (!RANGES && A.direct) {
+                    const uint64_t base = x == A.n ? A.lwe_in[(size_t)c * (A.kN + 1) + A.kN] : 0ull;
+                    A.out[(size_t)c * width + x] = base - val;
+                } else {
+                    atomicAdd((unsigned long long *)&A.out[(size_t)c * width + x], (unsigned long long)(0 - val));
+                }
             }
         }
+    };
+    uint32_t xt = begin / kb_pad, kb = begin % kb_pad, summed = 0;
+    for (uint32_t at = begin; at < end; at += 2 * KM_IT_KB) {
+        body(kw0, ok0, an0);
+        body(kw1, ok1, an1);
+        if (!RANGES) continue;
+        kb += 2 * KM_IT_KB;
+        summed += 2 * KM_IT_KB;
+        if (kb < kb_pad && at + 2 * KM_IT_KB < end && summed < A.kb_cap) continue;
+        // the sums of this x tile so far go out; what the next iterations need is on its way
+        add_up(xt);
+#pragma unroll
+        for (int p = 0; p < 8; p++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[p][r] = 0;
+        summed = 0;
+        if (kb == kb_pad) { kb = 0; xt++; }
     }
+    if (!RANGES) add_up(xt);
 }
 
 int slz_ksm_supported(const slz_params *p) {
@@ -332,13 +388,14 @@ static int ksm_run(const slz_params &p, void *dig, uint32_t max_tiles, const uin
         A.ct_groups = (A.n_tiles + KM_WAVES - 1) / KM_WAVES;
         A.out = lwe_out + (size_t)c0 * (p.n + 1);
         // segments of the row index: enough workgroups for three rounds over the 256 CUs (a workgroup spends about half
-        // its time outside the MFMA loop at cfg2's ten iterations, so fewer, longer segments with idle CUs measured no better)
+        // its time outside the MFMA loop at ten iterations, so fewer, longer segments with idle CUs measured no better)
         uint32_t segs = (KM_TARGET_WGS + A.x_tiles * A.ct_groups - 1) / (A.x_tiles * A.ct_groups);
         segs = max(1u, min(segs, (n_kb + 7) / 8));
         uint32_t kbs = ((n_kb + segs - 1) / segs + 2 * KM_IT_KB - 1) / (2 * KM_IT_KB) * (2 * KM_IT_KB);
         kbs = min(kbs, kb_cap);
         segs = (n_kb + kbs - 1) / kbs;
         A.kb_per_seg = kbs;
+        A.kb_cap = kb_cap;
         const uint64_t total = (uint64_t)segs * A.x_tiles * A.ct_groups;
         if (total > (1u << 30)) return SLZ_E_UNSUPPORTED;
         A.total = (uint32_t)total;
@@ -348,8 +405,26 @@ static int ksm_run(const slz_params &p, void *dig, uint32_t max_tiles, const uin
         hipLaunchKernelGGL(k_ksm_digits, dim3((kN + KD_WORDS - 1) / KD_WORDS, A.n_tiles), dim3(256), 0, s,
                            lwe_in + (size_t)c0 * (kN + 1), (v4i *)dig, kN, p.ks_base_log, p.ks_level, nb, n_kb,
                            A.direct ? nullptr : A.out, p.n);
-        if (kskp) hipLaunchKernelGGL(k_ksm_main<true>, dim3(A.per_xcd * 8), dim3(KM_THREADS), 0, s, A);
-        else hipLaunchKernelGGL(k_ksm_main<false>, dim3(A.per_xcd * 8), dim3(KM_THREADS), 0, s, A);
+        uint32_t grid = A.per_xcd * 8;
+        // Ranges of rows across x tiles, one per resident workgroup, instead of three rounds of segments: a workgroup's first loads and the
+        // sums it adds to the output come once (or twice, at the end of an x tile) and not three times.  us, segments / ranges, standard
+        // (prepared) key, kN = 2048, n = 742: 64 ciphertexts 27.9 / 23.3 (25.3 / 20.9), 512: 78 / 55 (75 / 51), 1024: 110 / 91 (105 / 80),
+        // 2048: 167 / 153 (159 / 136), 4096: 296 / 319 (275 / 260); kN = 1024, 777: 73 / 46 (67 / 42); kN = 4096, 1024: 203 / 167
+        // (192 / 146); kN = 32768, n = 1024, 24: 320 / 339 (292 / 240), 256: 518 / 527 (467 / 418).  Past 16 groups half of the workgroups
+        // would be left out; past 8 the recoding of a standard key, done by each of the groups, wants the third workgroup of a CU's queue.
+        // A standard key past the 256 MB of the memory-side cache comes from memory in rows of 8 (n + 1) bytes, of which the workgroups of
+        // an XCD read the whole width together only by segments.
+        const bool from_memory = !kskp && (uint64_t)kN * p.ks_level * (p.n + 1) * 8 > (256u << 20);
+        const bool ranges = segs > 1 && A.ct_groups <= (kskp ? KM_RANGES_GROUPS_PREP : KM_RANGES_GROUPS_STD) && !from_memory;
+        if (ranges) {
+            A.ranges_per_xcd = 32 / A.ct_groups;
+            const uint32_t n_ranges = 8 * A.ranges_per_xcd, unit = 2 * KM_IT_KB, positions = A.x_tiles * ksm_padded_blocks(n_kb);
+            A.range = ((positions + n_ranges - 1) / n_ranges + unit - 1) / unit * unit;
+            grid = n_ranges * A.ct_groups;
+        }
+        auto *kernel = kskp ? ranges ? k_ksm_main<true, true> : k_ksm_main<true, false>
+                            : ranges ? k_ksm_main<false, true> : k_ksm_main<false, false>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(KM_THREADS), 0, s, A);
     }
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;

@@ -173,6 +173,37 @@ def test_keyswitch_with_prepared_key_matches_oracle(slz, orc, batch, k, N, n, be
     assert np.array_equal(slz.to_host_u64(ctx_small.keyswitch_batch_prepared(d_cts, kskp)), want)
 
 
+@pytest.mark.parametrize("batch,N,n,l", [(2048, 256, 300, 5), (2049, 256, 300, 5), (4095, 256, 300, 5), (4097, 256, 300, 5),
+                                          (40, 64, 10, 8), (700, 512, 95, 5)])
+def test_keyswitch_by_ranges_of_rows_matches_oracle(slz, orc, batch, N, n, l):
+    # the last batch of ranges and the first of segments for either form of the key, ranges that end inside an x tile and
+    # that cross one, more workgroups than ranges, a row-block count that is no multiple of eight
+    p = tiny(n=n, N=N, k=1, ks_base_log=4, ks_level=l)
+    ksk = synth.raw_words(p, "raw_ksk", N * l * (n + 1)).reshape(N, l, n + 1)
+    cts = synth.raw_words(p, "raw_ct", batch * (N + 1)).reshape(batch, N + 1)
+    want = orc.keyswitch_batch(p, cts, ksk)
+    d_cts, d_ksk = slz.to_device_u64(cts), slz.to_device_u64(ksk)
+    ctx = slz.Context(p, batch)
+    kskp = ctx.ksk_prepare(d_ksk)
+    for _ in range(2):
+        assert np.array_equal(slz.to_host_u64(ctx.keyswitch_batch(d_cts, d_ksk)), want)
+        assert np.array_equal(slz.to_host_u64(ctx.keyswitch_batch_prepared(d_cts, kskp)), want)
+
+
+def test_keyswitch_by_ranges_adds_up_before_int32_overflows(slz, orc):
+    # 131072 rows, every digit and every key byte -128: 2^17 products of 2^14, one range longer than an x tile
+    p = tiny(n=543, N=16384, k=1, ks_base_log=8, ks_level=8)
+    batch, word = 2817, 0x7f7f7f7f7f7f7f80
+    cts = torch.full((batch, p.N + 1), word, dtype=torch.int64, device="cuda")
+    ksk = torch.full((p.N, 8, p.n + 1), word, dtype=torch.int64, device="cuda")
+    ctx = slz.Context(p, batch)
+    got = ctx.keyswitch_batch_prepared(cts, ctx.ksk_prepare(ksk))
+    want = (128 * 131072 * word) % 2**64                           # - sum of -128 * word
+    want = torch.full((batch, p.n + 1), want - 2**64 if want >= 2**63 else want, dtype=torch.int64, device="cuda")
+    want[:, p.n] += word
+    assert torch.equal(got, want)
+
+
 def test_keyswitch_with_prepared_key_extreme_bytes_and_errors(slz, orc):
     p = tiny(n=70, N=256, k=1, ks_base_log=8, ks_level=8)
     kN, l, n, batch = 256, 8, 70, 48
