@@ -271,7 +271,7 @@ static const host_tables &tables(uint32_t N) {
 static void pairs_init(slz_ctx *ctx) {
     const uint32_t N = ctx->prm.N;
     ctx->pair_asked = 1;
-    const uint32_t most = ctx->max_batch < SLZ_PAIR_MAX ? ctx->max_batch : SLZ_PAIR_MAX, pairs = slz_pairs_grid(most) / 2;
+    const uint32_t pairs = slz_pairs_most(ctx) / 2;
     const size_t words = (SLZ_PAIR_WORDS * sizeof(uint32_t) + 255) & ~(size_t)255;
     void *buf = nullptr;
     hipEvent_t ev;
@@ -301,7 +301,6 @@ int slz_pairs_release(slz_ctx *ctx, hipStream_t s) {
     ctx->pair_stream = s;
     return SLZ_OK;
 }
-slz_pairs slz_pairs_of(const slz_ctx *ctx) { return slz_pairs{ctx->pair_ctl}; }
 __global__ void __launch_bounds__(256) k_pairs_clear(uint32_t *ctl) {
     const uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i < SLZ_PAIR_WORDS) ctl[i] = 0;

@@ -32,6 +32,7 @@
 #include "slz_fft_wave.h"
 #include "slz_modarith.h"
 #include "slz_fused_common.h"
+#include "slz_xcd.h"
 
 #define FFT_WAVES 8                                 // waves per workgroup: four ciphertexts share one copy of the tables
 #define FFT_PAIRS (FFT_WAVES / 2)
@@ -486,7 +487,7 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
     // Up to 128 ciphertexts two workgroups take each (6.4 to 6.6 us per step against 9.2 to 9.3 with one), unless an overlapping or captured call needs the
     // kernel without memory of its own.
     if (n_steps && slz_pairs_acquire(ctx, batch, s)) {
-        const int rc = slz_fft2048_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);
+        const int rc = slz_fft2048_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, slz_pairs_grid(batch), SLZ_PAIR_PATIENCE, s);
         return rc == SLZ_OK ? slz_pairs_release(ctx, s) : rc;
     }
     if (batch <= FFT_TEAM_MAX) return slz_fft2048_team(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);

@@ -418,17 +418,18 @@ int slz_fft2048_pair_setup() {
 }
 
 int slz_fft2048_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
-                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s) {
+    if (!ctx->pair_ctl || batch > SLZ_PAIR_MAX || workgroups > slz_pairs_most(ctx)) return SLZ_E_INVALID_ARG;
     fft2048p_args A;
     A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;
     A.acc_out = acc_out; A.lwe_out = lwe_out;
-    A.pairs = slz_pairs_of(ctx);
+    A.pairs = slz_pairs{ctx->pair_ctl, patience};
     A.mail = (d2 *)ctx->pair_mail;
     A.n = ctx->prm.n; A.n_steps = n_steps; A.batch = batch; A.beta = ctx->prm.pbs_base_log;
     for (int q = 0; q < 15; q++)
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
     slz_pairs_clear(ctx, s);
-    hipLaunchKernelGGL(k_fft2048_pair, dim3(slz_pairs_grid(batch)), dim3(FP_THREADS), FP_LDS_BYTES, s, A);
+    hipLaunchKernelGGL(k_fft2048_pair, dim3(workgroups), dim3(FP_THREADS), FP_LDS_BYTES, s, A);
     SLZ_HIP(hipGetLastError());
-    return SLZ_OK;
+    return slz_fft2048_team(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s, ctx->pair_ctl);
 }

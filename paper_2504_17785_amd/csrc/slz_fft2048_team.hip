@@ -41,12 +41,14 @@ struct fft2048t_args {
     const d2 *tab;            // FFT_TAB_LEN entries
     uint64_t *acc_out;
     uint64_t *lwe_out;
+    const uint32_t *taken;    // where it is given: ciphertexts that a launch before this one has done (slz_xcd.h)
     uint32_t n, n_steps, batch, beta;
     double f1[15][2];         // lane-uniform twiddles of the first two forward layers: (v, v^2, v^3) of block 0 and of the next four blocks
 };
 
 __global__ void __launch_bounds__(FT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_fft2048_team(fft2048t_args A) {
+    if (A.taken && blockIdx.x < *A.taken) return;                     // one workgroup per ciphertext
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const uint32_t lds = (uint32_t)(uintptr_t)(LDS_AS unsigned char *)lds_raw;
     const uint32_t beta = A.beta;
@@ -383,10 +385,10 @@ int slz_fft2048_team_setup() {
 }
 
 int slz_fft2048_team(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
-                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s, const uint32_t *taken) {
     fft2048t_args A;
     A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;
-    A.acc_out = acc_out; A.lwe_out = lwe_out;
+    A.acc_out = acc_out; A.lwe_out = lwe_out; A.taken = taken;
     A.n = ctx->prm.n; A.n_steps = n_steps; A.batch = batch; A.beta = ctx->prm.pbs_base_log;
     for (int q = 0; q < 15; q++)
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];

@@ -35,6 +35,7 @@
 #include "slz_fft_wave.h"
 #include "slz_modarith.h"
 #include "slz_fused_common.h"
+#include "slz_xcd.h"
 
 #define F12_THREADS 512
 #define F12_BUF (544u * 16u)                        // bytes of a wave's buffer: 512 points, padded
@@ -49,12 +50,14 @@ struct fft4096_args {
     const d2 *tab;            // F12_TAB_LEN entries
     uint64_t *acc_out;
     uint64_t *lwe_out;
+    const uint32_t *taken;    // where it is given: ciphertexts that a launch before this one has done (slz_xcd.h)
     uint32_t n, n_steps, batch, beta;
     double f1[6][2];          // lane-uniform twiddles of the second forward layer: (v, v^2, v^3) of its two blocks
 };
 
 __global__ void __launch_bounds__(F12_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_fft4096_blind_rotate(fft4096_args A) {
+    if (A.taken && blockIdx.x < *A.taken) return;                     // one workgroup per ciphertext
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const uint32_t lds = (uint32_t)(uintptr_t)(LDS_AS unsigned char *)lds_raw;
     const uint32_t beta = A.beta;
@@ -390,20 +393,31 @@ int slz_fft4096_setup() {
     return slz_fft4096_pair_setup();
 }
 
-int slz_fft4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
-                             uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
-    // up to 128 ciphertexts two workgroups on each: 14.5 to 15.1 us per step against 16.4 to 16.6 (slz_fft2048.hip: when not)
-    if (n_steps && slz_pairs_acquire(ctx, batch, s)) {
-        const int rc = slz_fft4096_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);
-        return rc == SLZ_OK ? slz_pairs_release(ctx, s) : rc;
-    }
+static int all_of_them(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                       uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s, const uint32_t *taken) {
     fft4096_args A;
     A.lwe_in = lwe_in; A.luts = luts; A.lut_idx = lut_idx; A.key = (const d2 *)key; A.tab = (const d2 *)ctx->fft_tab;
-    A.acc_out = acc_out; A.lwe_out = lwe_out;
+    A.acc_out = acc_out; A.lwe_out = lwe_out; A.taken = taken;
     A.n = ctx->prm.n; A.n_steps = n_steps; A.batch = batch; A.beta = ctx->prm.pbs_base_log;
     for (int q = 0; q < 6; q++)
         for (int t = 0; t < 2; t++) A.f1[q][t] = ctx->fft_f1[q][t];
     hipLaunchKernelGGL(k_fft4096_blind_rotate, dim3(slz_fused_grid(batch, 1)), dim3(F12_THREADS), F12_LDS_BYTES, s, A);
     SLZ_HIP(hipGetLastError());
     return SLZ_OK;
+}
+
+int slz_fft4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                             uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
+    // up to 128 ciphertexts two workgroups on each: 14.5 to 15.1 us per step against 16.4 to 16.6 (slz_fft2048.hip: when not)
+    if (n_steps && slz_pairs_acquire(ctx, batch, s)) {
+        const int rc = slz_fft4096_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, slz_pairs_grid(batch), SLZ_PAIR_PATIENCE, s);
+        return rc == SLZ_OK ? slz_pairs_release(ctx, s) : rc;
+    }
+    return all_of_them(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s, nullptr);
+}
+
+int slz_fft4096_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s) {
+    const int rc = slz_fft4096_pair_launch(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, workgroups, patience, s);
+    return rc == SLZ_OK ? all_of_them(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s, ctx->pair_ctl) : rc;
 }

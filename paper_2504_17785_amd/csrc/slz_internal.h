@@ -137,13 +137,17 @@ int slz_fft4096_setup();
 int slz_fft2048_setup();
 int slz_fft2048_team_setup();
 int slz_fft2048_team(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
-                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s, const uint32_t *taken = nullptr);
+// two workgroups per ciphertext, and behind them one for each that no pair has taken: any number of workgroups and any patience
+// (slz_xcd.h) do all ciphertexts; the library takes slz_pairs_grid(batch) and SLZ_PAIR_PATIENCE, tests others
 int slz_fft2048_pair_setup();
 int slz_fft2048_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
-                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s);
 int slz_fft4096_pair_setup();
+int slz_fft4096_pair_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
+                            uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s);
 int slz_fft4096_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
-                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s);
+                     uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s);
 int slz_pairs_acquire(slz_ctx *ctx, uint32_t batch, hipStream_t s);
 int slz_pairs_release(slz_ctx *ctx, hipStream_t s);
 int slz_fft1024_setup();

@@ -34,20 +34,28 @@ __device__ __forceinline__ d2 lane_get_l2(const d2 *uniform_base, uint32_t lane)
 }
 
 // Pairs.  A workgroup takes a number on its XCD; two with successive numbers are a pair, the second of which asks for ciphertexts for both until
-// there are none left.  The first waits for the second to start.  It ends: the second is a workgroup of the same launch (or, where the launch
-// has none left, all ciphertexts get taken by other pairs and the first sees that), which starts as soon as a place is free; places are held by pairs, which
-// wait for nobody else, by kernels that do not wait, and by at most one such first workgroup per XCD and launch in flight, of which
-// there are fewer (hardware queues) than an XCD has compute units.
+// there are none left.  The first waits for the second to start, until every ciphertext is taken, or for `patience`; then it leaves, and so does the
+// second if it comes after that.  So a launch ends whatever places it is given (one compute unit of an XCD, under a mask of compute units, holds one of these
+// workgroups and never a pair); the ciphertexts that no pair has taken are left to a launch behind it that pairs nothing.  Once met, the two of
+// a pair wait for each other alone, and both run.
 #define SLZ_PAIR_MAX 128u                           // pairs of a launch: 256 workgroups
 #define SLZ_PAIR_NONE 0xffffffffu
+#define SLZ_PAIR_PATIENCE 200000u                   // 2 ms of the 100 MHz clock; where there is room the second starts within microseconds
 struct slz_pairs {
     uint32_t *ctl;            // words, zero at the start: [0] ciphertexts taken, [32] pairs, [64 + 32 x] numbers of XCD x, then [16][128] pair + 1 by
-};                            // XCD and number / 2, then a line of 32 words per pair: [8] progress of its waves, [8] the ciphertext at hand
+                              // XCD and number / 2, then a line of 32 words per pair: [8] progress of its waves, [8] the ciphertext at hand
+    uint32_t patience;
+};
 #define SLZ_PAIR_MET 576u
 #define SLZ_PAIR_LINES (SLZ_PAIR_MET + 16u * 128u)
 #define SLZ_PAIR_WORDS (SLZ_PAIR_LINES + 32u * SLZ_PAIR_MAX)
 __device__ __forceinline__ uint32_t *slz_pair_line(slz_pairs P, uint32_t pair) { return P.ctl + SLZ_PAIR_LINES + 32u * pair; }
 
+// The word by which two workgroups meet has one value after zero: whoever comes first writes it.  Returns that value.
+__device__ __forceinline__ uint32_t slz_pair_settle(uint32_t *met, uint32_t value) {
+    uint32_t seen = 0;
+    return __hip_atomic_compare_exchange_strong(met, &seen, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? value : seen;
+}
 // One thread: 2 pair + (0 first, 1 second), or SLZ_PAIR_NONE
 __device__ __forceinline__ uint32_t slz_pair_join(slz_pairs P, uint32_t batch) {
     const uint32_t x = slz_xcc_id();
@@ -55,18 +63,15 @@ __device__ __forceinline__ uint32_t slz_pair_join(slz_pairs P, uint32_t batch) {
     uint32_t *met = P.ctl + SLZ_PAIR_MET + 128 * x + number / 2;
     if (number & 1u) {
         const uint32_t pair = __hip_atomic_fetch_add(P.ctl + 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // in the L2 before a ciphertext is taken: a first workgroup that sees the last one taken sees this too
-        __hip_atomic_store(met, pair + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        return 2 * pair + 1;
+        return slz_pair_settle(met, pair + 1) == SLZ_PAIR_NONE ? SLZ_PAIR_NONE : 2 * pair + 1;
     }
-    for (;;) {
-        const bool over = ld_agent(P.ctl) >= batch;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // seen before the next look at the other word
-        const uint32_t pair = ld_agent(met);
-        if (pair) return 2 * (pair - 1);
-        if (over) return SLZ_PAIR_NONE;
-    }
+    const uint64_t since = wall_clock64();
+    uint32_t pair;
+    do {
+        pair = ld_agent(met);
+        if (!pair && (ld_agent(P.ctl) >= batch || wall_clock64() - since >= P.patience)) pair = slz_pair_settle(met, SLZ_PAIR_NONE);
+    } while (!pair);
+    return pair == SLZ_PAIR_NONE ? SLZ_PAIR_NONE : 2 * (pair - 1);
 }
 // One thread of either workgroup: the pair's ciphertext of this round, or one past the last
 __device__ __forceinline__ uint32_t slz_pair_next(slz_pairs P, uint32_t pair, uint32_t second, uint32_t round) {
@@ -82,7 +87,8 @@ __device__ __forceinline__ uint32_t slz_pair_next(slz_pairs P, uint32_t pair, ui
     }
 }
 
+// Two workgroups per ciphertext of every XCD's share, and the most that a context has memory for
+static inline uint32_t slz_pairs_grid(uint32_t batch) { return 16u * ((batch + 7) / 8); }
+static inline uint32_t slz_pairs_most(const slz_ctx *ctx) { return slz_pairs_grid(ctx->max_batch < SLZ_PAIR_MAX ? ctx->max_batch : SLZ_PAIR_MAX); }
 // host (slz_fft.hip)
-static inline uint32_t slz_pairs_grid(uint32_t batch) { return 16u * ((batch + 7) / 8); }      // two workgroups per ciphertext of every XCD's share
-slz_pairs slz_pairs_of(const slz_ctx *ctx);
 void slz_pairs_clear(slz_ctx *ctx, hipStream_t s);

@@ -1,5 +1,7 @@
 """N = 2048 and 4096 with few ciphertexts, where two workgroups share each: against the kernels with one workgroup per ciphertext (which larger
 batches, captured calls and calls beside another stream's take) bit for bit; those are compared with the oracle elsewhere."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -65,3 +67,28 @@ def test_pairs_of_workgroups_beside_other_streams_and_in_graphs(slz, N):
             ctx.pbs_batch(*few, out=outs[0])
         torch.cuda.synchronize()
         assert torch.equal(out, every[:count]) and torch.equal(outs[0], every[:count]), rep
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
+def test_pairs_of_workgroups_do_every_ciphertext_whatever_their_number_and_patience(slz, N):
+    # the launch's driver (an internal function, by its mangled name).  A workgroup per XCD or fewer: nobody has a partner, all leave and the launch
+    # behind takes everything.  17 to 40: one to three of an XCD, so pairs with many ciphertexts each and workgroups left over.  Without
+    # patience a workgroup leaves unless its partner is there already, and partners come too late.
+    count = 100
+    ctx, d = _case(slz, N, 129, 6)
+    run = getattr(slz.lib(), "_Z16slz_fft%d_pairP7slz_ctxPKmS2_PKjPKvjPmS7_jjjP12ihipStream_t" % N)
+    run.argtypes = [ctypes.c_void_p] * 5 + [ctypes.c_uint32] + [ctypes.c_void_p] * 2 + [ctypes.c_uint32] * 3 + [ctypes.c_void_p]
+    run.restype = ctypes.c_int
+    key = d[3].data_ptr() + 6 * 2 * 4 * N * 8            # the transform form, behind the residues
+    ctx.blind_rotate_batch(d[0][:1], d[1], d[2][:1], d[3], 1)         # allocates what pairs need
+    for steps in (1, 5, 6):
+        want = ctx.blind_rotate_batch(*d, steps)[:count]
+        for workgroups in (1, 7, 8, 16, 17, 18, 31, 40, 208, 256):
+            for patience in (200000, 0):
+                out = torch.full_like(want, -1)
+                torch.cuda.synchronize()
+                assert run(ctx._h, d[0].data_ptr(), d[1].data_ptr(), d[2].data_ptr(), key, steps, out.data_ptr(), None, count, workgroups, patience,
+                           None) == 0
+                torch.cuda.synchronize()
+                assert torch.equal(out, want), (steps, workgroups, patience)
+    assert run(ctx._h, d[0].data_ptr(), d[1].data_ptr(), d[2].data_ptr(), key, 1, want.data_ptr(), None, count, 257, 0, None) == slz.SLZ_E_INVALID_ARG
