@@ -43,8 +43,8 @@ def _inputs(slz, batch, beta, n=3, extreme=False, N=2048):
     ctx = slz.Context(p, batch)
     assert ctx.path == "fused_n%d" % N
     # the prepared key: the residue form, and behind it the transform form where the error bound holds
-    steps = {2048: 5 * 2 * 8 * 4 * 64, 1024: 5 * 8 * 4 * 64, 512: 3 * 4 * 8 * 64}
-    transform = n * steps[N] * 16 if beta <= {2048: 23, 1024: 23, 512: 14}[N] else 0
+    steps = {4096: 5 * 4 * 8 * 4 * 64, 2048: 5 * 2 * 8 * 4 * 64, 1024: 5 * 8 * 4 * 64, 512: 3 * 4 * 8 * 64}
+    transform = n * steps[N] * 16 if beta <= {4096: 22, 2048: 23, 1024: 23, 512: 14}[N] else 0
     assert ctx.bsk_prepared_bytes() == n * 2 * 4 * l * N * 8 + transform
     d = [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy(idx.astype(np.int32)).cuda(),
          ctx.bsk_prepare(slz.to_device_u64(bsk.reshape(n, 2, l, 2, N)))]

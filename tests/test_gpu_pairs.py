@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import synth
+from tests.test_gpu_fft import _inputs
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -29,9 +30,10 @@ def _case(slz, N, batch, n):
 
 @pytest.mark.parametrize("N", [2048, 4096])
 def test_pairs_of_workgroups_match_one_workgroup(slz, N):
-    # 129 ciphertexts are one past the pairs' last; 8 and 9: one pair per XCD and a second on each; one step and an odd and an even number of them
-    ctx, d = _case(slz, N, 129, 6)
-    for steps in (1, 5, 6):
+    # 129 ciphertexts are one past the pairs' last; 8 and 9: one pair per XCD and a second on each; odd and even numbers of steps, from the fewest on that
+    # pairs take (N = 2048: 8; N = 4096: 8 up to 64 ciphertexts, 32 above) and below
+    ctx, d = _case(slz, N, 129, 41)
+    for steps in (1, 7, 8, 9, 31, 32, 41):
         every = ctx.blind_rotate_batch(*d, steps)
         for count in (1, 2, 8, 9, 63, 127, 128):
             part = ctx.blind_rotate_batch(d[0][:count], d[1], d[2][:count], d[3], steps)
@@ -39,6 +41,23 @@ def test_pairs_of_workgroups_match_one_workgroup(slz, N):
     every = ctx.pbs_batch(*d)
     for _ in range(3):
         assert torch.equal(ctx.pbs_batch(d[0][:100], d[1], d[2][:100], d[3]), every[:100])
+
+
+@pytest.mark.parametrize("N,batch,beta,extreme", [(2048, 1, 23, False), (2048, 5, 12, True), (2048, 37, 1, False), (2048, 100, 23, True), (2048, 128, 8, True),
+                                                   (4096, 1, 22, True), (4096, 37, 1, False), (4096, 64, 13, True)])
+def test_pairs_of_workgroups_match_generic_path_and_oracle(slz, N, batch, beta, extreme):
+    import oracle as orc
+    n = 9
+    p, ctx, bsk, luts, cts, idx, d = _inputs(slz, batch, beta, n=n, extreme=extreme, N=N)
+    got = {s: ctx.blind_rotate_batch(*d, s) for s in (8, 9)}
+    out, out0 = ctx.pbs_batch(*d), ctx.pbs_batch(d[0], d[1], None, d[3])
+    ctx.set_option(slz.SLZ_OPT_FORCE_GENERIC, 1)                       # the same prepared key
+    for s, acc in got.items():
+        assert torch.equal(acc, ctx.blind_rotate_batch(*d, s)), s
+    assert torch.equal(out, ctx.pbs_batch(*d))
+    assert torch.equal(out0, ctx.pbs_batch(d[0], d[1], None, d[3]))
+    sample = np.unique([0, batch // 2, batch - 1])
+    assert np.array_equal(slz.to_host_u64(out)[sample], orc.pbs_batch(p, cts[sample], luts, idx[sample], bsk))
 
 
 @pytest.mark.parametrize("N", [2048, 4096])
@@ -74,13 +93,13 @@ def test_pairs_of_workgroups_do_every_ciphertext_whatever_their_number_and_patie
     # the launch's driver (an internal function, by its mangled name).  A workgroup per XCD or fewer: nobody has a partner, all leave and the launch
     # behind takes everything.  17 to 40: one to three of an XCD, so pairs with many ciphertexts each and workgroups left over.  Without
     # patience a workgroup leaves unless its partner is there already, and partners come too late.
-    count = 100
-    ctx, d = _case(slz, N, 129, 6)
+    count, n = 100, 33
+    ctx, d = _case(slz, N, 129, n)
     run = getattr(slz.lib(), "_Z16slz_fft%d_pairP7slz_ctxPKmS2_PKjPKvjPmS7_jjjP12ihipStream_t" % N)
     run.argtypes = [ctypes.c_void_p] * 5 + [ctypes.c_uint32] + [ctypes.c_void_p] * 2 + [ctypes.c_uint32] * 3 + [ctypes.c_void_p]
     run.restype = ctypes.c_int
-    key = d[3].data_ptr() + 6 * 2 * 4 * N * 8            # the transform form, behind the residues
-    ctx.blind_rotate_batch(d[0][:1], d[1], d[2][:1], d[3], 1)         # allocates what pairs need
+    key = d[3].data_ptr() + n * 2 * 4 * N * 8            # the transform form, behind the residues
+    ctx.blind_rotate_batch(d[0][:1], d[1], d[2][:1], d[3], n)         # allocates what pairs need
     for steps in (1, 5, 6):
         want = ctx.blind_rotate_batch(*d, steps)[:count]
         for workgroups in (1, 7, 8, 16, 17, 18, 31, 40, 208, 256):
