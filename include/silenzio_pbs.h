@@ -96,13 +96,14 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      once; v < 0 disarms */
 
 /* Allocation and graph capture: slz_pbs_batch, slz_blind_rotate_batch, slz_keyswitch_batch and slz_ks_pbs_batch allocate
- * their scratch (and the large-N path its two internal streams) in the first call on a context; later calls with a batch
+ * their scratch (and the large-N path its two internal streams) in the first call on a context, whatever its batch; later calls with a batch
  * no larger than max_batch record only kernels and event edges on the given stream and may be captured into a HIP graph
  * (warm up once outside the capture). */
 
-/* Streams: at N = 2048 and N = 4096 (k = l = 1) a call with up to 128 ciphertexts uses memory of its context, allocated by the first such call.  Calls of one
- * context on several streams may overlap all the same: one that finds that memory in use by another stream, and one that is being captured,
- * runs the kernel without (same results, 1.1 to 1.4 times the time). */
+/* Streams: calls on one context share its scratch and must not overlap: order them on one stream or with events.  Excepted are lookups (slz_pbs_batch,
+ * slz_blind_rotate_batch) where slz_pbs_path names a fused kernel: these may overlap each other on several streams.  At N = 2048 and N = 4096
+ * (k = l = 1) such a call with up to 128 ciphertexts takes memory of its context; one that finds it in use by another stream, one that is being
+ * captured, and all where there was no room for it run the kernel without (same results, 1.1 to 1.4 times the time). */
 
 /* Creates a context on the current device.  Allocates transform tables and scratch sized for
  * `max_batch` ciphertexts.  Fails with SLZ_E_UNSUPPORTED when the exactness bound

@@ -266,30 +266,42 @@ static const host_tables &tables(uint32_t N) {
 
 // ---- pairs of workgroups (slz_xcd.h) ------------------------------------------------------------------------------------
 
-// Their words and mail: 32 bytes per coefficient and pair, for as many pairs as a launch makes; asked for once, by
-// the first call that could use them.  A context without them (no room) runs every batch with one workgroup per ciphertext.
-static void pairs_init(slz_ctx *ctx) {
-    const uint32_t N = ctx->prm.N;
+static bool in_capture(hipStream_t s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+    return capture != hipStreamCaptureStatusNone;
+}
+// While a stream is being captured, the runtime refuses allocations and queries of events to every thread that does not allow them itself.  What is
+// asked for here has nothing to do with what is being captured.
+struct beside_captures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    beside_captures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~beside_captures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Their words and mail: 32 bytes per coefficient and pair, for as many pairs as a launch makes; asked for once, by the context's first
+// call outside a capture, whatever its batch: later ones allocate nothing.  A context without them (no room) runs every batch with one workgroup per ciphertext.
+static void pairs_scratch(slz_ctx *ctx) {
     ctx->pair_asked = 1;
     const uint32_t pairs = slz_pairs_most(ctx) / 2;
     const size_t words = (SLZ_PAIR_WORDS * sizeof(uint32_t) + 255) & ~(size_t)255;
     void *buf = nullptr;
     hipEvent_t ev;
-    if (hipMalloc(&buf, words + (size_t)pairs * 2 * 2 * (N / 2) * 16) != hipSuccess) { (void)hipGetLastError(); return; }
+    if (slz_scratch_alloc(&buf, words + (size_t)pairs * 2 * 2 * (ctx->prm.N / 2) * 16) != SLZ_OK) return;
     if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(buf); return; }
     ctx->pair_ctl = (uint32_t *)buf;
     ctx->pair_mail = (char *)buf + words;
     ctx->pair_done = ev;
 }
 
-// The context's words and mail for a launch on s, or 0: calls of one context on several streams may overlap, and a captured call may be
+// The context's words and mail for a launch on s (where it wants them), or 0: calls of one context on several streams may overlap, and a captured call may be
 // replayed at any time, so those that could meet an earlier launch's use of them keep to the kernels that need none.
-int slz_pairs_acquire(slz_ctx *ctx, uint32_t batch, hipStream_t s) {
-    if (batch > SLZ_PAIR_MAX) return 0;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
-    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return 0; }
-    if (!ctx->pair_asked) pairs_init(ctx);
-    if (!ctx->pair_ctl) return 0;
+int slz_pairs_acquire(slz_ctx *ctx, int wanted, hipStream_t s) {
+    if (ctx->pair_asked && !wanted) return 0;
+    if (in_capture(s)) return 0;
+    beside_captures allowed;
+    if (!ctx->pair_asked) pairs_scratch(ctx);
+    if (!wanted || !ctx->pair_ctl) return 0;
     if (!ctx->pair_used) return 1;
     if (ctx->pair_stream != s && hipEventQuery((hipEvent_t)ctx->pair_done) != hipSuccess) { (void)hipGetLastError(); return 0; }
     // the same stream's earlier launches come first anyway, unless the handle has passed on to a new stream

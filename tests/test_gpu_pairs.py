@@ -28,6 +28,14 @@ def _case(slz, N, batch, n):
     return ctx, [slz.to_device_u64(cts), slz.to_device_u64(luts), torch.from_numpy((np.arange(batch) % 2).astype(np.int32)).cuda(), d_bsk]
 
 
+def _driver(slz, N):
+    """The launch with any number of workgroups and any patience (an internal function, by its mangled name)."""
+    run = getattr(slz.lib(), "_Z16slz_fft%d_pairP7slz_ctxPKmS2_PKjPKvjPmS7_jjjP12ihipStream_t" % N)
+    run.argtypes = [ctypes.c_void_p] * 5 + [ctypes.c_uint32] + [ctypes.c_void_p] * 2 + [ctypes.c_uint32] * 3 + [ctypes.c_void_p]
+    run.restype = ctypes.c_int
+    return run
+
+
 @pytest.mark.parametrize("N", [2048, 4096])
 def test_pairs_of_workgroups_match_one_workgroup(slz, N):
     # 129 ciphertexts are one past the pairs' last; 8 and 9: one pair per XCD and a second on each; odd and even numbers of steps, from the fewest on that
@@ -89,15 +97,54 @@ def test_pairs_of_workgroups_beside_other_streams_and_in_graphs(slz, N):
 
 
 @pytest.mark.parametrize("N", [2048, 4096])
+def test_pairs_memory_comes_with_the_first_call_and_may_be_refused(slz, N):
+    def pairs_ran(ctx, d):
+        out = torch.zeros((100, 2, N), dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        rc = _driver(slz, N)(ctx._h, d[0].data_ptr(), d[1].data_ptr(), d[2].data_ptr(), d[3].data_ptr() + 33 * 2 * 4 * N * 8, 33, out.data_ptr(), None, 100,
+                             208, 200000, None)
+        torch.cuda.synchronize()
+        assert rc == slz.SLZ_E_INVALID_ARG or torch.equal(out, ctx.blind_rotate_batch(*d, 33)[:100])
+        return rc == slz.SLZ_OK
+
+    ctx, d = _case(slz, N, 129, 33)
+    few = [d[0][:100].clone(), d[1], d[2][:100].clone(), d[3]]
+    ctx.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, 0)     # the first call's allocation: that call and all after it run without pairs
+    every = ctx.pbs_batch(*d)
+    assert torch.equal(ctx.pbs_batch(*few), every[:100]) and not pairs_ran(ctx, d)
+    other, e = _case(slz, N, 129, 33)                   # a batch that makes no pairs brings their memory, and later calls ask for none
+    other.pbs_batch(*e)
+    assert pairs_ran(other, e)
+    other.set_option(slz.SLZ_OPT_FAIL_ALLOC_AFTER, 0)
+    assert torch.equal(other.pbs_batch(*few), every[:100])
+    with pytest.raises(slz.SlzError) as err:            # still armed: the keyswitch's digit scratch meets it
+        other.keyswitch_batch(every, torch.zeros((N, other.p.ks_level, 34), dtype=torch.int64, device="cuda"))
+    assert err.value.code == slz.SLZ_E_NOMEM
+    # a first call beside another stream's capture, which may allocate nothing itself
+    third, e = _case(slz, N, 129, 33)
+    side, graph, out, again = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.empty_like(every), torch.empty_like(every)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        other.pbs_batch(*d, out=out)
+        with torch.cuda.stream(side):
+            third.pbs_batch(*e, out=again)
+    torch.cuda.synchronize()
+    assert torch.equal(again, every) and pairs_ran(third, e)
+    out.zero_()
+    for rep in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, every), rep
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
 def test_pairs_of_workgroups_do_every_ciphertext_whatever_their_number_and_patience(slz, N):
-    # the launch's driver (an internal function, by its mangled name).  A workgroup per XCD or fewer: nobody has a partner, all leave and the launch
+    # A workgroup per XCD or fewer: nobody has a partner, all leave and the launch
     # behind takes everything.  17 to 40: one to three of an XCD, so pairs with many ciphertexts each and workgroups left over.  Without
     # patience a workgroup leaves unless its partner is there already, and partners come too late.
     count, n = 100, 33
     ctx, d = _case(slz, N, 129, n)
-    run = getattr(slz.lib(), "_Z16slz_fft%d_pairP7slz_ctxPKmS2_PKjPKvjPmS7_jjjP12ihipStream_t" % N)
-    run.argtypes = [ctypes.c_void_p] * 5 + [ctypes.c_uint32] + [ctypes.c_void_p] * 2 + [ctypes.c_uint32] * 3 + [ctypes.c_void_p]
-    run.restype = ctypes.c_int
+    run = _driver(slz, N)
     key = d[3].data_ptr() + n * 2 * 4 * N * 8            # the transform form, behind the residues
     ctx.blind_rotate_batch(d[0][:1], d[1], d[2][:1], d[3], n)         # allocates what pairs need
     for steps in (1, 5, 6):
