@@ -294,23 +294,34 @@ static void pairs_scratch(slz_ctx *ctx) {
     ctx->pair_done = ev;
 }
 
-// The context's words and mail for a launch on s (where it wants them), or 0: calls of one context on several streams may overlap, and a captured call may be
-// replayed at any time, so those that could meet an earlier launch's use of them keep to the kernels that need none.
-int slz_pairs_acquire(slz_ctx *ctx, int wanted, hipStream_t s) {
-    if (ctx->pair_asked && !wanted) return 0;
-    if (in_capture(s)) return 0;
+static int pairs_free(slz_ctx *ctx, int wanted, hipStream_t s) {
     beside_captures allowed;
     if (!ctx->pair_asked) pairs_scratch(ctx);
     if (!wanted || !ctx->pair_ctl) return 0;
     if (!ctx->pair_used) return 1;
-    if (ctx->pair_stream != s && hipEventQuery((hipEvent_t)ctx->pair_done) != hipSuccess) { (void)hipGetLastError(); return 0; }
     // the same stream's earlier launches come first anyway, unless the handle has passed on to a new stream
-    return hipStreamWaitEvent(s, (hipEvent_t)ctx->pair_done, 0) == hipSuccess;
+    const bool done = ctx->pair_stream == s || hipEventQuery((hipEvent_t)ctx->pair_done) == hipSuccess;
+    if (done && hipStreamWaitEvent(s, (hipEvent_t)ctx->pair_done, 0) == hipSuccess) return 1;
+    (void)hipGetLastError();
+    return 0;
 }
-int slz_pairs_release(slz_ctx *ctx, hipStream_t s) {
+// The context's words and mail for a launch on s (where it wants them), or 0: calls of one context on several streams may overlap, and a captured call may be
+// replayed at any time, so those that could meet an earlier launch's use of them keep to the kernels that need none; so does a call that comes while
+// another thread's has them in hand, between here and slz_pairs_release.
+int slz_pairs_acquire(slz_ctx *ctx, int wanted, hipStream_t s) {
+    if (in_capture(s) || __atomic_exchange_n(&ctx->pair_held, 1, __ATOMIC_ACQUIRE)) return 0;
+    if (pairs_free(ctx, wanted, s)) return 1;
+    __atomic_store_n(&ctx->pair_held, 0, __ATOMIC_RELEASE);
+    return 0;
+}
+// rc: of the launches.  Where one of them or the event behind them failed, nothing tells when the memory is free again: it stays held, and the
+// context runs without pairs from then on.
+int slz_pairs_release(slz_ctx *ctx, int rc, hipStream_t s) {
+    if (rc != SLZ_OK) return rc;
     SLZ_HIP(hipEventRecord((hipEvent_t)ctx->pair_done, s));
     ctx->pair_used = 1;
     ctx->pair_stream = s;
+    __atomic_store_n(&ctx->pair_held, 0, __ATOMIC_RELEASE);
     return SLZ_OK;
 }
 __global__ void __launch_bounds__(256) k_pairs_clear(uint32_t *ctl) {

@@ -61,6 +61,7 @@ struct slz_ctx {
     void *pair_mail;
     void *pair_done;          // hipEvent_t: behind the last launch that used them
     int pair_asked;           // their allocation has been tried
+    int pair_held;            // a call has them in hand (atomic)
     int pair_used;            // there has been such a launch
     void *pair_stream;        // its stream
     int has_bign;             // large-N three-pass path available (N = 2048 G, k = 1)
@@ -149,7 +150,7 @@ int slz_fft4096_pair_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t
 int slz_fft4096_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                      uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s);
 int slz_pairs_acquire(slz_ctx *ctx, int wanted, hipStream_t s);
-int slz_pairs_release(slz_ctx *ctx, hipStream_t s);
+int slz_pairs_release(slz_ctx *ctx, int rc, hipStream_t s);
 int slz_fft1024_setup();
 int slz_fft512_setup();
 int slz_fft512_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,

@@ -1,6 +1,7 @@
 """N = 2048 and 4096 with few ciphertexts, where two workgroups share each: against the kernels with one workgroup per ciphertext (which larger
 batches, captured calls and calls beside another stream's take) bit for bit; those are compared with the oracle elsewhere."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -83,6 +84,20 @@ def test_pairs_of_workgroups_beside_other_streams_and_in_graphs(slz, N):
     torch.cuda.synchronize()
     for i, out in enumerate(outs):
         assert torch.equal(out, every[:count]), i
+    def calls(i):                                       # and by two threads
+        with torch.cuda.stream(streams[i]):
+            for _ in range(20):
+                ctx.pbs_batch(*few, out=outs[i])
+    threads = [threading.Thread(target=calls, args=(i,)) for i in range(2)]
+    for out in outs:
+        out.zero_()
+    torch.cuda.synchronize()
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], every[:count]) and torch.equal(outs[1], every[:count])
     graph, out = torch.cuda.CUDAGraph(), torch.empty_like(outs[0])
     with torch.cuda.graph(graph):
         ctx.pbs_batch(*few, out=out)
