@@ -411,7 +411,7 @@ int slz_fft4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
     // up to 128 ciphertexts two workgroups on each: 14.5 to 15.1 us per step against 16.4 to 16.6 (slz_fft2048.hip: when not).  us with one workgroup /
     // two, the launches around them included: 4 steps 73 / 70 at 1 ciphertext, 76 / 81 at 64; 8 steps 144 / 138 at 64, 144 / 152 at 100; 24 steps 410 / 417 at 128, 32 steps
     // 543 / 540.
-    if (slz_pairs_acquire(ctx, batch <= SLZ_PAIR_MAX && n_steps >= (batch <= 64 ? 8u : 32u), s))
+    if (slz_pairs_acquire(ctx, n_steps >= (batch <= 64 ? 8u : 32u) && slz_pairs_fit(batch, s), s))
         return slz_pairs_release(ctx, slz_fft4096_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, slz_pairs_grid(batch), SLZ_PAIR_PATIENCE, s), s);
     return all_of_them(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s, nullptr);
 }

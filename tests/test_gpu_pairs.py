@@ -173,3 +173,24 @@ def test_pairs_of_workgroups_do_every_ciphertext_whatever_their_number_and_patie
                 torch.cuda.synchronize()
                 assert torch.equal(out, want), (steps, workgroups, patience)
     assert run(ctx._h, d[0].data_ptr(), d[1].data_ptr(), d[2].data_ptr(), key, 1, want.data_ptr(), None, count, 257, 0, None) == slz.SLZ_E_INVALID_ARG
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
+def test_lookups_on_streams_limited_to_some_compute_units(slz, N):
+    # one, two and eight compute units of every XCD; 7 ciphertexts make 8 pairs at most, which fit the last two, 100 fit none of them
+    ctx, d = _case(slz, N, 129, 33)
+    every = ctx.pbs_batch(*d)
+    fits = slz.lib()._Z13slz_pairs_fitjP12ihipStream_t
+    fits.argtypes, fits.restype = [ctypes.c_uint32, ctypes.c_void_p], ctypes.c_int
+    assert fits(128, None) and not fits(129, None)
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    for units in (8, 16, 64):
+        handle = ctypes.c_void_p()
+        mask = (ctypes.c_uint32 * 8)(*[min(0xffffffff, (1 << max(0, units - 32 * i)) - 1) for i in range(8)])
+        assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+        assert [bool(fits(count, handle)) for count in (1, 7, 32, 33)] == [units >= 16, units >= 16, units >= 64, False]
+        with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+            for count in (1, 7, 100):
+                got = ctx.pbs_batch(d[0][:count], d[1], d[2][:count], d[3])
+                torch.cuda.synchronize()
+                assert torch.equal(got, every[:count]), (units, count)
