@@ -29,6 +29,13 @@ int slz_scratch_alloc(void **out, size_t bytes) {
     return SLZ_OK;
 }
 
+uint32_t slz_compute_units(hipStream_t s) {
+    uint32_t mask[32] = {}, n = 0;
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) { (void)hipGetLastError(); return 0xffffffffu; }
+    for (uint32_t word : mask) n += (uint32_t)__builtin_popcount(word);
+    return n;
+}
+
 // Tables of the context and of every path that takes its parameter set (host vectors: may throw std::bad_alloc).
 static int init_paths(slz_ctx *ctx) {
     const slz_params *params = &ctx->prm;

@@ -960,7 +960,9 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
     const slz_params &p = ctx->prm;
     const uint32_t N = p.N, BS = (uint32_t)ctx->bign_block, G = N / BS, R = 2 * p.pbs_level;
     if (n_steps == 0) return SLZ_OK;
-    if (ctx->bign_latency && BS == 1024 && ctx->bign_ctl && slz_bign_xcd_takes(G, p.pbs_level, batch))
+    // (on a stream limited to some compute units the workgroups that run do the others' tasks in turn, where the launches below deal theirs evenly: 12 steps on
+    // 128 of 256 compute units, us in one launch / below: 1 ciphertext 697 / 284, 8: 716 / 528, 24: 2080 / 773)
+    if (ctx->bign_latency && BS == 1024 && ctx->bign_ctl && slz_bign_xcd_takes(G, p.pbs_level, batch) && slz_compute_units(s) >= SLZ_XCD_WORKGROUPS)
         return slz_bign_xcd_run(ctx, lwe_in, bskp, n_steps, acc, batch, SLZ_XCD_WORKGROUPS, s);
     // few ciphertexts otherwise: every step in two launches (1024-blocks only, and where there was room for the second accumulator)
     const bool lat = ctx->bign_latency && BS == 1024 && batch <= slz_bign_latency_max_batch(G, p.pbs_level) && ctx->bign_spare;

@@ -294,17 +294,10 @@ static void pairs_scratch(slz_ctx *ctx) {
     ctx->pair_done = ev;
 }
 
-// Compute units that a launch on s may use: fewer than the device has where the stream or the process is limited to some of them.
-static uint32_t compute_units(hipStream_t s) {
-    uint32_t mask[32] = {}, n = 0;
-    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) { (void)hipGetLastError(); return 0xffffffffu; }
-    for (uint32_t word : mask) n += (uint32_t)__builtin_popcount(word);
-    return n;
-}
 // Whether pairs for `batch` ciphertexts all find a place at once, two compute units each; otherwise one workgroup on each is faster.  100 steps of N = 2048, us with
 // one workgroup / pairs: on 64 compute units 32 ciphertexts 943 / 675, 64: 945 / 1325; on 240 compute units 128: 949 / 1321; on 8 (one of each XCD,
 // where a pair has no place) 1: 939 / 2950.
-int slz_pairs_fit(uint32_t batch, hipStream_t s) { return batch <= SLZ_PAIR_MAX && slz_pairs_grid(batch) <= compute_units(s); }
+int slz_pairs_fit(uint32_t batch, hipStream_t s) { return batch <= SLZ_PAIR_MAX && slz_pairs_grid(batch) <= slz_compute_units(s); }
 
 static int pairs_free(slz_ctx *ctx, int wanted, hipStream_t s) {
     beside_captures allowed;

@@ -95,6 +95,8 @@ struct slz_ctx {
 
 // scratch allocation of the entry points (slz_api.hip): SLZ_OK or SLZ_E_NOMEM, *out null on failure
 int slz_scratch_alloc(void **out, size_t bytes);
+// compute units that a launch on s may use: fewer than the device has where the stream or the process is limited to some of them
+uint32_t slz_compute_units(hipStream_t s);
 
 // host side (slz_tables.cpp)
 int slz_build_tables(slz_ctx *ctx);

@@ -1101,3 +1101,22 @@ def test_large_n_one_launch_needs_no_number_of_workgroups(slz, orc, count):
         assert run(case.ctx._h, case.d_cts.data_ptr(), case.d_bsk.data_ptr(), p.n, acc.data_ptr(), count, workgroups, None) == 0
         torch.cuda.synchronize()
         assert torch.equal(acc, want), workgroups
+
+
+def test_large_n_on_a_stream_limited_to_some_compute_units(slz, orc):
+    # eight compute units of every XCD: batches that the one launch takes elsewhere run as on the whole device
+    p = tiny(n=3, N=32768, k=1, pbs_base_log=15, pbs_level=2)
+    case = Case(slz, orc, p, 9, raw_inputs=True)
+    want = case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)
+    units = slz.lib()._Z17slz_compute_unitsP12ihipStream_t
+    units.argtypes, units.restype = [ctypes.c_void_p], ctypes.c_uint32
+    assert units(None) == units(torch.cuda.Stream().cuda_stream) == torch.cuda.get_device_properties(0).multi_processor_count
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    handle = ctypes.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, (ctypes.c_uint32 * 8)(0xffffffff, 0xffffffff)) == 0
+    assert units(handle) == 64
+    with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+        for count in (1, 9):
+            got = case.ctx.pbs_batch(case.d_cts[:count], case.d_luts, case.d_idx[:count], case.d_bsk)
+            torch.cuda.synchronize()
+            assert torch.equal(got, want[:count]), count
