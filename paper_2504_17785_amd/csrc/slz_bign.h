@@ -76,6 +76,7 @@ __device__ __forceinline__ void cols_mirror_last(double &f, double &g, const dou
 // slz_bign_xcd.hip: all CMux steps of a batch in one launch.  a.acc [batch][2][N] initialised, a.X for min(batch, 8) ciphertexts, a.bskp_step the key of step 0,
 // ctl slz_bign_xcd_ctl_bytes() bytes
 #define SLZ_XCD_WORKGROUPS 256u
+#define SLZ_XCD_PATIENCE (1u << 22)      // looks at the L2 of half a microsecond and more: seconds, where a phase takes microseconds
 int slz_bign_xcd_setup();
 size_t slz_bign_xcd_ctl_bytes();
-int slz_bign_xcd_launch(const bign_args &a, uint32_t *ctl, uint32_t n_steps, uint32_t workgroups, hipStream_t s);
+int slz_bign_xcd_launch(const bign_args &a, uint32_t *ctl, uint32_t n_steps, uint32_t workgroups, uint32_t patience, hipStream_t s);

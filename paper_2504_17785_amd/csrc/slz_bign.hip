@@ -946,12 +946,17 @@ uint32_t slz_bign_xcd_takes(uint32_t G, uint32_t l, uint32_t batch) {
     return batch <= 16 || (batch >= 22 && batch <= 24) || (batch >= 31 && batch <= 40);
 }
 
-// The one launch on `workgroups` workgroups; any number of them goes through all steps (tests run fewer), SLZ_XCD_WORKGROUPS are one per slot.
+// The one launch on `workgroups` workgroups; any number of them goes through all steps (tests run fewer), SLZ_XCD_WORKGROUPS are one per slot.  patience:
+// slz_bign_xcd.hip; tests take less than SLZ_XCD_PATIENCE.
 int slz_bign_xcd_run(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc, uint32_t batch, uint32_t workgroups,
                      hipStream_t s) {
+    return slz_bign_xcd_run(ctx, lwe_in, bskp, n_steps, acc, batch, workgroups, SLZ_XCD_PATIENCE, s);
+}
+int slz_bign_xcd_run(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc, uint32_t batch, uint32_t workgroups,
+                     uint32_t patience, hipStream_t s) {
     bign_args a = args_of(ctx, 1024, lwe_in, acc, 0, batch);
     a.bskp_step = bskp;
-    return slz_bign_xcd_launch(a, ctx->bign_ctl, n_steps, workgroups, s);
+    return slz_bign_xcd_launch(a, ctx->bign_ctl, n_steps, workgroups, patience, s);
 }
 
 // Runs steps [0, n_steps) on accumulators that the caller has initialised in `acc` ([batch][2][N]).

@@ -17,7 +17,10 @@
 // Every wait ends.  A slot (1 / XCD_SLOTS of every phase's tasks) belongs to the workgroup that joined with its number, or is claimed phase by
 // phase by a workgroup that has done its own part of the phase; a claim is only made by a workgroup that runs, and waits only for tasks of
 // earlier phases.  So the first unfinished phase always has all its tasks either claimed by running workgroups that wait for nothing, or claimed next by
-// one of them; nothing depends on how many workgroups are resident, or on which XCDs the launch was dealt to.
+// one of them; nothing depends on how many workgroups are resident, or on which XCDs the launch was dealt to.  That holds for control words that this
+// launch alone writes.  A call that overlaps another one on its context, which its caller has to prevent, clears them under it: accumulators and transforms are
+// lost then, as in the other kernels, and a wait would have no end.  So a wait gives up after `patience` looks, and so do all behind it; what a
+// workgroup reads and writes does not go out of range by that, as no address is taken from another's results.
 #include "slz_bign.h"
 
 #define XCD_LISTS 8u             // one per XCD
@@ -35,6 +38,7 @@ struct xcd_args {
     bign_args a;                 // X [list][2][R][N], acc [batch][2][N]; bskp_step: the key of step 0; step: not used
     uint32_t *ctl;               // [lists][XCD_CTL], zero
     uint32_t lists, n_steps;
+    uint32_t patience;           // looks of a wait until it gives up, one at least
 };
 
 __device__ __forceinline__ double ld_l2(const double *uniform_base, uint32_t lane_byte_off) {
@@ -52,10 +56,13 @@ __device__ __forceinline__ uint32_t xcd_lane() {
 
 // done[slot]: how many of the list's phases the slot's tasks are done of.  Words of one line that 32 workgroups store to and 32 lanes of a
 // wave read at once: a counter instead, 32 atomic additions to one word: 17.0 us per step against 16.2.
-// All slots' tasks of the phases before `phase` are done.  Ends: see above.
-__device__ __forceinline__ void xcd_wait(const uint32_t *done, uint32_t phase) {
-    if (threadIdx.x < XCD_SLOTS)
-        while (__builtin_amdgcn_ballot_w64(__hip_atomic_load(done + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < phase)) {}
+// All slots' tasks of the phases before `phase` are done, or this was the last of `patience` looks (see above): then every wait after it takes one.
+__device__ __forceinline__ void xcd_wait(const uint32_t *done, uint32_t phase, uint32_t wave, uint32_t &patience) {
+    if (wave == 0) {
+        uint32_t left = patience;
+        while (__builtin_amdgcn_ballot_w64(__hip_atomic_load(done + (threadIdx.x & (XCD_SLOTS - 1u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < phase))
+            if (--left == 0) { patience = left = 1; break; }
+    }
     __syncthreads();
 }
 __device__ __forceinline__ void xcd_finish(uint32_t *done, uint32_t slot, uint32_t phase) {
@@ -77,7 +84,7 @@ struct xcd_ct {                  // the ciphertext at hand
 // Lift, columns 64 (task >> 1) .. of component task & 1.  (prime, quarter of the rows) run the inverse stages inside a
 // quarter; each wave then takes an eighth of the row quadruples (j, j + G / 4, ..) for the last two stages, both primes, and the lift.
 template <int G>
-__device__ __forceinline__ void xcd_lift(const xcd_args &K, const xcd_ct &ct, double *res, uint32_t wave, uint32_t task, const uint32_t *done, uint32_t phase) {
+__device__ __forceinline__ void xcd_lift(const xcd_args &K, const xcd_ct &ct, double *res, uint32_t wave, uint32_t task, const uint32_t *done, uint32_t phase, uint32_t &patience) {
     constexpr int Q = G / 4, J = Q / 8;
     static_assert(J >= 1, "eight waves share the quadruples");
     const bign_args &A = K.a;
@@ -85,7 +92,7 @@ __device__ __forceinline__ void xcd_lift(const xcd_args &K, const xcd_ct &ct, do
     const uint32_t comp = task & 1u, c = 64 * (task >> 1) + lane;
     const uint32_t N = 1024u * G;
     uint64_t *acc = ct.acc + (size_t)comp * N;
-    xcd_wait(done, phase);
+    xcd_wait(done, phase, wave, patience);
     const uint32_t j0 = wave * J;
     uint64_t w[J][4];
     {
@@ -158,7 +165,7 @@ __device__ __forceinline__ bool xcd_collects(uint32_t wave) { return ((wave >> 1
 // half of the rows) run the forward stages.
 template <int G>
 __device__ __forceinline__ void xcd_turn(const xcd_args &K, const xcd_ct &ct, int32_t *digits, uint32_t wave,
-                                         uint32_t task, uint32_t at, const uint32_t *done, uint32_t phase) {
+                                         uint32_t task, uint32_t at, const uint32_t *done, uint32_t phase, uint32_t &patience) {
     constexpr int H = G / 2, D = G / 8;
     constexpr uint32_t N = 1024u * G;
     const bign_args &A = K.a;
@@ -166,7 +173,7 @@ __device__ __forceinline__ void xcd_turn(const xcd_args &K, const xcd_ct &ct, in
     const uint32_t comp = task & 1u, c = 64 * (task >> 1) + lane;
     const uint32_t u = c + 2 * N - at, urow = u >> 10;           // X^at moves coefficient u (mod 2N, negated from N on) to c
     const uint64_t *acc = ct.acc + (size_t)comp * N;
-    xcd_wait(done, phase);
+    xcd_wait(done, phase, wave, patience);
     uint64_t own[D], other[D];
 #pragma unroll
     for (int k = 0; k < D; k++) {
@@ -215,7 +222,7 @@ __device__ __forceinline__ void xcd_turn(const xcd_args &K, const xcd_ct &ct, in
 // half of them from the sums of the step before on (kk_half: done), half during the forward stages.
 template <int G>
 __device__ __forceinline__ void xcd_rows(const xcd_args &K, const xcd_ct &ct, double (&kk)[2][16], bool kk_half, const uint64_t *ahead, uint64_t &ahead_word, const double *key, const double *next, double *lds, const double *tabs, uint32_t wave,
-                                         uint32_t slot, const uint32_t *done, uint32_t phase) {
+                                         uint32_t slot, const uint32_t *done, uint32_t phase, uint32_t &patience) {
     constexpr uint32_t R = 4, N = 1024u * G;
     const bign_args &A = K.a;
     const uint32_t lane = xcd_lane();
@@ -227,7 +234,7 @@ __device__ __forceinline__ void xcd_rows(const xcd_args &K, const xcd_ct &ct, do
     asm volatile("s_mov_b32 %0, 0" : "=s"(z));
     double x[16];
     if (!kk_half) xcd_key_load<0, 8>(kk, key, N);
-    xcd_wait(done, phase);
+    xcd_wait(done, phase, wave, patience);
     {
         const double *src = ct.X + ((size_t)q * R + r) * N + 1024u * row;
 #pragma unroll
@@ -324,6 +331,7 @@ k_big_xcd(xcd_args K) {
     double kk[2][16];
     const double *kk_of = nullptr;                               // the block and step whose first half of the key words kk holds
     uint32_t tab_slot = ~0u;
+    uint32_t patience = K.patience;
     auto broadcast = [&](uint32_t v) -> uint32_t {               // thread 0's value to all
         __syncthreads();
         if (threadIdx.x == 0) *told = v;
@@ -354,7 +362,7 @@ k_big_xcd(xcd_args K) {
         uint64_t mask_word;                                      // of the step
         auto turn = [&](uint32_t slot, uint32_t p) {
             constexpr uint32_t logN2 = 11 + (G == 2 ? 1 : G == 4 ? 2 : G == 8 ? 3 : G == 16 ? 4 : 5);
-            xcd_turn<G>(K, ct, reinterpret_cast<int32_t *>(lds), wave, slot, slz_modswitch(mask_word, logN2), done, 3 * p);
+            xcd_turn<G>(K, ct, reinterpret_cast<int32_t *>(lds), wave, slot, slz_modswitch(mask_word, logN2), done, 3 * p, patience);
             xcd_finish(done, slot, 3 * p);
         };
         auto rows = [&](uint32_t slot, uint32_t p, uint32_t step, const uint64_t *ahead, uint64_t &ahead_word) {
@@ -367,12 +375,12 @@ k_big_xcd(xcd_args K) {
                 tab_slot = slot;                                 // read behind the barriers of xcd_wait
             }
             const double *key = xcd_key<G>(K, wave, slot, step), *next = xcd_key<G>(K, wave, slot, step + 1 < K.n_steps ? step + 1 : 0);
-            xcd_rows<G>(K, ct, kk, kk_of == key, ahead, ahead_word, key, next, lds, tabs, wave, slot, done, 3 * p + 1);
+            xcd_rows<G>(K, ct, kk, kk_of == key, ahead, ahead_word, key, next, lds, tabs, wave, slot, done, 3 * p + 1, patience);
             kk_of = next;
             xcd_finish(done, slot, 3 * p + 1);
         };
         auto lift = [&](uint32_t slot, uint32_t p) {
-            xcd_lift<G>(K, ct, lds, wave, slot, done, 3 * p + 2);
+            xcd_lift<G>(K, ct, lds, wave, slot, done, 3 * p + 2, patience);
             xcd_finish(done, slot, 3 * p + 2);
         };
         // the slot of this workgroup's number is its own from the first phase on that nobody has claimed it for
@@ -434,12 +442,13 @@ int slz_bign_xcd_setup() {
 
 size_t slz_bign_xcd_ctl_bytes() { return XCD_LISTS * XCD_CTL * sizeof(uint32_t); }
 
-int slz_bign_xcd_launch(const bign_args &a, uint32_t *ctl, uint32_t n_steps, uint32_t workgroups, hipStream_t s) {
+int slz_bign_xcd_launch(const bign_args &a, uint32_t *ctl, uint32_t n_steps, uint32_t workgroups, uint32_t patience, hipStream_t s) {
     xcd_args K;
     K.a = a;
     K.ctl = ctl;
     K.lists = a.batch < XCD_LISTS ? a.batch : XCD_LISTS;
     K.n_steps = n_steps;
+    K.patience = patience;
     hipLaunchKernelGGL(k_xcd_clear, dim3(K.lists * XCD_CTL / 256), dim3(256), 0, s, ctl, K.lists * XCD_CTL);
     hipLaunchKernelGGL(k_big_xcd<32>, dim3(workgroups), dim3(512), XCD_LDS, s, K);
     SLZ_HIP(hipGetLastError());

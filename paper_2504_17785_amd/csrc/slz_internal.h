@@ -175,6 +175,8 @@ int slz_bign_cmux_steps(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp
 uint32_t slz_bign_xcd_takes(uint32_t G, uint32_t l, uint32_t batch);
 int slz_bign_xcd_run(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc, uint32_t batch, uint32_t workgroups,
                      hipStream_t s);
+int slz_bign_xcd_run(slz_ctx *ctx, const uint64_t *lwe_in, const double *bskp, uint32_t n_steps, uint64_t *acc, uint32_t batch, uint32_t workgroups,
+                     uint32_t patience, hipStream_t s);
 uint32_t slz_bign_latency_max_batch(uint32_t G, uint32_t l);
 uint32_t slz_bign_first_of_even_lanes(uint32_t G, uint32_t batch, uint32_t half);
 // keyswitch / lincomb (slz_keyswitch.hip)

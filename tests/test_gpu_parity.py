@@ -1103,6 +1103,25 @@ def test_large_n_one_launch_needs_no_number_of_workgroups(slz, orc, count):
         assert torch.equal(acc, want), workgroups
 
 
+@pytest.mark.parametrize("patience", [1, 2])
+def test_large_n_one_launch_ends_when_its_waits_give_up(slz, orc, patience):
+    # what ends a launch whose control words another call clears: the driver with next to no patience.  Its words are worth nothing then, unless one
+    # workgroup does all tasks, which waits for nobody; the launch after it finds everything as it should be
+    p = tiny(n=3, N=32768, k=1, pbs_base_log=15, pbs_level=2)
+    case = Case(slz, orc, p, 9, raw_inputs=True)
+    want = case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, p.n)
+    start = case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, 0)
+    run = slz.lib()._Z16slz_bign_xcd_runP7slz_ctxPKmPKdjPmjjjP12ihipStream_t
+    run.argtypes, run.restype = [ctypes.c_void_p] * 3 + [ctypes.c_uint32, ctypes.c_void_p] + [ctypes.c_uint32] * 3 + [ctypes.c_void_p], ctypes.c_int
+    for workgroups in (1, 13, 256):
+        acc = start.clone()
+        torch.cuda.synchronize()
+        assert run(case.ctx._h, case.d_cts.data_ptr(), case.d_bsk.data_ptr(), p.n, acc.data_ptr(), 9, workgroups, patience, None) == 0
+        torch.cuda.synchronize()
+        assert workgroups > 1 or torch.equal(acc, want)
+        assert torch.equal(case.ctx.blind_rotate_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk, p.n), want), workgroups
+
+
 def test_large_n_on_a_stream_limited_to_some_compute_units(slz, orc):
     # eight compute units of every XCD: batches that the one launch takes elsewhere run as on the whole device
     p = tiny(n=3, N=32768, k=1, pbs_base_log=15, pbs_level=2)
