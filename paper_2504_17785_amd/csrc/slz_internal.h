@@ -188,6 +188,7 @@ void slz_ksm_destroy(slz_ctx *ctx);
 int slz_ksm_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *ksk, const void *kskp, uint64_t *lwe_out, uint32_t batch,
                    hipStream_t s);
 size_t slz_ksm_prepared_bytes(const slz_params *p);
+int slz_ksm_takes_ranges(const slz_params *p, uint32_t batch, int prepared);
 int slz_ksm_prepare(slz_ctx *ctx, const uint64_t *ksk, void *dst, hipStream_t s);
 // matrix-core linear combination (slz_lincomb_mfma.hip)
 void slz_lcm_destroy(slz_ctx *ctx);

@@ -20,6 +20,7 @@
 #define KM_TARGET_WGS 768               // workgroups aimed for when the row index is cut into segments (three per CU)
 #define KM_RANGES_GROUPS_PREP 16        // ciphertext groups up to which workgroups take ranges of rows across x tiles: operand form,
 #define KM_RANGES_GROUPS_STD 8          // standard key
+#define KM_ROUND_BLOCKS 20              // a further round of workgroups (first loads, sums) in blocks of a workgroup's work
 #define KM_BUF_V4 (KM_IT_KB * 2 * 8 * 32)   // 16-byte slots per LDS buffer: [block][half][plane][x]
 
 // ---- digits --------------------------------------------------------------------------------------------------------
@@ -372,63 +373,81 @@ void slz_ksm_destroy(slz_ctx *ctx) {
     ctx->ks_dig = nullptr;
 }
 
+// How the contraction of `batch` ciphertexts is cut, into A: its grid by segments, or, with A.ranges_per_xcd not 0, by ranges.
+static int ksm_plan(const slz_params &p, uint32_t batch, bool prepared, ksm_args &A, uint32_t &grid) {
+    const uint32_t kN = p.k * p.N;
+    const uint32_t n_kb = (uint32_t)((uint64_t)p.ks_level * kN / 32);
+    A.kN = kN; A.n = p.n; A.l = p.ks_level;
+    A.n_kb = n_kb;
+    A.x_tiles = (p.n + 1 + 31) / 32;
+    A.batch = batch;
+    A.n_tiles = (batch + 31) / 32;
+    A.ct_groups = (A.n_tiles + KM_WAVES - 1) / KM_WAVES;
+    // int32 accumulators: 32 kb_per_seg rows of |digit * byte| <= 2^(beta-1) * 2^7 must stay strictly below 2^31
+    A.kb_cap = (1u << (20 - p.ks_base_log)) - 2 * KM_IT_KB;
+    // segments of the row index: enough workgroups for three rounds over the 256 CUs (a workgroup spends about half
+    // its time outside the MFMA loop at ten iterations, so fewer, longer segments with idle CUs measured no better)
+    uint32_t segs = (KM_TARGET_WGS + A.x_tiles * A.ct_groups - 1) / (A.x_tiles * A.ct_groups);
+    segs = max(1u, min(segs, (n_kb + 7) / 8));
+    uint32_t kbs = ((n_kb + segs - 1) / segs + 2 * KM_IT_KB - 1) / (2 * KM_IT_KB) * (2 * KM_IT_KB);
+    kbs = min(kbs, A.kb_cap);
+    segs = (n_kb + kbs - 1) / kbs;
+    A.kb_per_seg = kbs;
+    const uint64_t total = (uint64_t)segs * A.x_tiles * A.ct_groups;
+    if (total > (1u << 30)) return SLZ_E_UNSUPPORTED;
+    A.total = (uint32_t)total;
+    A.per_xcd = (A.total + 7) / 8;
+    A.direct = segs == 1;
+    A.ranges_per_xcd = A.range = 0;
+    grid = A.per_xcd * 8;
+    // Ranges of rows across x tiles, one per resident workgroup, instead of three rounds of segments: a workgroup's first loads and the
+    // sums it adds to the output come once (or twice, at the end of an x tile) and not three times.  us, segments / ranges, standard
+    // (prepared) key, kN = 2048, n = 742: 64 ciphertexts 27.9 / 23.3 (25.3 / 20.9), 512: 79 / 55 (74 / 51), 1024: 112 / 86 (104 / 79),
+    // 2048: 171 / 148 (160 / 133), 4096: 294 / 287 (272 / 253); kN = 1024, 777: 73 / 46 (67 / 42); kN = 4096, 1024: 210 / 161
+    // (196 / 145); kN = 32768, n = 1024, 24: 320 / 339 (293 / 241), 256: 518 / 527 (472 / 413).  Past 16 groups half of the workgroups
+    // would be left out; past 8 the recoding of a standard key, done by each of the groups, wants the third workgroup of a CU's queue.
+    // A standard key past the 256 MB of the memory-side cache comes from memory in rows of 8 (n + 1) bytes, of which the workgroups of
+    // an XCD read the whole width together only by segments.
+    const bool from_memory = !prepared && (uint64_t)kN * p.ks_level * (p.n + 1) * 8 > (256u << 20);
+    if (segs == 1 || A.ct_groups > (prepared ? KM_RANGES_GROUPS_PREP : KM_RANGES_GROUPS_STD) || from_memory) return SLZ_OK;
+    // Whether they are the shorter way, counted in blocks.  They are not where a number of groups that does not divide 32 leaves workgroups out and the
+    // segments come out even (kN = 4096, n = 800, prepared key, blocks by segments / ranges: 11 groups 4 x 216 / 1040, 419 / 437 us, 13: 452 / 478;
+    // 9: 4 x 160 / 696, 336 / 320, 14: 5 x 216 / 1040, 533 / 498; kN = 32768, 7: 4 x 1280 / 5280, 2514 / 2687), nor where the segments are one round and no
+    // range is longer than one of them (kN = 2048, n = 300, l = 3, 256 ciphertexts, standard key: 24.2 / 27.3).
+    const uint32_t per_xcd = 32 / A.ct_groups, unit = 2 * KM_IT_KB, positions = A.x_tiles * ksm_padded_blocks(n_kb);
+    const uint32_t range = ((positions + 8 * per_xcd - 1) / (8 * per_xcd) + unit - 1) / unit * unit;
+    const uint64_t rounds = (A.total + 255) / 256;
+    if (range >= rounds * kbs + KM_ROUND_BLOCKS * (rounds - 1)) return SLZ_OK;
+    A.ranges_per_xcd = per_xcd;
+    A.range = range;
+    grid = 8 * per_xcd * A.ct_groups;
+    return SLZ_OK;
+}
+// tested on the host
+int slz_ksm_takes_ranges(const slz_params *p, uint32_t batch, int prepared) {
+    ksm_args A;
+    uint32_t grid;
+    return ksm_plan(*p, batch, prepared, A, grid) == SLZ_OK && A.ranges_per_xcd;
+}
+
 // The launches of one keyswitch given its digit scratch (`dig`: room for max_tiles 32-ciphertext tiles).
 static int ksm_run(const slz_params &p, void *dig, uint32_t max_tiles, const uint64_t *lwe_in, const uint64_t *ksk, const void *kskp,
                    uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
     const uint32_t kN = p.k * p.N;
-    const uint32_t n_kb = (uint32_t)((uint64_t)p.ks_level * kN / 32);
     ksm_args A;
     A.ksk = ksk;
     A.kskp = (const v4i *)kskp;
     A.dig = (const v4i *)dig;
-    A.kN = kN; A.n = p.n; A.l = p.ks_level;
-    A.n_kb = n_kb;
-    A.x_tiles = (p.n + 1 + 31) / 32;
-    // int32 accumulators: 32 kb_per_seg rows of |digit * byte| <= 2^(beta-1) * 2^7 must stay strictly below 2^31
-    const uint32_t kb_cap = (1u << (20 - p.ks_base_log)) - 2 * KM_IT_KB;
     for (uint32_t c0 = 0; c0 < batch; c0 += max_tiles * 32) {
-        const uint32_t nb = min(batch - c0, max_tiles * 32);
-        A.batch = nb;
-        A.n_tiles = (nb + 31) / 32;
-        A.ct_groups = (A.n_tiles + KM_WAVES - 1) / KM_WAVES;
+        uint32_t grid;
+        const int rc = ksm_plan(p, min(batch - c0, max_tiles * 32), kskp, A, grid);
+        if (rc != SLZ_OK) return rc;
         A.out = lwe_out + (size_t)c0 * (p.n + 1);
-        // segments of the row index: enough workgroups for three rounds over the 256 CUs (a workgroup spends about half
-        // its time outside the MFMA loop at ten iterations, so fewer, longer segments with idle CUs measured no better)
-        uint32_t segs = (KM_TARGET_WGS + A.x_tiles * A.ct_groups - 1) / (A.x_tiles * A.ct_groups);
-        segs = max(1u, min(segs, (n_kb + 7) / 8));
-        uint32_t kbs = ((n_kb + segs - 1) / segs + 2 * KM_IT_KB - 1) / (2 * KM_IT_KB) * (2 * KM_IT_KB);
-        kbs = min(kbs, kb_cap);
-        segs = (n_kb + kbs - 1) / kbs;
-        A.kb_per_seg = kbs;
-        A.kb_cap = kb_cap;
-        const uint64_t total = (uint64_t)segs * A.x_tiles * A.ct_groups;
-        if (total > (1u << 30)) return SLZ_E_UNSUPPORTED;
-        A.total = (uint32_t)total;
-        A.per_xcd = (A.total + 7) / 8;
         A.lwe_in = lwe_in + (size_t)c0 * (kN + 1);
-        A.direct = segs == 1;
-        hipLaunchKernelGGL(k_ksm_digits, dim3((kN + KD_WORDS - 1) / KD_WORDS, A.n_tiles), dim3(256), 0, s,
-                           lwe_in + (size_t)c0 * (kN + 1), (v4i *)dig, kN, p.ks_base_log, p.ks_level, nb, n_kb,
-                           A.direct ? nullptr : A.out, p.n);
-        uint32_t grid = A.per_xcd * 8;
-        // Ranges of rows across x tiles, one per resident workgroup, instead of three rounds of segments: a workgroup's first loads and the
-        // sums it adds to the output come once (or twice, at the end of an x tile) and not three times.  us, segments / ranges, standard
-        // (prepared) key, kN = 2048, n = 742: 64 ciphertexts 27.9 / 23.3 (25.3 / 20.9), 512: 78 / 55 (75 / 51), 1024: 110 / 91 (105 / 80),
-        // 2048: 167 / 153 (159 / 136), 4096: 296 / 319 (275 / 260); kN = 1024, 777: 73 / 46 (67 / 42); kN = 4096, 1024: 203 / 167
-        // (192 / 146); kN = 32768, n = 1024, 24: 320 / 339 (292 / 240), 256: 518 / 527 (467 / 418).  Past 16 groups half of the workgroups
-        // would be left out; past 8 the recoding of a standard key, done by each of the groups, wants the third workgroup of a CU's queue.
-        // A standard key past the 256 MB of the memory-side cache comes from memory in rows of 8 (n + 1) bytes, of which the workgroups of
-        // an XCD read the whole width together only by segments.
-        const bool from_memory = !kskp && (uint64_t)kN * p.ks_level * (p.n + 1) * 8 > (256u << 20);
-        const bool ranges = segs > 1 && A.ct_groups <= (kskp ? KM_RANGES_GROUPS_PREP : KM_RANGES_GROUPS_STD) && !from_memory;
-        if (ranges) {
-            A.ranges_per_xcd = 32 / A.ct_groups;
-            const uint32_t n_ranges = 8 * A.ranges_per_xcd, unit = 2 * KM_IT_KB, positions = A.x_tiles * ksm_padded_blocks(n_kb);
-            A.range = ((positions + n_ranges - 1) / n_ranges + unit - 1) / unit * unit;
-            grid = n_ranges * A.ct_groups;
-        }
-        auto *kernel = kskp ? ranges ? k_ksm_main<true, true> : k_ksm_main<true, false>
-                            : ranges ? k_ksm_main<false, true> : k_ksm_main<false, false>;
+        hipLaunchKernelGGL(k_ksm_digits, dim3((kN + KD_WORDS - 1) / KD_WORDS, A.n_tiles), dim3(256), 0, s, A.lwe_in, (v4i *)dig, kN, p.ks_base_log,
+                           p.ks_level, A.batch, A.n_kb, A.direct ? nullptr : A.out, p.n);
+        auto *kernel = kskp ? A.ranges_per_xcd ? k_ksm_main<true, true> : k_ksm_main<true, false>
+                            : A.ranges_per_xcd ? k_ksm_main<false, true> : k_ksm_main<false, false>;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(KM_THREADS), 0, s, A);
     }
     SLZ_HIP(hipGetLastError());

@@ -272,6 +272,22 @@ def test_large_n_one_launch_is_taken_where_it_wins():
     assert not any(f(G, l, b) for G in (2, 4, 8, 16, 32, 64) for l in (1, 2, 3, 4) for b in range(1, 65) if (G, l) != (32, 2))
 
 
+def test_keyswitch_takes_ranges_where_they_win():
+    # (words, n, levels): groups of 256 ciphertexts up to 20 with the standard and with the prepared key; segments win by 4 to 13 % at the groups left out
+    # up to the limits of 8 and 16, and by 15 to 30 % past the latter
+    f = slz.lib()._Z20slz_ksm_takes_rangesPK10slz_paramsji
+    f.argtypes, f.restype = [ctypes.POINTER(slz.SlzParams), ctypes.c_uint32, ctypes.c_int], ctypes.c_int
+    to8, to16 = list(range(1, 9)), list(range(1, 17))
+    want = {(2048, 742, 5): (to8, to16), (1024, 630, 5): (to8, to16), (2048, 300, 3): (to8[1:], to16[1:]), (512, 500, 4): (to8[2:], to16[2:]),
+            (256, 128, 2): ([], []), (4096, 800, 5): (to8, to16[:10] + [14, 15, 16]), (8192, 900, 4): (to8, to16[:10] + [14, 15, 16]),
+            (32768, 1024, 5): ([], to16[:6] + [8, 16])}
+    for (kN, n, l), groups in want.items():
+        cp = slz.make_params(synth.CONFIGS[2].with_(N=kN, n=n, k=1, ks_base_log=4, ks_level=l))
+        got = tuple([g for g in range(1, 21) if f(ctypes.byref(cp), 256 * g, prepared)] for prepared in (0, 1))
+        assert got == groups, (kN, n, l)
+        assert all(f(ctypes.byref(cp), 256 * g - 255, q) == f(ctypes.byref(cp), 256 * g, q) for g in range(1, 21) for q in (0, 1))
+
+
 def test_bench_counts_the_key_form_and_the_operations_of_the_path_that_runs():
     import sys
     sys.path.insert(0, ROOT)

@@ -174,10 +174,10 @@ def test_keyswitch_with_prepared_key_matches_oracle(slz, orc, batch, k, N, n, be
 
 
 @pytest.mark.parametrize("batch,N,n,l", [(2048, 256, 300, 5), (2049, 256, 300, 5), (4095, 256, 300, 5), (4097, 256, 300, 5),
-                                          (40, 64, 10, 8), (700, 512, 95, 5)])
+                                          (40, 64, 10, 8), (700, 512, 95, 5), (1300, 64, 1750, 5), (2600, 64, 1750, 5)])
 def test_keyswitch_by_ranges_of_rows_matches_oracle(slz, orc, batch, N, n, l):
     # the last batch of ranges and the first of segments for either form of the key, ranges that end inside an x tile and
-    # that cross one, more workgroups than ranges, a row-block count that is no multiple of eight
+    # that cross one, more workgroups than ranges, a row-block count that is no multiple of eight; (40, ..) and (700, ..): one round of segments
     p = tiny(n=n, N=N, k=1, ks_base_log=4, ks_level=l)
     ksk = synth.raw_words(p, "raw_ksk", N * l * (n + 1)).reshape(N, l, n + 1)
     cts = synth.raw_words(p, "raw_ct", batch * (N + 1)).reshape(batch, N + 1)
@@ -190,10 +190,11 @@ def test_keyswitch_by_ranges_of_rows_matches_oracle(slz, orc, batch, N, n, l):
         assert np.array_equal(slz.to_host_u64(ctx.keyswitch_batch_prepared(d_cts, kskp)), want)
 
 
-def test_keyswitch_by_ranges_adds_up_before_int32_overflows(slz, orc):
-    # 131072 rows, every digit and every key byte -128: 2^17 products of 2^14, one range longer than an x tile
+@pytest.mark.parametrize("batch", [2817, 3841])
+def test_keyswitch_by_ranges_adds_up_before_int32_overflows(slz, orc, batch):
+    # 131072 rows, every digit and every key byte -128: 2^17 products of 2^14; 3841: ranges, one of them longer than an x tile, 2817: segments
     p = tiny(n=543, N=16384, k=1, ks_base_log=8, ks_level=8)
-    batch, word = 2817, 0x7f7f7f7f7f7f7f80
+    word = 0x7f7f7f7f7f7f7f80
     cts = torch.full((batch, p.N + 1), word, dtype=torch.int64, device="cuda")
     ksk = torch.full((p.N, 8, p.n + 1), word, dtype=torch.int64, device="cuda")
     ctx = slz.Context(p, batch)
