@@ -406,12 +406,15 @@ static int all_of_them(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *lut
     return SLZ_OK;
 }
 
+// Steps from which on two workgroups take each of `batch` ciphertexts.  What pairs cost beside the steps they have to win back: us with one workgroup / two, the
+// launches around them included: 4 steps 73 / 70 at 1 ciphertext, 76 / 81 at 64; 8 steps 144 / 138 at 64, 144 / 152 at 100; 32 steps 538 / 508 at 80,
+// 538 / 533 at 100, 537 / 553 at 128; 48 steps 802 / 810 at 120, 64 steps 1065 / 1048.
+uint32_t slz_fft4096_pair_steps(uint32_t batch) { return batch <= 64 ? 8 : batch <= 100 ? 32 : 64; }
+
 int slz_fft4096_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                              uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, hipStream_t s) {
-    // up to 128 ciphertexts two workgroups on each: 14.5 to 15.1 us per step against 16.4 to 16.6 (slz_fft2048.hip: when not).  us with one workgroup /
-    // two, the launches around them included: 4 steps 73 / 70 at 1 ciphertext, 76 / 81 at 64; 8 steps 144 / 138 at 64, 144 / 152 at 100; 24 steps 410 / 417 at 128, 32 steps
-    // 543 / 540.
-    if (slz_pairs_acquire(ctx, n_steps >= (batch <= 64 ? 8u : 32u) && slz_pairs_fit(batch, s), s))
+    // up to 128 ciphertexts two workgroups on each: 14.5 to 15.1 us per step against 16.4 to 16.6 (slz_fft2048.hip: when not)
+    if (slz_pairs_acquire(ctx, n_steps >= slz_fft4096_pair_steps(batch) && slz_pairs_fit(batch, s), s))
         return slz_pairs_release(ctx, slz_fft4096_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, slz_pairs_grid(batch), SLZ_PAIR_PATIENCE, s), s);
     return all_of_them(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s, nullptr);
 }

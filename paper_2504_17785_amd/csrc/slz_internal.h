@@ -151,6 +151,7 @@ int slz_fft4096_pair_launch(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t
                             uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s);
 int slz_fft4096_pair(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_t *luts, const uint32_t *lut_idx, const void *key,
                      uint32_t n_steps, uint64_t *acc_out, uint64_t *lwe_out, uint32_t batch, uint32_t workgroups, uint32_t patience, hipStream_t s);
+uint32_t slz_fft4096_pair_steps(uint32_t batch);                 // tested on the host
 int slz_pairs_fit(uint32_t batch, hipStream_t s);
 int slz_pairs_acquire(slz_ctx *ctx, int wanted, hipStream_t s);
 int slz_pairs_release(slz_ctx *ctx, int rc, hipStream_t s);

@@ -272,6 +272,12 @@ def test_large_n_one_launch_is_taken_where_it_wins():
     assert not any(f(G, l, b) for G in (2, 4, 8, 16, 32, 64) for l in (1, 2, 3, 4) for b in range(1, 65) if (G, l) != (32, 2))
 
 
+def test_n4096_pairs_take_as_many_steps_as_win_back_their_launches():
+    f = slz.lib()._Z22slz_fft4096_pair_stepsj
+    f.argtypes, f.restype = [ctypes.c_uint32], ctypes.c_uint32
+    assert [f(b) for b in (1, 64, 65, 100, 101, 128)] == [8, 8, 32, 32, 64, 64]
+
+
 def test_keyswitch_takes_ranges_where_they_win():
     # (words, n, levels): groups of 256 ciphertexts up to 20 with the standard and with the prepared key; segments win by 4 to 13 % at the groups left out
     # up to the limits of 8 and 16, and by 15 to 30 % past the latter

@@ -40,11 +40,11 @@ def _driver(slz, N):
 @pytest.mark.parametrize("N", [2048, 4096])
 def test_pairs_of_workgroups_match_one_workgroup(slz, N):
     # 129 ciphertexts are one past the pairs' last; 8 and 9: one pair per XCD and a second on each; odd and even numbers of steps, from the fewest on that
-    # pairs take (N = 2048: 8; N = 4096: 8 up to 64 ciphertexts, 32 above) and below
-    ctx, d = _case(slz, N, 129, 41)
-    for steps in (1, 7, 8, 9, 31, 32, 41):
+    # pairs take (N = 2048: 8; N = 4096: 8 up to 64 ciphertexts, 32 up to 100, 64 above) and below
+    ctx, d = _case(slz, N, 129, 65)
+    for steps in (1, 7, 8, 9, 31, 32, 41, 63, 64, 65):
         every = ctx.blind_rotate_batch(*d, steps)
-        for count in (1, 2, 8, 9, 63, 127, 128):
+        for count in (1, 2, 8, 9, 63, 100, 127, 128):
             part = ctx.blind_rotate_batch(d[0][:count], d[1], d[2][:count], d[3], steps)
             assert torch.equal(part, every[:count]), (steps, count)
     every = ctx.pbs_batch(*d)
