@@ -282,7 +282,7 @@ struct beside_captures {
 // Their words and mail: 32 bytes per coefficient and pair, for as many pairs as a launch makes; asked for once, by the context's first
 // call outside a capture, whatever its batch: later ones allocate nothing.  A context without them (no room) runs every batch with one workgroup per ciphertext.
 static void pairs_scratch(slz_ctx *ctx) {
-    ctx->pair_asked = 1;
+    __atomic_store_n(&ctx->pair_asked, 1, __ATOMIC_RELAXED);
     const uint32_t pairs = slz_pairs_most(ctx) / 2;
     const size_t words = (SLZ_PAIR_WORDS * sizeof(uint32_t) + 255) & ~(size_t)255;
     void *buf = nullptr;
@@ -314,6 +314,7 @@ static int pairs_free(slz_ctx *ctx, int wanted, hipStream_t s) {
 // replayed at any time, so those that could meet an earlier launch's use of them keep to the kernels that need none; so does a call that comes while
 // another thread's has them in hand, between here and slz_pairs_release.
 int slz_pairs_acquire(slz_ctx *ctx, int wanted, hipStream_t s) {
+    if (!wanted && __atomic_load_n(&ctx->pair_asked, __ATOMIC_RELAXED)) return 0;
     if (in_capture(s) || __atomic_exchange_n(&ctx->pair_held, 1, __ATOMIC_ACQUIRE)) return 0;
     if (pairs_free(ctx, wanted, s)) return 1;
     __atomic_store_n(&ctx->pair_held, 0, __ATOMIC_RELEASE);
