@@ -245,3 +245,32 @@ def test_large_n_two_launch_steps_up_to_their_line(slz, N, l, beta, last, lanes)
         nodes = ctypes.c_size_t(0)
         assert slz.lib().hipGraphGetNodes(ctypes.c_void_p(int(graph.raw_cuda_graph())), None, ctypes.byref(nodes)) == 0
         assert nodes.value == kernels + 2, count
+
+
+# N = 32768 with two levels, by the kernels of a captured call: the one launch (behind a kernel that clears its words) up to 16, 22 to 24 and 31 to 40, the
+# two-launch steps between on two lanes, three launches past it
+def test_large_n_one_launch_and_two_launch_steps_take_turns(slz):
+    import ctypes
+    N, l, n, batch = 32768, 2, 3, 41
+    p = synth.CONFIGS[2].with_(name="turns", N=N, n=n, pbs_level=l, pbs_base_log=15, msg_bits=3, batch=batch)
+    d_key = synth.raw_words(p, "raw_bsk", n * 4 * l * N).reshape(n, 2, l, 2, N)
+    d_luts = slz.to_device_u64(synth.raw_words(p, "misc", N).reshape(1, N))
+    d_in = slz.to_device_u64(synth.raw_words(p, "raw_ct", batch * (n + 1)).reshape(batch, n + 1))
+    ctx = slz.Context(p, batch)
+    d_key = ctx.bsk_prepare(slz.to_device_u64(d_key))
+    want = ctx.pbs_batch(d_in, d_luts, None, d_key)
+    one, two, three = 2, 2 * (2 * n + 1), 2 * 3 * n
+    for count, kernels in ((16, one), (17, two), (21, two), (22, one), (24, one), (25, two), (30, two), (31, one), (40, one), (41, three)):
+        out = torch.empty((count, N + 1), dtype=torch.int64, device="cuda")
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            ctx.pbs_batch(d_in[:count], d_luts, None, d_key, out=out)
+        nodes = ctypes.c_size_t(0)
+        assert slz.lib().hipGraphGetNodes(ctypes.c_void_p(int(graph.raw_cuda_graph())), None, ctypes.byref(nodes)) == 0
+        assert nodes.value == kernels + 2, count
+        graph.instantiate()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[:count]), count

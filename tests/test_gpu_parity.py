@@ -783,7 +783,7 @@ def test_large_n_path_matches_oracle_and_generic(slz, orc, shape, block):
     want = orc.pbs_batch(p, case.cts, case.luts, case.lut_idx, case.keys.bsk)
     got = slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk))
     assert np.array_equal(got, want)
-    # five ciphertexts on 1024-blocks took the two-launch steps; the same call on the throughput kernels, after one more
+    # five ciphertexts on 1024-blocks took the two-launch steps (N = 32768 with two levels: the one launch); the same call on the throughput kernels, after one more
     # step count on them
     case.ctx.set_option(slz.SLZ_OPT_LARGE_N_LATENCY, 0)
     assert np.array_equal(slz.to_host_u64(case.ctx.pbs_batch(case.d_cts, case.d_luts, case.d_idx, case.d_bsk)), want)
@@ -1017,7 +1017,8 @@ def test_lookup_replays_from_a_hip_graph(slz, orc, shape, batch):
     (8192, 1, 20, 2, [1, 5, 96]),           # G = 8, eight waves per 64 columns, two rows; five ciphertexts: pairs split over the XCDs
     (8192, 3, 12, 3, [4]),                  # three levels over eight waves
     (16384, 2, 15, 3, [3, 32, 33, 56]),     # G = 16; one lane up to 32
-    (32768, 2, 15, 2, [2, 16, 17, 32]),     # G = 32; one lane up to 16
+    (32768, 2, 15, 2, [2, 16, 17, 32]),     # G = 32; one lane up to 16 (2, 16 and 32: the one launch)
+    (32768, 2, 15, 3, [17, 21, 25, 27, 30]),    # the ends of the two-launch steps' windows, two lanes
 ])
 def test_large_n_two_launch_steps_match_the_throughput_kernels(slz, orc, N, l, beta, n, batches):
     # the largest batches the two-launch steps take and sizes where their form changes, odd and even step counts (the accumulator
@@ -1033,9 +1034,9 @@ def test_large_n_two_launch_steps_match_the_throughput_kernels(slz, orc, N, l, b
         assert np.array_equal(got, want[:count]), count
 
 
-@pytest.mark.parametrize("N,largest,counts", [(32768, 40, [32, 17, 3]), (16384, 70, [56, 33]), (8192, 100, [96, 65])])
+@pytest.mark.parametrize("N,largest,counts", [(32768, 40, [32, 27, 17, 3]), (16384, 70, [56, 33]), (8192, 100, [96, 65])])
 def test_large_n_calls_after_the_first_allocate_nothing(slz, orc, N, largest, counts):
-    # the first call has a batch of the throughput kernels; smaller ones then take the two-launch steps without an allocation: with the next one
+    # the first call has a batch of the throughput kernels (N = 32768: as 32 and 3, of the one launch); smaller ones then take the two-launch steps without an allocation: with the next one
     # forced to fail, and inside a graph capture
     p = tiny(n=2, N=N, k=1, pbs_base_log=15, pbs_level=2)
     case = Case(slz, orc, p, largest, raw_inputs=True)
