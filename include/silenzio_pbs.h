@@ -103,7 +103,9 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
 /* Streams: calls on one context share its scratch and must not overlap: order them on one stream or with events.  Excepted are lookups (slz_pbs_batch,
  * slz_blind_rotate_batch) where slz_pbs_path names a fused kernel: these may overlap each other on several streams.  At N = 2048 and N = 4096
  * (k = l = 1) such a call with up to 128 ciphertexts takes memory of its context; one that finds it in use by another stream, one that is being
- * captured, and all where there was no room for it run the kernel without (same results, 1.1 to 1.4 times the time). */
+ * captured, and all where there was no room for it run the kernel without (same results, 1.1 to 1.4 times the time).  It takes two compute units per
+ * ciphertext where those are idle when it starts, so a call alone is faster; calls of several contexts that keep the device busy together may take up to 1.4
+ * times the time that they would with one compute unit per ciphertext. */
 
 /* Creates a context on the current device.  Allocates transform tables and scratch sized for
  * `max_batch` ciphertexts.  Fails with SLZ_E_UNSUPPORTED when the exactness bound

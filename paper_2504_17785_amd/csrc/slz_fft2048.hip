@@ -485,8 +485,8 @@ int slz_fft2048_blind_rotate(slz_ctx *ctx, const uint64_t *lwe_in, const uint64_
     // Up to one ciphertext per compute unit its eight waves take one together (742 steps: one 7.2 ms against 8.5 with two pairs on it, 256
     // 8.3 against 8.6); from 257 on that needs a second round (301: 14.6 ms against 11.5).
     // Up to 128 ciphertexts two workgroups take each (6.4 to 6.6 us per step against 9.2 to 9.3 with one), unless an overlapping or captured call needs the
-    // kernel without memory of its own.  To clear their words, to meet and the launch behind them cost 10 to 13 us: 4 steps take one workgroup / two 44 / 44 us
-    // at 1 ciphertext and 46 / 53 at 128, 8 steps 80 / 69 and 83 / 81.
+    // kernel without memory of its own.  To clear their words, to meet and the launch behind them cost 12 to 16 us: 4 steps take one workgroup / two 44 / 44 us
+    // at 1 ciphertext and 46 / 53 at 128, 8 steps 80 / 70 and 82 / 80.
     if (slz_pairs_acquire(ctx, n_steps >= 8 && slz_pairs_fit(batch, s), s))
         return slz_pairs_release(ctx, slz_fft2048_pair(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, slz_pairs_grid(batch), SLZ_PAIR_PATIENCE, s), s);
     if (batch <= FFT_TEAM_MAX) return slz_fft2048_team(ctx, lwe_in, luts, lut_idx, key, n_steps, acc_out, lwe_out, batch, s);

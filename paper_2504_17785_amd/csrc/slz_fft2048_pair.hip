@@ -64,7 +64,7 @@ k_fft2048_pair(fft2048p_args A) {
         __syncthreads();
         return __builtin_amdgcn_readfirstlane(*(const LDS_AS uint32_t *)(uintptr_t)told);
     };
-    const uint32_t place = broadcast(threadIdx.x == 0 ? slz_pair_join(A.pairs, A.batch) : 0u);
+    const uint32_t place = broadcast(threadIdx.x == 0 ? slz_pair_join(A.pairs) : 0u);
     if (place == SLZ_PAIR_NONE) return;
     const uint32_t h = place & 1u, box = place >> 1;                                        // component; pair
     uint32_t *line = slz_pair_line(A.pairs, box);

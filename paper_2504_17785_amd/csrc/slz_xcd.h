@@ -34,16 +34,21 @@ __device__ __forceinline__ d2 lane_get_l2(const d2 *uniform_base, uint32_t lane)
 }
 
 // Pairs.  A workgroup takes a number on its XCD; two with successive numbers are a pair, the second of which asks for ciphertexts for both until
-// there are none left.  The first waits for the second to start, until every ciphertext is taken, or for `patience`; then it leaves, and so does the
-// second if it comes after that.  So a launch ends whatever places it is given (one compute unit of an XCD, under a mask of compute units, holds one of these
-// workgroups and never a pair); the ciphertexts that no pair has taken are left to a launch behind it that pairs nothing.  Once met, the two of
-// a pair wait for each other alone, and both run.
+// there are none left.  First all workgroups of the launch have to have come, within `patience` of the one that waits longest; otherwise all leave, those
+// that come later too, and a launch behind this one that pairs nothing takes the ciphertexts.  So a launch ends whatever places it is given (one
+// compute unit of an XCD, under a mask of compute units, holds one of these workgroups and never a pair), and takes twice the compute units of the kernel that
+// pairs nothing only where they stand idle: beside other calls two of them do less than one on each of two ciphertexts.  200 steps of N = 2048 by
+// several contexts on streams of their own, us with one workgroup / pairs at once / this: 2 x 64 ciphertexts
+// 1877 / 1383 / 1389, 2 x 100: 1880 / 2429 / 2115, 3 x 80: 1890 / 2942 / 2109, 4 x 60: 1890 / 2694 / 2228; 2 x 128, where each finds all compute units free in
+// turn, 1903 / 2673 / 2692; N = 4096, 3 x 80: 3398 / 6804 / 3925.  It costs a call of its own 1 to 3 us.
+// Once all have come, the two of a pair wait for each other alone, and both run; a first one without a second leaves.
 #define SLZ_PAIR_MAX 128u                           // pairs of a launch: 256 workgroups
 #define SLZ_PAIR_NONE 0xffffffffu
-#define SLZ_PAIR_PATIENCE 200000u                   // 2 ms of the 100 MHz clock; where there is room the second starts within microseconds
+#define SLZ_PAIR_PATIENCE 2000u                     // 20 us of the 100 MHz clock; where there is room the last one comes within 1 (16 workgroups) to 6 us (256) of the first
 struct slz_pairs {
-    uint32_t *ctl;            // words, zero at the start: [0] ciphertexts taken, [32] pairs, [64 + 32 x] numbers of XCD x, then [16][128] pair + 1 by
-                              // XCD and number / 2, then a line of 32 words per pair: [8] progress of its waves, [8] the ciphertext at hand
+    uint32_t *ctl;            // words, zero at the start: [0] ciphertexts taken, [16] whether there are pairs, [32] workgroups that have come and, times 2^16, pairs,
+                              // [64 + 32 x] numbers of XCD x, then [16][128] pair + 1 by XCD and number / 2, then a line of 32 words per pair: [8] progress of
+                              // its waves, [8] the ciphertext at hand
     uint32_t patience;
 };
 #define SLZ_PAIR_MET 576u
@@ -51,27 +56,32 @@ struct slz_pairs {
 #define SLZ_PAIR_WORDS (SLZ_PAIR_LINES + 32u * SLZ_PAIR_MAX)
 __device__ __forceinline__ uint32_t *slz_pair_line(slz_pairs P, uint32_t pair) { return P.ctl + SLZ_PAIR_LINES + 32u * pair; }
 
-// The word by which two workgroups meet has one value after zero: whoever comes first writes it.  Returns that value.
-__device__ __forceinline__ uint32_t slz_pair_settle(uint32_t *met, uint32_t value) {
-    uint32_t seen = 0;
-    return __hip_atomic_compare_exchange_strong(met, &seen, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? value : seen;
-}
 // One thread: 2 pair + (0 first, 1 second), or SLZ_PAIR_NONE
-__device__ __forceinline__ uint32_t slz_pair_join(slz_pairs P, uint32_t batch) {
+__device__ __forceinline__ uint32_t slz_pair_join(slz_pairs P) {
+    enum : uint32_t { GO = 1, LEAVE = 2 };
     const uint32_t x = slz_xcc_id();
-    const uint32_t number = __hip_atomic_fetch_add(P.ctl + 64 + 32 * x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t *decision = P.ctl + 16, *numbers = P.ctl + 64 + 32 * x;
+    auto settle = [&](uint32_t value) -> uint32_t {                 // the word has one value after zero: whoever comes first writes it
+        uint32_t seen = 0;
+        return __hip_atomic_compare_exchange_strong(decision, &seen, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? value : seen;
+    };
+    const uint32_t number = __hip_atomic_fetch_add(numbers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t second = number & 1u;
     uint32_t *met = P.ctl + SLZ_PAIR_MET + 128 * x + number / 2;
-    if (number & 1u) {
-        const uint32_t pair = __hip_atomic_fetch_add(P.ctl + 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return slz_pair_settle(met, pair + 1) == SLZ_PAIR_NONE ? SLZ_PAIR_NONE : 2 * pair + 1;
-    }
+    const uint32_t before = __hip_atomic_fetch_add(P.ctl + 32, 1u + (second << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t pair = (before >> 16) + 1;
+    if (second) __hip_atomic_store(met, pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     const uint64_t since = wall_clock64();
-    uint32_t pair;
-    do {
-        pair = ld_agent(met);
-        if (!pair && (ld_agent(P.ctl) >= batch || wall_clock64() - since >= P.patience)) pair = slz_pair_settle(met, SLZ_PAIR_NONE);
-    } while (!pair);
-    return pair == SLZ_PAIR_NONE ? SLZ_PAIR_NONE : 2 * (pair - 1);
+    uint32_t found = (before & 0xffffu) + 1 == gridDim.x ? settle(GO) : 0;
+    while (!found) {
+        found = ld_agent(decision);
+        if (!found && wall_clock64() - since >= P.patience) found = settle(LEAVE);
+    }
+    if (found == LEAVE) return SLZ_PAIR_NONE;
+    if (second) return 2 * (pair - 1) + 1;
+    if (ld_agent(numbers) == number + 1) return SLZ_PAIR_NONE;      // all have taken their numbers
+    while (!(pair = ld_agent(met))) {}                              // the second is past its number, and writes this next
+    return 2 * (pair - 1);
 }
 // One thread of either workgroup: the pair's ciphertext of this round, or one past the last
 __device__ __forceinline__ uint32_t slz_pair_next(slz_pairs P, uint32_t pair, uint32_t second, uint32_t round) {

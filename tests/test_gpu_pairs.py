@@ -112,6 +112,24 @@ def test_pairs_of_workgroups_beside_other_streams_and_in_graphs(slz, N):
 
 
 @pytest.mark.parametrize("N", [2048, 4096])
+def test_pairs_of_workgroups_of_several_contexts_at_once(slz, N):
+    # 2 x 64 ciphertexts have room for their pairs together, 3 x 80 and 2 x 128 have not: those that do not find all their places leave the ciphertexts to
+    # the kernel with one workgroup on each
+    cases = [_case(slz, N, 128, 65) for _ in range(3)]
+    streams = [torch.cuda.Stream() for _ in cases]
+    d = cases[0][1]
+    want = _case(slz, N, 129, 65)[0].pbs_batch(torch.cat([d[0], d[0][:1]]), d[1], torch.cat([d[2], d[2][:1]]), d[3])[:128]
+    for contexts, count in ((2, 64), (3, 80), (2, 128)):
+        outs = [torch.zeros_like(want[:count]) for _ in range(4 * contexts)]
+        torch.cuda.synchronize()
+        for i, out in enumerate(outs):
+            with torch.cuda.stream(streams[i % contexts]):
+                cases[i % contexts][0].pbs_batch(d[0][:count], d[1], d[2][:count], d[3], out=out)
+        torch.cuda.synchronize()
+        assert all(torch.equal(out, want[:count]) for out in outs), (contexts, count)
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
 def test_pairs_memory_comes_with_the_first_call_and_may_be_refused(slz, N):
     def pairs_ran(ctx, d):
         out = torch.zeros((100, 2, N), dtype=torch.int64, device="cuda")
@@ -155,8 +173,8 @@ def test_pairs_memory_comes_with_the_first_call_and_may_be_refused(slz, N):
 @pytest.mark.parametrize("N", [2048, 4096])
 def test_pairs_of_workgroups_do_every_ciphertext_whatever_their_number_and_patience(slz, N):
     # A workgroup per XCD or fewer: nobody has a partner, all leave and the launch
-    # behind takes everything.  17 to 40: one to three of an XCD, so pairs with many ciphertexts each and workgroups left over.  Without
-    # patience a workgroup leaves unless its partner is there already, and partners come too late.
+    # behind takes everything.  16 to 40: two to five of an XCD, so pairs with many ciphertexts each and workgroups left over.  Without
+    # patience the first one to come finds that not all have, and all leave.
     count, n = 100, 33
     ctx, d = _case(slz, N, 129, n)
     run = _driver(slz, N)
