@@ -84,7 +84,8 @@ typedef struct slz_ctx slz_ctx;   /* opaque: parameter copy, twiddle tables, scr
                                      more, shorter threads instead of three (lower latency, identical results; their second accumulator
                                      of (k+1) N words per such ciphertext is allocated by the context's first call of any batch size;
                                      if there is no room for it then, the context keeps to three launches).  At N = 32768 with pbs_level 2
-                                     batches of up to 16, 22 to 24 and 31 to 40 run all steps in one launch, identical results again.
+                                     batches of up to 16, 22 to 24 and 31 to 40 run all steps in one launch, identical results again (faster for one or two
+                                     contexts at a time; three and more that call at once with more than eight ciphertexts together take up to 1.5 times as long).
                                      0 keeps the throughput kernels at every batch size; SLZ_E_INVALID_ARG without a large-N path */
 
 #define SLZ_OPT_FUSED_PACING 6    /* values 0, 1 and 2, on the N = 2048 fused path: accepted and without effect.  They paced the workgroups of
