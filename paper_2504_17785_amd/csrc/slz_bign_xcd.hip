@@ -1,5 +1,5 @@
-// Blind rotation for large polynomials on 1024-blocks (N = 1024 G, k = 1, two levels; G = 32) as one launch whose workgroups go through all CMux
-// steps together.  A team of 32 workgroups, one per compute unit of an XCD, takes one ciphertext at a time: accumulator and transforms (2.5 MiB at
+// Blind rotation for N = 32768 (32 blocks of 1024, k = 1, two levels; no other set) as one launch whose workgroups go through all CMux steps
+// together.  A team of 32 workgroups, one per compute unit of an XCD, takes one ciphertext at a time: accumulator and transforms (2.5 MiB at
 // N = 32768) stay in that XCD's 4 MiB L2, where the passes as launches of their own (slz_bign.hip) write them back to the memory-side
 // cache at the end of every launch and read them from there; what an XCD reads past its L2 is the key, 4 MiB per step.
 //
@@ -22,6 +22,7 @@
 // lost then, as in the other kernels, and a wait would have no end.  So a wait gives up after `patience` looks, and so do all behind it; what a
 // workgroup reads and writes does not go out of range by that, as no address is taken from another's results.
 #include "slz_bign.h"
+#include "slz_xcd.h"
 
 #define XCD_LISTS 8u             // one per XCD
 #define XCD_SLOTS 32u
@@ -318,16 +319,14 @@ __device__ __forceinline__ void xcd_rows(const xcd_args &K, const xcd_ct &ct, do
 template <int G>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_big_xcd(xcd_args K) {
-    static_assert(G == 32, "a slot is one task of every phase");
+    static_assert(G == 32, "a slot is one task of every phase; 2 N = 2^16");
     constexpr uint32_t N = 1024u * G;
     extern __shared__ double lds[];
     double *tabs = lds + 8 * 1024;
     uint32_t *told = reinterpret_cast<uint32_t *>(tabs);
     const bign_args &A = K.a;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint32_t xcc;
-    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-    xcc &= 15u;
+    const uint32_t xcc = slz_xcc_id();
     double kk[2][16];
     const double *kk_of = nullptr;                               // the block and step whose first half of the key words kk holds
     uint32_t tab_slot = ~0u;
@@ -361,8 +360,7 @@ k_big_xcd(xcd_args K) {
         // phase 0, 1, 2 of the list's step p
         uint64_t mask_word;                                      // of the step
         auto turn = [&](uint32_t slot, uint32_t p) {
-            constexpr uint32_t logN2 = 11 + (G == 2 ? 1 : G == 4 ? 2 : G == 8 ? 3 : G == 16 ? 4 : 5);
-            xcd_turn<G>(K, ct, reinterpret_cast<int32_t *>(lds), wave, slot, slz_modswitch(mask_word, logN2), done, 3 * p, patience);
+            xcd_turn<G>(K, ct, reinterpret_cast<int32_t *>(lds), wave, slot, slz_modswitch(mask_word, 16), done, 3 * p, patience);
             xcd_finish(done, slot, 3 * p);
         };
         auto rows = [&](uint32_t slot, uint32_t p, uint32_t step, const uint64_t *ahead, uint64_t &ahead_word) {

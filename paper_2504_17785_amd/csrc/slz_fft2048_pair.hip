@@ -155,121 +155,121 @@ k_fft2048_pair(fft2048p_args A) {
 #pragma unroll
             for (int cc = 0; cc < 2; cc++) fwd4(D[cc][0], D[cc][1], D[cc][2], D[cc][3], f5[0], f5[1], f5[2]);
         };
-            // the group's key pieces, COUNT of them from FIRST on, side by side
-            auto run_pieces = [&](auto first, auto how_many, const d2 (&D)[2][4], uint32_t step) __attribute__((always_inline)) {
-                constexpr int FIRST = decltype(first)::value, COUNT = decltype(how_many)::value;
-                int z;
-                asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-                const uint32_t T = C0 + z, R = R0 + z;
-                const uint32_t tt = tab0 + z + FFT_F2_LEN * 16u;
-                d2 x[COUNT][4];
+        // the group's key pieces, COUNT of them from FIRST on, side by side
+        auto run_pieces = [&](auto first, auto how_many, const d2 (&D)[2][4], uint32_t step) __attribute__((always_inline)) {
+            constexpr int FIRST = decltype(first)::value, COUNT = decltype(how_many)::value;
+            int z;
+            asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+            const uint32_t T = C0 + z, R = R0 + z;
+            const uint32_t tt = tab0 + z + FFT_F2_LEN * 16u;
+            d2 x[COUNT][4];
+            FFT_FENCE();
+            const uint32_t free_seen = peek_four(freed, lane);
+#pragma unroll
+            for (int q = 0; q < COUNT; q++)
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const d2 k0 = kb[q][k][0], k1 = kb[q][k][1], a = D[0][k], b = D[1][k];
+                    x[q][k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
+                    x[q][k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
+                    pin(x[q][k]);
+                }
+            FFT_FENCE();
+            // the next step's key words (if there is one) arrive during this inverse transform and the front
+            const bool more = step + 1 < A.n_steps;
+            kp += FFT_KEY_STEP;
+            const uint32_t ln = fresh(lane);
+            const uint32_t t5 = tt + FFT_T5_OFF * 16u + 16u * (64u * g + ln);
+            // base addresses of the layouts: I1 (map Y), I2 in map Y and in map X, I3, I4
+            const uint32_t w1 = R + 16u * (17u * ((ln >> 4) * 4u + (ln & 3u)) + ((ln >> 2) & 3u) * 4u);
+            const uint32_t r2b = R + 16u * (17u * ((ln >> 4) * 4u) + (ln & 15u));                            // also I4 in map X
+            const uint32_t w2 = R + 16u * (17u * (((ln >> 2) & 3u) * 4u + (ln >> 4)) + (ln & 3u));
+            const uint32_t r3 = R + 16u * (17u * (ln >> 4) + (ln & 15u));
+            // A piece's points are read for the next pass as soon as they are written, and arrive while the other pieces go through this one.
+#pragma unroll
+            for (int q = 0; q < COUNT; q++) {                     // I1: half-sizes 1, 2; lane = b7..b2; register = b1 b0
+                add2(x[q][0], x[q][1]); add2(x[q][2], x[q][3]);
+                add2(x[q][0], x[q][2]); add2i(x[q][1], x[q][3]);
+                if (FIRST == 0 && q == 0) wait_four(freed, lane, free_seen, ex);  // the waves that read this one's buffers have done so (group 0: before it staged)
+#pragma unroll
+                for (int k = 0; k < 4; k++) lds_put(w1 + q * FP_SLOT + 16 * k, x[q][k]);
+#pragma unroll
+                for (int m = 0; m < 4; m++) x[q][m] = lds_get(r2b + q * FP_SLOT + 16 * 17 * m);
                 FFT_FENCE();
-                const uint32_t free_seen = peek_four(freed, lane);
+            }
+            if (more) request(0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < COUNT; q++) {                     // I2: half-sizes 4, 8; lane = b7 b6 b5 b4 b1 b0; register = b3 b2
+                inv4(x[q][0], x[q][1], x[q][2], x[q][3], v, v2, v3);
+#pragma unroll
+                for (int m = 0; m < 4; m++) lds_put(w2 + q * FP_SLOT + 16 * 4 * m, x[q][m]);
+#pragma unroll
+                for (int m = 0; m < 4; m++) x[q][m] = lds_get(r3 + q * FP_SLOT + 16 * 17 * 4 * m);
+                FFT_FENCE();
+            }
+            if (more) request(0, 0, 1);
+#pragma unroll
+            for (int q = 0; q < COUNT; q++) {                     // I3: half-sizes 16, 32; lane = b7 b6 b3..b0; register = b5 b4
+                inv2<false>(x[q][0], x[q][1], w30); inv2<false>(x[q][2], x[q][3], w30);
+                inv2<false>(x[q][0], x[q][2], w31); inv2<true>(x[q][1], x[q][3], w31);
+#pragma unroll
+                for (int m = 0; m < 4; m++) lds_put(r3 + q * FP_SLOT + 16 * 17 * 4 * m, x[q][m]);
+#pragma unroll
+                for (int m = 0; m < 4; m++) x[q][m] = lds_get(r2b + q * FP_SLOT + 16 * 17 * m);
+                FFT_FENCE();
+            }
+            if (more) request(1, 1, 0);
+#pragma unroll
+            for (int q = 0; q < COUNT; q++) {                     // I4: half-sizes 64, 128; lane = b5..b0; register = b7 b6
+                inv2<false>(x[q][0], x[q][1], w40); inv2<false>(x[q][2], x[q][3], w40);
+                inv2<false>(x[q][0], x[q][2], w41); inv2<true>(x[q][1], x[q][3], w41);
+#pragma unroll
+                for (int m = 0; m < 4; m++) lds_put(r2b + q * FP_SLOT + 16 * 17 * m, x[q][m]);
+            }
+            fft_signal(my_done, ++ex);
+            if (more) request(1, 1, 1);
+            {   // I5: half-sizes 256 and 512 with the twist; lane = b5..b0, wave = b7 b6; register = b9 b8
+                const d2 w0 = lds_get(t5);
+                d2 c1[2], c2[2];
+#pragma unroll
+                for (int e = 0; e < 2; e++) { c1[e] = lds_get(t5 + 4096 * (1 + 2 * e)); c2[e] = lds_get(t5 + 4096 * (2 + 2 * e)); }
+                FFT_FENCE();
+                wait_four(done, lane, peek_four(done, lane), ex);
+                const uint32_t r0 = T + 16u * (17u * ((ln >> 4) * 4u + g) + (ln & 15u));
 #pragma unroll
                 for (int q = 0; q < COUNT; q++)
 #pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        const d2 k0 = kb[q][k][0], k1 = kb[q][k][1], a = D[0][k], b = D[1][k];
-                        x[q][k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
-                        x[q][k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
-                        pin(x[q][k]);
-                    }
+                    for (int e = 0; e < 4; e++) x[q][e] = lds_get(r0 + q * FP_SLOT + e * FP_BUF);
+                fft_signal(my_free, ex);
                 FFT_FENCE();
-                // the next step's key words (if there is one) arrive during this inverse transform and the front
-                const bool more = step + 1 < A.n_steps;
-                kp += FFT_KEY_STEP;
-                const uint32_t ln = fresh(lane);
-                const uint32_t t5 = tt + FFT_T5_OFF * 16u + 16u * (64u * g + ln);
-                // base addresses of the layouts: I1 (map Y), I2 in map Y and in map X, I3, I4
-                const uint32_t w1 = R + 16u * (17u * ((ln >> 4) * 4u + (ln & 3u)) + ((ln >> 2) & 3u) * 4u);
-                const uint32_t r2b = R + 16u * (17u * ((ln >> 4) * 4u) + (ln & 15u));                            // also I4 in map X
-                const uint32_t w2 = R + 16u * (17u * (((ln >> 2) & 3u) * 4u + (ln >> 4)) + (ln & 3u));
-                const uint32_t r3 = R + 16u * (17u * (ln >> 4) + (ln & 15u));
-                // A piece's points are read for the next pass as soon as they are written, and arrive while the other pieces go through this one.
+                auto finish = [&](auto which, d2 (&y)[4]) __attribute__((always_inline)) {
+                    constexpr int piece = decltype(which)::value;
+                    inv2<false>(y[0], y[1], w0); inv2<false>(y[2], y[3], w0);
 #pragma unroll
-                for (int q = 0; q < COUNT; q++) {                     // I1: half-sizes 1, 2; lane = b7..b2; register = b1 b0
-                    add2(x[q][0], x[q][1]); add2(x[q][2], x[q][3]);
-                    add2(x[q][0], x[q][2]); add2i(x[q][1], x[q][3]);
-                    if (FIRST == 0 && q == 0) wait_four(freed, lane, free_seen, ex);  // the waves that read this one's buffers have done so (group 0: before it staged)
-#pragma unroll
-                    for (int k = 0; k < 4; k++) lds_put(w1 + q * FP_SLOT + 16 * k, x[q][k]);
-#pragma unroll
-                    for (int m = 0; m < 4; m++) x[q][m] = lds_get(r2b + q * FP_SLOT + 16 * 17 * m);
-                    FFT_FENCE();
-                }
-                if (more) request(0, 0, 0);
-#pragma unroll
-                for (int q = 0; q < COUNT; q++) {                     // I2: half-sizes 4, 8; lane = b7 b6 b5 b4 b1 b0; register = b3 b2
-                    inv4(x[q][0], x[q][1], x[q][2], x[q][3], v, v2, v3);
-#pragma unroll
-                    for (int m = 0; m < 4; m++) lds_put(w2 + q * FP_SLOT + 16 * 4 * m, x[q][m]);
-#pragma unroll
-                    for (int m = 0; m < 4; m++) x[q][m] = lds_get(r3 + q * FP_SLOT + 16 * 17 * 4 * m);
-                    FFT_FENCE();
-                }
-                if (more) request(0, 0, 1);
-#pragma unroll
-                for (int q = 0; q < COUNT; q++) {                     // I3: half-sizes 16, 32; lane = b7 b6 b3..b0; register = b5 b4
-                    inv2<false>(x[q][0], x[q][1], w30); inv2<false>(x[q][2], x[q][3], w30);
-                    inv2<false>(x[q][0], x[q][2], w31); inv2<true>(x[q][1], x[q][3], w31);
-#pragma unroll
-                    for (int m = 0; m < 4; m++) lds_put(r3 + q * FP_SLOT + 16 * 17 * 4 * m, x[q][m]);
-#pragma unroll
-                    for (int m = 0; m < 4; m++) x[q][m] = lds_get(r2b + q * FP_SLOT + 16 * 17 * m);
-                    FFT_FENCE();
-                }
-                if (more) request(1, 1, 0);
-#pragma unroll
-                for (int q = 0; q < COUNT; q++) {                     // I4: half-sizes 64, 128; lane = b5..b0; register = b7 b6
-                    inv2<false>(x[q][0], x[q][1], w40); inv2<false>(x[q][2], x[q][3], w40);
-                    inv2<false>(x[q][0], x[q][2], w41); inv2<true>(x[q][1], x[q][3], w41);
-#pragma unroll
-                    for (int m = 0; m < 4; m++) lds_put(r2b + q * FP_SLOT + 16 * 17 * m, x[q][m]);
-                }
-                fft_signal(my_done, ++ex);
-                if (more) request(1, 1, 1);
-                {   // I5: half-sizes 256 and 512 with the twist; lane = b5..b0, wave = b7 b6; register = b9 b8
-                    const d2 w0 = lds_get(t5);
-                    d2 c1[2], c2[2];
-#pragma unroll
-                    for (int e = 0; e < 2; e++) { c1[e] = lds_get(t5 + 4096 * (1 + 2 * e)); c2[e] = lds_get(t5 + 4096 * (2 + 2 * e)); }
-                    FFT_FENCE();
-                    wait_four(done, lane, peek_four(done, lane), ex);
-                    const uint32_t r0 = T + 16u * (17u * ((ln >> 4) * 4u + g) + (ln & 15u));
-#pragma unroll
-                    for (int q = 0; q < COUNT; q++)
-#pragma unroll
-                        for (int e = 0; e < 4; e++) x[q][e] = lds_get(r0 + q * FP_SLOT + e * FP_BUF);
-                    fft_signal(my_free, ex);
-                    FFT_FENCE();
-                    auto finish = [&](auto which, d2 (&y)[4]) __attribute__((always_inline)) {
-                        constexpr int piece = decltype(which)::value;
-                        inv2<false>(y[0], y[1], w0); inv2<false>(y[2], y[3], w0);
-#pragma unroll
-                        for (int e = 0; e < 2; e++) {
-                            d2 a = cmul(y[e], c1[e]), b = y[e + 2];
-                            inv2<false>(a, b, c2[e]);
-                            // coefficients 256 e + .. (a) and 512 + 256 e + .. (b turned by -45 degrees), rounded
-                            const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
-                            const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
-                            const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
-                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
-                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
-                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 2], y2);
-                            add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 2], y3);
-                            if (piece == 0) {                         // the bits of `magic` that shift 0 has left
-                                accr[e] -= 0x4338000000000000ull; acci[e] -= 0x4338000000000000ull;
-                                accr[e + 2] -= 0x4338000000000000ull; acci[e + 2] -= 0x4338000000000000ull;
-                            }
+                    for (int e = 0; e < 2; e++) {
+                        d2 a = cmul(y[e], c1[e]), b = y[e + 2];
+                        inv2<false>(a, b, c2[e]);
+                        // coefficients 256 e + .. (a) and 512 + 256 e + .. (b turned by -45 degrees), rounded
+                        const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
+                        const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
+                        const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 2], y2);
+                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 2], y3);
+                        if (piece == 0) {                         // the bits of `magic` that shift 0 has left
+                            accr[e] -= 0x4338000000000000ull; acci[e] -= 0x4338000000000000ull;
+                            accr[e + 2] -= 0x4338000000000000ull; acci[e + 2] -= 0x4338000000000000ull;
                         }
-                    };
-                    finish(fft_int<FIRST>(), x[0]);
-                    finish(fft_int<FIRST + 1>(), x[1]);
-                    if constexpr (COUNT == 3) finish(fft_int<FIRST + 2>(), x[2]);
+                    }
+                };
+                finish(fft_int<FIRST>(), x[0]);
+                finish(fft_int<FIRST + 1>(), x[1]);
+                if constexpr (COUNT == 3) finish(fft_int<FIRST + 2>(), x[2]);
 #pragma unroll
-                    for (int e = 0; e < 4; e++) { pin(accr[e]); pin(acci[e]); }
-                }
-            };
+                for (int e = 0; e < 4; e++) { pin(accr[e]); pin(acci[e]); }
+            }
+        };
         if (late) {
             __builtin_amdgcn_s_setprio(1);                            // it has the longer half: 6.63 -> 6.46 us per step
             for (uint32_t step = 0; step < A.n_steps; step++) {
@@ -375,15 +375,15 @@ k_fft2048_pair(fft2048p_args A) {
                 slz_xcd_report(line + 4u * h + g, tick + 1);
             }
             spectra(D);
-                run_pieces(fft_int<3>(), fft_int<2>(), D, step);
-                wait_four(freed, lane, peek_four(freed, lane), ex);   // the words below go into all four buffers
-                fft_wait(sums_done, fft_peek(sums_done), tick + 1);
-                const LDS_AS uint64_t *M = (const LDS_AS uint64_t *)(uintptr_t)M0 + fresh(lane);
+            run_pieces(fft_int<3>(), fft_int<2>(), D, step);
+            wait_four(freed, lane, peek_four(freed, lane), ex);   // the words below go into all four buffers
+            fft_wait(sums_done, fft_peek(sums_done), tick + 1);
+            const LDS_AS uint64_t *M = (const LDS_AS uint64_t *)(uintptr_t)M0 + fresh(lane);
 #pragma unroll
-                for (int e = 0; e < 4; e++) { accr[e] += M[64 * e]; acci[e] += M[256 + 64 * e]; }
+            for (int e = 0; e < 4; e++) { accr[e] += M[64 * e]; acci[e] += M[256 + 64 * e]; }
 #pragma unroll
-                for (int e = 0; e < 4; e++) stage(e);
-                fft_signal(my_done, ++ex);
+            for (int e = 0; e < 4; e++) stage(e);
+            fft_signal(my_done, ++ex);
             tick++;
         }
 

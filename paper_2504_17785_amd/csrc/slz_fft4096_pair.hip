@@ -134,110 +134,110 @@ k_fft4096_pair(fft4096p_args A) {
 #pragma unroll
                 for (int b = 0; b < 2; b++) fwd4(D[cc][4 * b], D[cc][4 * b + 1], D[cc][4 * b + 2], D[cc][4 * b + 3], f4[3 * b], f4[3 * b + 1], f4[3 * b + 2]);
         };
-            auto run_piece = [&](auto which, auto place_in_group, const d2 (&D)[2][8], uint32_t step) __attribute__((always_inline)) {
-                constexpr int piece = decltype(which)::value;
-                constexpr bool FIRST = decltype(place_in_group)::value == 0, LAST = piece == 2 || piece == 4;
-                int z;
-                asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-                const uint32_t T = C0 + z, R = R0 + z;
-                d2 x[8];
-                const uint32_t tb = tab0 + z;
-                d2 S[8];
+        auto run_piece = [&](auto which, auto place_in_group, const d2 (&D)[2][8], uint32_t step) __attribute__((always_inline)) {
+            constexpr int piece = decltype(which)::value;
+            constexpr bool FIRST = decltype(place_in_group)::value == 0, LAST = piece == 2 || piece == 4;
+            int z;
+            asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+            const uint32_t T = C0 + z, R = R0 + z;
+            d2 x[8];
+            const uint32_t tb = tab0 + z;
+            d2 S[8];
+            FFT_FENCE();
+            const uint32_t free_seen = peek_four(freed, lane);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const d2 k0 = kb[k][0], k1 = kb[k][1], a = D[0][k], b = D[1][k];
+                S[k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
+                S[k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
+                pin(S[k]);
+            }
+            FFT_FENCE();
+            // the group's next key words (the next step's after the last piece, if there is one) arrive during this inverse transform
+            const bool more = !LAST || step + 1 < A.n_steps;
+            if (LAST) kp += (piece == 2 ? 2 : 3) * PIECE;
+            if (more) request(0);
+            inv8(S);                                              // I1: half-sizes 1, 2, 4
+            if (!FIRST) wait_four(freed, lane, free_seen, ex);    // the waves that read this one's buffer have done so
+            {
+                const uint32_t ln = fresh(lane);                  // b8..b3; register = b2 b1 b0
+                const uint32_t w = R + 16u * (17u * (16u * (ln >> 5) + 8u * ((ln >> 4) & 1u) + (ln & 7u)) + 8u * ((ln >> 3) & 1u));
+#pragma unroll
+                for (int k = 0; k < 8; k++) lds_put(w + 16 * k, S[k]);
+            }
+            if (more) request(1);
+            {   // I2: half-sizes 8, 16, 32; lane = b8 b7 b6 b2 b1 b0; register = b5 b4 b3
+                const uint32_t ln = fresh(lane);
+                const uint32_t r0 = R + 16u * (17u * (16u * (ln >> 5) + 8u * ((ln >> 4) & 1u)) + 8u * ((ln >> 3) & 1u) + (ln & 7u));
+                const uint32_t t2 = tb + F12_I2_OFF * 16u + 16u * (ln & 7u);
+                const d2 i2v = lds_get(t2), i2v2 = lds_get(t2 + 128), i2v3 = lds_get(t2 + 256), i2w0 = lds_get(t2 + 384), i2w1 = lds_get(t2 + 512);
+#pragma unroll
+                for (int m = 0; m < 8; m++) x[m] = lds_get(r0 + 16 * 17 * m);
                 FFT_FENCE();
-                const uint32_t free_seen = peek_four(freed, lane);
+                inv4(x[0], x[1], x[2], x[3], i2v, i2v2, i2v3);
+                inv4(x[4], x[5], x[6], x[7], i2v, i2v2, i2v3);
+                inv2<false>(x[0], x[4], i2w0); inv2<false>(x[1], x[5], i2w1);
+                inv2<true>(x[2], x[6], i2w0); inv2<true>(x[3], x[7], i2w1);
+                const uint32_t w = R + 16u * (17u * (16u * (ln >> 5) + 4u * ((ln >> 4) & 1u) + 8u * ((ln >> 3) & 1u)) + (ln & 7u));
 #pragma unroll
-                for (int k = 0; k < 8; k++) {
-                    const d2 k0 = kb[k][0], k1 = kb[k][1], a = D[0][k], b = D[1][k];
-                    S[k].x = __builtin_fma(-b.y, k1.y, __builtin_fma(b.x, k1.x, __builtin_fma(-a.y, k0.y, a.x * k0.x)));
-                    S[k].y = __builtin_fma(b.y, k1.x, __builtin_fma(b.x, k1.y, __builtin_fma(a.y, k0.x, a.x * k0.y)));
-                    pin(S[k]);
-                }
+                for (int m = 0; m < 8; m++) lds_put(w + 16 * (17 * (m >> 1) + 8 * (m & 1)), x[m]);
+            }
+            if (more) request(2);
+            {   // I3: half-sizes 64, 128, 256; lane = b5..b0; register = b8 b7 b6
+                const uint32_t ln = fresh(lane);
+                const uint32_t t3 = tb + F12_I3_OFF * 16u + 16u * ln;
+                const d2 v = lds_get(t3), v2 = lds_get(t3 + 1024), v3 = lds_get(t3 + 2048), w0 = lds_get(t3 + 3072), w1 = lds_get(t3 + 4096);
+                const uint32_t r0 = R + 16u * (17u * (ln >> 4) + (ln & 15u));
+#pragma unroll
+                for (int m = 0; m < 8; m++) x[m] = lds_get(r0 + 16 * 17 * (16 * (m >> 2) + 4 * ((m >> 1) & 1) + 8 * (m & 1)));
                 FFT_FENCE();
-                // the group's next key words (the next step's after the last piece, if there is one) arrive during this inverse transform
-                const bool more = !LAST || step + 1 < A.n_steps;
-                if (LAST) kp += (piece == 2 ? 2 : 3) * PIECE;
-                if (more) request(0);
-                inv8(S);                                              // I1: half-sizes 1, 2, 4
-                if (!FIRST) wait_four(freed, lane, free_seen, ex);    // the waves that read this one's buffer have done so
-                {
-                    const uint32_t ln = fresh(lane);                  // b8..b3; register = b2 b1 b0
-                    const uint32_t w = R + 16u * (17u * (16u * (ln >> 5) + 8u * ((ln >> 4) & 1u) + (ln & 7u)) + 8u * ((ln >> 3) & 1u));
+                inv4(x[0], x[1], x[2], x[3], v, v2, v3);
+                inv4(x[4], x[5], x[6], x[7], v, v2, v3);
+                inv2<false>(x[0], x[4], w0); inv2<false>(x[1], x[5], w1);
+                inv2<true>(x[2], x[6], w0); inv2<true>(x[3], x[7], w1);
 #pragma unroll
-                    for (int k = 0; k < 8; k++) lds_put(w + 16 * k, S[k]);
-                }
-                if (more) request(1);
-                {   // I2: half-sizes 8, 16, 32; lane = b8 b7 b6 b2 b1 b0; register = b5 b4 b3
-                    const uint32_t ln = fresh(lane);
-                    const uint32_t r0 = R + 16u * (17u * (16u * (ln >> 5) + 8u * ((ln >> 4) & 1u)) + 8u * ((ln >> 3) & 1u) + (ln & 7u));
-                    const uint32_t t2 = tb + F12_I2_OFF * 16u + 16u * (ln & 7u);
-                    const d2 i2v = lds_get(t2), i2v2 = lds_get(t2 + 128), i2v3 = lds_get(t2 + 256), i2w0 = lds_get(t2 + 384), i2w1 = lds_get(t2 + 512);
+                for (int m = 0; m < 8; m++) lds_put(r0 + 16 * 17 * 4 * m, x[m]);
+            }
+            fft_signal(my_done, ++ex);
+            if (more) request(3);
+            {   // I4: half-sizes 512 and 1024 with the twist; lane = b5..b0, wave = b7 b6; register = b10 b9 b8
+                const uint32_t ln = fresh(lane);
+                const uint32_t t4 = tb + F12_I4_OFF * 16u + 16u * (64u * g + ln);
+                const d2 w0 = lds_get(t4);
+                d2 c1[2], c2[2];
+                c1[0] = lds_get(t4 + 4096); c2[0] = lds_get(t4 + 8192);
+                FFT_FENCE();
+                wait_four(done, lane, peek_four(done, lane), ex);
+                const uint32_t r0 = T + 16u * (17u * (4u * g + (ln >> 4)) + (ln & 15u));
 #pragma unroll
-                    for (int m = 0; m < 8; m++) x[m] = lds_get(r0 + 16 * 17 * m);
+                for (int e = 0; e < 8; e++) x[e] = lds_get(r0 + (e >> 1) * F12P_BUF + 16 * 17 * 16 * (e & 1));
+                fft_signal(my_free, ex);
+                FFT_FENCE();
+                inv2<false>(x[0], x[2], w0); inv2<true>(x[1], x[3], w0);
+                inv2<false>(x[4], x[6], w0); inv2<true>(x[5], x[7], w0);
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
                     FFT_FENCE();
-                    inv4(x[0], x[1], x[2], x[3], i2v, i2v2, i2v3);
-                    inv4(x[4], x[5], x[6], x[7], i2v, i2v2, i2v3);
-                    inv2<false>(x[0], x[4], i2w0); inv2<false>(x[1], x[5], i2w1);
-                    inv2<true>(x[2], x[6], i2w0); inv2<true>(x[3], x[7], i2w1);
-                    const uint32_t w = R + 16u * (17u * (16u * (ln >> 5) + 4u * ((ln >> 4) & 1u) + 8u * ((ln >> 3) & 1u)) + (ln & 7u));
-#pragma unroll
-                    for (int m = 0; m < 8; m++) lds_put(w + 16 * (17 * (m >> 1) + 8 * (m & 1)), x[m]);
-                }
-                if (more) request(2);
-                {   // I3: half-sizes 64, 128, 256; lane = b5..b0; register = b8 b7 b6
-                    const uint32_t ln = fresh(lane);
-                    const uint32_t t3 = tb + F12_I3_OFF * 16u + 16u * ln;
-                    const d2 v = lds_get(t3), v2 = lds_get(t3 + 1024), v3 = lds_get(t3 + 2048), w0 = lds_get(t3 + 3072), w1 = lds_get(t3 + 4096);
-                    const uint32_t r0 = R + 16u * (17u * (ln >> 4) + (ln & 15u));
-#pragma unroll
-                    for (int m = 0; m < 8; m++) x[m] = lds_get(r0 + 16 * 17 * (16 * (m >> 2) + 4 * ((m >> 1) & 1) + 8 * (m & 1)));
+                    if (e + 1 < 4) { c1[(e + 1) & 1] = lds_get(t4 + 4096 * (3 + 2 * e)); c2[(e + 1) & 1] = lds_get(t4 + 4096 * (4 + 2 * e)); }
                     FFT_FENCE();
-                    inv4(x[0], x[1], x[2], x[3], v, v2, v3);
-                    inv4(x[4], x[5], x[6], x[7], v, v2, v3);
-                    inv2<false>(x[0], x[4], w0); inv2<false>(x[1], x[5], w1);
-                    inv2<true>(x[2], x[6], w0); inv2<true>(x[3], x[7], w1);
-#pragma unroll
-                    for (int m = 0; m < 8; m++) lds_put(r0 + 16 * 17 * 4 * m, x[m]);
-                }
-                fft_signal(my_done, ++ex);
-                if (more) request(3);
-                {   // I4: half-sizes 512 and 1024 with the twist; lane = b5..b0, wave = b7 b6; register = b10 b9 b8
-                    const uint32_t ln = fresh(lane);
-                    const uint32_t t4 = tb + F12_I4_OFF * 16u + 16u * (64u * g + ln);
-                    const d2 w0 = lds_get(t4);
-                    d2 c1[2], c2[2];
-                    c1[0] = lds_get(t4 + 4096); c2[0] = lds_get(t4 + 8192);
-                    FFT_FENCE();
-                    wait_four(done, lane, peek_four(done, lane), ex);
-                    const uint32_t r0 = T + 16u * (17u * (4u * g + (ln >> 4)) + (ln & 15u));
-#pragma unroll
-                    for (int e = 0; e < 8; e++) x[e] = lds_get(r0 + (e >> 1) * F12P_BUF + 16 * 17 * 16 * (e & 1));
-                    fft_signal(my_free, ex);
-                    FFT_FENCE();
-                    inv2<false>(x[0], x[2], w0); inv2<true>(x[1], x[3], w0);
-                    inv2<false>(x[4], x[6], w0); inv2<true>(x[5], x[7], w0);
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        FFT_FENCE();
-                        if (e + 1 < 4) { c1[(e + 1) & 1] = lds_get(t4 + 4096 * (3 + 2 * e)); c2[(e + 1) & 1] = lds_get(t4 + 4096 * (4 + 2 * e)); }
-                        FFT_FENCE();
-                        d2 a = cmul(x[e], c1[e & 1]), b = x[e + 4];
-                        inv2<false>(a, b, c2[e & 1]);
-                        // coefficients 256 e + .. (a) and 1024 + 256 e + .. (b turned by -45 degrees), rounded
-                        const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
-                        const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
-                        const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 4], y2);
-                        add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 4], y3);
-                        if (piece == 0) {                             // the bits of `magic` that shift 0 has left
-                            accr[e] -= 0x4338000000000000ull; acci[e] -= 0x4338000000000000ull;
-                            accr[e + 4] -= 0x4338000000000000ull; acci[e + 4] -= 0x4338000000000000ull;
-                        }
-                        pin(accr[e]); pin(acci[e]); pin(accr[e + 4]); pin(acci[e + 4]);
+                    d2 a = cmul(x[e], c1[e & 1]), b = x[e + 4];
+                    inv2<false>(a, b, c2[e & 1]);
+                    // coefficients 256 e + .. (a) and 1024 + 256 e + .. (b turned by -45 degrees), rounded
+                    const uint64_t y0 = (uint64_t)__double_as_longlong(a.x + magic), y1 = (uint64_t)__double_as_longlong(a.y + magic);
+                    const uint64_t y2 = (uint64_t)__double_as_longlong(__builtin_fma(b.x + b.y, r2, magic));
+                    const uint64_t y3 = (uint64_t)__double_as_longlong(__builtin_fma(b.y - b.x, r2, magic));
+                    add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e], y0);
+                    add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e], y1);
+                    add_shifted<SLZ_FFT_PIECE_BITS * piece>(accr[e + 4], y2);
+                    add_shifted<SLZ_FFT_PIECE_BITS * piece>(acci[e + 4], y3);
+                    if (piece == 0) {                             // the bits of `magic` that shift 0 has left
+                        accr[e] -= 0x4338000000000000ull; acci[e] -= 0x4338000000000000ull;
+                        accr[e + 4] -= 0x4338000000000000ull; acci[e + 4] -= 0x4338000000000000ull;
                     }
+                    pin(accr[e]); pin(acci[e]); pin(accr[e + 4]); pin(acci[e + 4]);
                 }
-            };
+            }
+        };
         if constexpr (late) {
             __builtin_amdgcn_s_setprio(1);                            // it has the longer half: 15.7 -> 14.75 us per step at 100 ciphertexts
             for (uint32_t step = 0; step < A.n_steps; step++) {

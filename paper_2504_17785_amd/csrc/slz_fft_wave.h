@@ -20,8 +20,6 @@ __device__ __forceinline__ void lane_put(d2 *uniform_base, uint32_t lane, d2 v) 
     *reinterpret_cast<d2 *>(reinterpret_cast<char *>(uniform_base) + lane * 16u) = v;
 }
 
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
 template <int V> struct fft_int { static constexpr int value = V; };
 
 // x w for a plain complex factor
