@@ -79,7 +79,11 @@ __device__ __forceinline__ uint32_t slz_pair_join(slz_pairs P) {
     }
     if (found == LEAVE) return SLZ_PAIR_NONE;
     if (second) return 2 * (pair - 1) + 1;
-    if (ld_agent(numbers) == number + 1) return SLZ_PAIR_NONE;      // all have taken their numbers
+    // All have taken their numbers.  Read by an atomic addition like those that made it, as it is looked at once: a first workgroup that overlooked its
+    // second would leave that one waiting.  (Of a zero that the compiler sees it makes a load.)
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));
+    if (__hip_atomic_fetch_add(numbers, zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == number + 1) return SLZ_PAIR_NONE;
     while (!(pair = ld_agent(met))) {}                              // the second is past its number, and writes this next
     return 2 * (pair - 1);
 }
